@@ -156,7 +156,9 @@ def prepare(case, seed):
     need = list(A.astro_group_attn_workspace_bytes(cache, n, c["group"]))
     if c["kind"] == "full":
         need.append(A.astro_chunk_attn_bwd_full_workspace_bytes(cache, n))
-    s["workspace"] = torch.empty(max(need), dtype=torch.uint8, device=DEV)
+    # Two workspaces in turn, as for two layers or two steps in flight: a handle that may reuse staged
+    # operands then stages those of every forward, and only the backward behind it picks them up.
+    s["workspaces"] = [torch.empty(max(need), dtype=torch.uint8, device=DEV) for _ in range(2)]
     s["out"] = [torch.empty_like(q) for _ in chunks]
     s["lse"] = [torch.empty((q.shape[0], c["heads"], q.shape[1]), dtype=torch.float32, device=DEV) for _ in chunks]
     if c["kind"] in ("update", "full"):
@@ -182,23 +184,25 @@ def run(state):
         for _, k, v, _ in s["chunks"]:
             A.astro_kvcache_append(cache, k, v, n)
         return _ring(cache)
+    workspace = s["workspaces"][0]
+    s["workspaces"].reverse()
     if s["kind"] == "rollout":
         A.astro_kvcache_reset(cache)
         for (q, k, v, _), out, lse in zip(s["chunks"], s["out"], s["lse"]):
-            A.astro_chunk_attn_fwd(cache, q, k, v, n, out, lse, s["workspace"])
+            A.astro_chunk_attn_fwd(cache, q, k, v, n, out, lse, workspace)
             A.astro_kvcache_append(cache, k, v, n)
         return s["out"] + s["lse"] + _ring(cache)
     (q, k, v, dout), out, lse = s["chunks"][0], s["out"][0], s["lse"][0]
     if s["group"] > 1:
-        A.astro_group_attn_fwd(cache, q, k, v, n, s["group"], out, lse, s["workspace"])
+        A.astro_group_attn_fwd(cache, q, k, v, n, s["group"], out, lse, workspace)
     else:
-        A.astro_chunk_attn_fwd(cache, q, k, v, n, out, lse, s["workspace"])
+        A.astro_chunk_attn_fwd(cache, q, k, v, n, out, lse, workspace)
     if s["kind"] == "forward":
         return [out, lse]
     if s["kind"] == "update":
-        A.astro_chunk_attn_bwd(cache, q, k, v, out, lse, dout, n, *s["grads"], s["workspace"])
+        A.astro_chunk_attn_bwd(cache, q, k, v, out, lse, dout, n, *s["grads"], workspace)
         return [out, lse] + s["grads"]
-    A.astro_chunk_attn_bwd_full(cache, q, k, v, out, lse, dout, n, *s["grads"], *s["ring_grads"], s["workspace"])
+    A.astro_chunk_attn_bwd_full(cache, q, k, v, out, lse, dout, n, *s["grads"], *s["ring_grads"], workspace)
     return [out, lse] + s["grads"] + s["ring_grads"]
 
 
