@@ -1,5 +1,5 @@
 // Chunk attention backward with the cached context detached (Sec. 3.3), bf16 MFMA with
-// fp32 accumulation.  Two kernels, no atomics, deterministic:
+// fp32 accumulation.  Two kernels (one for launches with few rows, below), no atomics, deterministic:
 //   dq    : one workgroup per query tile, walks ALL visible keys (ring + chunk):
 //             Delta[q] = <dO_q, O_q> (taken while the query's dO row is loaded, and
 //             written out for the second kernel),
@@ -153,25 +153,68 @@ struct DqWave {
   // the first two operand fragments of the dP and dQ products requested one phase early (4.54 vs 4.48 ms).
   __device__ __forceinline__ void tile(const char* ks, const char* vs, const int (&live)[2], int live_min) {
 #pragma unroll
-    for (int kb = 0; kb < KT / 32; ++kb) {
-      f32x4 s[2][2], dp[2][2];  // [16-key half][query sub-block]
-      bf16x8 dsb[2];
-      s_product(ks, kb, s);
-      if (live_min < 32 * (kb + 1)) mask(kb, live, s);
-      // keep the phases apart: hoisting every LDS read of a key block to its top costs
-      // more registers than two resident waves per SIMD have
-      __builtin_amdgcn_sched_barrier(0);
-      probabilities(s);
-      dp_product(vs, kb, dp);
+    for (int kb = 0; kb < KT / 32; ++kb) block(ks, vs, kb, live, live_min);
+  }
+  __device__ __forceinline__ void block(const char* ks, const char* vs, int kb, const int (&live)[2], int live_min) {
+    f32x4 s[2][2], dp[2][2];  // [16-key half][query sub-block]
+    bf16x8 dsb[2];
+    s_product(ks, kb, s);
+    if (live_min < 32 * (kb + 1)) mask(kb, live, s);
+    // keep the phases apart: hoisting every LDS read of a key block to its top costs
+    // more registers than two resident waves per SIMD have
+    __builtin_amdgcn_sched_barrier(0);
+    probabilities(s);
+    dp_product(vs, kb, dp);
 #pragma unroll
-      for (int i = 0; i < 4 * KS; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // one exponential
+    for (int i = 0; i < 4 * KS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+      __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // one exponential
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    ds_operand(s, dp, dsb);
+    __builtin_amdgcn_sched_barrier(0);
+    dq_product(ks, kb, dsb);
+  }
+
+  // Q~ and dO rows of the lane's two queries, their row terms -LSE*log2(e) and -Delta; bh = stream-head
+  // pair of the chunk tensors, write_terms: this wave leaves the row terms for later launches
+  __device__ __forceinline__ void load_queries(const BwdParams& p, int b, int h, int q0, bool write_terms) {
+    const int64_t bh = (int64_t)b * p.H + h;
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs) {
+      const int q = q0 + 16 * qs;
+      const bool live = q < p.Nq;
+      const __bf16* qrow = p.q_rot + (bh * p.Nq + (live ? q : 0)) * D;
+      const int64_t token_row = (((int64_t)b * p.Nq + (live ? q : 0)) * p.H + h) * D;
+      const __bf16* drow = p.dout + token_row;
+      const __bf16* orow = p.out + token_row;
+      // Delta = <dO_q, O_q>: this lane holds the quarter 32*st + 8g .. +7 of the row, the lanes
+      // i + 16, i + 32, i + 48 the others
+      float dsum = 0.f;
+#pragma unroll
+      for (int st = 0; st < KS; ++st) {
+        bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0}, y = x, o = x;
+        if (live) {
+          x = *reinterpret_cast<const bf16x8*>(qrow + st * 32 + g * 8);
+          y = *reinterpret_cast<const bf16x8*>(drow + st * 32 + g * 8);
+          o = *reinterpret_cast<const bf16x8*>(orow + st * 32 + g * 8);
+        }
+        qreg[qs][st] = x;
+        doreg[qs][st] = y;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dsum = fmaf((float)y[j], (float)o[j], dsum);
       }
-      __builtin_amdgcn_sched_barrier(0);
-      ds_operand(s, dp, dsb);
-      __builtin_amdgcn_sched_barrier(0);
-      dq_product(ks, kb, dsb);
+      dsum += __shfl_xor(dsum, 16);
+      dsum += __shfl_xor(dsum, 32);
+      // a dead query row gets P = exp2(0 - big) = 0 everywhere
+      const float nl = live ? -p.lse[bh * p.Nq + q] * kLog2e : -1.0e30f;
+      neg_lse2[qs] = f32x4{nl, nl, nl, nl};
+      neg_delta[qs] = f32x4{-dsum, -dsum, -dsum, -dsum};
+      // the row terms of the query, for the dK/dV kernel (negative there too)
+      if (write_terms && live && g == 0) {
+        p.delta[bh * p.Nq + q] = -dsum;
+        p.lse2[bh * p.Nq + q] = nl;
+      }
     }
   }
 };
@@ -206,42 +249,7 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams
 
   Wave w;
   w.init(lane);
-#pragma unroll
-  for (int qs = 0; qs < 2; ++qs) {
-    const int q = q0 + 16 * qs;
-    const bool live = q < p.Nq;
-    const __bf16* qrow = p.q_rot + (bh * p.Nq + (live ? q : 0)) * D;
-    const int64_t token_row = (((int64_t)b * p.Nq + (live ? q : 0)) * p.H + h) * D;
-    const __bf16* drow = p.dout + token_row;
-    const __bf16* orow = p.out + token_row;
-    // Delta = <dO_q, O_q>: this lane holds the quarter 32*st + 8g .. +7 of the row, the lanes
-    // i + 16, i + 32, i + 48 the others
-    float dsum = 0.f;
-#pragma unroll
-    for (int st = 0; st < Wave::KS; ++st) {
-      bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0}, y = x, o = x;
-      if (live) {
-        x = *reinterpret_cast<const bf16x8*>(qrow + st * 32 + g * 8);
-        y = *reinterpret_cast<const bf16x8*>(drow + st * 32 + g * 8);
-        o = *reinterpret_cast<const bf16x8*>(orow + st * 32 + g * 8);
-      }
-      w.qreg[qs][st] = x;
-      w.doreg[qs][st] = y;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dsum = fmaf((float)y[j], (float)o[j], dsum);
-    }
-    dsum += __shfl_xor(dsum, 16);
-    dsum += __shfl_xor(dsum, 32);
-    // a dead query row gets P = exp2(0 - big) = 0 everywhere
-    const float nl = live ? -p.lse[bh * p.Nq + q] * kLog2e : -1.0e30f;
-    w.neg_lse2[qs] = f32x4{nl, nl, nl, nl};
-    w.neg_delta[qs] = f32x4{-dsum, -dsum, -dsum, -dsum};
-    // the row terms of the query, for the dK/dV kernel (negative there too)
-    if (live && g == 0) {
-      p.delta[bh * p.Nq + q] = -dsum;
-      p.lse2[bh * p.Nq + q] = nl;
-    }
-  }
+  w.load_queries(p, b, h, q0, true);
 
   const RowSegment k_hist = make_segment(p.k_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
   const RowSegment v_hist = make_segment(p.v_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
@@ -669,6 +677,319 @@ __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams
     dkv_wave<D, false>(p, item, wave, lds);
 }
 
+// ---- launches with few rows ------------------------------------------------------------------------
+// With 128 queries (or keys) per workgroup a chunk of a few hundred tokens and a few heads is a
+// handful of workgroups that walk all rows of the other side one tile after another.  Here a
+// workgroup owns ONE block of 32 queries (dQ) or 32 chunk keys (dK and dV), its waves share the
+// other side (FewRows), and both kinds of workgroup go out in ONE launch: the key side takes Delta
+// from dO and O itself instead of waiting for the query side.  All sums over the waves are fp32 in a
+// fixed order.  What bounds it: the tiles a CU pulls per 32 queries, as in the forward's kernel of
+// this kind; for short walks the chain launch, operand loads, tile, combine (7 us at D = 64).
+// One wave of the key side: S = Q~ K~^T, P and dV^T += dO^T P, or (kDk) also dP = dO V^T, dS and
+// dK~^T += Q~^T dS.  One wave of 256 registers does not hold both accumulators at D = 128, so half of
+// the waves take dV and half dK; S is computed by both.  Layout as in the pair of waves above.
+template <int D, bool kDk>
+struct FewKeysWave {
+  static constexpr int KS = D / 32, DT = D / 16;
+  bf16x8 kreg[2][KS], vreg[2][KS];
+  f32x4 acc[DT][2];
+  OperandAddr16<D> addr;
+  int g;
+
+  __device__ __forceinline__ void init(int lane) {
+    g = lane >> 4;
+    addr.init(lane);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) acc[dt][ks] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // lse_t / delta_t = -LSE*log2(e) and -Delta of the tile's rows; rows below first[ks] do not see the
+  // lane's key ks (first_max: largest over the wave)
+  __device__ __forceinline__ void tile(const char* qs, const char* dos, const float* lse_t, const float* delta_t,
+                                       const int (&first)[2], int first_max) {
+    f32x4 s[2][2];
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+#pragma unroll
+      for (int qh = 0; qh < 2; ++qh) {
+        const bf16x8 a = read_rows16<D>(qs, addr.row[st], 16 * qh);
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_t + 16 * qh + 4 * g);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) s[qh][ks] = mfma16(a, kreg[ks][st], st == 0 ? l4 : s[qh][ks]);
+      }
+    if (first_max > 0) {
+#pragma unroll
+      for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[qh][ks][r] = 16 * qh + 4 * g + r < first[ks] ? kNegBig : s[qh][ks][r];
+    }
+    bf16x8 x[2];  // P or dS as the B operand of the last product
+    if constexpr (kDk) {
+      f32x4 dp[2][2];
+#pragma unroll
+      for (int st = 0; st < KS; ++st)
+#pragma unroll
+        for (int qh = 0; qh < 2; ++qh) {
+          const bf16x8 a = read_rows16<D>(dos, addr.row[st], 16 * qh);
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(delta_t + 16 * qh + 4 * g);
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) dp[qh][ks] = mfma16(a, vreg[ks][st], st == 0 ? d4 : dp[qh][ks]);
+        }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[ks][4 * qh + r] = (__bf16)(fast_exp2(s[qh][ks][r]) * dp[qh][ks][r]);
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[ks][4 * qh + r] = (__bf16)fast_exp2(s[qh][ks][r]);
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const bf16x8 a = read_cols16<D>(kDk ? qs : dos, addr.tr[dt], 0);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) acc[dt][ks] = mfma16(a, x[ks], acc[dt][ks]);
+    }
+  }
+};
+
+template <int D, int kWaves>
+__device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item, char* lds) {
+  using F = FewRows<D, kWaves>;
+  using Wave = DqWave<D>;
+  const PairIndex pair = split_pair(item.bh, p.H, p.group);
+  const int b = pair.b, h = pair.h;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  const int hist = p.hist_rows.v[pair.cache_b];
+  const int64_t bh = (int64_t)b * p.H + h;
+  const int q_first = item.tile * 32, q0 = q_first + i16, q_last = p.Nq - 1;
+  const int vis_first = visible_chunk_rows(q_first, p.Nq, p.block_rows);
+  const int vis_last = visible_chunk_rows(q_first + 31 < q_last ? q_first + 31 : q_last, p.Nq, p.block_rows);
+  int vis[2];
+#pragma unroll
+  for (int qs = 0; qs < 2; ++qs) vis[qs] = visible_chunk_rows(q0 + 16 * qs < q_last ? q0 + 16 * qs : q_last, p.Nq, p.block_rows);
+  const int hist_tiles = (hist + 31) / 32, ntiles = hist_tiles + (vis_last + 31) / 32;
+  const int t_begin = F::begin(wave, kWaves, 0, ntiles), t_end = F::begin(wave + 1, kWaves, 0, ntiles);
+
+  const u32x4 k_hist = segment_words(p.k_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
+  const u32x4 v_hist = segment_words(p.v_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
+  const u32x4 k_chunk = segment_words(p.kc_rot + bh * p.Nq * D, D, p.Nq, D);
+  const u32x4 v_chunk = segment_words(p.v_chunk + ((int64_t)b * p.Nq * p.H + h) * D, (int64_t)p.H * D, p.Nq, D);
+  char* ktile = lds + wave * F::kWaveBytes;
+  char* vtile = ktile + F::kTileBytes;
+  PrivateStream<D> ps;
+  ps.init(lane);
+  auto issue_k = [&](int t) __attribute__((always_inline)) {
+    const bool in_hist = t < hist_tiles;
+    ps.issue(in_hist ? k_hist : k_chunk, D * 2, (in_hist ? t : t - hist_tiles) * 32, ktile);
+  };
+  auto issue_v = [&](int t) __attribute__((always_inline)) {
+    const bool in_hist = t < hist_tiles;
+    ps.issue(in_hist ? v_hist : v_chunk, in_hist ? D * 2 : p.H * D * 2, (in_hist ? t : t - hist_tiles) * 32, vtile);
+  };
+  if (t_begin < t_end) {
+    issue_k(t_begin);
+    issue_v(t_begin);
+  }
+  Wave w;
+  w.init(lane);
+  w.load_queries(p, b, h, q0, wave == 0);
+  for (int t = t_begin; t < t_end; ++t) {
+    const int row0 = (t < hist_tiles ? t : t - hist_tiles) * 32;
+    const int live[2] = {(t < hist_tiles ? hist : vis[0]) - row0, (t < hist_tiles ? hist : vis[1]) - row0};
+    wait_vmem_except<PrivateStream<D>::kInsts>();  // the K tile; the V tile behind it may be in flight
+    wave_lds_sync();
+    f32x4 s[2][2], dp[2][2];
+    bf16x8 dsb[2];
+    w.s_product(ktile, 0, s);
+    if ((t < hist_tiles ? hist : vis_first) - row0 < 32) w.mask(0, live, s);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmem();
+    wave_lds_sync();
+    w.probabilities(s);
+    w.dp_product(vtile, 0, dp);
+    w.ds_operand(s, dp, dsb);
+    w.dq_product(ktile, 0, dsb);
+    wait_lds();
+    wave_lds_sync();
+    // (V refilled right behind dP, so that S has to wait for both, was slower: 35.5 against 33.5 us at
+    // 70 workgroups x 133 tiles, D = 128)
+    if (t + 1 < t_end) {
+      issue_k(t + 1);
+      issue_v(t + 1);
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int dt = 0; dt < Wave::DT; ++dt)
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs) *reinterpret_cast<f32x4*>(ktile + ((dt * 2 + qs) * 64 + lane) * 16) = w.dq[dt][qs];
+  __syncthreads();
+  const bool rope = p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  constexpr int kShare = F::kUnits / kWaves;
+#pragma unroll
+  for (int u = 0; u < kShare; ++u) {
+    const int unit = wave * kShare + u, dt = unit >> 1, q = q0 + 16 * (unit & 1);
+    if (q >= p.Nq) continue;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int wv = 0; wv < kWaves; ++wv) x += *reinterpret_cast<const f32x4*>(lds + wv * F::kWaveBytes + (unit * 64 + lane) * 16);
+    x = x * p.scale;
+    if (rope) x = unrotate_quad(p.rot, token_tables(p.rot, b, q), 4 * dt + g, x);
+    *reinterpret_cast<f32x4*>(p.dq + (((int64_t)b * p.Nq + q) * p.H + h) * D + 16 * dt + 4 * g) = x;
+  }
+}
+
+// Row terms of all queries of one pair: terms[0][q] = -LSE*log2(e), terms[1][q] = -Delta = -<dO, O>.
+// Rows past the end (up to the tile) are 0: their Q~ and dO rows are zero in LDS, so they add nothing.
+constexpr int kFewMaxRows = 2048;
+template <int D, int kWaves>
+__device__ __forceinline__ void few_row_terms(const BwdParams& p, int b, int h, float (*terms)[kFewMaxRows]) {
+  constexpr int CPR = D / 8, kRows = kWaves * 64 / CPR, kUnroll = 4;
+  const int64_t bh = (int64_t)b * p.H + h;
+  const int n = (p.Nq + 31) & ~31;
+  const int r = threadIdx.x / CPR, c = threadIdx.x % CPR;
+  for (int q0 = 0; q0 < n; q0 += kRows * kUnroll) {
+    bf16x8 x[kUnroll], y[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int q = q0 + u * kRows + r;
+      const int64_t at = (((int64_t)b * p.Nq + (q < p.Nq ? q : 0)) * p.H + h) * D + c * 8;
+      x[u] = *reinterpret_cast<const bf16x8*>(p.dout + at);
+      y[u] = *reinterpret_cast<const bf16x8*>(p.out + at);
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int q = q0 + u * kRows + r;
+      float d = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) d = fmaf((float)x[u][j], (float)y[u][j], d);
+#pragma unroll
+      for (int m = 1; m < CPR; m <<= 1) d += __shfl_xor(d, m);
+      if (c == 0 && q < n) terms[1][q] = q < p.Nq ? -d : 0.f;
+    }
+  }
+  for (int q = threadIdx.x; q < n; q += kWaves * 64) terms[0][q] = q < p.Nq ? -p.lse[bh * p.Nq + q] * kLog2e : 0.f;
+}
+
+// one wave's share of the key side; part = its share of the query tiles among kWaves / 2
+template <int D, int kWaves, bool kDk>
+__device__ __forceinline__ void few_dkv_wave(const BwdParams& p, const WorkItem& item, int wave, char* lds,
+                                             const float (*terms)[kFewMaxRows]) {
+  using F = FewRows<D, kWaves>;
+  using Wave = FewKeysWave<D, kDk>;
+  const int part = wave % (kWaves / 2);
+  const int b = item.bh / p.H, h = item.bh % p.H;
+  const int lane = threadIdx.x & 63;
+  const int i16 = lane & 15, g = lane >> 4;
+  const int64_t bh = (int64_t)b * p.H + h;
+  const int j_first = item.tile * 32, j0 = j_first + i16, j_last = p.Nq - 1;
+  int first_q[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(j0 + 16 * ks < j_last ? j0 + 16 * ks : j_last, p.block_rows);
+  const int first_q_max = first_query_row_seeing(j_first + 31 < j_last ? j_first + 31 : j_last, p.block_rows);
+  const int t_first = first_query_row_seeing(j_first, p.block_rows) / 32, ntiles = (p.Nq + 31) / 32;
+  const int t_begin = F::begin(part, kWaves / 2, t_first, ntiles), t_end = F::begin(part + 1, kWaves / 2, t_first, ntiles);
+
+  const int64_t tok = ((int64_t)b * p.Nq * p.H + h) * D;
+  const u32x4 q_rows = segment_words(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
+  const u32x4 do_rows = segment_words(p.dout + tok, (int64_t)p.H * D, p.Nq, D);
+  char* qtile = lds + wave * F::kWaveBytes;
+  char* dotile = qtile + F::kTileBytes;
+  PrivateStream<D> ps;
+  ps.init(lane);
+  if (t_begin < t_end) {
+    ps.issue(q_rows, D * 2, t_begin * 32, qtile);
+    ps.issue(do_rows, p.H * D * 2, t_begin * 32, dotile);
+  }
+  Wave w;
+  w.init(lane);
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int j = j0 + 16 * ks < p.Nq ? j0 + 16 * ks : 0;  // a key past the end is computed like key 0 and never stored
+    const __bf16* krow = p.kc_rot + (bh * p.Nq + j) * D;
+    const __bf16* vrow = p.v_chunk + tok + (int64_t)j * p.H * D;
+#pragma unroll
+    for (int st = 0; st < D / 32; ++st) {
+      w.kreg[ks][st] = *reinterpret_cast<const bf16x8*>(krow + st * 32 + g * 8);
+      if constexpr (kDk) w.vreg[ks][st] = *reinterpret_cast<const bf16x8*>(vrow + st * 32 + g * 8);
+    }
+  }
+  for (int t = t_begin; t < t_end; ++t) {
+    const int first[2] = {first_q[0] - t * 32, first_q[1] - t * 32};
+    wait_vmem();
+    wave_lds_sync();
+    w.tile(qtile, dotile, terms[0] + t * 32, terms[1] + t * 32, first, first_q_max - t * 32);
+    wait_lds();
+    wave_lds_sync();
+    if (t + 1 < t_end) {
+      ps.issue(q_rows, D * 2, (t + 1) * 32, qtile);
+      ps.issue(do_rows, p.H * D * 2, (t + 1) * 32, dotile);
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int dt = 0; dt < Wave::DT; ++dt)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) *reinterpret_cast<f32x4*>(qtile + ((dt * 2 + ks) * 64 + lane) * 16) = w.acc[dt][ks];
+}
+
+template <int D, int kWaves>
+__device__ __forceinline__ void few_dkv(const BwdParams& p, const WorkItem& item, char* lds, float (*terms)[kFewMaxRows]) {
+  using F = FewRows<D, kWaves>;
+  const int b = item.bh / p.H, h = item.bh % p.H;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  few_row_terms<D, kWaves>(p, b, h, terms);
+  __syncthreads();
+  constexpr int kHalf = kWaves / 2;
+  const bool is_dv = wave < kHalf;
+  if (is_dv)
+    few_dkv_wave<D, kWaves, false>(p, item, wave, lds, terms);
+  else
+    few_dkv_wave<D, kWaves, true>(p, item, wave, lds, terms);
+  __syncthreads();
+  const bool rope = !is_dv && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  constexpr int kShare = F::kUnits / kHalf;
+#pragma unroll
+  for (int u = 0; u < kShare; ++u) {
+    const int unit = (wave % kHalf) * kShare + u, dt = unit >> 1, j = item.tile * 32 + i16 + 16 * (unit & 1);
+    if (j >= p.Nq) continue;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int wv = 0; wv < kHalf; ++wv)
+      x += *reinterpret_cast<const f32x4*>(lds + (wv + (is_dv ? 0 : kHalf)) * F::kWaveBytes + (unit * 64 + lane) * 16);
+    if (!is_dv) x = x * kLn2;  // dK~ = dS^T Q~ / sqrt(D), and the staged Q~ carries log2(e)/sqrt(D)
+    if (rope) x = unrotate_quad(p.rot, token_tables(p.rot, b, j), 4 * dt + g, x);
+    *reinterpret_cast<f32x4*>((is_dv ? p.dv : p.dk) + (((int64_t)b * p.Nq + j) * p.H + h) * D + 16 * dt + 4 * g) = x;
+  }
+}
+
+// grid: first the workgroups of the query side (the longer walk), then those of the key side;
+// p.tiles = blocks of 32 rows per pair, the same number on both sides
+template <int D, int kWaves>
+__global__ void __launch_bounds__(kWaves * 64, 2) attn_bwd_few_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) char lds[kWaves * FewRows<D, kWaves>::kWaveBytes];
+  __shared__ __attribute__((aligned(16))) float terms[2][kFewMaxRows];
+  const int n_side = p.tiles * p.BH;
+  const bool key_side = (int)blockIdx.x >= n_side;
+  const WorkItem item = work_item(p.tiles, p.BH, true, (int)blockIdx.x - (key_side ? n_side : 0));
+  if (!item.valid) return;
+  if (key_side)
+    few_dkv<D, kWaves>(p, item, lds, terms);
+  else
+    few_dq<D, kWaves>(p, item, lds);
+}
+
 template <int D>
 BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out, const float* lse, const void* dout,
                       float* dq, float* dk, float* dv, void* scratch) {
@@ -702,10 +1023,37 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   return p;
 }
 
+// Which launches take blocks of 32 rows: those whose blocks of 128 rows would leave most CUs with one
+// workgroup or none.  Measured (graph replays of the backward, us; few / general):
+//   D = 128: 2 blocks of 128 11 / 25, 48 25 / 55, 80 (nk 2880) 63 / 98, 104 (nk 20280) 273 / 477, 156 (nk 29640)
+//            524 / 670; lost: 192 (nk 910) 70 / 60, 216 (nk 10400) 298 / 268, 256 (nk 400) 46 / 42
+//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 138 / 313, 192 32 / 38, 216 160 / 175, 256 23 / 26
+// Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
+// does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
+// with four), four otherwise (208 x 37: 30.0 against 34.3).
+int few_waves(const DevGeom& g, const AttnOperands& op) {
+  const int64_t blocks = (int64_t)((op.Nq + 127) / 128) * g.B * g.H;
+  if (op.Nq > kFewMaxRows || 8 * blocks > (g.D == 128 ? 5 : 8) * (int64_t)g.n_cus) return 0;
+  int hist = 0;
+  for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
+  const int64_t wgs = (int64_t)((op.Nq + 31) / 32) * g.B * g.H;
+  return 8 * wgs <= 5 * (int64_t)g.n_cus && (hist + op.Nq) / 32 >= 64 ? 8 : 4;
+}
+
 template <int D>
 hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, const float* lse, const void* dout,
                   float* dq, float* dk, float* dv, void* scratch, hipStream_t stream) {
   BwdParams p = make_params<D>(g, op, out, lse, dout, dq, dk, dv, scratch);
+  if (const int waves = few_waves(g, op)) {
+    ProfileScope prof("attn_bwd_few_bf16", stream);
+    p.tiles = (op.Nq + 31) / 32;
+    const dim3 grid(2 * work_grid_size(p.tiles, p.BH));
+    if (waves == 8)
+      attn_bwd_few_kernel<D, 8><<<grid, 8 * 64, 0, stream>>>(p);
+    else
+      attn_bwd_few_kernel<D, 4><<<grid, 4 * 64, 0, stream>>>(p);
+    return hipGetLastError();
+  }
   {
     ProfileScope prof("attn_bwd_dq_bf16", stream);
     const int qtile = kDqWaves * 32;

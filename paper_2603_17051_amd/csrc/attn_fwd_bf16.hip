@@ -38,6 +38,8 @@ namespace {
 
 constexpr int KT = 32;                 // keys per LDS tile
 constexpr float kSumLimit = 0x1p44f;  // a lane's 16 probabilities may sum to this before the reference moves
+// a first tile whose rows sum to less than this relative to 0 takes its reference from its maximum instead
+constexpr float kFirstSumLimit = 0x1p-32f;
 
 struct FwdParams {
   const __bf16* q_rot;
@@ -89,6 +91,17 @@ struct FwdWave {
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int qs = 0; qs < 2; ++qs) o[dt][qs] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  __device__ __forceinline__ void init_zero_ref() {
+    mc[0] = mc[1] = 0.f;
+    zero_ref = true;
+  }
+
+  // over the four lanes that share a query
+  static __device__ __forceinline__ float row_sum(float x) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
   }
 
   // p = exp2(s - mc) (kZeroRef: mc is 0 for the whole wave, no subtraction) rounded to bf16, packed as the B operands of the PV
@@ -172,9 +185,12 @@ struct FwdWave {
 
   // One 32-key tile: kf = its K operands (read from ks), vs = its V rows in LDS; live (per
   // lane and query) and any_dead (wave-uniform) are only looked at when kTail.
-  template <bool kTail>
+  // first (wave-uniform): the wave's first tile, tried with the reference 0 that init_zero_ref() has set;
+  // if a row's probabilities come out too small for it, the reference is taken from the tile's maximum.
+  // before_pv() runs when the K tile is done with and before the V tile is read.
+  template <bool kTail, typename Hook>
   __device__ __forceinline__ void tile(const bf16x8 (&kf)[KH], const char* ks, const char* vs, const int (&live)[2],
-                                       bool any_dead) {
+                                       bool any_dead, bool first, Hook before_pv) {
     // Probabilities relative to the current reference.  No maximum is taken on the common
     // path: a tile whose logits outgrow the reference shows up as a huge (or infinite) row
     // sum; only then the scores are computed again (the first copy is gone: the exponentials
@@ -189,7 +205,12 @@ struct FwdWave {
       else
         probabilities<false>(s, pb, sum);
     }
-    if (__builtin_expect(__any(!(sum[0] <= kSumLimit) || !(sum[1] <= kSumLimit)), 0)) {
+    bool rescale = __any(!(sum[0] <= kSumLimit) || !(sum[1] <= kSumLimit));
+    if (first) {
+      rescale = rescale || __any(!(row_sum(sum[0]) >= kFirstSumLimit) || !(row_sum(sum[1]) >= kFirstSumLimit));
+      if (rescale) mc[0] = mc[1] = kNegBig;  // nothing is accumulated yet
+    }
+    if (__builtin_expect(rescale, 0)) {
       f32x4 s[2][2];
       scores_again<kTail>(ks, live, any_dead, s);
 #pragma unroll
@@ -222,6 +243,7 @@ struct FwdWave {
     // O^T += V^T P^T.  Half of the V operand fragments are requested up front; those of the
     // second half are read one by one behind the MFMAs of the first, into the registers
     // these have just released.
+    before_pv();
     constexpr int HALF = DT / 2;
     bf16x8 v0[HALF], v1[HALF];
 #pragma unroll
@@ -364,10 +386,10 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (MODE == kGeneric) {
       const int live[2] = {live_in(t, 0), live_in(t, 1)};
-      w.template tile<true>(kf, stage, stage + TILE_BYTES, live, any_dead_in(t));
+      w.template tile<true>(kf, stage, stage + TILE_BYTES, live, any_dead_in(t), false, [] {});
     } else {
       const int live[2] = {KT, KT};
-      w.template tile<false>(kf, stage, stage + TILE_BYTES, live, false);
+      w.template tile<false>(kf, stage, stage + TILE_BYTES, live, false, false, [] {});
     }
     // keep the next tile's K reads behind this tile's last MFMA: started earlier they
     // would need registers that are not there
@@ -407,9 +429,7 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
 #pragma unroll
   for (int qs = 0; qs < 2; ++qs) {
     // the query's row sum: over the four lanes that share it
-    float l_tot = w.l_run[qs];
-    l_tot += __shfl_xor(l_tot, 16);
-    l_tot += __shfl_xor(l_tot, 32);
+    const float l_tot = Wave::row_sum(w.l_run[qs]);
     const bool nothing = !(l_tot > 0.f);
     const float inv = nothing ? 0.f : 1.f / l_tot;
     const int q = q0 + 16 * qs;
@@ -423,6 +443,143 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
         *reinterpret_cast<bf16x4*>(orow + 16 * dt + 4 * g) = x;
       }
       if (g == 0) lse[bh * p.Nq + q] = nothing ? kNegBig : w.mc[qs] * kLn2 + __logf(l_tot);
+    }
+  }
+}
+
+// ---- launches with few queries -------------------------------------------------------------------
+// With 128 queries per workgroup a call of a few hundred queries and a few heads is a handful of
+// workgroups that walk all keys one tile after another while most of the chip idles.  Here a
+// workgroup owns ONE block of 32 queries and its waves share the KEYS: wave w walks its own
+// contiguous part of the key tiles through its own LDS buffers (no barrier in the loop), and the
+// waves' unnormalised results are combined through LDS at the end.  Against the key split over
+// workgroups that needs no second launch, and partial results stay fp32.  What bounds it: a CU pulls
+// 16 KB of tiles (D = 128) per 32 keys for 32 queries, about 0.18 us at the 40 B per clock and CU these
+// loads reach; calls of a few tiles are the chain launch, operand loads, tile, combine (7 us).
+// The first tile's reference is tried at 0 (init_zero_ref): a wave walks few tiles, so recomputing the
+// first one's scores for its maximum, as the general kernel does, would be a large part of the work.
+template <int D, int kWaves, bool kCausal>
+__global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams p) {
+  using F = FewRows<D, kWaves>;
+  using Wave = FwdWave<D>;
+  __shared__ __attribute__((aligned(1024))) char lds[kWaves * F::kWaveBytes];
+  __shared__ float2 stats[kWaves][32];  // softmax reference and row sum of each wave's keys
+
+  const WorkItem item = work_item(p.q_tiles, p.BH, true);
+  if (!item.valid) return;
+  const PairIndex pair = split_pair(item.bh, p.H, p.group);
+  const int b = pair.b, h = pair.h;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  const int hist = p.hist_rows.v[pair.cache_b];
+  const int64_t bh = (int64_t)b * p.H + h;
+  const int q_first = item.tile * 32, q_last = p.Nq - 1;
+  const int q0 = q_first + i16;  // this lane's queries: q0 and q0 + 16
+  const int block_rows = kCausal ? p.block_rows : 0;
+  const int vis_first = visible_chunk_rows(q_first, p.Nq, block_rows);
+  const int vis_last = visible_chunk_rows(q_first + 31 < q_last ? q_first + 31 : q_last, p.Nq, block_rows);
+  int vis[2];
+#pragma unroll
+  for (int qs = 0; qs < 2; ++qs) vis[qs] = visible_chunk_rows(q0 + 16 * qs < q_last ? q0 + 16 * qs : q_last, p.Nq, block_rows);
+  const int hist_tiles = (hist + KT - 1) / KT;
+  const int ntiles = hist_tiles + (vis_last + KT - 1) / KT;
+  const int t_begin = F::begin(wave, kWaves, 0, ntiles), t_end = F::begin(wave + 1, kWaves, 0, ntiles);
+
+  const u32x4 k_hist = segment_words(p.k_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
+  const u32x4 v_hist = segment_words(p.v_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
+  const u32x4 k_chunk = segment_words(p.kc_rot + bh * p.Nq * D, D, p.Nq, D);
+  const u32x4 v_chunk = segment_words(p.v_chunk + ((int64_t)b * p.Nq * p.H + h) * D, (int64_t)p.H * D, p.Nq, D);
+  char* ktile = lds + wave * F::kWaveBytes;
+  char* vtile = ktile + F::kTileBytes;
+  PrivateStream<D> ps;
+  ps.init(lane);
+  auto issue_k = [&](int t) __attribute__((always_inline)) {
+    const bool in_hist = t < hist_tiles;
+    ps.issue(in_hist ? k_hist : k_chunk, D * 2, (in_hist ? t : t - hist_tiles) * KT, ktile);
+  };
+  auto issue_v = [&](int t) __attribute__((always_inline)) {
+    const bool in_hist = t < hist_tiles;
+    ps.issue(in_hist ? v_hist : v_chunk, in_hist ? D * 2 : p.H * D * 2, (in_hist ? t : t - hist_tiles) * KT, vtile);
+  };
+  if (t_begin < t_end) {
+    issue_k(t_begin);
+    issue_v(t_begin);
+  }
+
+  Wave w;
+  w.init(lane);
+  w.init_zero_ref();
+#pragma unroll
+  for (int qs = 0; qs < 2; ++qs) {
+    const int q = q0 + 16 * qs;
+    const __bf16* qrow = p.q_rot + (bh * p.Nq + (q < p.Nq ? q : 0)) * D;
+#pragma unroll
+    for (int st = 0; st < Wave::KS; ++st) {
+      bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (q < p.Nq) x = *reinterpret_cast<const bf16x8*>(qrow + st * 32 + g * 8);
+      w.qreg[qs][st] = x;
+    }
+  }
+  for (int t = t_begin; t < t_end; ++t) {
+    wait_vmem_except<PrivateStream<D>::kInsts>();  // the K tile; the V tile behind it may be in flight
+    wave_lds_sync();
+    bf16x8 kf[Wave::KH];
+    w.read_k(ktile, kf);
+    const int row0 = (t < hist_tiles ? t : t - hist_tiles) * KT;
+    const int live[2] = {(t < hist_tiles ? hist : vis[0]) - row0, (t < hist_tiles ? hist : vis[1]) - row0};
+    // each buffer is refilled as soon as its tile is done with
+    w.template tile<true>(kf, ktile, vtile, live, (t < hist_tiles ? hist : vis_first) - row0 < KT, t == t_begin, [&] {
+      wait_lds();
+      wave_lds_sync();
+      if (t + 1 < t_end) {
+        issue_k(t + 1);
+        wait_vmem_except<PrivateStream<D>::kInsts>();
+      } else {
+        wait_vmem();
+      }
+      wave_lds_sync();
+    });
+    wait_lds();
+    wave_lds_sync();
+    if (t + 1 < t_end) issue_v(t + 1);
+  }
+
+  // every wave leaves its unnormalised result and its statistics (own buffer, own tiles are done) ...
+  wave_lds_sync();
+#pragma unroll
+  for (int qs = 0; qs < 2; ++qs) {
+    const float l = Wave::row_sum(w.l_run[qs]);
+    // a wave without tiles, or whose keys this query does not see (row sum 0), has weight 0
+    if (g == 0) stats[wave][16 * qs + i16] = make_float2(l > 0.f ? w.mc[qs] : kNegBig, l);
+#pragma unroll
+    for (int dt = 0; dt < Wave::DT; ++dt) *reinterpret_cast<f32x4*>(ktile + ((dt * 2 + qs) * 64 + lane) * 16) = w.o[dt][qs];
+  }
+  __syncthreads();
+  // ... and takes a share of the blocks of the sum, weighted to the largest reference
+  constexpr int kShare = F::kUnits / kWaves;
+#pragma unroll
+  for (int u = 0; u < kShare; ++u) {
+    const int unit = wave * kShare + u, dt = unit >> 1, qs = unit & 1;
+    const int q = q0 + 16 * qs;
+    float m = kNegBig, l = 0.f;
+#pragma unroll
+    for (int wv = 0; wv < kWaves; ++wv) m = fmaxf(m, stats[wv][16 * qs + i16].x);
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int wv = 0; wv < kWaves; ++wv) {
+      const float2 st = stats[wv][16 * qs + i16];
+      const float wt = fast_exp2(st.x - m);
+      l = fmaf(wt, st.y, l);
+      x += *reinterpret_cast<const f32x4*>(lds + wv * F::kWaveBytes + (unit * 64 + lane) * 16) * wt;
+    }
+    if (q < p.Nq) {
+      const bool nothing = !(l > 0.f);  // as in the general kernel: logits that are not finite
+      const float inv = nothing ? 0.f : 1.f / l;
+      bf16x4 y;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) y[c] = (__bf16)(x[c] * inv);
+      *reinterpret_cast<bf16x4*>(p.out + (((int64_t)b * p.Nq + q) * p.H + h) * D + 16 * dt + 4 * g) = y;
+      if (dt == 0 && g == 0) p.lse[bh * p.Nq + q] = nothing ? kNegBig : m * kLn2 + __logf(l);
     }
   }
 }
@@ -460,8 +617,7 @@ __global__ void __launch_bounds__(256) fwd_merge_kernel(FwdParams p, int64_t n_r
   if (lane == 0) p.lse[lse_at] = m + __logf(tot);
 }
 
-template <int D, int kStages, int kWaves, int OCC, bool kCausal>
-hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* lse, void* parts, hipStream_t stream) {
+FwdParams make_params(const DevGeom& g, const AttnOperands& op, void* out, float* lse) {
   FwdParams p;
   p.q_rot = (const __bf16*)op.q_rot;
   p.kc_rot = (const __bf16*)op.kc_rot;
@@ -476,8 +632,27 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
   p.hist_rows = op.hist_rows;
   p.group = op.group;
   p.block_rows = op.block_rows;
-  const int qtile = kWaves * 32;
   p.BH = g.B * g.H;
+  p.q_tiles = 0;
+  p.splits = 1;
+  p.out_part = nullptr;
+  p.lse_part = nullptr;
+  return p;
+}
+
+template <int D, int kWaves, bool kCausal>
+hipError_t launch_few(const DevGeom& g, const AttnOperands& op, void* out, float* lse, hipStream_t stream) {
+  FwdParams p = make_params(g, op, out, lse);
+  p.q_tiles = (op.Nq + 31) / 32;
+  ProfileScope prof("attn_fwd_few_bf16", stream);
+  attn_fwd_few_kernel<D, kWaves, kCausal><<<dim3(work_grid_size(p.q_tiles, p.BH)), dim3(kWaves * 64), 0, stream>>>(p);
+  return hipGetLastError();
+}
+
+template <int D, int kStages, int kWaves, int OCC, bool kCausal>
+hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* lse, void* parts, hipStream_t stream) {
+  FwdParams p = make_params(g, op, out, lse);
+  const int qtile = kWaves * 32;
   p.q_tiles = (op.Nq + qtile - 1) / qtile;
   // a launch that would leave the chip under two rounds of workgroups is split over the keys
   p.splits = bf16_fwd_splits(g, op, parts != nullptr);
@@ -529,9 +704,43 @@ int bf16_fwd_splits(const DevGeom& g, const AttnOperands& op, bool have_parts) {
   return s < 1 ? 1 : s;
 }
 
+// ---- which launches take one block of 32 queries per workgroup -------------------------------------
+// Such a workgroup pulls every key tile for 32 queries only, four times the tile traffic per query of
+// the general kernel, and needs no merge launch.  Its time follows rounds * tiles, rounds = workgroups
+// per CU, at least 1; that product is bounded below.  Measured (graph replays, us; few / general):
+//   D = 128: 4 workgroups x 10 tiles 7.1 / 10.7, 144 x 33 12.2 / 23.8, 132 x 109 24.5 / 31.2, 140 x 133
+//            28.1 / 33.7, 320 x 140 42 / 48, 624 x 29 24 / 48; lost: 70 x 133 26.7 / 24.5, 156 x 232 45.1 /
+//            43.8, 392 x 634 167 / 161, 792 x 325 195 / 162
+//   D = 64:  4 x 10 5.1 / 9.6, 144 x 33 8.2 / 19.9, 140 x 133 16.3 / 26.6, 156 x 232 25.6 / 34.0, 792 x 325
+//            109 / 112; lost: 588 x 927 230 / 178
+// Below half a round the general kernel's key split reaches CUs that this one leaves idle, hence the
+// lower bound there.  Returns the waves per workgroup, 0 = the general kernel: eight waves pay when
+// every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
+// with four); two workgroups of four waves share a CU otherwise (312 x 86: 30.2 against 36.4).
+static int few_waves(const DevGeom& g, const AttnOperands& op) {
+  int hist = 0;
+  for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
+  const int64_t wgs = (int64_t)((op.Nq + 31) / 32) * g.B * g.H;
+  const int64_t tiles = (hist + KT - 1) / KT + (op.Nq + KT - 1) / KT;
+  const int64_t walk = wgs > g.n_cus ? tiles * wgs / g.n_cus : tiles;
+  const bool half_full = 2 * wgs >= g.n_cus;
+  const int64_t limit = g.D == 128 ? (half_full ? 200 : 112) : (half_full ? 900 : 300);
+  if (walk > limit) return 0;
+  return wgs <= g.n_cus && tiles >= 64 ? 8 : 4;
+}
+
 hipError_t launch_attn_fwd_bf16(const DevGeom& g, const AttnOperands& op, void* out, float* lse, void* parts,
                                 hipStream_t stream) {
   const bool causal = op.block_rows > 0;
+  const int waves = few_waves(g, op);
+  if (waves != 0 && g.D == 128) {
+    if (waves == 8) return causal ? launch_few<128, 8, true>(g, op, out, lse, stream) : launch_few<128, 8, false>(g, op, out, lse, stream);
+    return causal ? launch_few<128, 4, true>(g, op, out, lse, stream) : launch_few<128, 4, false>(g, op, out, lse, stream);
+  }
+  if (waves != 0) {
+    if (waves == 8) return causal ? launch_few<64, 8, true>(g, op, out, lse, stream) : launch_few<64, 8, false>(g, op, out, lse, stream);
+    return causal ? launch_few<64, 4, true>(g, op, out, lse, stream) : launch_few<64, 4, false>(g, op, out, lse, stream);
+  }
   if (g.D == 128)
     return causal ? launch<128, 3, 4, 3, true>(g, op, out, lse, parts, stream) : launch<128, 3, 4, 3, false>(g, op, out, lse, parts, stream);
   return causal ? launch<64, 3, 4, 3, true>(g, op, out, lse, parts, stream) : launch<64, 3, 4, 3, false>(g, op, out, lse, parts, stream);

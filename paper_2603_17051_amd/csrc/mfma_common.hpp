@@ -160,14 +160,68 @@ struct TileStreamer {
   }
 };
 
+// Orders a wave's own LDS accesses around a point where its lanes exchange data (the hardware serves
+// them in order; this keeps the compiler to that order).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A [32 rows][D] tile that belongs to ONE wave (no barrier around it), filled by direct-to-LDS loads;
+// rows past the segment's end read as zeros.  The loads are issued from assembly: the
+// compiler waits for ALL of its own direct-to-LDS loads before the next LDS read, since it cannot
+// tell the buffers apart, and a wave's two tiles are refilled at different times.  It does not count
+// these, so the caller waits (wait_vmem) before it reads the tile, and has its reads of the old
+// contents returned before the refill (wait_lds).
+template <int D>
+struct PrivateStream {
+  static constexpr int CPR = D / 8, kRowsPerInst = 64 / CPR, kInsts = 32 / kRowsPerInst;
+  static constexpr int kPatterns = 16 / kRowsPerInst;  // the swizzle repeats every 16 rows
+  uint32_t chunk[kPatterns];  // byte offset within its row of the chunk this lane fetches
+  uint32_t lane_row;
+
+  __device__ __forceinline__ void init(int lane) {
+    lane_row = lane / CPR;
+#pragma unroll
+    for (int u = 0; u < kPatterns; ++u) chunk[u] = ((lane % CPR) ^ swizzle16<CPR>(u * kRowsPerInst + lane / CPR)) * 16;
+  }
+  __device__ __forceinline__ void issue(const u32x4 rsrc, uint32_t stride_bytes, int row0, const char* lds_tile) const {
+    typedef const char __attribute__((address_space(3))) * lds_ptr;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr)lds_tile);
+#pragma unroll
+    for (int u = 0; u < kInsts; ++u) {
+      const uint32_t off = ((uint32_t)(row0 + u * kRowsPerInst) + lane_row) * stride_bytes + chunk[u % kPatterns];
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst + u * 1024), "v"(off), "s"(rsrc)
+                   : "memory");
+    }
+  }
+};
+// raw buffer descriptor words of a row source (see make_segment) for PrivateStream
+__device__ __forceinline__ u32x4 segment_words(const __bf16* base, int64_t stride_elems, int n_rows, int D) {
+  const int64_t bytes = n_rows > 0 ? (int64_t)(n_rows - 1) * stride_elems * 2 + D * 2 : 0;
+  const uint64_t a = (uint64_t)base;
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)bytes, 0x00020000u};
+}
+
+// Launches with few rows: a workgroup owns ONE block of 32 queries (or keys) and its waves share the
+// walk over the other side, each through two private tiles; per-wave results are combined through LDS.
+template <int D, int WAVES>
+struct FewRows {
+  static constexpr int kTileBytes = 32 * D * 2;
+  static constexpr int kWaveBytes = 2 * kTileBytes;  // two tiles; at the end one 32 x D fp32 result
+  static constexpr int kUnits = 2 * D / 16;          // 16 x 16 blocks of that result, 1 KB each
+  // share [begin(i), begin(i + 1)) of part i of `parts` in tiles [first, n)
+  static __device__ __forceinline__ int begin(int i, int parts, int first, int n) { return n > first ? first + i * (n - first) / parts : first; }
+};
+
 // ---- workgroup -> (tile, stream*head) mapping -------------------------------------------
 // 1-D grid.  Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  With
-// `by_xcd`, and when the (stream, head) pairs divide evenly over the XCDs, XCD x gets the
-// contiguous range of pairs [x*BH/8, (x+1)*BH/8), tiles of one pair consecutive: a pair's
-// K/V is then pulled through ONE L2 instead of all eight (an eighth of the fabric reads;
-// measured 1.5-2.5 % faster for the kernels that walk the whole window).  Otherwise (e.g.
-// 12 heads of one stream, where that split would leave XCDs idle) the plain pair-major
-// order is used, in which every XCD streams every pair in flight.
+// `by_xcd` XCD x gets a contiguous eighth of the items, tiles of one pair consecutive: a pair's
+// K/V is then pulled through one or two L2s instead of all eight (an eighth of the fabric reads;
+// 1.5-2.5 % faster for the kernels that walk the whole window; with 10 pairs of 14 blocks of 32
+// queries over 4256 keys the forward takes 28.1 instead of 33.3 us).  The eighths are cut by items, not by pairs, so
+// 12 heads of one stream fill all XCDs too.
 struct WorkItem {
   int tile, bh;
   bool valid;
@@ -176,15 +230,16 @@ constexpr int kXcds = 8;
 __host__ __device__ inline int work_grid_size(int tiles_per_head, int BH) { return tiles_per_head * BH; }
 __device__ __forceinline__ WorkItem work_item(int tiles_per_head, int BH, bool by_xcd, int i) {
   WorkItem w;
-  w.valid = i < tiles_per_head * BH;
-  int j = i, first = 0;
-  if (by_xcd && BH % kXcds == 0) {
-    j = i / kXcds;                       // index among this XCD's workgroups
-    first = (i % kXcds) * (BH / kXcds);  // first pair of this XCD
+  const int n = tiles_per_head * BH;
+  w.valid = i < n;
+  int j = i;
+  if (by_xcd) {
+    // XCD x takes the contiguous range of items [x*n/8, (x+1)*n/8) (the first n % 8 one item more)
+    const int x = i % kXcds, q = n / kXcds, r = n % kXcds;
+    j = x * q + (x < r ? x : r) + i / kXcds;
   }
-  const int rel = j / tiles_per_head;
-  w.bh = first + rel;
-  w.tile = j - rel * tiles_per_head;
+  w.bh = j / tiles_per_head;
+  w.tile = j - w.bh * tiles_per_head;
   return w;
 }
 
@@ -254,6 +309,8 @@ __device__ __forceinline__ f32x4 unrotate_quad(const RotaryTables& r, const Toke
   return f32x4{x[0] * a.x + x[1] * a.y, x[1] * a.x - x[0] * a.y, x[2] * b.x + x[3] * b.y, x[3] * b.x - x[2] * b.y};
 }
 
+// wait until this wave's outstanding LDS accesses are done
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0) only
 // wait until this wave's outstanding global loads (including direct-to-LDS ones) are done
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0) only
 // ... all but the N most recently issued ones (loads complete in issue order)

@@ -1,0 +1,55 @@
+"""GPU parity of the kernels for launches with few rows (one block of 32 queries or keys per workgroup,
+its waves sharing the walk over the other side), at the sizes where their tiling can go wrong, and of
+the general kernels at ragged sizes just beyond the lines where they take over; fp64 oracle, outputs
+pre-filled with NaN, the kernel that ran taken from the launch names."""
+import pytest
+
+import workloads as wl
+from helpers import Lockstep, assert_bf16_close, host_f64
+from test_gpu_parity import _fill_history
+
+pytestmark = pytest.mark.gpu
+
+P64, P128 = (12, 10, 10), (22, 21, 21)
+
+
+@pytest.mark.parametrize("D,pairs,gh,gw,B,H,C,Fc,bf,resident,fwd_few,bwd_few", [
+    # one query, one ragged tile, waves without a tile.  40 keys: with two, dS = p1 p2 (dP1 - dP2) and a Delta taken from
+    # the bf16 output (error |dO| |O| 2^-9, about 0.5 % of that difference) is past the gates, which are derived at 64 keys and more
+    (128, P128, 1, 1, 1, 1, 39, 1, 0, 39, True, True),
+    (64, P64, 1, 31, 1, 2, 3, 1, 0, 3, True, True),        # a block and every tile one row short
+    (128, P128, 3, 11, 2, 3, 4, 2, 1, 2, True, True),      # 33-token frames, causal: one row past a block
+    (64, P64, 4, 8, 1, 1, 4, 3, 2, 0, True, True),         # frames of exactly one block on an empty ring
+    (128, P128, 10, 13, 1, 2, 18, 3, 0, 18, True, True),   # a long walk: eight waves
+    (64, P64, 10, 13, 1, 3, 18, 3, 1, 18, True, True),     # ... D 64, causal
+    (128, P128, 10, 13, 6, 8, 18, 3, 1, 18, False, False),  # general kernels: ragged frames, causal
+    (64, P64, 10, 13, 8, 16, 3, 2, 0, 3, True, False),     # general backward at D 64
+    (64, P64, 16, 20, 2, 16, 36, 2, 1, 36, False, True),   # general forward at D 64
+])
+def test_fwd_bwd_on_both_sides_of_the_few_rows_lines(D, pairs, gh, gw, B, H, C, Fc, bf, resident, fwd_few, bwd_few):
+    import torch
+    w = wl.Workload("few_rows", 51, B, H, D, gh, gw, C, 0, Fc, resident, pairs)
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[3 + 11 * b for b in range(B)], block_frames=bf)
+    if resident:
+        _fill_history(ls, w, *wl.history_frame_pool(w, 3), resident)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    dev = [ls.dev(x) for x in (q, k, v, do)]
+    nan = lambda dtype, shape: torch.full(shape, float("nan"), dtype=dtype, device="cuda:0")
+    out, lse = nan(torch.bfloat16, dev[0].shape), nan(torch.float32, (B, H, w.n_q))
+    grads = [nan(torch.float32, dev[0].shape) for _ in range(3)]
+    ls.A.astro_profile_begin()
+    ls.A.astro_chunk_attn_fwd(ls.cache, *dev[:3], Fc, out, lse)
+    ls.A.astro_chunk_attn_bwd(ls.cache, *dev[:3], out, lse, dev[3], Fc, *grads)
+    launched = ls.A.astro_profile_end()
+    assert ("attn_fwd_few_bf16" in launched) == fwd_few and ("attn_fwd_bf16" in launched) != fwd_few, launched
+    assert ("attn_bwd_few_bf16" in launched) == bwd_few and ("attn_bwd_dq_bf16" in launched) != bwd_few, launched
+    # the oracle on the first and the last stream-head pair
+    wide = [ls.wide(x) for x in (q, k, v, do)]
+    for b, h in {(0, 0), (B - 1, H - 1)}:
+        ro, rl = ls.oracle.attn_fwd(*wide[:3], Fc, streams=[b], heads=[h])
+        ref = ls.oracle.attn_bwd(*wide, Fc, streams=[b], heads=[h])
+        for got, r, what in [(out[b, :, h], ro[b, :, h], "out"), (lse[b, h], rl[b, h], "lse")] + \
+                [(g[b, :, h], r[b, :, h], n) for g, r, n in zip(grads, ref, ("dq", "dk", "dv"))]:
+            assert_bf16_close(host_f64(got), r, f"pair {b, h} {what}")
+    assert all(bool(torch.isfinite(x.float()).all()) for x in [out, lse] + grads)
+    ls.close()
