@@ -11,10 +11,9 @@
 namespace astro {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;  // of the prepare launch
 constexpr int kElemsPerBlock = 16384;  // elements of one sample a workgroup walks
 
 struct NftParams {
@@ -49,25 +48,23 @@ __global__ void __launch_bounds__(kThreads) nft_prepare_kernel(NftParams p) {
   if (threadIdx.x == 0) *p.n_masked = (float)cnt[0];
 }
 
+// Four elements of a tensor.  Also for bf16, where that is an 8-byte load: a lane's gradients are then
+// the 16 bytes next to its neighbour's, and a wave's store is 1 KB in one piece (eight elements per lane
+// make two stores that each touch every other 16 bytes: 142 us instead of 121 at 192 clips).
+constexpr int N = 4;
 template <typename Elem>
-struct Chunk;
-template <>
-struct Chunk<__bf16> {
-  static constexpr int N = 8;
-  static __device__ __forceinline__ void load(const void* base, int64_t i, float (&x)[N]) {
-    const bf16x8 v = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(base) + i));
-#pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = (float)v[j];
+struct Chunk {
+  typedef Elem Vec __attribute__((ext_vector_type(N)));
+  // chunks of every tensor in flight per thread, and the most threads of a workgroup.  Measured at 24 /
+  // 192 clips of 299520 elements: bf16 20.2 / 122 us (1024 threads: 20.8 / 130, 256: 21.4 / 130, two chunks and 512
+  // threads: 20.5 / 126), fp32 29.3 / 196 (512 threads and four chunks: 29.6 / 204, 256 and four: 30.1 / 213)
+  static constexpr int kUnroll = sizeof(Elem) == 2 ? 4 : 2;
+  static constexpr int kThreads = sizeof(Elem) == 2 ? 512 : 1024;
+  Vec v;
+  __device__ __forceinline__ void load(const void* base, int64_t i) {
+    v = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(static_cast<const Elem*>(base) + i));
   }
-};
-template <>
-struct Chunk<float> {
-  static constexpr int N = 4;
-  static __device__ __forceinline__ void load(const void* base, int64_t i, float (&x)[N]) {
-    const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + i));
-#pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = v[j];
-  }
+  __device__ __forceinline__ float operator[](int j) const { return (float)v[j]; }
 };
 
 // Up to this many samples every workgroup derives r~ of its sample and the number of masked
@@ -75,24 +72,50 @@ struct Chunk<float> {
 // three dependent launches took 28 us for 17 us of memory traffic.
 constexpr int kMaxSamplesInline = 1024;
 
-// grid (blocks_per_sample, n)
+// HBM-bound.  A workgroup walks kElemsPerBlock elements of one sample (one triple of partial sums each,
+// which is what the workspace holds).  24 clips are 456 workgroups, fewer than two per CU, so a
+// workgroup needs many bytes in flight; the first trip's loads are issued before the masked samples are
+// counted, so that chain runs under their latency.  With 256 threads and one 16-byte load per tensor at
+// a time: 24.9 / 142 us in bf16 at 24 / 192 clips, 32.1 / 221 us in fp32; now 20.2 / 122 and 29.3 / 196.
+
+// grid (blocks_per_sample, n); blockDim.x a multiple of 64 up to Chunk::kThreads
 template <typename Elem, bool kInline>
-__global__ void __launch_bounds__(kThreads) nft_loss_kernel(NftParams p) {
-  constexpr int N = Chunk<Elem>::N;
+__global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftParams p) {
+  using C = Chunk<Elem>;
+  constexpr int kUnroll = C::kUnroll;
+  const int threads = blockDim.x, waves = threads / 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = blockIdx.y;
+  const int64_t lo = (int64_t)blockIdx.x * kElemsPerBlock;
+  const int64_t hi = lo + kElemsPerBlock < p.E ? lo + kElemsPerBlock : p.E;
+  const int64_t base = (int64_t)i * p.E;
+  C vt[kUnroll], vo[kUnroll], vr[kUnroll], tg[kUnroll];
+  auto load = [&](int64_t e0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int64_t e = e0 + (int64_t)u * threads * N;
+      if (e < hi) {
+        vt[u].load(p.v_theta, base + e);
+        vo[u].load(p.v_old, base + e);
+        vr[u].load(p.v_ref, base + e);
+        tg[u].load(p.target, base + e);
+      }
+    }
+  };
+  int64_t e0 = lo + (int64_t)threadIdx.x * N;
+  load(e0);
+
+  __shared__ float red[3][C::kThreads / 64];
   float r, nm;
   if constexpr (kInline) {
-    __shared__ int cnt[kThreads / 64];
     int c = 0;
-    for (int j = threadIdx.x; j < p.n; j += kThreads) c += p.kl_mask[j] != 0 ? 1 : 0;
+    for (int j = threadIdx.x; j < p.n; j += threads) c += p.kl_mask[j] != 0 ? 1 : 0;
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) c += __shfl_xor(c, sh);
-    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = c;
+    if (lane == 0) red[0][wave] = (float)c;  // counts up to 1024: exact
     __syncthreads();
-    int total = 0;
-#pragma unroll
-    for (int wv = 0; wv < kThreads / 64; ++wv) total += cnt[wv];
-    nm = (float)total;
+    nm = 0.f;
+    for (int wv = 0; wv < waves; ++wv) nm += red[0][wv];
+    __syncthreads();
     r = fminf(fmaxf(p.advantage[i] * p.inv_a_max, -1.f), 1.f) * 0.5f + 0.5f;
     // the first workgroup leaves both where the final sum reads them
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -105,78 +128,82 @@ __global__ void __launch_bounds__(kThreads) nft_loss_kernel(NftParams p) {
   }
   const float c_pol = 2.f * p.beta / (float)p.n;
   const float c_kl = (p.kl_mask[i] != 0 && nm > 0.f) ? 2.f * p.lambda_kl / nm : 0.f;
-  const int64_t lo = (int64_t)blockIdx.x * kElemsPerBlock;
-  const int64_t hi = lo + kElemsPerBlock < p.E ? lo + kElemsPerBlock : p.E;
-  const int64_t base = (int64_t)i * p.E;
   float s_pos = 0.f, s_neg = 0.f, s_ref = 0.f;
-  for (int64_t e = lo + (int64_t)threadIdx.x * N; e < hi; e += (int64_t)kThreads * N) {
-    float vt[N], vo[N], vr[N], tg[N];
-    Chunk<Elem>::load(p.v_theta, base + e, vt);
-    Chunk<Elem>::load(p.v_old, base + e, vo);
-    Chunk<Elem>::load(p.v_ref, base + e, vr);
-    Chunk<Elem>::load(p.target, base + e, tg);
-    float g[N];
+  for (; e0 < hi;) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const float bd = p.beta * (vt[j] - vo[j]);  // v+ = v_old + beta (v_theta - v_old), v- = v_old - beta (...)
-      const float e_pos = (vo[j] - tg[j]) + bd;
-      const float e_neg = (vo[j] - tg[j]) - bd;
-      const float d_ref = vt[j] - vr[j];
-      s_pos = fmaf(e_pos, e_pos, s_pos);
-      s_neg = fmaf(e_neg, e_neg, s_neg);
-      s_ref = fmaf(d_ref, d_ref, s_ref);
-      g[j] = c_pol * (r * e_pos - (1.f - r) * e_neg) + c_kl * d_ref;
+    for (int u = 0; u < kUnroll; ++u) {
+      const int64_t e = e0 + (int64_t)u * threads * N;
+      if (e >= hi) continue;
+      float g[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const float bd = p.beta * (vt[u][j] - vo[u][j]);  // v+ = v_old + beta (v_theta - v_old), v- = v_old - beta (...)
+        const float e_pos = (vo[u][j] - tg[u][j]) + bd;
+        const float e_neg = (vo[u][j] - tg[u][j]) - bd;
+        const float d_ref = vt[u][j] - vr[u][j];
+        s_pos = fmaf(e_pos, e_pos, s_pos);
+        s_neg = fmaf(e_neg, e_neg, s_neg);
+        s_ref = fmaf(d_ref, d_ref, s_ref);
+        g[j] = c_pol * (r * e_pos - (1.f - r) * e_neg) + c_kl * d_ref;
+      }
+      float* go = p.grad + base + e;
+#pragma unroll
+      for (int j = 0; j < N; j += 4)
+        __builtin_nontemporal_store(f32x4{g[j], g[j + 1], g[j + 2], g[j + 3]}, reinterpret_cast<f32x4*>(go + j));
     }
-    float* go = p.grad + base + e;
-#pragma unroll
-    for (int j = 0; j < N; j += 4)
-      __builtin_nontemporal_store(f32x4{g[j], g[j + 1], g[j + 2], g[j + 3]}, reinterpret_cast<f32x4*>(go + j));
+    e0 += (int64_t)kUnroll * threads * N;
+    load(e0);
   }
   // block reduction of the three sums
-  __shared__ float red[3][kThreads / 64];
   float v[3] = {s_pos, s_neg, s_ref};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1) v[k] += __shfl_xor(v[k], s);
-    if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = v[k];
+    if (lane == 0) red[k][wave] = v[k];
   }
   __syncthreads();
   if (threadIdx.x < 3) {
     float t = 0.f;
-#pragma unroll
-    for (int wv = 0; wv < kThreads / 64; ++wv) t += red[threadIdx.x][wv];
+    for (int wv = 0; wv < waves; ++wv) t += red[threadIdx.x][wv];
     p.partials[((int64_t)i * p.blocks_per_sample + blockIdx.x) * 3 + threadIdx.x] = t;
   }
 }
 
-// one workgroup: L_policy = (1/n) sum_i [r~_i S+_i + (1 - r~_i) S-_i], L_KL = (1/|M|) sum_{i in M} Sref_i
-__global__ void __launch_bounds__(kThreads) nft_finalize_kernel(NftParams p) {
-  __shared__ double pol[kThreads], kl[kThreads];
+// One workgroup: L_policy = (1/n) sum_i [r~_i S+_i + (1 - r~_i) S-_i], L_KL = (1/|M|) sum_{i in M} Sref_i.
+// Both are sums over all triples of partial sums with the weights of their sample, so the threads
+// share the triples (one thread per sample walked its triples one after another: 5.5 us at 24 clips
+// of 19 triples, most of it latency).  fp64, fixed order.
+constexpr int kFinalThreads = 1024;
+__global__ void __launch_bounds__(kFinalThreads) nft_finalize_kernel(NftParams p) {
+  __shared__ double pol[kFinalThreads / 64], kl[kFinalThreads / 64];
+  const int64_t n_triples = (int64_t)p.n * p.blocks_per_sample;
   double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < p.n; i += kThreads) {
-    double s[3] = {0.0, 0.0, 0.0};
-    const float* part = p.partials + (int64_t)i * p.blocks_per_sample * 3;
-    for (int blk = 0; blk < p.blocks_per_sample; ++blk)
-      for (int k = 0; k < 3; ++k) s[k] += (double)part[blk * 3 + k];
+  for (int64_t t = threadIdx.x; t < n_triples; t += kFinalThreads) {
+    const int i = (int)(t / p.blocks_per_sample);
     const double r = (double)p.r_tilde[i];
-    a += r * s[0] + (1.0 - r) * s[1];
-    if (p.kl_mask[i] != 0) b += s[2];
+    a += r * (double)p.partials[3 * t] + (1.0 - r) * (double)p.partials[3 * t + 1];
+    if (p.kl_mask[i] != 0) b += (double)p.partials[3 * t + 2];
   }
-  pol[threadIdx.x] = a;
-  kl[threadIdx.x] = b;
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    a += __shfl_xor(a, s);
+    b += __shfl_xor(b, s);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    pol[threadIdx.x >> 6] = a;
+    kl[threadIdx.x >> 6] = b;
+  }
   __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      pol[threadIdx.x] += pol[threadIdx.x + s];
-      kl[threadIdx.x] += kl[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
+    a = b = 0.0;
+    for (int wv = 0; wv < kFinalThreads / 64; ++wv) {
+      a += pol[wv];
+      b += kl[wv];
+    }
     const double nm = (double)*p.n_masked;
-    const double l_pol = pol[0] / (double)p.n;
-    const double l_kl = nm > 0.0 ? kl[0] / nm : 0.0;
+    const double l_pol = a / (double)p.n;
+    const double l_kl = nm > 0.0 ? b / nm : 0.0;
     p.loss[0] = (float)(l_pol + (double)p.lambda_kl * l_kl);
     p.loss[1] = (float)l_pol;
     p.loss[2] = (float)l_kl;
@@ -228,19 +255,26 @@ int run_nft_loss(const void* v_theta, const void* v_old, const void* v_ref, cons
     // the entry point that must not allocate never creates timing events, even while profiling is on
     ProfileScope prof("nft_loss", stream, timed);
     const dim3 grid(p.blocks_per_sample, n_samples);
+    // as many threads as a workgroup's share has groups of kUnroll chunks, in whole waves
+    const int64_t share = elems_per_sample < kElemsPerBlock ? elems_per_sample : kElemsPerBlock;
+    const bool is_bf16 = dtype == ASTRO_BF16;
+    const int per_thread = N * (is_bf16 ? Chunk<__bf16>::kUnroll : Chunk<float>::kUnroll);
+    const int most = is_bf16 ? Chunk<__bf16>::kThreads : Chunk<float>::kThreads;
+    const int64_t want = ((share + per_thread - 1) / per_thread + 63) / 64 * 64;
+    const int threads = want < most ? (int)want : most;
     if (n_samples <= kMaxSamplesInline) {
-      if (dtype == ASTRO_BF16)
-        nft_loss_kernel<__bf16, true><<<grid, kThreads, 0, stream>>>(p);
+      if (is_bf16)
+        nft_loss_kernel<__bf16, true><<<grid, threads, 0, stream>>>(p);
       else
-        nft_loss_kernel<float, true><<<grid, kThreads, 0, stream>>>(p);
+        nft_loss_kernel<float, true><<<grid, threads, 0, stream>>>(p);
     } else {
       nft_prepare_kernel<<<1, kThreads, 0, stream>>>(p);
-      if (dtype == ASTRO_BF16)
-        nft_loss_kernel<__bf16, false><<<grid, kThreads, 0, stream>>>(p);
+      if (is_bf16)
+        nft_loss_kernel<__bf16, false><<<grid, threads, 0, stream>>>(p);
       else
-        nft_loss_kernel<float, false><<<grid, kThreads, 0, stream>>>(p);
+        nft_loss_kernel<float, false><<<grid, threads, 0, stream>>>(p);
     }
-    nft_finalize_kernel<<<1, kThreads, 0, stream>>>(p);
+    nft_finalize_kernel<<<1, kFinalThreads, 0, stream>>>(p);
   }
   return hipGetLastError() == hipSuccess ? ASTRO_OK : ASTRO_ERR_HIP;
 }
