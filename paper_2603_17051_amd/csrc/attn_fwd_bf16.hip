@@ -37,6 +37,7 @@ namespace astro {
 namespace {
 
 constexpr int KT = 32;                 // keys per LDS tile
+constexpr int kMaxFwdSplits = 8;       // most key ranges of a launch
 constexpr float kSumLimit = 0x1p44f;  // a lane's 16 probabilities may sum to this before the reference moves
 // a first tile whose rows sum to less than this relative to 0 takes its reference from its maximum instead
 constexpr float kFirstSumLimit = 0x1p-32f;
@@ -585,36 +586,47 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
 }
 
 // Combine the per-split results: softmax over the union of the splits' keys is the average of the
-// splits' outputs weighted by exp(lse_s - lse).  One wave per (stream, query, head) row.
+// splits' outputs weighted by exp(lse_s - lse).  Bound by the parts' bytes (they were written just
+// before: 57 MB at 4 splits of 4680 x 12 rows of 128).  Sixteen bytes per lane, so a wave takes 64 / CPR rows of
+// (stream, query, head), and all parts of a row are in flight before the first is used (one wave per
+// row and 4 bytes per lane, a part at a time: 29 us there).
 template <int D>
 __global__ void __launch_bounds__(256) fwd_merge_kernel(FwdParams p, int64_t n_rows) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (b*Nq + q)*H + h
+  constexpr int CPR = D / 8;
+  const int64_t row = (int64_t)blockIdx.x * (256 / CPR) + threadIdx.x / CPR;  // (b*Nq + q)*H + h
   if (row >= n_rows) return;
-  const int lane = threadIdx.x & 63;
+  const int c = threadIdx.x % CPR;
   const int h = (int)(row % p.H);
   const int64_t bq = row / p.H;
   const int q = (int)(bq % p.Nq);
   const int64_t b = bq / p.Nq;
   const int64_t lse_at = (b * p.H + h) * p.Nq + q;
   const int64_t out_stride = (int64_t)p.BH * p.Nq * D, lse_stride = (int64_t)p.BH * p.Nq;
+  bf16x8 o[kMaxFwdSplits];
+  float l[kMaxFwdSplits];
   float m = kNegBig;
-  for (int s = 0; s < p.splits; ++s) m = fmaxf(m, p.lse_part[s * lse_stride + lse_at]);
-  float tot = 0.f, a0 = 0.f, a1 = 0.f;
-  for (int s = 0; s < p.splits; ++s) {
-    const float w = __expf(p.lse_part[s * lse_stride + lse_at] - m);
-    tot += w;
-    if (lane < D / 2) {
-      const bf16x2 o = *reinterpret_cast<const bf16x2*>(p.out_part + s * out_stride + row * D + lane * 2);
-      a0 = fmaf(w, (float)o[0], a0);
-      a1 = fmaf(w, (float)o[1], a1);
+#pragma unroll
+  for (int s = 0; s < kMaxFwdSplits; ++s)
+    if (s < p.splits) {
+      o[s] = *reinterpret_cast<const bf16x8*>(p.out_part + s * out_stride + row * D + c * 8);
+      l[s] = p.lse_part[s * lse_stride + lse_at];
+      m = fmaxf(m, l[s]);
     }
-  }
+  float tot = 0.f, a[8] = {};
+#pragma unroll
+  for (int s = 0; s < kMaxFwdSplits; ++s)
+    if (s < p.splits) {
+      const float w = __expf(l[s] - m);
+      tot += w;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) a[j] = fmaf(w, (float)o[s][j], a[j]);
+    }
   const float inv = 1.f / tot;
-  if (lane < D / 2) {
-    const bf16x2 o = {(__bf16)(a0 * inv), (__bf16)(a1 * inv)};
-    *reinterpret_cast<bf16x2*>(p.out + row * D + lane * 2) = o;
-  }
-  if (lane == 0) p.lse[lse_at] = m + __logf(tot);
+  bf16x8 x;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x[j] = (__bf16)(a[j] * inv);
+  *reinterpret_cast<bf16x8*>(p.out + row * D + c * 8) = x;
+  if (c == 0) p.lse[lse_at] = m + __logf(tot);
 }
 
 FwdParams make_params(const DevGeom& g, const AttnOperands& op, void* out, float* lse) {
@@ -666,7 +678,8 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
   if (p.splits > 1) {
     const int64_t n_rows = (int64_t)p.BH * op.Nq;
     ProfileScope prof("attn_fwd_merge", stream);
-    fwd_merge_kernel<D><<<dim3((unsigned)((n_rows + 3) / 4)), 256, 0, stream>>>(p, n_rows);
+    constexpr int kRows = 256 / (D / 8);
+    fwd_merge_kernel<D><<<dim3((unsigned)((n_rows + kRows - 1) / kRows)), 256, 0, stream>>>(p, n_rows);
   }
   return hipGetLastError();
 }
@@ -678,7 +691,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
 // stream of 12 heads and 37 query tiles is 444 workgroups on 768 places) each (pair, query
 // tile) is cut into `splits` key ranges, enough for two rounds, at most kMaxFwdSplits and
 // never less than kMinTilesPerSplit key tiles each.
-constexpr int kMaxFwdSplits = 8, kMinTilesPerSplit = 4, kFwdWorkgroupsPerCu = 3;
+constexpr int kMinTilesPerSplit = 4, kFwdWorkgroupsPerCu = 3;
 
 static int fwd_work_items(const DevGeom& g, int Nq) { return ((Nq + 127) / 128) * g.B * g.H; }
 
