@@ -128,7 +128,8 @@ def _ptr(t) -> c_void_p:
 
 def _stream(stream) -> c_void_p:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without building a Stream object (2.7 us of a small call's 13)
+        return c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return c_void_p(stream.cuda_stream)
 
 
@@ -162,6 +163,9 @@ class KVCache:
         self.v_storage = v_storage
         self.k_sink_storage = k_sink_storage
         self._workspace = None
+        # the desc as plain values: every call checks its tensors against them
+        self._dims = (desc.batch, desc.grid_h * desc.grid_w, desc.heads, desc.head_dim)
+        self._torch_dtype = torch.bfloat16 if desc.dtype == ASTRO_BF16 else torch.float32
 
     @property
     def tokens_per_frame(self) -> int:
@@ -169,7 +173,7 @@ class KVCache:
 
     @property
     def torch_dtype(self):
-        return torch.bfloat16 if self.desc.dtype == ASTRO_BF16 else torch.float32
+        return self._torch_dtype
 
     def workspace(self, nbytes: int, device) -> torch.Tensor:
         if self._workspace is None or self._workspace.numel() < nbytes:
@@ -220,10 +224,11 @@ def astro_kvcache_reset(cache: KVCache, stream_index: int = -1, start_frame: int
 
 
 def _check_chunk_tensor(cache: KVCache, t: torch.Tensor, n_frames: int, name: str, dtype=None, group: int = 1) -> None:
-    d = cache.desc
-    shape = (d.batch * group, n_frames * cache.tokens_per_frame, d.heads, d.head_dim)
-    if tuple(t.shape) != shape or not t.is_contiguous() or t.dtype != (dtype or cache.torch_dtype):
-        raise ValueError(f"{name}: expected contiguous {dtype or cache.torch_dtype} tensor of shape {shape}, "
+    batch, tokens, heads, head_dim = cache._dims
+    shape = (batch * group, n_frames * tokens, heads, head_dim)
+    want = dtype or cache._torch_dtype
+    if t.shape != shape or t.dtype != want or not t.is_contiguous():
+        raise ValueError(f"{name}: expected contiguous {want} tensor of shape {shape}, "
                          f"got {t.dtype} {tuple(t.shape)}")
     if not t.is_cuda:
         raise ValueError(f"{name}: must be a device tensor")
