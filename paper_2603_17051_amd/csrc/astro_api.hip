@@ -61,10 +61,10 @@ DevGeom dev_geom(const astro_kvcache* c, int group = 1) {
 }
 
 struct Workspace {
-  size_t q_rot, kc_rot, tab_t, staged_end, dq_rot, dk_rot, scratch, dk_hist_rot, total;
+  size_t q_rot, kc_rot, tab_t, staged_end, dq_rot, dk_rot, scratch, total;
 };
 
-Workspace carve(const astro_kvcache* c, int n_frames, bool bwd, int group, bool ring_grads = false) {
+Workspace carve(const astro_kvcache* c, int n_frames, bool bwd, int group) {
   const RingGeometry& g = c->geo;
   const size_t nq = (size_t)n_frames * g.T;
   const size_t rot = align256((size_t)g.B * group * g.H * nq * g.D * g.elem_bytes());
@@ -91,8 +91,6 @@ Workspace carve(const astro_kvcache* c, int n_frames, bool bwd, int group, bool 
     off += align256(bf16_bwd_workspace_bytes(d, (int)nq));
   else
     off += align256(bf16_fwd_split_bytes(d, (int)nq));
-  w.dk_hist_rot = off;
-  if (ring_grads) off += align256((size_t)g.B * g.H * g.rows_per_head() * g.D * sizeof(float));
   w.total = off;
   return w;
 }
@@ -404,7 +402,7 @@ int astro_chunk_attn_bwd_full_workspace_bytes(const astro_kvcache_t* cache, int3
   if (!cache || !bytes) return ASTRO_ERR_INVALID_ARG;
   if (n_frames < 1 || n_frames > cache->geo.max_chunk) return ASTRO_ERR_INVALID_ARG;
   if (cache->geo.dtype != ASTRO_BF16) return ASTRO_ERR_UNSUPPORTED;
-  *bytes = carve(cache, n_frames, true, 1, true).total;
+  *bytes = carve(cache, n_frames, true, 1).total;
   return ASTRO_OK;
 }
 
@@ -416,29 +414,25 @@ int astro_chunk_attn_bwd_full(astro_kvcache_t* cache, const void* q, const void*
   if (rc != ASTRO_OK) return rc;
   if (cache->geo.dtype != ASTRO_BF16) return ASTRO_ERR_UNSUPPORTED;
   if (!dk_cache || !dv_cache) return ASTRO_ERR_INVALID_ARG;
-  const Workspace w = carve(cache, n_frames, true, 1, true);
+  const Workspace w = carve(cache, n_frames, true, 1);
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace & 255)) return ASTRO_ERR_WORKSPACE;
   // the detached backward first (it also leaves the row terms the ring-row kernels need) ...
   const int rc2 = astro_group_attn_bwd(cache, q, k_chunk, v_chunk, out, lse, dout, n_frames, 1, dq, dk_chunk, dv_chunk,
                                        workspace, workspace_bytes, hip_stream);
   if (rc2 != ASTRO_OK) return rc2;
-  // ... then dK~, dV of the resident ring rows, and the inverse rotation at each slot's frame
+  // ... then dK, dV of the resident ring rows
   char* ws = (char*)workspace;
-  hipStream_t stream = (hipStream_t)hip_stream;
   const AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, 1);
-  const DevGeom d = dev_geom(cache);
-  float* dk_hist_rot = (float*)(ws + w.dk_hist_rot);
-  if (launch_attn_bwd_hist_bf16(d, op, lse, dout, dk_hist_rot, dv_cache, ws + w.scratch, stream) != hipSuccess)
-    return ASTRO_ERR_HIP;
   StreamInts start, next, sink_shift;
   for (int b = 0; b < ASTRO_MAX_BATCH; ++b) {
     start.v[b] = b < cache->geo.B ? cache->tables.start(b) : 0;
     next.v[b] = b < cache->geo.B ? cache->tables.next_n(b) : 0;
     sink_shift.v[b] = b < cache->geo.B && cache->geo.sinks_move() ? cache->tables.evicted(b) : 0;
   }
-  if (launch_rope_unscatter_ring_f32(d, dk_hist_rot, dk_cache, start, next, sink_shift, stream) != hipSuccess)
-    return ASTRO_ERR_HIP;
-  return ASTRO_OK;
+  return launch_attn_bwd_hist_bf16(dev_geom(cache), op, lse, dout, dk_cache, dv_cache, start, next, sink_shift, ws + w.scratch,
+                                   (hipStream_t)hip_stream) == hipSuccess
+             ? ASTRO_OK
+             : ASTRO_ERR_HIP;
 }
 
 int astro_chunk_attn_workspace_bytes(const astro_kvcache_t* cache, int32_t n_frames, size_t* fwd_bytes,

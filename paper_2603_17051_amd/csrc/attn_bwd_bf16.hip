@@ -15,6 +15,7 @@
 // the tile's rows).
 #include "kernels.hpp"
 #include "mfma_common.hpp"
+#include "ring_state.hpp"
 
 namespace astro {
 namespace {
@@ -39,9 +40,6 @@ struct BwdParams {
   float* dk;      // [B, Nq, H, D]  w.r.t. the un-rotated chunk keys
   float* dv;      // [B, Nq, H, D]
   RotaryTables rot;
-  float* dk_hist_rot;  // [B][H][C*T][D]   (only when hist_keys)
-  float* dv_hist;      // [B, C*T, H, D]
-  int hist_keys;       // dK/dV kernel: 0 = the chunk's keys, 1 = the resident ring rows (group must be 1)
   int H, Nq, BH, tiles;  // BH = candidates * heads; tiles = workgroups per pair of the kernel being launched
   int group;             // candidates per cache stream
   int block_rows;        // causal block inside the chunk in token rows, 0 = none
@@ -527,10 +525,34 @@ struct KeyWave {
   }
 };
 
+// The dK/dV kernel over the resident ring rows instead of the chunk's keys (non-detached backward, group
+// 1): where the gradients go and what is needed to turn dK~ back at the frame each slot holds.
+struct RingGrads {
+  float* dk;  // [B, C*T, H, D]  w.r.t. the keys as they were appended (un-rotated)
+  float* dv;  // [B, C*T, H, D]
+  const double* inv_freq_t;
+  int C, S;
+  StreamInts start, next_n, sink_shift;  // see launch_attn_bwd_hist_bf16
+};
+struct ChunkGrads {};  // the chunk's keys: everything is in BwdParams
+
+// (cos, sin) of the temporal pairs at the frames of ring slots first .. first + n - 1 of stream b, for `threads` threads
+__device__ __forceinline__ void fill_slot_table(float2* tab, const BwdParams& p, const RingGrads& r, int b, int first, int n,
+                                                int thread, int threads) {
+  for (int e = thread; e < n * p.rot.n_t; e += threads) {
+    const int slot = first + e / p.rot.n_t, j = e % p.rot.n_t;
+    const int frame = r.start.v[b] + (int)frame_number_in_slot(slot, r.next_n.v[b], r.C, r.S) + (slot < r.S ? r.sink_shift.v[b] : 0);
+    double sn, cs;
+    sincos((double)frame * r.inv_freq_t[j], &sn, &cs);
+    tab[e] = make_float2((float)cs, (float)sn);
+  }
+}
+
 // Everything one wave does, in its role (kKey: a key wave, else a value wave).  Both roles
 // stream the tiles and meet at the same barriers, one per period.
-template <int D, bool kKey>
-__device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& item, int wave, char* lds) {
+template <int D, bool kKey, typename Grads>
+__device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads, const WorkItem& item, int wave, char* lds) {
+  constexpr bool kRing = std::is_same_v<Grads, RingGrads>;
   using L = DkvLds<D>;
   using Wave = std::conditional_t<kKey, KeyWave<D>, ValueWave<D>>;
   const int b = item.bh / p.H, h = item.bh % p.H;
@@ -539,12 +561,12 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& ite
   const int i16 = lane & 15, g = lane >> 4;
   const int64_t bh = (int64_t)b * p.H + h;
   // this lane's two keys jc and jc + 16: chunk rows, or (non-detached backward) resident ring rows of the stream
-  const int n_keys = p.hist_keys ? p.hist_rows.v[b] : p.Nq;
+  const int n_keys = kRing ? p.hist_rows.v[b] : p.Nq;
   const int jc = (item.tile * 4 + kw) * 32 + i16;
   const int ntiles = (p.Nq + QT - 1) / QT;
   // first query row that sees each of this lane's keys (ring rows are seen by every query), the
   // largest over the wave (its last key) and the smallest over the workgroup (its first key)
-  const int block_rows = p.hist_keys ? 0 : p.block_rows;
+  const int block_rows = kRing ? 0 : p.block_rows;
   const int j_last = n_keys - 1;
   int first_q[2];
 #pragma unroll
@@ -562,9 +584,9 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& ite
     const int j0 = live ? jc + 16 * ks : 0;
     const __bf16* row;
     if constexpr (kKey)
-      row = p.hist_keys ? p.v_cache + (bh * p.cache_rows + j0) * D : p.v_chunk + (((int64_t)b * p.Nq + j0) * p.H + h) * D;
+      row = kRing ? p.v_cache + (bh * p.cache_rows + j0) * D : p.v_chunk + (((int64_t)b * p.Nq + j0) * p.H + h) * D;
     else
-      row = p.hist_keys ? p.k_cache + (bh * p.cache_rows + j0) * D : p.kc_rot + (bh * p.Nq + j0) * D;
+      row = kRing ? p.k_cache + (bh * p.cache_rows + j0) * D : p.kc_rot + (bh * p.Nq + j0) * D;
 #pragma unroll
     for (int st = 0; st < D / 32; ++st) {
       bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -604,6 +626,21 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& ite
   // Period n: the value waves work on tile n (slot S), the key waves on tile n - 1 (slot S - 1),
   // tile n + 1 streams into slot S + 1; the last period has only the key waves' tile left.
   const int probs_lane = kw * (QT / 32) * 2 * 1024 + lane * 16;
+  // Ring rows: the epilogue needs (cos, sin) of the temporal pairs at the frames of this workgroup's
+  // keys.  The value waves have no tile in the last period: they compute the table there, into that
+  // period's own slot, which no tile was loaded for.  (By the key waves in their idle first period, into
+  // LDS of its own, the loop came out slower: 3661 against 3531 us for the whole pass of one clip.)  Where it
+  // does not fit the slot (frames of a token and many temporal pairs) all waves do it afterwards in the
+  // idle tile ring.
+  int slot_first = 0, slot_count = 0;
+  bool in_slot = true;
+  if constexpr (kRing) {
+    const int j_first = item.tile * 128, j_end = j_first + 128 < n_keys ? j_first + 128 : n_keys;
+    slot_first = j_first / p.rot.T;
+    slot_count = (j_end - 1) / p.rot.T - slot_first + 1;
+    static_assert(129 * (D / 2) * 8 <= 3 * L::SLOT_TILES, "the largest table fits the tile ring");
+    in_slot = slot_count * p.rot.n_t * (int)sizeof(float2) <= L::SLOT_TILES;
+  }
   auto period = [&](int n, auto slot_c) __attribute__((always_inline)) {
     constexpr int S = decltype(slot_c)::value, PREV = (S + 2) % 3, NEXT = (S + 1) % 3;
     if (n + 1 < ntiles) issue(n + 1, NEXT);
@@ -613,6 +650,10 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& ite
                reinterpret_cast<const float*>(lds + L::kTerms + PREV * L::SLOT_TERMS) + QT,
                lds + L::kProbs + PREV * L::SLOT_PROBS + probs_lane);
     } else {
+      if constexpr (kRing) {
+        if (n == ntiles && in_slot)
+          fill_slot_table(reinterpret_cast<float2*>(lds + S * L::SLOT_TILES), p, grads, b, slot_first, slot_count, threadIdx.x, 256);
+      }
       if (n < ntiles) {
         const int first[2] = {first_q[0] - n * QT, first_q[1] - n * QT};
         w.tile(lds + S * L::SLOT_TILES, lds + S * L::SLOT_TILES + L::TILE_BYTES,
@@ -632,21 +673,33 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& ite
     if (++n > ntiles) break;
   }
 
-  // dV as it is; dK~ of chunk keys is turned back to dK here (ring rows keep the rotated frame:
-  // the frame a slot holds is looked up by the pass that follows)
-  const bool rope = kKey && !p.hist_keys && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  const float2* slot_tab = nullptr;
+  if constexpr (kRing) {
+    slot_tab = reinterpret_cast<const float2*>(lds + (in_slot ? (ntiles - t_begin) % 3 * L::SLOT_TILES : 0));
+    if (!in_slot) {
+      fill_slot_table(reinterpret_cast<float2*>(lds), p, grads, b, slot_first, slot_count, threadIdx.x, kPairThreads);
+      __syncthreads();
+    }
+  }
+
+  // dV as it is; dK~ is turned back to dK here
+  const bool rope = kKey && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     const int j = jc + 16 * ks;
     if (j >= n_keys) continue;
     float* row;
-    if constexpr (kKey)
-      row = p.hist_keys ? p.dk_hist_rot + (bh * p.cache_rows + j) * D : p.dk + (((int64_t)b * p.Nq + j) * p.H + h) * D;
-    else
-      row = p.hist_keys ? p.dv_hist + (((int64_t)b * p.cache_rows + j) * p.H + h) * D
-                        : p.dv + (((int64_t)b * p.Nq + j) * p.H + h) * D;
     TokenTables tt{};
-    if (rope) tt = token_tables(p.rot, b, j);
+    if constexpr (kRing) {
+      row = (kKey ? grads.dk : grads.dv) + (((int64_t)b * p.cache_rows + j) * p.H + h) * D;
+      if (rope) {
+        const int slot = j / p.rot.T, rem = j - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
+        tt = TokenTables{slot_tab + (slot - slot_first) * p.rot.n_t, p.rot.tab_h + y * p.rot.n_h, p.rot.tab_w + x * p.rot.n_w};
+      }
+    } else {
+      row = (kKey ? p.dk : p.dv) + (((int64_t)b * p.Nq + j) * p.H + h) * D;
+      if (rope) tt = token_tables(p.rot, b, j);
+    }
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt) {
       f32x4 x;
@@ -661,20 +714,21 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const WorkItem& ite
   }
 }
 
-template <int D>
-__global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams p) {
+template <int D, typename Grads>
+__global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams p, Grads grads) {
+  constexpr bool kRing = std::is_same_v<Grads, RingGrads>;
   __shared__ __attribute__((aligned(1024))) char lds[DkvLds<D>::kTotal];
   const WorkItem item = work_item(p.tiles, p.BH, false);
   if (!item.valid) return;
-  const int n_keys = p.hist_keys ? p.hist_rows.v[item.bh / p.H] : p.Nq;
+  const int n_keys = kRing ? p.hist_rows.v[item.bh / p.H] : p.Nq;
   if (item.tile * 128 >= n_keys) return;  // whole workgroup, before any barrier
   // waves 0..3 accumulate dV, waves 4..7 dK; the branch is per wave, and both sides execute
   // the same sequence of barriers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave >= 4)
-    dkv_wave<D, true>(p, item, wave, lds);
+    dkv_wave<D, true>(p, grads, item, wave, lds);
   else
-    dkv_wave<D, false>(p, item, wave, lds);
+    dkv_wave<D, false>(p, grads, item, wave, lds);
 }
 
 // ---- launches with few rows ------------------------------------------------------------------------
@@ -1017,9 +1071,6 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   p.hist_rows = op.hist_rows;
   p.group = op.group;
   p.block_rows = op.block_rows;
-  p.dk_hist_rot = nullptr;
-  p.dv_hist = nullptr;
-  p.hist_keys = 0;
   return p;
 }
 
@@ -1064,35 +1115,34 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   {
     ProfileScope prof("attn_bwd_dkv_bf16", stream);
     p.tiles = (op.Nq + ktile - 1) / ktile;
-    attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p);
+    attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, ChunkGrads{});
   }
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* lse, const void* dout, float* dk_hist_rot,
-                       float* dv_hist, const void* scratch, hipStream_t stream) {
+hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* lse, const void* dout, const RingGrads& grads,
+                       const void* scratch, hipStream_t stream) {
   BwdParams p = make_params<D>(g, op, nullptr, lse, dout, nullptr, nullptr, nullptr, const_cast<void*>(scratch));
-  p.dk_hist_rot = dk_hist_rot;
-  p.dv_hist = dv_hist;
-  p.hist_keys = 1;
   int max_hist = 0;
   for (int b = 0; b < g.B; ++b) max_hist = op.hist_rows.v[b] > max_hist ? op.hist_rows.v[b] : max_hist;
   if (max_hist == 0) return hipSuccess;
   const int ktile = 128;
   p.tiles = (max_hist + ktile - 1) / ktile;
   ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
-  attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p);
+  attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, grads);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_attn_bwd_hist_bf16(const DevGeom& g, const AttnOperands& op, const float* lse, const void* dout,
-                                     float* dk_hist_rot, float* dv_hist, const void* scratch, hipStream_t stream) {
+                                     float* dk_hist, float* dv_hist, const StreamInts& start, const StreamInts& next_n,
+                                     const StreamInts& sink_shift, const void* scratch, hipStream_t stream) {
   if (op.group != 1) return hipErrorInvalidValue;
-  if (g.D == 128) return launch_hist<128>(g, op, lse, dout, dk_hist_rot, dv_hist, scratch, stream);
-  return launch_hist<64>(g, op, lse, dout, dk_hist_rot, dv_hist, scratch, stream);
+  const RingGrads grads{dk_hist, dv_hist, g.inv_freq_t, g.C, g.S, start, next_n, sink_shift};
+  if (g.D == 128) return launch_hist<128>(g, op, lse, dout, grads, scratch, stream);
+  return launch_hist<64>(g, op, lse, dout, grads, scratch, stream);
 }
 
 // Delta and LSE*log2e per (stream, head, query)

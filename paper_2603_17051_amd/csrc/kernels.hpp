@@ -64,14 +64,6 @@ hipError_t launch_rope_scatter(const DevGeom& g, int dtype, const void* a_in, co
 hipError_t launch_rope_unscatter_f32(const DevGeom& g, const float* src, float* dst, int n_frames,
                                      const StreamInts& first_frame, hipStream_t stream);
 
-// The same for gradients of the ring rows: src [B][H][C*T][D] (rotated frame) -> dst
-// [B, C*T, H, D] w.r.t. the un-rotated keys; the frame a slot holds follows from start and
-// next_n (frames appended); rows of empty slots are not written.  sink_shift.v[b] = how far
-// ahead of their own frame index stream b's sink slots are rotated (0 with absolute positions).
-hipError_t launch_rope_unscatter_ring_f32(const DevGeom& g, const float* src, float* dst,
-                                          const StreamInts& start, const StreamInts& next_n,
-                                          const StreamInts& sink_shift, hipStream_t stream);
-
 // Window-relative temporal positions: rotate the sink frames' keys again from their un-rotated
 // copy sink_raw [B, S*T, H, D] into ring slots 0 .. S-1 of k_cache [B][H][C*T][D]; sink s of
 // stream b is rotated at frame position first_pos.v[b] + s, and only the first count.v[b]
@@ -119,12 +111,15 @@ size_t bf16_bwd_workspace_bytes(const DevGeom& g, int Nq);  // beyond q_rot / kc
 hipError_t launch_attn_bwd_bf16(const DevGeom& g, const AttnOperands& op, const void* out,
                                 const float* lse, const void* dout, float* dq, float* dk,
                                 float* dv, void* scratch, hipStream_t stream);
-// Gradients of the ring rows (the non-detached backward): dk_hist_rot [B][H][C*T][D] w.r.t. the
-// rotated keys as cached, dv_hist [B, C*T, H, D]; rows of empty slots are not written.  Needs
+// Gradients of the ring rows (the non-detached backward): dk_hist, dv_hist [B, C*T, H, D] w.r.t. the
+// keys as they were appended (un-rotated) and the values; rows of empty slots are not written.  The
+// frame a slot holds follows from start and next_n (frames appended); sink_shift.v[b] = how far ahead
+// of their own frame index stream b's sink slots are rotated (0 with absolute positions).  Needs
 // the row terms launch_attn_bwd_bf16 left in `scratch` (same call sequence, same stream);
 // group must be 1.
 hipError_t launch_attn_bwd_hist_bf16(const DevGeom& g, const AttnOperands& op, const float* lse,
-                                     const void* dout, float* dk_hist_rot, float* dv_hist,
-                                     const void* scratch, hipStream_t stream);
+                                     const void* dout, float* dk_hist, float* dv_hist, const StreamInts& start,
+                                     const StreamInts& next_n, const StreamInts& sink_shift, const void* scratch,
+                                     hipStream_t stream);
 
 }  // namespace astro

@@ -297,10 +297,12 @@ __device__ __forceinline__ TokenTables token_tables(const RotaryTables& r, int b
   const int row = rem / r.gw, col = rem - row * r.gw;
   return TokenTables{r.tab_t + ((int64_t)b * r.n_frames + fi) * r.n_t, r.tab_h + row * r.n_h, r.tab_w + col * r.n_w};
 }
+// One load from a selected address: with a branch per table the 16 or 32 look-ups of an epilogue waited
+// for one another.
 __device__ __forceinline__ float2 pair_cos_sin(const RotaryTables& r, const TokenTables& t, int pair) {
-  if (pair < r.n_t) return t.t[pair];
-  pair -= r.n_t;
-  return pair < r.n_h ? t.h[pair] : t.w[pair - r.n_h];
+  const int nb = r.n_t + r.n_h;
+  const float2* base = pair < r.n_t ? t.t : (pair < nb ? t.h : t.w);
+  return base[pair < r.n_t ? pair : (pair < nb ? pair - r.n_t : pair - nb)];
 }
 // x = four consecutive components 4*quad .. 4*quad+3 (two adjacent pairs) of a gradient w.r.t. the
 // rotated vector; returns them w.r.t. the un-rotated one: R(phi)^T applied to each pair.

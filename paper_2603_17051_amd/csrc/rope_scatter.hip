@@ -179,21 +179,6 @@ __global__ void __launch_bounds__(kThreads) rope_unscatter_f32_kernel(DevGeom g,
   unrotate_row(g, tab, rope, src, dst, b, h, (int64_t)fi * g.T + (int64_t)row * g.gw, (int64_t)n_frames * g.T);
 }
 
-// gradients of the ring rows: slot s of stream b holds the frame the closed form names; empty
-// slots are skipped (their rows of dst are not written)
-__global__ void __launch_bounds__(kThreads) rope_unscatter_ring_f32_kernel(DevGeom g, const float* __restrict__ src,
-                                                                           float* __restrict__ dst, StreamInts start,
-                                                                           StreamInts next_n, StreamInts sink_shift) {
-  __shared__ float2 tab[kMaxBlockPairs];
-  const int slot = blockIdx.x / g.gh, row = blockIdx.x % g.gh;
-  const int h = blockIdx.y, b = blockIdx.z;
-  const int64_t n = frame_number_in_slot(slot, next_n.v[b], g.C, g.S);
-  if (n < 0) return;  // whole block
-  const bool rope = (g.n_t + g.n_h + g.n_w) != 0;
-  if (rope) fill_block_table(tab, g, start.v[b] + (int)n + (slot < g.S ? sink_shift.v[b] : 0), row);
-  unrotate_row(g, tab, rope, src, dst, b, h, (int64_t)slot * g.T + (int64_t)row * g.gw, (int64_t)g.C * g.T);
-}
-
 // Sink keys rotated again at a new frame position (window-relative temporal positions): one
 // block = one token row of one sink frame of one head; un-rotated token-major rows in,
 // head-major ring rows (slot = the sink's own number) out.  A few MB per call: one 16-byte
@@ -260,14 +245,6 @@ hipError_t launch_rope_unscatter_f32(const DevGeom& g, const float* src, float* 
   dim3 grid(n_frames * g.gh, g.H, g.B), block(kThreads);
   ProfileScope prof("grad_rope_unstage", stream);
   rope_unscatter_f32_kernel<<<grid, block, 0, stream>>>(g, src, dst, n_frames, first_frame);
-  return hipGetLastError();
-}
-
-hipError_t launch_rope_unscatter_ring_f32(const DevGeom& g, const float* src, float* dst, const StreamInts& start,
-                                          const StreamInts& next_n, const StreamInts& sink_shift, hipStream_t stream) {
-  dim3 grid(g.C * g.gh, g.H, g.B), block(kThreads);
-  ProfileScope prof("grad_rope_unstage_ring", stream);
-  rope_unscatter_ring_f32_kernel<<<grid, block, 0, stream>>>(g, src, dst, start, next_n, sink_shift);
   return hipGetLastError();
 }
 
