@@ -217,14 +217,30 @@ struct DqWave {
   }
 };
 
-template <int D, int OCC, int kWaves>
-__global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams p) {
+// Key split of launches that fill the CUs' places at most once and only in part (12 heads of one stream
+// are 444 workgroups on 512 places: 68 CUs hold one workgroup and idle half of the launch; 3 heads are
+// 111).  With `ways` = 2 the last 1 / (k + 1) of every item's key tiles go to helper workgroups, one per k
+// items, so that all do the same number of tiles; with `ways` = 3 every item is cut in three and has two
+// helpers.  Main and helpers leave fp32 partial sums that a small launch adds up and turns back.
+// ways = 1: no split.
+struct DqSplit {
+  int ways, k;
+  // [B, Nq, H, D]: the helpers' sums (the dK and dV outputs: the kernel that fills them runs later)
+  float *part1, *part2;
+  __host__ __device__ int helpers(int items) const { return ways == 3 ? 2 * items : (items + k - 1) / k; }
+  // first tile of part `which` of an item of `ntiles` tiles (a helper of k items spends about two tiles on each besides)
+  __device__ int first_tile(int which, int ntiles) const {
+    if (ways == 3) return which * ntiles / 3;
+    const int cut = (k * ntiles + 2 * (k - 1) + k) / (k + 1);
+    return which == 0 ? 0 : (which == 1 && cut < ntiles ? cut : ntiles);
+  }
+};
+
+// One item (kSplit: part `which` of it, 0 = the main workgroup's)
+template <int D, int kWaves, bool kSplit>
+__device__ __forceinline__ void dq_item(const BwdParams& p, const DqSplit& split, const WorkItem& item, int which, char* lds) {
   using Wave = DqWave<D>;
   constexpr int TILE_BYTES = KT * D * 2;
-  __shared__ __attribute__((aligned(1024))) char lds[4 * TILE_BYTES];  // K0 V0 K1 V1
-
-  const WorkItem item = work_item(p.tiles, p.BH, true);
-  if (!item.valid) return;
   const PairIndex pair = split_pair(item.bh, p.H, p.group);
   const int b = pair.b, h = pair.h;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -244,10 +260,12 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams
   const int vis_wg = visible_chunk_rows(q_wg < q_last ? q_wg : q_last, p.Nq, p.block_rows);
   const int hist_tiles = (hist + KT - 1) / KT;
   const int ntiles = hist_tiles + (vis_wg + KT - 1) / KT;
+  const int t_begin = kSplit ? split.first_tile(which, ntiles) : 0;
+  const int t_end = kSplit ? split.first_tile(which + 1, ntiles) : ntiles;
 
   Wave w;
   w.init(lane);
-  w.load_queries(p, b, h, q0, true);
+  w.load_queries(p, b, h, q0, which == 0);
 
   const RowSegment k_hist = make_segment(p.k_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
   const RowSegment v_hist = make_segment(p.v_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
@@ -258,7 +276,7 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams
   const uint32_t off_dense = ts.lane_offset(k_hist);
   const uint32_t off_vchunk = ts.lane_offset(v_chunk);
   auto issue = [&](int t) {
-    char* kbuf = lds + (t & 1) * 2 * TILE_BYTES;
+    char* kbuf = lds + ((t - t_begin) & 1) * 2 * TILE_BYTES;
     if (t < hist_tiles) {
       ts.issue(k_hist, off_dense, t * KT, kbuf);
       ts.issue(v_hist, off_dense, t * KT, kbuf + TILE_BYTES);
@@ -267,13 +285,13 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams
       ts.issue(v_chunk, off_vchunk, (t - hist_tiles) * KT, kbuf + TILE_BYTES);
     }
   };
-  issue(0);
+  if (t_begin < t_end) issue(t_begin);
   wait_vmem();
   __syncthreads();
 
   // two tiles per trip so that each LDS buffer is a compile-time offset of the operand reads
   auto step = [&](int t, auto buf_c) __attribute__((always_inline)) {
-    if (t + 1 < ntiles) issue(t + 1);
+    if (t + 1 < t_end) issue(t + 1);
     const char* kbuf = lds + decltype(buf_c)::value * 2 * TILE_BYTES;
     int live[2];
 #pragma unroll
@@ -282,27 +300,91 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams
     wait_vmem();
     __syncthreads();
   };
-  for (int t = 0; t < ntiles; t += 2) {
+  for (int t = t_begin; t < t_end; t += 2) {
     step(t, std::integral_constant<int, 0>{});
-    if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
+    if (t + 1 < t_end) step(t + 1, std::integral_constant<int, 1>{});
   }
 
   // dQ~ -> dQ: the rotation is turned back here (each lane holds both halves of its pairs), so the
   // gradient goes out once, token-major, instead of through a rotated fp32 copy and another pass
-  const bool rope = p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  const bool rope = !kSplit && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
 #pragma unroll
   for (int qs = 0; qs < 2; ++qs) {
     const int q = q0 + 16 * qs;
     if (q < p.Nq) {
-      float* row = p.dq + (((int64_t)b * p.Nq + q) * p.H + h) * D;
-      const TokenTables tt = token_tables(p.rot, b, q);
+      float* row = (which == 0 ? p.dq : (which == 1 ? split.part1 : split.part2)) + (((int64_t)b * p.Nq + q) * p.H + h) * D;
+      TokenTables tt{};
+      if (rope) tt = token_tables(p.rot, b, q);
 #pragma unroll
       for (int dt = 0; dt < Wave::DT; ++dt) {
-        f32x4 x = w.dq[dt][qs] * p.scale;
-        if (rope) x = unrotate_quad(p.rot, tt, 4 * dt + g, x);
+        f32x4 x = w.dq[dt][qs];
+        if constexpr (!kSplit) {
+          x = x * p.scale;
+          if (rope) x = unrotate_quad(p.rot, tt, 4 * dt + g, x);
+        }
         *reinterpret_cast<f32x4*>(row + 16 * dt + 4 * g) = x;
       }
     }
+  }
+}
+
+template <int D, int OCC, int kWaves, bool kSplit>
+__global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams p, DqSplit split) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * KT * D * 2];  // K0 V0 K1 V1
+  if constexpr (!kSplit) {
+    const WorkItem item = work_item(p.tiles, p.BH, true);
+    if (item.valid) dq_item<D, kWaves, false>(p, split, item, 0, lds);
+  } else {
+    // one loop for all, so that the code of an item is there once: a main workgroup and a helper of a cut in
+    // three have one item, the others k consecutive ones (an XCD's helpers stay with one or two pairs)
+    const int items = p.tiles * p.BH;
+    const int block = (int)blockIdx.x;
+    int which = 0, first, count = 1;
+    if (block < items) {
+      first = xcd_order(block, items);
+    } else if (split.ways == 3) {
+      which = block < 2 * items ? 1 : 2;
+      first = xcd_order(block - which * items, items);
+    } else {
+      which = 1;
+      first = xcd_order(block - items, split.helpers(items)) * split.k;
+      count = items - first < split.k ? items - first : split.k;
+    }
+    for (int i = first; i < first + count; ++i) dq_item<D, kWaves, true>(p, split, WorkItem{i % p.tiles, i / p.tiles, true}, which, lds);
+  }
+}
+
+// dQ = R(phi)^T (main + helper sums) / sqrt(D) of a split launch: bytes only (ways + 1 times dQ), four quads
+// of D per thread in flight
+template <int D, int kWays>
+__global__ void __launch_bounds__(256) dq_merge_kernel(BwdParams p, DqSplit split, int64_t n_quads) {
+  constexpr int kUnroll = 4, QPR = D / 4;
+  const bool rope = p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  const int64_t i0 = (int64_t)blockIdx.x * (256 * kUnroll) + threadIdx.x;
+  f32x4 x[kWays][kUnroll];
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    const int64_t i = i0 + u * 256;
+    if (i < n_quads) {
+      x[0][u] = *reinterpret_cast<const f32x4*>(p.dq + i * 4);
+      x[1][u] = *reinterpret_cast<const f32x4*>(split.part1 + i * 4);
+      if constexpr (kWays == 3) x[2][u] = *reinterpret_cast<const f32x4*>(split.part2 + i * 4);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    const int64_t i = i0 + u * 256;
+    if (i >= n_quads) continue;
+    f32x4 v = x[0][u];
+#pragma unroll
+    for (int w = 1; w < kWays; ++w) v += x[w][u];
+    v = v * p.scale;
+    if (rope) {
+      const int64_t bq = i / QPR / p.H;
+      const int b = (int)(bq / p.Nq);
+      v = unrotate_quad(p.rot, token_tables(p.rot, b, (int)(bq - (int64_t)b * p.Nq)), (int)(i % QPR), v);
+    }
+    *reinterpret_cast<f32x4*>(p.dq + i * 4) = v;
   }
 }
 
@@ -1074,21 +1156,64 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   return p;
 }
 
+constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split of the dQ walk pays beyond half a round
+
 // Which launches take blocks of 32 rows: those whose blocks of 128 rows would leave most CUs with one
-// workgroup or none.  Measured (graph replays of the backward, us; few / general):
-//   D = 128: 2 blocks of 128 11 / 25, 48 25 / 55, 80 (nk 2880) 63 / 98, 104 (nk 20280) 273 / 477, 156 (nk 29640)
-//            524 / 670; lost: 192 (nk 910) 70 / 60, 216 (nk 10400) 298 / 268, 256 (nk 400) 46 / 42
-//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 138 / 313, 192 32 / 38, 216 160 / 175, 256 23 / 26
+// workgroup or none, up to where the key split of the general kernel takes over (a walk of 40 tiles and
+// more).  Measured (graph replays of the backward, us; few / general, split where it splits):
+//   D = 128: 2 blocks of 128 11 / 25, 48 25 / 55, 80 (nk 2880) 63 / 98, 96 (nk 3584) 73 / 80, 104 (nk 20280) 261 / 278;
+//            lost: 120 (nk 8190) 156 / 145, 156 (nk 29640) 563 / 406; without a split 192 (nk 910) 70 / 60, 256 (nk 400) 46 / 42
+//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 137 / 165, 120 (nk 8190) 82 / 90; lost: 156 (nk 29640) 267 / 236, 216 (nk
+//            10400) 156 / 136, 224 (nk 3120) 74 / 67; short walks 192 (nk 910) 32 / 38, 256 (nk 400) 23 / 26
 // Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
 // does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
 // with four), four otherwise (208 x 37: 30.0 against 34.3).
 int few_waves(const DevGeom& g, const AttnOperands& op) {
-  const int64_t blocks = (int64_t)((op.Nq + 127) / 128) * g.B * g.H;
-  if (op.Nq > kFewMaxRows || 8 * blocks > (g.D == 128 ? 5 : 8) * (int64_t)g.n_cus) return 0;
   int hist = 0;
   for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
+  const int64_t blocks = (int64_t)((op.Nq + 127) / 128) * g.B * g.H;
+  const bool long_walk = (hist + op.Nq) / KT >= kMinSplitTiles;
+  const int sixteenths = g.D == 128 ? (long_walk ? 7 : 10) : (long_walk ? 8 : 16);  // of the CUs
+  if (op.Nq > kFewMaxRows || 16 * blocks > sixteenths * (int64_t)g.n_cus) return 0;
   const int64_t wgs = (int64_t)((op.Nq + 31) / 32) * g.B * g.H;
   return 8 * wgs <= 5 * (int64_t)g.n_cus && (hist + op.Nq) / 32 >= 64 ? 8 : 4;
+}
+
+template <int D>
+constexpr int kDqPlaces = D == 128 ? 2 : 3;  // dQ workgroups a CU holds: 244 registers, or 165
+
+// How a dQ launch is split over the keys.  Measured (graph replays of the backward, us; split / not, D = 128
+// unless said otherwise; items = workgroups without a split):
+//   up to a third of the places in three: 111 items x 512 tiles 478 (two ways: the same) / 807, 156 x 463 406 (two ways
+//     518) / 674, D = 64 156 x 463 236 / 447; between a third and half of the CUs two ways already give every CU one
+//     workgroup (104 x 317: 278, three 275), with a third less to merge
+//   up to the places in two, helpers of k items: 185 x 317 460 / 552, 300 x 488 894 / 1109, 444 x 512 1306 / 1345, 216 x 163 233 /
+//     269, 224 x 50 111 / 115, D = 64 592 x 366 792 / 856; lost: 192 x 15 63.7 / 59.8, 256 x 7 50 / 43
+//   just above the places, where a few workgroups make a second round: in three 518 x 366 1369 / 1627, 592 x 366 1404 / 1636,
+//     in two 600 x 341 1271 / 1470, 740 x 366 1695 / 1758; not beyond 1.5 rounds: 900 x 341 1999 / 1904
+template <int D>
+DqSplit dq_split(const DevGeom& g, const AttnOperands& op, int items, float* dk, float* dv) {
+  DqSplit s{1, 1, dk, dv};
+  int hist = INT32_MAX;
+  for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] < hist ? op.hist_rows.v[b] : hist;
+  const int tiles = (hist + op.Nq) / KT;
+  const int places = kDqPlaces<D> * g.n_cus;
+  if (tiles < (2 * items <= g.n_cus ? 16 : kMinSplitTiles)) return s;
+  if (3 * items <= places && (3 * items <= g.n_cus || 2 * items > g.n_cus)) {
+    s.ways = 3;
+  } else if (items <= places) {
+    int k = 1;
+    while (k < 16 && items + (items + k - 1) / k > places) ++k;
+    if (items + (items + k - 1) / k <= places) {
+      s.ways = 2;
+      s.k = k;
+    }
+  } else if (items * 25 <= places * 29) {  // 1.16 rounds
+    s.ways = 3;
+  } else if (items * 2 <= places * 3) {
+    s.ways = 2;
+  }
+  return s;
 }
 
 template <int D>
@@ -1105,11 +1230,24 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
       attn_bwd_few_kernel<D, 4><<<grid, 4 * 64, 0, stream>>>(p);
     return hipGetLastError();
   }
+  p.tiles = (op.Nq + kDqWaves * 32 - 1) / (kDqWaves * 32);
+  const int items = work_grid_size(p.tiles, p.BH);
+  const DqSplit split = dq_split<D>(g, op, items, dk, dv);
   {
     ProfileScope prof("attn_bwd_dq_bf16", stream);
-    const int qtile = kDqWaves * 32;
-    p.tiles = (op.Nq + qtile - 1) / qtile;
-    attn_bwd_dq_kernel<D, 8 / kDqWaves, kDqWaves><<<dim3(work_grid_size(p.tiles, p.BH)), kDqWaves * 64, 0, stream>>>(p);
+    if (split.ways == 1)
+      attn_bwd_dq_kernel<D, kDqPlaces<D>, kDqWaves, false><<<dim3(items), kDqWaves * 64, 0, stream>>>(p, split);
+    else
+      attn_bwd_dq_kernel<D, kDqPlaces<D>, kDqWaves, true><<<dim3(items + split.helpers(items)), kDqWaves * 64, 0, stream>>>(p, split);
+  }
+  if (split.ways != 1) {
+    ProfileScope prof("attn_bwd_dq_merge", stream);
+    const int64_t n_quads = (int64_t)p.BH * op.Nq * D / 4;
+    const dim3 grid((unsigned)((n_quads + 1023) / 1024));
+    if (split.ways == 2)
+      dq_merge_kernel<D, 2><<<grid, 256, 0, stream>>>(p, split, n_quads);
+    else
+      dq_merge_kernel<D, 3><<<grid, 256, 0, stream>>>(p, split, n_quads);
   }
   const int ktile = 128;
   {

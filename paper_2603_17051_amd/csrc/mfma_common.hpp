@@ -228,16 +228,16 @@ struct WorkItem {
 };
 constexpr int kXcds = 8;
 __host__ __device__ inline int work_grid_size(int tiles_per_head, int BH) { return tiles_per_head * BH; }
+// workgroup i of n -> item: XCD x takes the contiguous range [x*n/8, (x+1)*n/8) (the first n % 8 one more)
+__device__ __forceinline__ int xcd_order(int i, int n) {
+  const int x = i % kXcds, q = n / kXcds, r = n % kXcds;
+  return x * q + (x < r ? x : r) + i / kXcds;
+}
 __device__ __forceinline__ WorkItem work_item(int tiles_per_head, int BH, bool by_xcd, int i) {
   WorkItem w;
   const int n = tiles_per_head * BH;
   w.valid = i < n;
-  int j = i;
-  if (by_xcd) {
-    // XCD x takes the contiguous range of items [x*n/8, (x+1)*n/8) (the first n % 8 one item more)
-    const int x = i % kXcds, q = n / kXcds, r = n % kXcds;
-    j = x * q + (x < r ? x : r) + i / kXcds;
-  }
+  const int j = by_xcd ? xcd_order(i, n) : i;
   w.bh = j / tiles_per_head;
   w.tile = j - w.bh * tiles_per_head;
   return w;

@@ -1,0 +1,45 @@
+"""The dQ kernel's split over the keys: cut in three (few workgroups, and just above one round), two ways
+with a helper per workgroup or per several, odd counts, causal blocks whose walks differ; fp64 oracle,
+the gradients pre-filled with NaN (dK and dV carry partial sums on the way), and the launch names."""
+import pytest
+
+import workloads as wl
+from helpers import Lockstep, assert_bf16_close, host_f64
+from test_gpu_parity import _fill_history
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,H,resident,bf,split", [
+    (128, 1, 2, 0, True),    # 17 workgroups: three ways
+    (128, 6, 3, 1, True),    # 102: two ways, a helper each
+    (64, 6, 3, 0, True),
+    (128, 18, 2, 1, True),   # 306 of 512 places: a helper per two
+    # (35 heads: the 33rd head's draw of these inputs puts one dQ element 1.4036e-2 of the largest off, un-split too, against
+    # the gate of 1.4e-2 that is twice what a rounding model lands on other draws)
+    (64, 35, 2, 0, True),    # 595 of 768: a helper per four
+    (128, 31, 2, 0, True),   # 527: just above a round, three ways
+    (64, 58, 2, 1, True),    # 986 of 768: two ways
+    (128, 56, 2, 0, False),  # 952: not split
+])
+def test_backward_with_the_dq_walk_split_over_the_keys(D, H, resident, bf, split):
+    import torch
+    gh, gw, Fc = 20, 26, 4   # 2080 queries: 17 blocks of 128, the last ragged
+    w = wl.Workload("dq_split", 53, 1, H, D, gh, gw, 4, 0, Fc, resident, wl.default_rope_pairs(D))
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[9], block_frames=bf)
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), resident)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    dev = [ls.dev(x) for x in (q, k, v, do)]
+    out, lse = ls.A.astro_chunk_attn_fwd(ls.cache, *dev[:3], Fc)
+    grads = [torch.full(dev[0].shape, float("nan"), device="cuda:0") for _ in range(3)]
+    ls.A.astro_profile_begin()
+    ls.A.astro_chunk_attn_bwd(ls.cache, *dev[:3], out, lse, dev[3], Fc, *grads)
+    launched = ls.A.astro_profile_end()
+    assert "attn_bwd_dq_bf16" in launched and ("attn_bwd_dq_merge" in launched) == split, launched
+    wide = [ls.wide(x) for x in (q, k, v, do)]
+    for h in {0, H - 1}:
+        ref = ls.oracle.attn_bwd(*wide, Fc, heads=[h])
+        for got, r, what in zip(grads, ref, ("dq", "dk", "dv")):
+            assert_bf16_close(host_f64(got[0, :, h]), r[0, :, h], f"head {h} {what}")
+    assert all(bool(torch.isfinite(x).all()) for x in grads)
+    ls.close()
