@@ -689,8 +689,8 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
 // ---- key-range split of launches that cannot fill the chip -----------------------------------
 // The forward holds three workgroups per CU.  With fewer than two rounds of workgroups (one
 // stream of 12 heads and 37 query tiles is 444 workgroups on 768 places) each (pair, query
-// tile) is cut into `splits` key ranges, enough for two rounds, at most kMaxFwdSplits and
-// never less than kMinTilesPerSplit key tiles each.
+// tile) may be cut into `splits` key ranges, at most kMaxFwdSplits and never less than
+// kMinTilesPerSplit key tiles each.
 constexpr int kMinTilesPerSplit = 4, kFwdWorkgroupsPerCu = 3;
 
 static int fwd_work_items(const DevGeom& g, int Nq) { return ((Nq + 127) / 128) * g.B * g.H; }
@@ -711,10 +711,28 @@ int bf16_fwd_splits(const DevGeom& g, const AttnOperands& op, bool have_parts) {
   // queries: both report weight 0 to the merge)
   const int chunk_rows = op.block_rows > 0 && op.block_rows < op.Nq ? op.block_rows : op.Nq;
   const int tiles = (min_hist + KT - 1) / KT + (chunk_rows + KT - 1) / KT;
+  // Enough parts for two rounds ...
   int s = (2 * places + items - 1) / items;
   if (s > kMaxFwdSplits) s = kMaxFwdSplits;
   if (s > tiles / kMinTilesPerSplit) s = tiles / kMinTilesPerSplit;
-  return s < 1 ? 1 : s;
+  if (s <= 1) return 1;
+  // ... unless another count is clearly better by this estimate, in units of one key tile of a full CU
+  // (1.14 us at D = 128): items * s / places rounds of 1 / s of the walk each, where a last round with one,
+  // two or three workgroups on a CU takes 0.45, 0.72 or 1 of a full one, plus 0.018 per part and item for
+  // writing and merging it, plus the merge launch.  It is within 3 % of most times measured at D = 128, so 7 %
+  // decide: 480 x 183 tiles 1 part 168 us (4 parts 188), 400 x 682 5 parts 502 (4: 522), 200 x 358 7 parts 150 (8: 161), 111
+  // x 1024 6 parts 232 (8: 239).  At D = 64, with four workgroups per CU, it only tells when not to split at all
+  // (480 x 183: 104 us, 4 parts 110).
+  auto cost = [&](int c) {
+    const int wgs = items * c, rest = wgs % places;
+    const double tail = rest == 0 ? 0. : 3 * rest <= places ? 0.45 : 3 * rest <= 2 * places ? 0.72 : 1.;
+    return (wgs / places + tail) * tiles / c + (c > 1 ? 3.5 + 0.018 * wgs : 0.);
+  };
+  const double bar = (g.D == 128 ? 0.93 : 0.91) * cost(s);
+  int best = s;
+  for (int c = 1; c <= (g.D == 128 ? kMaxFwdSplits : 1) && c <= tiles / kMinTilesPerSplit; ++c)
+    if (cost(c) < bar && cost(c) < cost(best)) best = c;
+  return best;
 }
 
 // ---- which launches take one block of 32 queries per workgroup -------------------------------------
