@@ -173,7 +173,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // compiler waits for ALL of its own direct-to-LDS loads before the next LDS read, since it cannot
 // tell the buffers apart, and a wave's two tiles are refilled at different times.  It does not count
 // these, so the caller waits (wait_vmem) before it reads the tile, and has its reads of the old
-// contents returned before the refill (wait_lds).
+// contents returned before the refill (wait_lds).  m0 (the LDS address) is named as overwritten: the
+// compiler's own direct-to-LDS loads hold theirs there too, and would take it as still set.
 template <int D>
 struct PrivateStream {
   static constexpr int CPR = D / 8, kRowsPerInst = 64 / CPR, kInsts = 32 / kRowsPerInst;
@@ -193,7 +194,7 @@ struct PrivateStream {
     for (int u = 0; u < kInsts; ++u) {
       const uint32_t off = ((uint32_t)(row0 + u * kRowsPerInst) + lane_row) * stride_bytes + chunk[u % kPatterns];
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst + u * 1024), "v"(off), "s"(rsrc)
-                   : "memory");
+                   : "memory", "m0");
     }
   }
 };
