@@ -174,11 +174,14 @@ __device__ __forceinline__ void wave_lds_sync() {
 // tell the buffers apart, and a wave's two tiles are refilled at different times.  It does not count
 // these, so the caller waits (wait_vmem) before it reads the tile, and has its reads of the old
 // contents returned before the refill (wait_lds).  m0 (the LDS address) is named as overwritten: the
-// compiler's own direct-to-LDS loads hold theirs there too, and would take it as still set.
+// compiler's own direct-to-LDS loads hold theirs there too, and would take it as still set.  The five
+// wait states before the load are what a buffer load needs after a vector instruction wrote one of its
+// descriptor's words (a lane read just before); m0 alone would need one.
 template <int D>
 struct PrivateStream {
   static constexpr int CPR = D / 8, kRowsPerInst = 64 / CPR, kInsts = 32 / kRowsPerInst;
   static constexpr int kPatterns = 16 / kRowsPerInst;  // the swizzle repeats every 16 rows
+  static_assert(kInsts % 4 == 0, "issue() takes four at a time");
   uint32_t chunk[kPatterns];  // byte offset within its row of the chunk this lane fetches
   uint32_t lane_row;
 
@@ -190,11 +193,20 @@ struct PrivateStream {
   __device__ __forceinline__ void issue(const u32x4 rsrc, uint32_t stride_bytes, int row0, const char* lds_tile) const {
     typedef const char __attribute__((address_space(3))) * lds_ptr;
     const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr)lds_tile);
+    // four instructions to an asm block, so that the wait states are spent once
 #pragma unroll
-    for (int u = 0; u < kInsts; ++u) {
-      const uint32_t off = ((uint32_t)(row0 + u * kRowsPerInst) + lane_row) * stride_bytes + chunk[u % kPatterns];
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst + u * 1024), "v"(off), "s"(rsrc)
-                   : "memory", "m0");
+    for (int u0 = 0; u0 < kInsts; u0 += 4) {
+      uint32_t off[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        off[u] = ((uint32_t)(row0 + (u0 + u) * kRowsPerInst) + lane_row) * stride_bytes + chunk[(u0 + u) % kPatterns];
+      asm volatile(
+          "s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %5, 0 offen lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %5, 0 offen lds\n\t"
+          "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %4, %5, 0 offen lds" ::"s"(dst + u0 * 1024),
+          "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(rsrc)
+          : "memory", "m0", "scc");
     }
   }
 };
