@@ -173,6 +173,10 @@ int astro_chunk_attn_fwd(astro_kvcache_t *cache, const void *q, const void *k_ch
  * no gradient.  q, k_chunk, v_chunk, out, lse must be those of a forward call on
  * the same cache state.  dout has the cache dtype.
  * workspace: device, >= bwd_bytes, 256-byte aligned.
+ * The outputs must not overlap v_chunk, dout or the workspace.  dk_chunk and dv_chunk may overlap
+ * each other, dq, out and lse (bf16 caches: the call then takes the route that reads all of it
+ * first; what was written last stays).  They hold partial sums while the call runs, so calls that
+ * overlap in time need dk_chunk and dv_chunk of their own even where only dq is wanted.
  * With ASTRO_FLAG_REUSE_STAGED (the re-forward + backward of gradient checkpointing, Table S1):
  * an attention call whose q, k_chunk, workspace pointer, n_frames and group equal those of the
  * handle's previous attention call, with no reset or append in between, skips the rotation

@@ -145,6 +145,32 @@ AttnOperands attn_operands(const astro_kvcache* c, char* ws, const Workspace& w,
   return op;
 }
 
+struct Span {
+  const void* at;
+  size_t bytes;
+};
+
+bool overlap(const Span& a, const Span& b) {
+  const uintptr_t x = (uintptr_t)a.at, y = (uintptr_t)b.at;
+  return x < y + b.bytes && y < x + a.bytes;
+}
+
+// Whether dK or dV of a bf16 backward shares bytes with the other, with dQ or with what only the query side
+// reads.  The two plain launches put up with that: the first reads all of these and writes dQ, the second
+// writes dK and dV (one buffer for gradients that are not wanted, gradients over an output that is
+// done with).  One launch for both sides does not, nor does a split dQ walk, whose partial sums pass through
+// the dK and dV outputs.
+bool outputs_overlap(const astro_kvcache* c, int n_frames, int group, const void* out, const float* lse, const float* dq,
+                     const float* dk, const float* dv) {
+  const RingGeometry& g = c->geo;
+  const size_t rows = (size_t)g.B * group * n_frames * g.T * g.H, grad = rows * g.D * sizeof(float);
+  const Span read[] = {{dq, grad}, {out, rows * g.D * g.elem_bytes()}, {lse, rows * sizeof(float)},
+                       {c->k_storage, g.storage_bytes()}, {c->v_storage, g.storage_bytes()}};
+  bool any = overlap({dk, grad}, {dv, grad});
+  for (const Span& r : read) any = any || overlap({dk, grad}, r) || overlap({dv, grad}, r);
+  return any;
+}
+
 // rotate Q and K_chunk into the workspace (head-major), unless the handle may reuse staged copies
 // and the last pre-pass was made for exactly this call's chunk, workspace and table state
 hipError_t stage_chunk(astro_kvcache* c, const void* q, const void* k_chunk, char* ws, const Workspace& w,
@@ -379,7 +405,8 @@ int astro_group_attn_bwd(astro_kvcache_t* cache, const void* q, const void* k_ch
   char* ws = (char*)workspace;
   hipStream_t stream = (hipStream_t)hip_stream;
   if (stage_chunk(cache, q, k_chunk, ws, w, n_frames, group, stream) != hipSuccess) return ASTRO_ERR_HIP;
-  const AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
+  AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
+  op.in_order = outputs_overlap(cache, n_frames, group, out, lse, dq, dk_chunk, dv_chunk);
   const DevGeom d = dev_geom(cache, group);
   if (cache->geo.dtype == ASTRO_BF16)  // gradients leave the kernels un-rotated and token-major
     return launch_attn_bwd_bf16(d, op, out, lse, dout, dq, dk_chunk, dv_chunk, ws + w.scratch, stream) == hipSuccess

@@ -1171,6 +1171,7 @@ constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split o
 // does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
 // with four), four otherwise (208 x 37: 30.0 against 34.3).
 int few_waves(const DevGeom& g, const AttnOperands& op) {
+  if (op.in_order) return 0;
   int hist = 0;
   for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
   const int64_t blocks = (int64_t)((op.Nq + 127) / 128) * g.B * g.H;
@@ -1200,7 +1201,7 @@ DqSplit dq_split(const DevGeom& g, const AttnOperands& op, int items, float* dk,
   for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] < hist ? op.hist_rows.v[b] : hist;
   const int tiles = (hist + op.Nq) / KT;
   const int places = kDqPlaces<D> * g.n_cus;
-  if (tiles < (2 * items <= g.n_cus ? 16 : kMinSplitTiles)) return s;
+  if (op.in_order || tiles < (2 * items <= g.n_cus ? 16 : kMinSplitTiles)) return s;
   if (3 * items <= places && (3 * items <= g.n_cus || 2 * items > g.n_cus)) {
     s.ways = 3;
   } else if (items <= places) {

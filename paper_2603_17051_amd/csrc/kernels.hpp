@@ -99,6 +99,9 @@ struct AttnOperands {
   int group;             // candidates per cache stream (1 = plain chunk attention)
   int block_rows;        // causal block inside the chunk, in token rows; 0 = none (whole chunk)
   StreamInts hist_rows;  // resident ring rows per CACHE stream
+  // An output shares bytes with something that a route of this call would still read after writing it: take the
+  // route that reads it all first (see outputs_overlap in astro_api.hip).
+  bool in_order = false;
 };
 
 // ---- fp32 debug path -------------------------------------------------------
