@@ -162,7 +162,9 @@ int astro_chunk_attn_workspace_bytes(const astro_kvcache_t *cache, int32_t n_fra
  * q, k_chunk, v_chunk: device, un-rotated, [B, n_frames*T, H, D];
  * out: device [B, n_frames*T, H, D] (dtype of the cache); lse: device fp32
  * [B, H, n_frames*T].  Does not modify the cache or its tables (append does).
- * workspace: device, >= fwd_bytes, 256-byte aligned; contents undefined after. */
+ * workspace: device, >= fwd_bytes, 256-byte aligned; contents undefined after.
+ * out and lse must not overlap each other, the workspace or, unless the launch is one whose key
+ * ranges are merged afterwards (attn_fwd_merge in the kernel times), v_chunk. */
 int astro_chunk_attn_fwd(astro_kvcache_t *cache, const void *q, const void *k_chunk,
                          const void *v_chunk, int32_t n_frames, void *out, float *lse,
                          void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -171,6 +171,14 @@ bool outputs_overlap(const astro_kvcache* c, int n_frames, int group, const void
   return any;
 }
 
+// The same for a forward: out or lse over the chunk's values.  A launch whose key ranges are merged afterwards
+// puts up with it; where there are workgroups enough without key ranges no route does.
+bool output_over_values(const astro_kvcache* c, int n_frames, int group, const void* v_chunk, const void* out, const float* lse) {
+  const RingGeometry& g = c->geo;
+  const size_t rows = (size_t)g.B * group * n_frames * g.T * g.H, chunk = rows * g.D * g.elem_bytes();
+  return overlap({out, chunk}, {v_chunk, chunk}) || overlap({lse, rows * sizeof(float)}, {v_chunk, chunk});
+}
+
 // rotate Q and K_chunk into the workspace (head-major), unless the handle may reuse staged copies
 // and the last pre-pass was made for exactly this call's chunk, workspace and table state
 hipError_t stage_chunk(astro_kvcache* c, const void* q, const void* k_chunk, char* ws, const Workspace& w,
@@ -383,7 +391,8 @@ int astro_group_attn_fwd(astro_kvcache_t* cache, const void* q, const void* k_ch
   char* ws = (char*)workspace;
   hipStream_t stream = (hipStream_t)hip_stream;
   if (stage_chunk(cache, q, k_chunk, ws, w, n_frames, group, stream) != hipSuccess) return ASTRO_ERR_HIP;
-  const AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
+  AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
+  op.in_order = output_over_values(cache, n_frames, group, v_chunk, out, lse);
   const DevGeom d = dev_geom(cache, group);
   hipError_t e;
   if (cache->geo.dtype == ASTRO_F32)

@@ -716,6 +716,7 @@ int bf16_fwd_splits(const DevGeom& g, const AttnOperands& op, bool have_parts) {
   if (s > kMaxFwdSplits) s = kMaxFwdSplits;
   if (s > tiles / kMinTilesPerSplit) s = tiles / kMinTilesPerSplit;
   if (s <= 1) return 1;
+  if (op.in_order) return s;  // the merge launch writes the outputs
   // ... unless another count is clearly better by this estimate, in units of one key tile of a full CU
   // (1.14 us at D = 128): items * s / places rounds of 1 / s of the walk each, where a last round with one,
   // two or three workgroups on a CU takes 0.45, 0.72 or 1 of a full one, plus 0.018 per part and item for
@@ -749,6 +750,7 @@ int bf16_fwd_splits(const DevGeom& g, const AttnOperands& op, bool have_parts) {
 // every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
 // with four); two workgroups of four waves share a CU otherwise (312 x 86: 30.2 against 36.4).
 static int few_waves(const DevGeom& g, const AttnOperands& op) {
+  if (op.in_order) return 0;
   int hist = 0;
   for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
   const int64_t wgs = (int64_t)((op.Nq + 31) / 32) * g.B * g.H;

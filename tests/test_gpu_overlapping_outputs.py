@@ -1,6 +1,6 @@
-"""Gradients written over memory that the call still reads on another route: the launches that take both sides
-at once or pass partial sums through dK and dV leave such calls to the two plain launches, whose first
-reads it all.  Each layout at a size of either route, against the fp64 oracle."""
+"""Outputs over memory that the call still reads on another route: such calls take the route that reads it all
+first (backward: the two plain launches instead of one for both sides or partial sums in dK and dV;
+forward: key ranges merged at the end).  Each layout at a size of either route, against the fp64 oracle."""
 import pytest
 
 import workloads as wl
@@ -45,4 +45,26 @@ def test_backward_outputs_over_memory_the_query_side_reads(D, H, gh, gw, residen
     for got, r, what in zip((dq, dk, dv), ref, "qkv"):
         if what in wanted:
             assert_bf16_close(host_f64(got[0, :, H - 1]), r[0, :, H - 1], f"{layout}: d{what}")
+    ls.close()
+
+
+@pytest.mark.parametrize("H,gh,gw,resident,apart", [
+    (2, 7, 9, 3, "attn_fwd_few_bf16"),
+    (12, 30, 36, 2, "attn_fwd_merge"),  # 408 workgroups
+])
+def test_forward_in_place_of_the_chunk_values(H, gh, gw, resident, apart):
+    D, Fc = 128, 4
+    w = wl.Workload("overlap_fwd", 55, 1, H, D, gh, gw, 4, 0, Fc, resident, wl.default_rope_pairs(D))
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[9])
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), resident)
+    q, k, v = wl.chunk_inputs(w)
+    ref, ref_lse = ls.oracle.attn_fwd(*[ls.wide(x) for x in (q, k, v)], Fc, heads=[H - 1])
+    for in_place in (False, True):
+        dev = [ls.dev(x) for x in (q, k, v)]
+        ls.A.astro_profile_begin()
+        out, lse = ls.A.astro_chunk_attn_fwd(ls.cache, *dev, Fc, out=dev[2] if in_place else None)
+        launched = ls.A.astro_profile_end()
+        assert ("attn_fwd_merge" if in_place else apart) in launched, launched
+        assert_bf16_close(host_f64(out[0, :, H - 1]), ref[0, :, H - 1], f"in place {in_place}: out")
+        assert_bf16_close(host_f64(lse[0, H - 1]), ref_lse[0, H - 1], f"in place {in_place}: lse")
     ls.close()
