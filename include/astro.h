@@ -197,7 +197,8 @@ int astro_chunk_attn_bwd(astro_kvcache_t *cache, const void *q, const void *k_ch
  * Sec. 4.5, Table 4(a)): everything astro_chunk_attn_bwd writes, plus the gradients the detach drops,
  *   dk_cache, dv_cache: device fp32 [B, C*T, H, D], row = slot*T + token, w.r.t. the keys
  *   (UN-rotated, as they were appended) and values of the frames resident in the ring.
- * Rows of slots that hold no frame are not written.  bf16 caches only (ASTRO_ERR_UNSUPPORTED
+ * Rows of slots that hold no frame are not written.  They are written after everything else;
+ * dk_cache may overlap dout, and dv_cache (whose bytes it then replaces).  bf16 caches only (ASTRO_ERR_UNSUPPORTED
  * for ASTRO_F32).  workspace: >= astro_chunk_attn_bwd_full_workspace_bytes, 256-byte aligned. */
 int astro_chunk_attn_bwd_full_workspace_bytes(const astro_kvcache_t *cache, int32_t n_frames,
                                               size_t *bytes);

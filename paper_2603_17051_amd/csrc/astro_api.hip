@@ -458,7 +458,21 @@ int astro_chunk_attn_bwd_full(astro_kvcache_t* cache, const void* q, const void*
   if (rc2 != ASTRO_OK) return rc2;
   // ... then dK, dV of the resident ring rows
   char* ws = (char*)workspace;
-  const AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, 1);
+  AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, 1);
+  // dK over dV, or over dout, which the launch reads to its end: dK is what stays, so dV goes out in a launch of
+  // its own, and dout is read from a copy where the rotated chunk keys were (done with by now)
+  const RingGeometry& g = cache->geo;
+  const size_t chunk = (size_t)g.B * n_frames * g.T * g.H * g.D * g.elem_bytes();
+  const size_t ring = (size_t)g.B * g.rows_per_head() * g.H * g.D * sizeof(float);
+  op.in_order = overlap({dk_cache, ring}, {dv_cache, ring});
+  if (overlap({dk_cache, ring}, {dout, chunk})) {
+    cache->staged.valid = false;
+    if (hipMemcpyAsync(ws + w.kc_rot, dout, chunk, hipMemcpyDeviceToDevice, (hipStream_t)hip_stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return ASTRO_ERR_HIP;
+    }
+    dout = ws + w.kc_rot;
+  }
   StreamInts start, next, sink_shift;
   for (int b = 0; b < ASTRO_MAX_BATCH; ++b) {
     start.v[b] = b < cache->geo.B ? cache->tables.start(b) : 0;

@@ -610,8 +610,8 @@ struct KeyWave {
 // The dK/dV kernel over the resident ring rows instead of the chunk's keys (non-detached backward, group
 // 1): where the gradients go and what is needed to turn dK~ back at the frame each slot holds.
 struct RingGrads {
-  float* dk;  // [B, C*T, H, D]  w.r.t. the keys as they were appended (un-rotated)
-  float* dv;  // [B, C*T, H, D]
+  float* dk;  // [B, C*T, H, D]  w.r.t. the keys as they were appended (un-rotated); null = not stored
+  float* dv;  // [B, C*T, H, D]; null = not stored
   const double* inv_freq_t;
   int C, S;
   StreamInts start, next_n, sink_shift;  // see launch_attn_bwd_hist_bf16
@@ -762,6 +762,7 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
       fill_slot_table(reinterpret_cast<float2*>(lds), p, grads, b, slot_first, slot_count, threadIdx.x, kPairThreads);
       __syncthreads();
     }
+    if (!(kKey ? grads.dk : grads.dv)) return;
   }
 
   // dV as it is; dK~ is turned back to dK here
@@ -1270,8 +1271,20 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   if (max_hist == 0) return hipSuccess;
   const int ktile = 128;
   p.tiles = (max_hist + ktile - 1) / ktile;
-  ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
-  attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, grads);
+  auto run = [&](const RingGrads& to) {
+    ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
+    attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, to);
+  };
+  if (op.in_order) {  // dV and dK share bytes, dK's stay: one after the other
+    RingGrads one = grads;
+    one.dk = nullptr;
+    run(one);
+    one.dk = grads.dk;
+    one.dv = nullptr;
+    run(one);
+  } else {
+    run(grads);
+  }
   return hipGetLastError();
 }
 

@@ -68,3 +68,28 @@ def test_forward_in_place_of_the_chunk_values(H, gh, gw, resident, apart):
         assert_bf16_close(host_f64(out[0, :, H - 1]), ref[0, :, H - 1], f"in place {in_place}: out")
         assert_bf16_close(host_f64(lse[0, H - 1]), ref_lse[0, H - 1], f"in place {in_place}: lse")
     ls.close()
+
+
+@pytest.mark.parametrize("D,window_relative", [(128, False), (64, True)])
+@pytest.mark.parametrize("layout", ["one buffer for dk_cache and dv_cache", "dk_cache over dout", "dk_cache over dout and dv_cache"])
+def test_ring_gradients_over_each_other_and_over_dout(D, window_relative, layout):
+    import torch
+    Fc, C = 2, 5
+    w = wl.Workload("overlap_ring", 56, 2, 2, D, 7, 9, C, 1, Fc, 7, wl.default_rope_pairs(D))
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[9, 2], window_relative=window_relative)
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), 7)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    dev = [ls.dev(x) for x in (q, k, v, do)]
+    out, lse = ls.A.astro_chunk_attn_fwd(ls.cache, *dev[:3], Fc)
+    want = ls.A.astro_chunk_attn_bwd_full(ls.cache, *dev[:3], out, lse, dev[3], Fc)
+    dkc = torch.full_like(want[3], float("nan"))
+    dvc = torch.full_like(want[4], float("nan")) if layout == "dk_cache over dout" else dkc
+    dout = dev[3]
+    if "dout" in layout:
+        dout = dkc.view(-1).view(torch.bfloat16)[-dout.numel():].view(dout.shape)
+        dout.copy_(dev[3])
+    got = ls.A.astro_chunk_attn_bwd_full(ls.cache, *dev[:3], out, lse, dout, Fc, dk_cache=dkc, dv_cache=dvc)
+    assert all(torch.equal(a, b) for a, b in zip(got[:4], want[:4]))  # the same kernels in the same order of sums
+    if dvc is not dkc:
+        assert torch.equal(dvc, want[4])
+    ls.close()
