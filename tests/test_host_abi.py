@@ -195,3 +195,17 @@ def test_tables_follow_the_naive_ring_simulation(C, S, Fc, start, window_relativ
     assert sf[1] == [-1] * C and nn[1] == 0
     assert sf[0] == sims[0].slot_frame() and sf[2] == sims[2].slot_frame()
     c.close()
+
+
+def test_current_stream_without_the_raw_handle_of_torch(monkeypatch):
+    """The handle of the current stream comes from a function of torch's private module; a torch without it
+    has torch.cuda.current_stream()."""
+    import torch
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert binding._stream(None).value == 0x1234
