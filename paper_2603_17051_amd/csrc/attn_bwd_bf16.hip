@@ -23,7 +23,7 @@ namespace {
 // Waves per dQ workgroup.  Eight (one workgroup per CU, half the tile traffic from L2) was
 // measured slower, 4.87 vs 4.73 ms: a barrier over eight waves and a wider ragged last query tile.
 constexpr int kDqWaves = 4;
-constexpr int KT = 64;  // rows per LDS tile
+constexpr int KT = kBwdKeyTile;  // rows per LDS tile
 
 struct BwdParams {
   const __bf16* q_rot;
@@ -990,7 +990,6 @@ __device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item,
 
 // Row terms of all queries of one pair: terms[0][q] = -LSE*log2(e), terms[1][q] = -Delta = -<dO, O>.
 // Rows past the end (up to the tile) are 0: their Q~ and dO rows are zero in LDS, so they add nothing.
-constexpr int kFewMaxRows = 2048;
 template <int D, int kWaves>
 __device__ __forceinline__ void few_row_terms(const BwdParams& p, int b, int h, float (*terms)[kFewMaxRows]) {
   constexpr int CPR = D / 8, kRows = kWaves * 64 / CPR, kUnroll = 4;
@@ -1159,72 +1158,15 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   return p;
 }
 
-constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split of the dQ walk pays beyond half a round
-
-// Which launches take blocks of 32 rows: those whose blocks of 128 rows would leave most CUs with one
-// workgroup or none, up to where the key split of the general kernel takes over (a walk of 40 tiles and
-// more).  Measured (graph replays of the backward, us; few / general, split where it splits):
-//   D = 128: 2 blocks of 128 11 / 25, 48 25 / 55, 80 (nk 2880) 63 / 98, 96 (nk 3584) 73 / 80, 104 (nk 20280) 261 / 278;
-//            lost: 120 (nk 8190) 156 / 145, 156 (nk 29640) 563 / 406; without a split 192 (nk 910) 70 / 60, 256 (nk 400) 46 / 42
-//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 137 / 165, 120 (nk 8190) 82 / 90; lost: 156 (nk 29640) 267 / 236, 216 (nk
-//            10400) 156 / 136, 224 (nk 3120) 74 / 67; short walks 192 (nk 910) 32 / 38, 256 (nk 400) 23 / 26
-// Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
-// does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
-// with four), four otherwise (208 x 37: 30.0 against 34.3).
-int few_waves(const DevGeom& g, const AttnOperands& op) {
-  if (op.in_order) return 0;
-  int hist = 0;
-  for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
-  const int64_t blocks = (int64_t)((op.Nq + 127) / 128) * g.B * g.H;
-  const bool long_walk = (hist + op.Nq) / KT >= kMinSplitTiles;
-  const int sixteenths = g.D == 128 ? (long_walk ? 7 : 10) : (long_walk ? 8 : 16);  // of the CUs
-  if (op.Nq > kFewMaxRows || 16 * blocks > sixteenths * (int64_t)g.n_cus) return 0;
-  const int64_t wgs = (int64_t)((op.Nq + 31) / 32) * g.B * g.H;
-  return 8 * wgs <= 5 * (int64_t)g.n_cus && (hist + op.Nq) / 32 >= 64 ? 8 : 4;
-}
-
 template <int D>
-constexpr int kDqPlaces = D == 128 ? 2 : 3;  // dQ workgroups a CU holds: 244 registers, or 165
-
-// How a dQ launch is split over the keys.  Measured (graph replays of the backward, us; split / not, D = 128
-// unless said otherwise; items = workgroups without a split):
-//   up to a third of the places in three: 111 items x 512 tiles 478 (two ways: the same) / 807, 156 x 463 406 (two ways
-//     518) / 674, D = 64 156 x 463 236 / 447; between a third and half of the CUs two ways already give every CU one
-//     workgroup (104 x 317: 278, three 275), with a third less to merge
-//   up to the places in two, helpers of k items: 185 x 317 460 / 552, 300 x 488 894 / 1109, 444 x 512 1306 / 1345, 216 x 163 233 /
-//     269, 224 x 50 111 / 115, D = 64 592 x 366 792 / 856; lost: 192 x 15 63.7 / 59.8, 256 x 7 50 / 43
-//   just above the places, where a few workgroups make a second round: in three 518 x 366 1369 / 1627, 592 x 366 1404 / 1636,
-//     in two 600 x 341 1271 / 1470, 740 x 366 1695 / 1758; not beyond 1.5 rounds: 900 x 341 1999 / 1904
-template <int D>
-DqSplit dq_split(const DevGeom& g, const AttnOperands& op, int items, float* dk, float* dv) {
-  DqSplit s{1, 1, dk, dv};
-  int hist = INT32_MAX;
-  for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] < hist ? op.hist_rows.v[b] : hist;
-  const int tiles = (hist + op.Nq) / KT;
-  const int places = kDqPlaces<D> * g.n_cus;
-  if (op.in_order || tiles < (2 * items <= g.n_cus ? 16 : kMinSplitTiles)) return s;
-  if (3 * items <= places && (3 * items <= g.n_cus || 2 * items > g.n_cus)) {
-    s.ways = 3;
-  } else if (items <= places) {
-    int k = 1;
-    while (k < 16 && items + (items + k - 1) / k > places) ++k;
-    if (items + (items + k - 1) / k <= places) {
-      s.ways = 2;
-      s.k = k;
-    }
-  } else if (items * 25 <= places * 29) {  // 1.16 rounds
-    s.ways = 3;
-  } else if (items * 2 <= places * 3) {
-    s.ways = 2;
-  }
-  return s;
-}
+constexpr int kDqPlaces = dq_places_per_cu(D);
 
 template <int D>
 hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, const float* lse, const void* dout,
                   float* dq, float* dk, float* dv, void* scratch, hipStream_t stream) {
   BwdParams p = make_params<D>(g, op, out, lse, dout, dq, dk, dv, scratch);
-  if (const int waves = few_waves(g, op)) {
+  const CallShape shape = call_shape(g, op);
+  if (const int waves = bwd_few_waves(shape)) {
     ProfileScope prof("attn_bwd_few_bf16", stream);
     p.tiles = (op.Nq + 31) / 32;
     const dim3 grid(2 * work_grid_size(p.tiles, p.BH));
@@ -1236,7 +1178,8 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   }
   p.tiles = (op.Nq + kDqWaves * 32 - 1) / (kDqWaves * 32);
   const int items = work_grid_size(p.tiles, p.BH);
-  const DqSplit split = dq_split<D>(g, op, items, dk, dv);
+  const DqWays ways = dq_ways(shape);
+  const DqSplit split{ways.ways, ways.k, dk, dv};
   {
     ProfileScope prof("attn_bwd_dq_bf16", stream);
     if (split.ways == 1)

@@ -36,8 +36,7 @@
 namespace astro {
 namespace {
 
-constexpr int KT = 32;                 // keys per LDS tile
-constexpr int kMaxFwdSplits = 8;       // most key ranges of a launch
+constexpr int KT = kFwdKeyTile;
 constexpr float kSumLimit = 0x1p44f;  // a lane's 16 probabilities may sum to this before the reference moves
 // a first tile whose rows sum to less than this relative to 0 takes its reference from its maximum instead
 constexpr float kFirstSumLimit = 0x1p-32f;
@@ -667,7 +666,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
   const int qtile = kWaves * 32;
   p.q_tiles = (op.Nq + qtile - 1) / qtile;
   // a launch that would leave the chip under two rounds of workgroups is split over the keys
-  p.splits = bf16_fwd_splits(g, op, parts != nullptr);
+  p.splits = parts ? fwd_splits(call_shape(g, op)) : 1;
   p.out_part = (__bf16*)parts;
   p.lse_part = (float*)((char*)parts + (size_t)p.splits * p.BH * op.Nq * D * 2);
   dim3 grid(work_grid_size(p.q_tiles, p.BH * p.splits));
@@ -686,86 +685,15 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
 
 }  // namespace
 
-// ---- key-range split of launches that cannot fill the chip -----------------------------------
-// The forward holds three workgroups per CU.  With fewer than two rounds of workgroups (one
-// stream of 12 heads and 37 query tiles is 444 workgroups on 768 places) each (pair, query
-// tile) may be cut into `splits` key ranges, at most kMaxFwdSplits and never less than
-// kMinTilesPerSplit key tiles each.
-constexpr int kMinTilesPerSplit = 4, kFwdWorkgroupsPerCu = 3;
-
-static int fwd_work_items(const DevGeom& g, int Nq) { return ((Nq + 127) / 128) * g.B * g.H; }
-
 size_t bf16_fwd_split_bytes(const DevGeom& g, int Nq) {
-  if (fwd_work_items(g, Nq) >= 2 * kFwdWorkgroupsPerCu * g.n_cus) return 0;
+  if (!fwd_may_split(g.n_cus, g.B * g.H, Nq)) return 0;
   return (size_t)kMaxFwdSplits * g.B * g.H * Nq * ((size_t)g.D * 2 + sizeof(float));
-}
-
-int bf16_fwd_splits(const DevGeom& g, const AttnOperands& op, bool have_parts) {
-  if (!have_parts) return 1;
-  const int items = fwd_work_items(g, op.Nq), places = kFwdWorkgroupsPerCu * g.n_cus;
-  if (items >= 2 * places) return 1;
-  int min_hist = INT32_MAX;
-  for (int b = 0; b < g.B / op.group; ++b) min_hist = op.hist_rows.v[b] < min_hist ? op.hist_rows.v[b] : min_hist;
-  // key tiles of the workgroup that sees the fewest: under causal blocks that is the first query
-  // tile, which sees one block of the chunk (a range may still come out empty or unseen for some
-  // queries: both report weight 0 to the merge)
-  const int chunk_rows = op.block_rows > 0 && op.block_rows < op.Nq ? op.block_rows : op.Nq;
-  const int tiles = (min_hist + KT - 1) / KT + (chunk_rows + KT - 1) / KT;
-  // Enough parts for two rounds ...
-  int s = (2 * places + items - 1) / items;
-  if (s > kMaxFwdSplits) s = kMaxFwdSplits;
-  if (s > tiles / kMinTilesPerSplit) s = tiles / kMinTilesPerSplit;
-  if (s <= 1) return 1;
-  if (op.in_order) return s;  // the merge launch writes the outputs
-  // ... unless another count is clearly better by this estimate, in units of one key tile of a full CU
-  // (1.14 us at D = 128): items * s / places rounds of 1 / s of the walk each, where a last round with one,
-  // two or three workgroups on a CU takes 0.45, 0.72 or 1 of a full one, plus 0.018 per part and item for
-  // writing and merging it, plus the merge launch.  It is within 3 % of most times measured at D = 128, so 7 %
-  // decide: 480 x 183 tiles 1 part 168 us (4 parts 188), 400 x 682 5 parts 502 (4: 522), 200 x 358 7 parts 150 (8: 161), 111
-  // x 1024 6 parts 232 (8: 239).  At D = 64, with four workgroups per CU, it only tells when not to split at all
-  // (480 x 183: 104 us, 4 parts 110).
-  auto cost = [&](int c) {
-    const int wgs = items * c, rest = wgs % places;
-    const double tail = rest == 0 ? 0. : 3 * rest <= places ? 0.45 : 3 * rest <= 2 * places ? 0.72 : 1.;
-    return (wgs / places + tail) * tiles / c + (c > 1 ? 3.5 + 0.018 * wgs : 0.);
-  };
-  const double bar = (g.D == 128 ? 0.93 : 0.91) * cost(s);
-  int best = s;
-  for (int c = 1; c <= (g.D == 128 ? kMaxFwdSplits : 1) && c <= tiles / kMinTilesPerSplit; ++c)
-    if (cost(c) < bar && cost(c) < cost(best)) best = c;
-  return best;
-}
-
-// ---- which launches take one block of 32 queries per workgroup -------------------------------------
-// Such a workgroup pulls every key tile for 32 queries only, four times the tile traffic per query of
-// the general kernel, and needs no merge launch.  Its time follows rounds * tiles, rounds = workgroups
-// per CU, at least 1; that product is bounded below.  Measured (graph replays, us; few / general):
-//   D = 128: 4 workgroups x 10 tiles 7.1 / 10.7, 144 x 33 12.2 / 23.8, 132 x 109 24.5 / 31.2, 140 x 133
-//            28.1 / 33.7, 320 x 140 42 / 48, 624 x 29 24 / 48; lost: 70 x 133 26.7 / 24.5, 156 x 232 45.1 /
-//            43.8, 392 x 634 167 / 161, 792 x 325 195 / 162
-//   D = 64:  4 x 10 5.1 / 9.6, 144 x 33 8.2 / 19.9, 140 x 133 16.3 / 26.6, 156 x 232 25.6 / 34.0, 792 x 325
-//            109 / 112; lost: 588 x 927 230 / 178
-// Below half a round the general kernel's key split reaches CUs that this one leaves idle, hence the
-// lower bound there.  Returns the waves per workgroup, 0 = the general kernel: eight waves pay when
-// every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
-// with four); two workgroups of four waves share a CU otherwise (312 x 86: 30.2 against 36.4).
-static int few_waves(const DevGeom& g, const AttnOperands& op) {
-  if (op.in_order) return 0;
-  int hist = 0;
-  for (int b = 0; b < g.B / op.group; ++b) hist = op.hist_rows.v[b] > hist ? op.hist_rows.v[b] : hist;
-  const int64_t wgs = (int64_t)((op.Nq + 31) / 32) * g.B * g.H;
-  const int64_t tiles = (hist + KT - 1) / KT + (op.Nq + KT - 1) / KT;
-  const int64_t walk = wgs > g.n_cus ? tiles * wgs / g.n_cus : tiles;
-  const bool half_full = 2 * wgs >= g.n_cus;
-  const int64_t limit = g.D == 128 ? (half_full ? 200 : 112) : (half_full ? 900 : 300);
-  if (walk > limit) return 0;
-  return wgs <= g.n_cus && tiles >= 64 ? 8 : 4;
 }
 
 hipError_t launch_attn_fwd_bf16(const DevGeom& g, const AttnOperands& op, void* out, float* lse, void* parts,
                                 hipStream_t stream) {
   const bool causal = op.block_rows > 0;
-  const int waves = few_waves(g, op);
+  const int waves = fwd_few_waves(call_shape(g, op));
   if (waves != 0 && g.D == 128) {
     if (waves == 8) return causal ? launch_few<128, 8, true>(g, op, out, lse, stream) : launch_few<128, 8, false>(g, op, out, lse, stream);
     return causal ? launch_few<128, 4, true>(g, op, out, lse, stream) : launch_few<128, 4, false>(g, op, out, lse, stream);

@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "../../include/astro.h"
+#include "launch_rules.hpp"
 
 namespace astro {
 
@@ -104,6 +105,16 @@ struct AttnOperands {
   bool in_order = false;
 };
 
+inline CallShape call_shape(const DevGeom& g, const AttnOperands& op) {
+  CallShape c{g.D, g.n_cus, g.B * g.H, op.Nq, op.block_rows, op.hist_rows.v[0], op.hist_rows.v[0], op.in_order};
+  for (int b = 1; b < g.B / op.group; ++b) {
+    const int n = op.hist_rows.v[b];
+    c.min_hist = n < c.min_hist ? n : c.min_hist;
+    c.max_hist = n > c.max_hist ? n : c.max_hist;
+  }
+  return c;
+}
+
 // ---- fp32 debug path -------------------------------------------------------
 size_t f32_fwd_workspace_floats(const DevGeom& g, int Nq);  // beyond q_rot / kc_rot
 size_t f32_bwd_workspace_floats(const DevGeom& g, int Nq);
@@ -117,7 +128,6 @@ hipError_t launch_attn_bwd_f32(const DevGeom& g, const AttnOperands& op, const f
 // `parts`: bf16_fwd_split_bytes() bytes of scratch for the per-split results of a launch that is
 // split over the keys (0 bytes when the shape fills the chip without), or null = never split.
 size_t bf16_fwd_split_bytes(const DevGeom& g, int Nq);
-int bf16_fwd_splits(const DevGeom& g, const AttnOperands& op, bool have_parts);
 hipError_t launch_attn_fwd_bf16(const DevGeom& g, const AttnOperands& op, void* out, float* lse, void* parts,
                                 hipStream_t stream);
 size_t bf16_bwd_workspace_bytes(const DevGeom& g, int Nq);  // beyond q_rot / kc_rot

@@ -1,0 +1,154 @@
+// Which kernel an attention call of the bf16 path takes and into how many key ranges it is cut: plain functions of
+// sizes, without HIP.
+#pragma once
+#include <cstddef>
+#include <cstdint>
+
+namespace astro {
+
+// What the rules look at of one call.
+struct CallShape {
+  int D, n_cus;
+  int pairs;               // candidates * heads
+  int Nq, block_rows;      // chunk rows; causal block in rows, 0 = none
+  int min_hist, max_hist;  // resident rows of the stream with the fewest and with the most
+  bool in_order;           // see AttnOperands::in_order
+};
+
+inline int blocks_of(int rows, int block) { return (rows + block - 1) / block; }
+
+// ==== forward ======================================================================================
+constexpr int kMaxFwdSplits = 8;  // most key ranges of a launch
+constexpr int kFwdKeyTile = 32;   // keys per LDS tile
+
+// ---- key-range split of launches that cannot fill the chip -----------------------------------
+// The forward holds three workgroups per CU.  With fewer than two rounds of workgroups (one
+// stream of 12 heads and 37 query tiles is 444 workgroups on 768 places) each (pair, query
+// tile) may be cut into `splits` key ranges, at most kMaxFwdSplits and never less than
+// kMinTilesPerSplit key tiles each.
+constexpr int kMinTilesPerSplit = 4, kFwdWorkgroupsPerCu = 3;
+
+// whether a launch of this size may be cut at all (the workspace then holds kMaxFwdSplits partial results)
+inline bool fwd_may_split(int n_cus, int pairs, int Nq) { return blocks_of(Nq, 128) * pairs < 2 * kFwdWorkgroupsPerCu * n_cus; }
+
+inline int fwd_splits(const CallShape& c) {
+  if (!fwd_may_split(c.n_cus, c.pairs, c.Nq)) return 1;
+  const int items = blocks_of(c.Nq, 128) * c.pairs, places = kFwdWorkgroupsPerCu * c.n_cus;
+  // key tiles of the workgroup that sees the fewest: under causal blocks that is the first query
+  // tile, which sees one block of the chunk (a range may still come out empty or unseen for some
+  // queries: both report weight 0 to the merge)
+  const int chunk_rows = c.block_rows > 0 && c.block_rows < c.Nq ? c.block_rows : c.Nq;
+  const int tiles = blocks_of(c.min_hist, kFwdKeyTile) + blocks_of(chunk_rows, kFwdKeyTile);
+  // Enough parts for two rounds ...
+  int s = (2 * places + items - 1) / items;
+  if (s > kMaxFwdSplits) s = kMaxFwdSplits;
+  if (s > tiles / kMinTilesPerSplit) s = tiles / kMinTilesPerSplit;
+  if (s <= 1) return 1;
+  if (c.in_order) return s;  // the merge launch writes the outputs
+  // ... unless another count is clearly better by this estimate, in units of one key tile of a full CU
+  // (1.14 us at D = 128): items * s / places rounds of 1 / s of the walk each, where a last round with one,
+  // two or three workgroups on a CU takes 0.45, 0.72 or 1 of a full one, plus 0.018 per part and item for
+  // writing and merging it, plus the merge launch.  It is within 3 % of most times measured at D = 128, so 7 %
+  // decide: 480 x 183 tiles 1 part 168 us (4 parts 188), 400 x 682 5 parts 502 (4: 522), 200 x 358 7 parts 150 (8: 161), 111
+  // x 1024 6 parts 232 (8: 239).  At D = 64, with four workgroups per CU, it only tells when not to split at all
+  // (480 x 183: 104 us, 4 parts 110).
+  auto cost = [&](int n) {
+    const int wgs = items * n, rest = wgs % places;
+    const double tail = rest == 0 ? 0. : 3 * rest <= places ? 0.45 : 3 * rest <= 2 * places ? 0.72 : 1.;
+    return (wgs / places + tail) * tiles / n + (n > 1 ? 3.5 + 0.018 * wgs : 0.);
+  };
+  const double bar = (c.D == 128 ? 0.93 : 0.91) * cost(s);
+  int best = s;
+  for (int n = 1; n <= (c.D == 128 ? kMaxFwdSplits : 1) && n <= tiles / kMinTilesPerSplit; ++n)
+    if (cost(n) < bar && cost(n) < cost(best)) best = n;
+  return best;
+}
+
+// ---- which launches take one block of 32 queries per workgroup -------------------------------------
+// Such a workgroup pulls every key tile for 32 queries only, four times the tile traffic per query of
+// the general kernel, and needs no merge launch.  Its time follows rounds * tiles, rounds = workgroups
+// per CU, at least 1; that product is bounded below.  Measured (graph replays, us; few / general):
+//   D = 128: 4 workgroups x 10 tiles 7.1 / 10.7, 144 x 33 12.2 / 23.8, 132 x 109 24.5 / 31.2, 140 x 133
+//            28.1 / 33.7, 320 x 140 42 / 48, 624 x 29 24 / 48; lost: 70 x 133 26.7 / 24.5, 156 x 232 45.1 /
+//            43.8, 392 x 634 167 / 161, 792 x 325 195 / 162
+//   D = 64:  4 x 10 5.1 / 9.6, 144 x 33 8.2 / 19.9, 140 x 133 16.3 / 26.6, 156 x 232 25.6 / 34.0, 792 x 325
+//            109 / 112; lost: 588 x 927 230 / 178
+// Below half a round the general kernel's key split reaches CUs that this one leaves idle, hence the
+// lower bound there.  Returns the waves per workgroup, 0 = the general kernel: eight waves pay when
+// every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
+// with four); two workgroups of four waves share a CU otherwise (312 x 86: 30.2 against 36.4).
+inline int fwd_few_waves(const CallShape& c) {
+  if (c.in_order) return 0;
+  const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
+  const int64_t tiles = blocks_of(c.max_hist, kFwdKeyTile) + blocks_of(c.Nq, kFwdKeyTile);
+  const int64_t walk = wgs > c.n_cus ? tiles * wgs / c.n_cus : tiles;
+  const bool half_full = 2 * wgs >= c.n_cus;
+  const int64_t limit = c.D == 128 ? (half_full ? 200 : 112) : (half_full ? 900 : 300);
+  if (walk > limit) return 0;
+  return wgs <= c.n_cus && tiles >= 64 ? 8 : 4;
+}
+
+// ==== backward =====================================================================================
+constexpr int kBwdKeyTile = 64;    // keys per LDS tile of the general dQ kernel
+constexpr int kFewMaxRows = 2048;  // most chunk rows of the kernel for few rows (it holds their row terms in LDS)
+constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split of the dQ walk pays beyond half a round
+
+// Which launches take blocks of 32 rows: those whose blocks of 128 rows would leave most CUs with one
+// workgroup or none, up to where the key split of the general kernel takes over (a walk of 40 tiles and
+// more).  Measured (graph replays of the backward, us; few / general, split where it splits):
+//   D = 128: 2 blocks of 128 11 / 25, 48 25 / 55, 80 (nk 2880) 63 / 98, 96 (nk 3584) 73 / 80, 104 (nk 20280) 261 / 278;
+//            lost: 120 (nk 8190) 156 / 145, 156 (nk 29640) 563 / 406; without a split 192 (nk 910) 70 / 60, 256 (nk 400) 46 / 42
+//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 137 / 165, 120 (nk 8190) 82 / 90; lost: 156 (nk 29640) 267 / 236, 216 (nk
+//            10400) 156 / 136, 224 (nk 3120) 74 / 67; short walks 192 (nk 910) 32 / 38, 256 (nk 400) 23 / 26
+// Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
+// does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
+// with four), four otherwise (208 x 37: 30.0 against 34.3).
+inline int bwd_few_waves(const CallShape& c) {
+  if (c.in_order) return 0;
+  const int64_t blocks = (int64_t)blocks_of(c.Nq, 128) * c.pairs;
+  const bool long_walk = (c.max_hist + c.Nq) / kBwdKeyTile >= kMinSplitTiles;
+  const int sixteenths = c.D == 128 ? (long_walk ? 7 : 10) : (long_walk ? 8 : 16);  // of the CUs
+  if (c.Nq > kFewMaxRows || 16 * blocks > sixteenths * (int64_t)c.n_cus) return 0;
+  const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
+  return 8 * wgs <= 5 * (int64_t)c.n_cus && (c.max_hist + c.Nq) / 32 >= 64 ? 8 : 4;
+}
+
+constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }  // dQ workgroups a CU holds: 244 registers, or 165
+
+// How a dQ launch is split over the keys: `ways` parts (1 = not, 2 = a helper per k items, 3 = two helpers per item).
+// Measured (graph replays of the backward, us; split / not, D = 128 unless said otherwise; items = workgroups
+// without a split):
+//   up to a third of the places in three: 111 items x 512 tiles 478 (two ways: the same) / 807, 156 x 463 406 (two ways
+//     518) / 674, D = 64 156 x 463 236 / 447; between a third and half of the CUs two ways already give every CU one
+//     workgroup (104 x 317: 278, three 275), with a third less to merge
+//   up to the places in two, helpers of k items: 185 x 317 460 / 552, 300 x 488 894 / 1109, 444 x 512 1306 / 1345, 216 x 163 233 /
+//     269, 224 x 50 111 / 115, D = 64 592 x 366 792 / 856; lost: 192 x 15 63.7 / 59.8, 256 x 7 50 / 43
+//   just above the places, where a few workgroups make a second round: in three 518 x 366 1369 / 1627, 592 x 366 1404 / 1636,
+//     in two 600 x 341 1271 / 1470, 740 x 366 1695 / 1758; not beyond 1.5 rounds: 900 x 341 1999 / 1904
+struct DqWays {
+  int ways = 1, k = 1;
+};
+inline DqWays dq_ways(const CallShape& c) {
+  DqWays s;
+  const int items = blocks_of(c.Nq, 128) * c.pairs;
+  const int tiles = (c.min_hist + c.Nq) / kBwdKeyTile;
+  const int places = dq_places_per_cu(c.D) * c.n_cus;
+  if (c.in_order || tiles < (2 * items <= c.n_cus ? 16 : kMinSplitTiles)) return s;
+  if (3 * items <= places && (3 * items <= c.n_cus || 2 * items > c.n_cus)) {
+    s.ways = 3;
+  } else if (items <= places) {
+    int k = 1;
+    while (k < 16 && items + (items + k - 1) / k > places) ++k;
+    if (items + (items + k - 1) / k <= places) {
+      s.ways = 2;
+      s.k = k;
+    }
+  } else if (items * 25 <= places * 29) {  // 1.16 rounds
+    s.ways = 3;
+  } else if (items * 2 <= places * 3) {
+    s.ways = 2;
+  }
+  return s;
+}
+
+}  // namespace astro

@@ -1,0 +1,48 @@
+"""CPU test of the rules that choose the kernel and the key ranges of an attention call
+(launch_rules.hpp), compiled for the host: the calls the rules were measured at."""
+import os
+import shutil
+import subprocess
+from collections import namedtuple
+
+import pytest
+
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k")
+
+
+@pytest.fixture(scope="module")
+def rules(repo_root, tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path_factory.mktemp("rules") / "rules")
+    src = os.path.join(repo_root, "tests", "host_rules", "rules_main.cpp")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", src, "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def ask(D, pairs, Nq, hist, block_rows=0, max_hist=None, in_order=False):
+        line = f"{D} {pairs} {Nq} {block_rows} {hist} {hist if max_hist is None else max_hist} {int(in_order)}\n"
+        out = subprocess.run([exe], input=line, capture_output=True, text=True, check=True).stdout
+        return Rule(*map(int, out.split()))
+    return ask
+
+
+@pytest.mark.parametrize("D,pairs,Nq,hist,want", [
+    (128, 12, 4680, 28080, Rule(0, 4, 0, 2, 7)),   # one production stream: 444 workgroups
+    (128, 48, 4680, 28080, Rule(0, 1, 0, 1, 1)),   # four
+    (128, 2, 252, 189, Rule(4, 1, 4, 1, 1)),       # a few rows
+    (64, 16, 4680, 20280, Rule(0, 3, 0, 2, 4)),
+])
+def test_named_sizes(rules, D, pairs, Nq, hist, want):
+    got = rules(D, pairs, Nq, hist)
+    # what a call's other route would be cut into does not matter
+    assert got.fwd_few == want.fwd_few and got.bwd_few == want.bwd_few
+    assert want.fwd_few or got.fwd_splits == want.fwd_splits
+    assert want.bwd_few or (got.ways, got.k) == (want.ways, want.k)
+
+
+def test_outputs_over_inputs_take_the_routes_that_read_first(rules):
+    for D, pairs, Nq, hist in [(128, 2, 252, 189), (128, 12, 4680, 28080), (64, 6, 2080, 1560), (128, 31, 2080, 1040)]:
+        got = rules(D, pairs, Nq, hist, in_order=True)
+        assert got.fwd_few == 0 and got.bwd_few == 0 and got.ways == 1
+    assert rules(128, 12, 4680, 2160, in_order=True).fwd_splits == 4 and rules(128, 12, 4680, 2160).fwd_splits != 4
