@@ -106,13 +106,7 @@ struct AttnOperands {
 };
 
 inline CallShape call_shape(const DevGeom& g, const AttnOperands& op) {
-  CallShape c{g.D, g.n_cus, g.B * g.H, op.Nq, op.block_rows, op.hist_rows.v[0], op.hist_rows.v[0], op.in_order};
-  for (int b = 1; b < g.B / op.group; ++b) {
-    const int n = op.hist_rows.v[b];
-    c.min_hist = n < c.min_hist ? n : c.min_hist;
-    c.max_hist = n > c.max_hist ? n : c.max_hist;
-  }
-  return c;
+  return make_call_shape(g.D, g.n_cus, g.B * g.H, op.Nq, op.block_rows, op.in_order, op.hist_rows.v, g.B / op.group);
 }
 
 // ---- fp32 debug path -------------------------------------------------------

@@ -12,10 +12,32 @@ struct CallShape {
   int pairs;               // candidates * heads
   int Nq, block_rows;      // chunk rows; causal block in rows, 0 = none
   int min_hist, max_hist;  // resident rows of the stream with the fewest and with the most
+  double mean_hist;
   bool in_order;           // see AttnOperands::in_order
 };
 
+inline CallShape make_call_shape(int D, int n_cus, int pairs, int Nq, int block_rows, bool in_order, const int32_t* hist, int streams) {
+  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], hist[0], 0., in_order};
+  for (int b = 0; b < streams; ++b) {
+    c.min_hist = hist[b] < c.min_hist ? hist[b] : c.min_hist;
+    c.max_hist = hist[b] > c.max_hist ? hist[b] : c.max_hist;
+    c.mean_hist += (double)hist[b] / streams;
+  }
+  return c;
+}
+
 inline int blocks_of(int rows, int block) { return (rows + block - 1) / block; }
+
+// keys a query sees, over all streams and, under causal blocks, over the chunk
+inline double mean_keys(const CallShape& c) {
+  if (c.block_rows <= 0 || c.block_rows >= c.Nq) return c.mean_hist + c.Nq;
+  double seen = 0.;
+  for (int first = 0; first < c.Nq; first += c.block_rows) {
+    const int end = first + c.block_rows < c.Nq ? first + c.block_rows : c.Nq;
+    seen += (double)(end - first) * end;
+  }
+  return c.mean_hist + seen / c.Nq;
+}
 
 // ==== forward ======================================================================================
 constexpr int kMaxFwdSplits = 8;  // most key ranges of a launch
@@ -34,15 +56,15 @@ inline bool fwd_may_split(int n_cus, int pairs, int Nq) { return blocks_of(Nq, 1
 inline int fwd_splits(const CallShape& c) {
   if (!fwd_may_split(c.n_cus, c.pairs, c.Nq)) return 1;
   const int items = blocks_of(c.Nq, 128) * c.pairs, places = kFwdWorkgroupsPerCu * c.n_cus;
-  // key tiles of the workgroup that sees the fewest: under causal blocks that is the first query
-  // tile, which sees one block of the chunk (a range may still come out empty or unseen for some
-  // queries: both report weight 0 to the merge)
-  const int chunk_rows = c.block_rows > 0 && c.block_rows < c.Nq ? c.block_rows : c.Nq;
-  const int tiles = blocks_of(c.min_hist, kFwdKeyTile) + blocks_of(chunk_rows, kFwdKeyTile);
+  // Key tiles of the mean workgroup.  Ranges of a stream with few frames, or of the first causal blocks, may come
+  // out empty or unseen for some queries: both report weight 0 to the merge.  (By the workgroup with the fewest
+  // tiles, four streams of 0, 7, 9 and 10 frames, 72 workgroups, were not cut at all because of the first: 236 us,
+  // 62 in seven ranges.)
+  const double tiles = mean_keys(c) / kFwdKeyTile;
   // Enough parts for two rounds ...
   int s = (2 * places + items - 1) / items;
   if (s > kMaxFwdSplits) s = kMaxFwdSplits;
-  if (s > tiles / kMinTilesPerSplit) s = tiles / kMinTilesPerSplit;
+  if (s > tiles / kMinTilesPerSplit) s = (int)(tiles / kMinTilesPerSplit);
   if (s <= 1) return 1;
   if (c.in_order) return s;  // the merge launch writes the outputs
   // ... unless another count is clearly better by this estimate, in units of one key tile of a full CU
