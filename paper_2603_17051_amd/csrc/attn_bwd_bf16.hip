@@ -43,6 +43,7 @@ struct BwdParams {
   int H, Nq, BH, tiles;  // BH = candidates * heads; tiles = workgroups per pair of the kernel being launched
   int group;             // candidates per cache stream
   int block_rows;        // causal block inside the chunk in token rows, 0 = none
+  bool by_xcd;           // order of the workgroups, see order_by_xcd()
   int64_t cache_rows;
   float scale;
   StreamInts hist_rows;
@@ -332,22 +333,23 @@ template <int D, int OCC, int kWaves, bool kSplit>
 __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams p, DqSplit split) {
   __shared__ __attribute__((aligned(1024))) char lds[4 * KT * D * 2];  // K0 V0 K1 V1
   if constexpr (!kSplit) {
-    const WorkItem item = work_item(p.tiles, p.BH, true);
+    const WorkItem item = work_item(p.tiles, p.BH, p.by_xcd);
     if (item.valid) dq_item<D, kWaves, false>(p, split, item, 0, lds);
   } else {
     // one loop for all, so that the code of an item is there once: a main workgroup and a helper of a cut in
     // three have one item, the others k consecutive ones (an XCD's helpers stay with one or two pairs)
     const int items = p.tiles * p.BH;
     const int block = (int)blockIdx.x;
+    auto order = [&](int i, int n) { return p.by_xcd ? xcd_order(i, n) : i; };
     int which = 0, first, count = 1;
     if (block < items) {
-      first = xcd_order(block, items);
+      first = order(block, items);
     } else if (split.ways == 3) {
       which = block < 2 * items ? 1 : 2;
-      first = xcd_order(block - which * items, items);
+      first = order(block - which * items, items);
     } else {
       which = 1;
-      first = xcd_order(block - items, split.helpers(items)) * split.k;
+      first = order(block - items, split.helpers(items)) * split.k;
       count = items - first < split.k ? items - first : split.k;
     }
     for (int i = first; i < first + count; ++i) dq_item<D, kWaves, true>(p, split, WorkItem{i % p.tiles, i / p.tiles, true}, which, lds);
@@ -803,7 +805,7 @@ __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams
   __shared__ __attribute__((aligned(1024))) char lds[DkvLds<D>::kTotal];
   // one pair's operands through one L2: 183 instead of 202 us at D = 64 (16 heads, 592 workgroups, causal); at D = 128,
   // where a pair's operands alone are half an L2, no gain (1.01 against 1.00 ms at batch 4)
-  const WorkItem item = work_item(p.tiles, p.BH, D == 64);
+  const WorkItem item = work_item(p.tiles, p.BH, D == 64 && (!kRing || p.by_xcd));
   if (!item.valid) return;
   const int n_keys = kRing ? p.hist_rows.v[item.bh / p.H] : p.Nq;
   if (item.tile * 128 >= n_keys) return;  // whole workgroup, before any barrier
@@ -1120,7 +1122,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_bwd_few_kernel(BwdParams 
   __shared__ __attribute__((aligned(16))) float terms[2][kFewMaxRows];
   const int n_side = p.tiles * p.BH;
   const bool key_side = (int)blockIdx.x >= n_side;
-  const WorkItem item = work_item(p.tiles, p.BH, true, (int)blockIdx.x - (key_side ? n_side : 0));
+  const WorkItem item = work_item(p.tiles, p.BH, p.by_xcd, (int)blockIdx.x - (key_side ? n_side : 0));
   if (!item.valid) return;
   if (key_side)
     few_dkv<D, kWaves>(p, item, lds, terms);
@@ -1155,6 +1157,7 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   p.hist_rows = op.hist_rows;
   p.group = op.group;
   p.block_rows = op.block_rows;
+  p.by_xcd = true;
   return p;
 }
 
@@ -1179,6 +1182,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   p.tiles = (op.Nq + kDqWaves * 32 - 1) / (kDqWaves * 32);
   const int items = work_grid_size(p.tiles, p.BH);
   const DqWays ways = dq_ways(shape);
+  p.by_xcd = order_by_xcd(shape, items);
   const DqSplit split{ways.ways, ways.k, dk, dv};
   {
     ProfileScope prof("attn_bwd_dq_bf16", stream);
@@ -1214,6 +1218,7 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   if (max_hist == 0) return hipSuccess;
   const int ktile = 128;
   p.tiles = (max_hist + ktile - 1) / ktile;
+  p.by_xcd = order_by_xcd(call_shape(g, op), work_grid_size(p.tiles, p.BH));
   auto run = [&](const RingGrads& to) {
     ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
     attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, to);

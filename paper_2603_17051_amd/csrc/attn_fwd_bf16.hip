@@ -56,6 +56,7 @@ struct FwdParams {
   float* lse_part;   // [splits][B][H][Nq]
   int H, Nq, BH, q_tiles, group;  // BH = candidates * heads; group = candidates per cache stream
   int block_rows;                 // causal block inside the chunk in token rows, 0 = none
+  bool by_xcd;                    // order of the workgroups, see order_by_xcd()
   int64_t cache_rows;  // C*T
   StreamInts hist_rows;
 };
@@ -278,7 +279,7 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
   // per-lane count of visible chunk rows: kept in LDS, not in a register the tile loop has no room for
   __shared__ int vis_lds[kCausal ? 2 * kWaves * 64 : 1];
 
-  const WorkItem item = work_item(p.q_tiles, p.BH * p.splits, true);
+  const WorkItem item = work_item(p.q_tiles, p.BH * p.splits, p.by_xcd);
   if (!item.valid) return;
   const int split = item.bh % p.splits;
   const PairIndex pair = split_pair(item.bh / p.splits, p.H, p.group);
@@ -465,7 +466,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * F::kWaveBytes];
   __shared__ float2 stats[kWaves][32];  // softmax reference and row sum of each wave's keys
 
-  const WorkItem item = work_item(p.q_tiles, p.BH, true);
+  const WorkItem item = work_item(p.q_tiles, p.BH, p.by_xcd);
   if (!item.valid) return;
   const PairIndex pair = split_pair(item.bh, p.H, p.group);
   const int b = pair.b, h = pair.h;
@@ -645,6 +646,7 @@ FwdParams make_params(const DevGeom& g, const AttnOperands& op, void* out, float
   p.block_rows = op.block_rows;
   p.BH = g.B * g.H;
   p.q_tiles = 0;
+  p.by_xcd = true;
   p.splits = 1;
   p.out_part = nullptr;
   p.lse_part = nullptr;
@@ -666,7 +668,9 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
   const int qtile = kWaves * 32;
   p.q_tiles = (op.Nq + qtile - 1) / qtile;
   // a launch that would leave the chip under two rounds of workgroups is split over the keys
-  p.splits = parts ? fwd_splits(call_shape(g, op)) : 1;
+  const CallShape shape = call_shape(g, op);
+  p.splits = parts ? fwd_splits(shape) : 1;
+  p.by_xcd = order_by_xcd(shape, p.q_tiles * p.BH * p.splits);
   p.out_part = (__bf16*)parts;
   p.lse_part = (float*)((char*)parts + (size_t)p.splits * p.BH * op.Nq * D * 2);
   dim3 grid(work_grid_size(p.q_tiles, p.BH * p.splits));

@@ -234,7 +234,7 @@ struct FewRows {
 // K/V is then pulled through one or two L2s instead of all eight (an eighth of the fabric reads;
 // 1.5-2.5 % faster for the kernels that walk the whole window; with 10 pairs of 14 blocks of 32
 // queries over 4256 keys the forward takes 28.1 instead of 33.3 us).  The eighths are cut by items, not by pairs, so
-// 12 heads of one stream fill all XCDs too.
+// 12 heads of one stream fill all XCDs too; items of different lengths: see order_by_xcd().
 struct WorkItem {
   int tile, bh;
   bool valid;

@@ -7,7 +7,7 @@ from collections import namedtuple
 
 import pytest
 
-Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k")
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd", defaults=[1])
 
 
 @pytest.fixture(scope="module")
@@ -55,3 +55,14 @@ def test_ranges_of_streams_of_different_lengths(rules):
     tokens, 72 workgroups: 236 us uncut, 62 in seven ranges), nor do causal blocks."""
     assert rules(128, 4, 2304, [0, 5376, 6912, 7680], block_rows=768).fwd_splits >= 5
     assert rules(64, 9, 4218, [1406, 2812, 16872], block_rows=1406).fwd_splits >= 4
+
+
+def test_order_of_streams_of_different_lengths(rules):
+    """A contiguous eighth of the workgroups per XCD while the heaviest eighth has little more than its share."""
+    for heads in (3, 8):  # pairs that do not divide evenly over the XCDs, and that do
+        for hist in ([28080] * 8, [28080] * 7 + [0], [15600, 14040], [9000] * 5 + [9900]):
+            assert rules(128, heads * len(hist), 4680, hist).by_xcd == 1
+        for hist in ([0, 15600], [500] * 5 + [9900], [0, 28080, 28080, 0]):
+            assert rules(128, heads * len(hist), 9360, hist).by_xcd == 0
+            # every workgroup on a CU of its own
+            assert rules(128, heads * len(hist), 128, hist).by_xcd == 1
