@@ -70,9 +70,8 @@ constexpr int kMaxFwdSplits = 8;  // most key ranges of a launch
 constexpr int kFwdKeyTile = 32;   // keys per LDS tile
 
 // ---- key-range split of launches that cannot fill the chip -----------------------------------
-// The forward holds three workgroups per CU.  With fewer than two rounds of workgroups (one
-// stream of 12 heads and 37 query tiles is 444 workgroups on 768 places) each (pair, query
-// tile) may be cut into `splits` key ranges, at most kMaxFwdSplits and never less than
+// With fewer than six workgroups per CU, two rounds at D = 128 (one stream of 12 heads and 37 query tiles is
+// 444 workgroups on 768 places), each (pair, query tile) may be cut into `splits` key ranges, at most kMaxFwdSplits and never less than
 // kMinTilesPerSplit key tiles each.
 constexpr int kMinTilesPerSplit = 4, kFwdWorkgroupsPerCu = 3;
 
@@ -93,23 +92,27 @@ inline int fwd_splits(const CallShape& c) {
   if (s > tiles / kMinTilesPerSplit) s = (int)(tiles / kMinTilesPerSplit);
   if (s <= 1) return 1;
   if (c.in_order) return s;  // the merge launch writes the outputs
-  // ... unless another count is clearly better by this estimate, in units of one key tile of a full CU
-  // (1.14 us at D = 128): items * s / places rounds of 1 / s of the walk each, where a last round with one,
-  // two or three workgroups on a CU takes 0.45, 0.72 or 1 of a full one, plus 0.018 per part and item for
-  // writing and merging it, plus the merge launch.  It is within 3 % of most times measured at D = 128, so 7 %
-  // decide: 480 x 183 tiles 1 part 168 us (4 parts 188), 400 x 682 5 parts 502 (4: 522), 200 x 358 7 parts 150 (8: 161), 111
-  // x 1024 6 parts 232 (8: 239).  At D = 64, with four workgroups per CU, it only tells when not to split at all
-  // (480 x 183: 104 us, 4 parts 110).
+  // ... unless another count is clearly better by this estimate, in us: items * n / places rounds of 1 / n of the walk
+  // each, where a last round with j workgroups on a CU takes tail[j] of a full one; a part and item for writing and
+  // merging it, and the merge launch; a share of what the longest stream's walk is over the mean.  Fitted to every
+  // count at 2517 shapes of 1 to 1535 workgroups (median error 3 %); what it then picks is 0.6 % (D = 128) and 1.1 % (D = 64)
+  // slower than the best count in the mean.  It replaces an estimate with three workgroups per CU and a merge twice as
+  // dear, which left D = 64 launches uncut that gain by it: 240 workgroups x 165 tiles 110 us uncut, 64 in four; 480 x 341
+  // 239 uncut, 194 in five.
+  const bool d128 = c.D == 128;
+  const int per_cu = d128 ? 3 : 4;  // workgroups a CU holds: 166 registers, or 108
+  const double per_tile = d128 ? 0.95 : 0.63, launch = d128 ? 3.4 : 3.5, per_part = d128 ? 0.013 : 0.006;
+  static constexpr double kTail[2][4] = {{0.53, 0.74, 1., 1.}, {0.51, 0.66, 0.88, 1.}};
   auto cost = [&](int n) {
-    const int wgs = items * n, rest = wgs % places;
-    const double tail = rest == 0 ? 0. : 3 * rest <= places ? 0.45 : 3 * rest <= 2 * places ? 0.72 : 1.;
-    return (wgs / places + tail) * tiles / n + (n > 1 ? 3.5 + 0.018 * wgs : 0.);
+    const int64_t wgs = (int64_t)items * n, round = (int64_t)per_cu * c.n_cus, rest = wgs % round;
+    const double rounds = (double)(wgs / round) + (rest ? kTail[d128 ? 0 : 1][(rest + c.n_cus - 1) / c.n_cus - 1] : 0.);
+    const double over = 0.4 * (c.max_hist - c.mean_hist) / kFwdKeyTile;
+    return per_tile * (rounds * tiles + over) / n + (n > 1 ? launch + per_part * wgs : 0.);
   };
-  const double bar = (c.D == 128 ? 0.93 : 0.91) * cost(s);
-  int best = s;
-  for (int n = 1; n <= (c.D == 128 ? kMaxFwdSplits : 1) && n <= tiles / kMinTilesPerSplit; ++n)
-    if (cost(n) < bar && cost(n) < cost(best)) best = n;
-  return best;
+  int best = 1;
+  for (int n = 2; n <= kMaxFwdSplits && n <= tiles / kMinTilesPerSplit; ++n)
+    if (cost(n) < cost(best)) best = n;
+  return cost(best) < 0.93 * cost(s) ? best : s;
 }
 
 // ---- which launches take one block of 32 queries per workgroup -------------------------------------

@@ -47,7 +47,7 @@ def test_outputs_over_inputs_take_the_routes_that_read_first(rules):
     for D, pairs, Nq, hist in [(128, 2, 252, 189), (128, 12, 4680, 28080), (64, 6, 2080, 1560), (128, 31, 2080, 1040)]:
         got = rules(D, pairs, Nq, hist, in_order=True)
         assert got.fwd_few == 0 and got.bwd_few == 0 and got.ways == 1
-    assert rules(128, 12, 4680, 2160, in_order=True).fwd_splits == 4 and rules(128, 12, 4680, 2160).fwd_splits != 4
+    assert rules(128, 480, 128, 5728, in_order=True).fwd_splits == 4 and rules(128, 480, 128, 5728).fwd_splits == 1
 
 
 def test_ranges_of_streams_of_different_lengths(rules):
@@ -66,3 +66,11 @@ def test_order_of_streams_of_different_lengths(rules):
             assert rules(128, heads * len(hist), 9360, hist).by_xcd == 0
             # every workgroup on a CU of its own
             assert rules(128, heads * len(hist), 128, hist).by_xcd == 1
+
+
+def test_ranges_of_launches_with_64_wide_heads(rules):
+    """Four workgroups fit a CU at D = 64: sizes that an estimate with three left uncut (240 workgroups x 165 tiles
+    110 us uncut, 65 in three or four ranges; 480 x 341 239 uncut, 194 - 200 in three to five; 256 x 165 106, 66)."""
+    assert rules(64, 40, 720, 4560, block_rows=240).fwd_splits in (3, 4)
+    assert rules(64, 96, 520, 10400).fwd_splits > 2
+    assert rules(64, 32, 960, 4320, block_rows=480).fwd_splits in (3, 4)
