@@ -117,24 +117,37 @@ inline int fwd_splits(const CallShape& c) {
 
 // ---- which launches take one block of 32 queries per workgroup -------------------------------------
 // Such a workgroup pulls every key tile for 32 queries only, four times the tile traffic per query of
-// the general kernel, and needs no merge launch.  Its time follows rounds * tiles, rounds = workgroups
-// per CU, at least 1; that product is bounded below.  Measured (graph replays, us; few / general):
+// the general kernel, and needs no merge launch.  Its time follows the workgroups on the fullest CU times the
+// tiles, so the product below is bounded, and lower where the last round of CUs is nearly empty.  Measured (us;
+// few / general):
 //   D = 128: 4 workgroups x 10 tiles 7.1 / 10.7, 144 x 33 12.2 / 23.8, 132 x 109 24.5 / 31.2, 140 x 133
 //            28.1 / 33.7, 320 x 140 42 / 48, 624 x 29 24 / 48; lost: 70 x 133 26.7 / 24.5, 156 x 232 45.1 /
-//            43.8, 392 x 634 167 / 161, 792 x 325 195 / 162
-//   D = 64:  4 x 10 5.1 / 9.6, 144 x 33 8.2 / 19.9, 140 x 133 16.3 / 26.6, 156 x 232 25.6 / 34.0, 792 x 325
-//            109 / 112; lost: 588 x 927 230 / 178
+//            43.8, 270 x 164 58 / 44, 288 x 136 55 / 39, 576 x 6 25 / 22, 640 x 8 28 / 26, 392 x 634 167 / 161
+//   D = 64:  4 x 10 5.1 / 9.6, 144 x 33 8.2 / 19.9, 140 x 133 16.3 / 26.6, 156 x 232 25.6 / 34.0, 960 x 112 55 / 58, 1440 x 60
+//            49 / 58; lost: 294 x 342 72 / 51, 279 x 495 88 / 65, 288 x 456 89 / 58, 294 x 634 117 / 80
 // Below half a round the general kernel's key split reaches CUs that this one leaves idle, hence the
-// lower bound there.  Returns the waves per workgroup, 0 = the general kernel: eight waves pay when
-// every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
+// lower bound there.  The walk is the longest stream's; where streams differ, the general kernel, which cuts
+// it, takes over at half the bounds and beyond three (D = 128) or five workgroups per CU (longest and mean walk: 1056 x
+// 180, 89 88 / 56; 432 x 216, 148 46 / 38; 1536 x 28, 19 61 / 48; the other way 480 x 54, 42 30 / 39; 7 % in the mean of 85 such
+// launches).  Returns the waves per workgroup, 0 = the general kernel: eight waves pay
+// when every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
 // with four); two workgroups of four waves share a CU otherwise (312 x 86: 30.2 against 36.4).
 inline int fwd_few_waves(const CallShape& c) {
   if (c.in_order) return 0;
   const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
   const int64_t tiles = blocks_of(c.max_hist, kFwdKeyTile) + blocks_of(c.Nq, kFwdKeyTile);
   const int64_t walk = wgs > c.n_cus ? tiles * wgs / c.n_cus : tiles;
-  const bool half_full = 2 * wgs >= c.n_cus;
-  const int64_t limit = c.D == 128 ? (half_full ? 200 : 112) : (half_full ? 900 : 300);
+  const int64_t per_cu = (wgs + c.n_cus - 1) / c.n_cus;  // on the fullest CU
+  const double fill = (double)wgs / (per_cu * c.n_cus);
+  const bool half_full = 2 * wgs >= c.n_cus, uneven = c.xcd_load >= 1.15;
+  int64_t limit;
+  if (c.D == 128) {
+    limit = !half_full ? 112 : per_cu == 2 && fill < 0.63 ? 100 : 200;
+    if (per_cu == 3 && fill < 0.84 && walk < 40) limit = 0;
+  } else {
+    limit = !half_full ? 300 : per_cu > 2 ? 900 : per_cu == 2 && fill < 0.7 ? 250 : 400;
+  }
+  if (uneven) limit = per_cu > (c.D == 128 ? 3 : 5) ? 0 : limit / 2;
   if (walk > limit) return 0;
   return wgs <= c.n_cus && tiles >= 64 ? 8 : 4;
 }

@@ -74,3 +74,13 @@ def test_ranges_of_launches_with_64_wide_heads(rules):
     assert rules(64, 40, 720, 4560, block_rows=240).fwd_splits in (3, 4)
     assert rules(64, 96, 520, 10400).fwd_splits > 2
     assert rules(64, 32, 960, 4320, block_rows=480).fwd_splits in (3, 4)
+
+
+def test_forward_with_few_rows_gives_way_where_the_general_kernel_is_faster(rules):
+    """Sizes measured with both: a second or third workgroup on a few CUs only, short walks, and streams of
+    different lengths, whose longest walk the general kernel cuts."""
+    for call in [(64, 6, 1560, 17160), (64, 3, 2970, 12870, 990), (128, 192, 96, 96), (128, 160, 126, 126, 63), (64, 12, 792, 11880),
+                 (128, 6, 1440, 3900), (64, 32, 1040, [2600, 1560, 4680, 2600, 0, 1040, 2080, 0]), (128, 480, 126, [63, 630, 630, 63])]:
+        assert rules(*call).fwd_few == 0, call
+    for call in [(128, 4, 32, 288), (64, 8, 570, 2570), (128, 12, 390, 3120), (128, 16, 240, 4240), (64, 32, 960, 2624), (128, 64, 320, 608)]:
+        assert rules(*call).fwd_few != 0, call
