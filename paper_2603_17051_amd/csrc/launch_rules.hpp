@@ -155,28 +155,30 @@ inline int fwd_few_waves(const CallShape& c) {
 // ==== backward =====================================================================================
 constexpr int kBwdKeyTile = 64;    // keys per LDS tile of the general dQ kernel
 constexpr int kFewMaxRows = 2048;  // most chunk rows of the kernel for few rows (it holds their row terms in LDS)
-constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split of the dQ walk pays beyond half a round
 
 // Which launches take blocks of 32 rows: those whose blocks of 128 rows would leave most CUs with one
-// workgroup or none, up to where the key split of the general kernel takes over (a walk of 40 tiles and
-// more).  Measured (graph replays of the backward, us; few / general, split where it splits):
-//   D = 128: 2 blocks of 128 11 / 25, 48 25 / 55, 80 (nk 2880) 63 / 98, 96 (nk 3584) 73 / 80, 104 (nk 20280) 261 / 278;
-//            lost: 120 (nk 8190) 156 / 145, 156 (nk 29640) 563 / 406; without a split 192 (nk 910) 70 / 60, 256 (nk 400) 46 / 42
-//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 137 / 165, 120 (nk 8190) 82 / 90; lost: 156 (nk 29640) 267 / 236, 216 (nk
-//            10400) 156 / 136, 224 (nk 3120) 74 / 67; short walks 192 (nk 910) 32 / 38, 256 (nk 400) 23 / 26
+// workgroup or none.  Measured (us of the backward; few / general, split where it splits; blocks of 128 x key tiles of 64):
+//   D = 128: 2 blocks 11 / 25, 48 25 / 55, 80 x 45 63 / 98, 96 x 56 73 / 80, 104 x 317 261 / 278; lost: 120 x 128 156 / 145,
+//            144 x 15 71 / 66, 144 x 21 96 / 78, 160 x 20 93 / 76, 156 x 463 563 / 406, 192 x 14 70 / 60
+//   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 137 / 165, 120 x 128 82 / 90, 192 x 14 32 / 38; lost: 156 x 463 267 / 236, 216 x 32
+//            83 / 67, 240 x 35 77 / 67, 256 x 35 90 / 70, 256 x 9 46 / 43, 224 x 49 74 / 67
+// Over 2600 shapes it takes 0.6 - 1.0 of the general kernels' time (medians by number of tiles) just below these lines (96
+// - 128 blocks, D = 64 129 - 192) and 1.0 - 1.3 just above them; walks of 40 tiles and more, which the general dQ
+// kernel splits, have the line lower.
 // Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
 // does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
 // with four), four otherwise (208 x 37: 30.0 against 34.3).
 inline int bwd_few_waves(const CallShape& c) {
   if (c.in_order) return 0;
   const int64_t blocks = (int64_t)blocks_of(c.Nq, 128) * c.pairs;
-  const bool long_walk = (c.max_hist + c.Nq) / kBwdKeyTile >= kMinSplitTiles;
-  const int sixteenths = c.D == 128 ? (long_walk ? 7 : 10) : (long_walk ? 8 : 16);  // of the CUs
+  const bool long_walk = (c.max_hist + c.Nq) / kBwdKeyTile >= 40;
+  const int sixteenths = c.D == 128 ? (long_walk ? 7 : 8) : (long_walk ? 8 : 12);  // of the CUs
   if (c.Nq > kFewMaxRows || 16 * blocks > sixteenths * (int64_t)c.n_cus) return 0;
   const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
   return 8 * wgs <= 5 * (int64_t)c.n_cus && (c.max_hist + c.Nq) / 32 >= 64 ? 8 : 4;
 }
 
+constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split of the dQ walk pays beyond half a round
 constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }  // dQ workgroups a CU holds: 244 registers, or 165
 
 // How a dQ launch is split over the keys: `ways` parts (1 = not, 2 = a helper per k items, 3 = two helpers per item).

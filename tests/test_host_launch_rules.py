@@ -84,3 +84,12 @@ def test_forward_with_few_rows_gives_way_where_the_general_kernel_is_faster(rule
         assert rules(*call).fwd_few == 0, call
     for call in [(128, 4, 32, 288), (64, 8, 570, 2570), (128, 12, 390, 3120), (128, 16, 240, 4240), (64, 32, 960, 2624), (128, 64, 320, 608)]:
         assert rules(*call).fwd_few != 0, call
+
+
+def test_backward_with_few_rows_gives_way_where_the_general_kernels_are_faster(rules):
+    """Blocks of 128 rows just above and below the lines, at both head sizes, short walks and long ones."""
+    for call in [(128, 24, 696, 696), (128, 32, 640, 640), (128, 48, 330, 660, 126), (64, 24, 1040, 1040), (64, 32, 960, 1280), (64, 48, 640, 1600),
+                 (64, 256, 128, 448), (128, 30, 390, 7800)]:
+        assert rules(*call).bwd_few == 0, call
+    for call in [(128, 16, 480, 2400), (128, 32, 390, 520), (64, 48, 390, 520), (64, 32, 390, 7800), (128, 2, 128, 448)]:
+        assert rules(*call).bwd_few != 0, call
