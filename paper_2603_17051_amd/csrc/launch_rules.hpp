@@ -3,6 +3,7 @@
 #pragma once
 #include <cstddef>
 #include <cstdint>
+#include <initializer_list>
 
 namespace astro {
 
@@ -11,7 +12,7 @@ struct CallShape {
   int D, n_cus;
   int pairs;               // candidates * heads
   int Nq, block_rows;      // chunk rows; causal block in rows, 0 = none
-  int min_hist, max_hist;  // resident rows of the stream with the fewest and with the most
+  int max_hist;            // resident rows of the stream with the most
   double mean_hist;
   double xcd_load;  // key rows in the heaviest contiguous eighth of the workgroups over the mean eighth's
   bool in_order;    // see AttnOperands::in_order
@@ -34,9 +35,8 @@ inline double heaviest_eighth(const int32_t* hist, int streams, int Nq) {
 }
 
 inline CallShape make_call_shape(int D, int n_cus, int pairs, int Nq, int block_rows, bool in_order, const int32_t* hist, int streams) {
-  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], hist[0], 0., heaviest_eighth(hist, streams, Nq), in_order};
+  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], 0., heaviest_eighth(hist, streams, Nq), in_order};
   for (int b = 0; b < streams; ++b) {
-    c.min_hist = hist[b] < c.min_hist ? hist[b] : c.min_hist;
     c.max_hist = hist[b] > c.max_hist ? hist[b] : c.max_hist;
     c.mean_hist += (double)hist[b] / streams;
   }
@@ -178,43 +178,55 @@ inline int bwd_few_waves(const CallShape& c) {
   return 8 * wgs <= 5 * (int64_t)c.n_cus && (c.max_hist + c.Nq) / 32 >= 64 ? 8 : 4;
 }
 
-constexpr int kMinSplitTiles = 40;  // key tiles of 64 rows from which a split of the dQ walk pays beyond half a round
-constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }  // dQ workgroups a CU holds: 244 registers, or 165
+// dQ workgroups a CU holds: 244 registers (split 256), or 165 (split 168, 8 more in scratch)
+constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }
 
-// How a dQ launch is split over the keys: `ways` parts (1 = not, 2 = a helper per k items, 3 = two helpers per item).
-// Measured (graph replays of the backward, us; split / not, D = 128 unless said otherwise; items = workgroups
-// without a split):
-//   up to a third of the places in three: 111 items x 512 tiles 478 (two ways: the same) / 807, 156 x 463 406 (two ways
-//     518) / 674, D = 64 156 x 463 236 / 447; between a third and half of the CUs two ways already give every CU one
-//     workgroup (104 x 317: 278, three 275), with a third less to merge
-//   up to the places in two, helpers of k items: 185 x 317 460 / 552, 300 x 488 894 / 1109, 444 x 512 1306 / 1345, 216 x 163 233 /
-//     269, 224 x 50 111 / 115, D = 64 592 x 366 792 / 856; lost: 192 x 15 63.7 / 59.8, 256 x 7 50 / 43
-//   just above the places, where a few workgroups make a second round: in three 518 x 366 1369 / 1627, 592 x 366 1404 / 1636,
-//     in two 600 x 341 1271 / 1470, 740 x 366 1695 / 1758; not beyond 1.5 rounds: 900 x 341 1999 / 1904
+// How a dQ launch is split over the keys: `ways` parts (1 = not, 2 = a helper per k items, 3 = two helpers per item;
+// items = workgroups without a split).  By an estimate in us: rounds of places times the tiles of a part, where a
+// last round with j workgroups on a CU takes tail[j] of a full one; with a split, the merge launch and a part of it per
+// item.  Fitted to every way at 2235 shapes of 2 to 1500 items (median error 3 %); what it picks is 0.3 % (D =
+// 128) and 0.6 % (D = 64) slower than the best way in the mean.  Measured (us of the backward; split / not, D = 128 unless
+// said otherwise):
+//   111 items x 512 tiles in three 478 / 807, 156 x 463 in three 406 (in two 518) / 674, 185 x 317 in two 460 / 552, 300 x
+//   488 894 / 1109, 444 x 512 a helper per seven 1306 / 1345, 518 x 366 in three 1369 / 1627, 740 x 366 in two 1695 /
+//   1758, D = 64 592 x 366 792 / 856; not split: 480 x 45 a helper per fifteen 241 / 195, 480 x 80 325 / 284, 384 x 40 187 / 181,
+//   D = 64 480 x 40 106 / 93, 640 x 45 157 / 149, 720 x 45 198 / 166, 432 x 86 174 / 163
+// A helper of several items whose walks differ finishes with the longest, so streams of different lengths have a helper each
+// (444 items, 1560 to 17160 rows, D = 64: a helper per eight 562, each 508).
 struct DqWays {
   int ways = 1, k = 1;
 };
 inline DqWays dq_ways(const CallShape& c) {
-  DqWays s;
-  const int items = blocks_of(c.Nq, 128) * c.pairs;
-  const int tiles = (c.min_hist + c.Nq) / kBwdKeyTile;
-  const int places = dq_places_per_cu(c.D) * c.n_cus;
-  if (c.in_order || tiles < (2 * items <= c.n_cus ? 16 : kMinSplitTiles)) return s;
-  if (3 * items <= places && (3 * items <= c.n_cus || 2 * items > c.n_cus)) {
-    s.ways = 3;
-  } else if (items <= places) {
-    int k = 1;
-    while (k < 16 && items + (items + k - 1) / k > places) ++k;
-    if (items + (items + k - 1) / k <= places) {
-      s.ways = 2;
-      s.k = k;
+  const int items = blocks_of(c.Nq, 128) * c.pairs, places = dq_places_per_cu(c.D) * c.n_cus;
+  if (c.in_order || 2 * items > 3 * places) return {};
+  const bool d128 = c.D == 128;
+  const double tiles = mean_keys(c) / kBwdKeyTile;
+  const double per_tile = d128 ? 2.17 : 1.71, launch = d128 ? 5.9 : 6.4, per_item = d128 ? 0.042 : 0.022;
+  static constexpr double kTail[2][3] = {{0.69, 1., 1.}, {0.52, 0.71, 1.}};
+  auto cost = [&](const DqWays& w) {
+    const int wgs = w.ways == 1 ? items : w.ways == 3 ? 3 * items : items + blocks_of(items, w.k), rest = wgs % places;
+    const double rounds = wgs / places + (rest ? kTail[d128 ? 0 : 1][blocks_of(rest, c.n_cus) - 1] : 0.);
+    // a helper spends about two tiles more on each item after its first
+    const double part = w.ways == 1 ? tiles : w.ways == 3 ? tiles / 3 : (w.k * tiles + 2 * (w.k - 1)) / (w.k + 1);
+    return per_tile * rounds * part + (w.ways == 1 ? 0. : launch + per_item * items * (w.ways == 3 ? 1.5 : 1.));
+  };
+  DqWays best;
+  double least = 0.98 * cost(best);  // (a split that gains less is not worth its partial sums)
+  auto consider = [&](const DqWays& w) {
+    if (cost(w) < least) {
+      least = cost(w);
+      best = w;
     }
-  } else if (items * 25 <= places * 29) {  // 1.16 rounds
-    s.ways = 3;
-  } else if (items * 2 <= places * 3) {
-    s.ways = 2;
+  };
+  consider({3, 1});
+  consider({2, 1});
+  if (c.xcd_load < 1.15) {
+    int fits = 1;  // fewest items per helper with which all fit the places at once
+    while (fits < 16 && items + blocks_of(items, fits) > places) ++fits;
+    for (const int k : {2, 4, 8, fits})
+      if (items + blocks_of(items, k) <= places) consider({2, k});
   }
-  return s;
+  return best;
 }
 
 }  // namespace astro

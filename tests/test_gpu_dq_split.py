@@ -17,15 +17,18 @@ pytestmark = pytest.mark.gpu
     (128, 18, 2, 1, True),   # 306 of 512 places: a helper per two
     # (35 heads: the 33rd head's draw of these inputs puts one dQ element 1.4036e-2 of the largest off, un-split too, against
     # the gate of 1.4e-2 that is twice what a rounding model lands on other draws)
-    (64, 35, 2, 0, True),    # 595 of 768: a helper per four
+    (64, 35, 2, 0, False),   # 595 of 768 over 48 tiles: a helper per four would cost more than it gives ...
+    (64, 35, 6, 0, True),    # ... and pays over 81
     (128, 31, 2, 0, True),   # 527: just above a round, three ways
-    (64, 58, 2, 1, True),    # 986 of 768: two ways
+    (64, 58, 2, 1, False),   # 986 of 768, not split
+    (64, 47, 6, 1, True),    # 799 of 768: just above a round
+    (128, 41, 16, 0, True),  # 697 of 512: two ways
     (128, 56, 2, 0, False),  # 952: not split
 ])
 def test_backward_with_the_dq_walk_split_over_the_keys(D, H, resident, bf, split):
     import torch
     gh, gw, Fc = 20, 26, 4   # 2080 queries: 17 blocks of 128, the last ragged
-    w = wl.Workload("dq_split", 53, 1, H, D, gh, gw, 4, 0, Fc, resident, wl.default_rope_pairs(D))
+    w = wl.Workload("dq_split", 53, 1, H, D, gh, gw, max(4, resident), 0, Fc, resident, wl.default_rope_pairs(D))
     ls = Lockstep(w, max_chunk=Fc, start_frames=[9], block_frames=bf)
     _fill_history(ls, w, *wl.history_frame_pool(w, 3), resident)
     q, k, v, do = wl.chunk_inputs(w, with_dout=True)

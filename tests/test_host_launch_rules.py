@@ -93,3 +93,17 @@ def test_backward_with_few_rows_gives_way_where_the_general_kernels_are_faster(r
         assert rules(*call).bwd_few == 0, call
     for call in [(128, 16, 480, 2400), (128, 32, 390, 520), (64, 48, 390, 520), (64, 32, 390, 7800), (128, 2, 128, 448)]:
         assert rules(*call).bwd_few != 0, call
+
+
+def test_split_of_the_dq_walk_only_where_it_gains(rules):
+    """Sizes measured both ways; and a helper per item where the walks of the items differ."""
+    for call in [(128, 120, 480, 2400), (128, 96, 640, 4480), (128, 96, 480, 2080), (64, 60, 1024, 1536), (64, 128, 640, 2240), (64, 144, 640, 2240),
+                 (64, 36, 1500, 4000), (128, 192, 480, 2400)]:
+        assert rules(*call).ways == 1, call
+    for call, ways in [((128, 3, 4680, 28080), (3,)), ((128, 5, 4680, 15600), (2, 3)), ((128, 12, 4680, 28080), (2,)), ((128, 14, 4680, 18720), (3,)),
+                       ((128, 20, 4680, 18720), (2, 3)), ((64, 16, 4680, 18720), (2,)), ((64, 4, 4680, 25000), (3,))]:
+        assert rules(*call).ways in ways, call
+    for D in (64, 128):
+        for pairs in range(4, 130, 6):
+            uneven = rules(D, pairs, 1560, [1560, 17160])
+            assert uneven.k == 1 or uneven.ways == 1
