@@ -910,7 +910,7 @@ __device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item,
   const int b = pair.b, h = pair.h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
-  const int hist = stream_int(p.hist_rows, pair.cache_b);
+  const int hist = p.hist_rows.v[pair.cache_b];
   const int64_t bh = (int64_t)b * p.H + h;
   const int q_first = item.tile * 32, q0 = q_first + i16, q_last = p.Nq - 1;
   const int vis_first = visible_chunk_rows(q_first, p.Nq, p.block_rows);

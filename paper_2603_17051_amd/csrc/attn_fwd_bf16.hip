@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
   const int b = pair.b, h = pair.h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
-  const int hist = stream_int(p.hist_rows, pair.cache_b);
+  const int hist = p.hist_rows.v[pair.cache_b];
   const int64_t bh = (int64_t)b * p.H + h;
   const int q_first = item.tile * 32, q_last = p.Nq - 1;
   const int q0 = q_first + i16;  // this lane's queries: q0 and q0 + 16

@@ -29,18 +29,6 @@ struct StreamInts {
   int32_t v[ASTRO_MAX_BATCH];
 };
 
-#ifdef __HIPCC__
-// Entry `b` (wave-uniform) of a launch argument: every lane loads one of the 64 entries, which waits for
-// nothing, and the wanted one is picked afterwards.  Indexed directly, the load could only start when b
-// had been computed from other arguments: a second trip to the argument memory at the start of a launch.
-// Eight production frames appended for 8 streams 549.5 -> 544.9 us, a forward + backward of a few hundred
-// rows at D = 64 26.9 -> 26.6 us.
-__device__ __forceinline__ int stream_int(const StreamInts& s, int b) {
-  static_assert(ASTRO_MAX_BATCH == 64, "one entry per lane");
-  return __builtin_amdgcn_readlane(s.v[threadIdx.x & 63], b);
-}
-#endif
-
 // Geometry and rotary tables every kernel needs.
 struct DevGeom {
   int B, H, D, gh, gw, T, C, S;

@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(kThreads) rope_scatter_kernel(DevGeom g, const
   const int h = blockIdx.y, b = blockIdx.z;
   const bool rope = (g.n_t + g.n_h + g.n_w) != 0;
   const int cpr = g.D / EPC;  // chunks per token row of one head
-  const int first_n = stream_int(first_frame, b), next = stream_int(next_n, b);
+  const int first_n = first_frame.v[b], next = next_n.v[b];
   const int dst_frame_row = ring ? ring_slot(next + fi, g.C, g.S) * g.T : fi * g.T;
   const int64_t in_tok0 = ((int64_t)b * n_frames + fi) * g.T + (int64_t)row * g.gw;
   const int64_t out_row0 = ((int64_t)b * g.H + h) * rows_per_head + dst_frame_row + (int64_t)row * g.gw;
