@@ -35,11 +35,16 @@ inline double heaviest_eighth(const int32_t* hist, int streams, int Nq) {
 }
 
 inline CallShape make_call_shape(int D, int n_cus, int pairs, int Nq, int block_rows, bool in_order, const int32_t* hist, int streams) {
-  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], 0., heaviest_eighth(hist, streams, Nq), in_order};
+  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], 0., 1., in_order};
+  int64_t sum = 0;
+  bool even = true;
   for (int b = 0; b < streams; ++b) {
     c.max_hist = hist[b] > c.max_hist ? hist[b] : c.max_hist;
-    c.mean_hist += (double)hist[b] / streams;
+    even = even && hist[b] == hist[0];
+    sum += hist[b];
   }
+  c.mean_hist = (double)sum / streams;
+  if (!even) c.xcd_load = heaviest_eighth(hist, streams, Nq);
   return c;
 }
 
@@ -125,6 +130,10 @@ inline int fwd_splits(const CallShape& c) {
 //            43.8, 270 x 164 58 / 44, 288 x 136 55 / 39, 576 x 6 25 / 22, 640 x 8 28 / 26, 392 x 634 167 / 161
 //   D = 64:  4 x 10 5.1 / 9.6, 144 x 33 8.2 / 19.9, 140 x 133 16.3 / 26.6, 156 x 232 25.6 / 34.0, 960 x 112 55 / 58, 1440 x 60
 //            49 / 58; lost: 294 x 342 72 / 51, 279 x 495 88 / 65, 288 x 456 89 / 58, 294 x 634 117 / 80
+// Many short walks are many prologues and combines: from the third workgroup per CU on it took, by tiles, 1.01 - 1.19
+// of the general kernel's time at D = 128 below 24 tiles and 0.97 - 1.07 above, 1.05 - 1.6 from the fifth on
+// (1728 x 8 51 / 44); at D = 64 0.82 - 1.0 up to the fifth, 0.97 - 1.05 from 12 tiles on up to the eighth, 1.0 - 1.27
+// beyond (8320 x 26 144 / 125).
 // Below half a round the general kernel's key split reaches CUs that this one leaves idle, hence the
 // lower bound there.  The walk is the longest stream's; where streams differ, the general kernel, which cuts
 // it, takes over at half the bounds and beyond three (D = 128) or five workgroups per CU (longest and mean walk: 1056 x
@@ -142,9 +151,10 @@ inline int fwd_few_waves(const CallShape& c) {
   const bool half_full = 2 * wgs >= c.n_cus, uneven = c.xcd_load >= 1.15;
   int64_t limit;
   if (c.D == 128) {
+    if (per_cu > 4 || (per_cu > 2 && tiles < 24)) return 0;
     limit = !half_full ? 112 : per_cu == 2 && fill < 0.63 ? 100 : 200;
-    if (per_cu == 3 && fill < 0.84 && walk < 40) limit = 0;
   } else {
+    if (per_cu > 8 || (per_cu > 5 && tiles < 12)) return 0;
     limit = !half_full ? 300 : per_cu > 2 ? 900 : per_cu == 2 && fill < 0.7 ? 250 : 400;
   }
   if (uneven) limit = per_cu > (c.D == 128 ? 3 : 5) ? 0 : limit / 2;

@@ -80,9 +80,10 @@ def test_forward_with_few_rows_gives_way_where_the_general_kernel_is_faster(rule
     """Sizes measured with both: a second or third workgroup on a few CUs only, short walks, and streams of
     different lengths, whose longest walk the general kernel cuts."""
     for call in [(64, 6, 1560, 17160), (64, 3, 2970, 12870, 990), (128, 192, 96, 96), (128, 160, 126, 126, 63), (64, 12, 792, 11880),
-                 (128, 6, 1440, 3900), (64, 32, 1040, [2600, 1560, 4680, 2600, 0, 1040, 2080, 0]), (128, 480, 126, [63, 630, 630, 63])]:
+                 (128, 6, 1440, 3900), (128, 576, 96, 160, 32), (64, 640, 390, 390), (128, 384, 54, 72),
+                 (64, 32, 1040, [2600, 1560, 4680, 2600, 0, 1040, 2080, 0]), (128, 480, 126, [63, 630, 630, 63])]:
         assert rules(*call).fwd_few == 0, call
-    for call in [(128, 4, 32, 288), (64, 8, 570, 2570), (128, 12, 390, 3120), (128, 16, 240, 4240), (64, 32, 960, 2624), (128, 64, 320, 608)]:
+    for call in [(128, 4, 32, 288), (64, 8, 570, 2570), (128, 12, 390, 3120), (128, 16, 240, 4240), (64, 32, 960, 2624), (128, 64, 320, 608), (64, 200, 130, 650), (128, 32, 768, 960)]:
         assert rules(*call).fwd_few != 0, call
 
 
