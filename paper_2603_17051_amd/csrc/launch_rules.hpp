@@ -172,17 +172,18 @@ constexpr int kFewMaxRows = 2048;  // most chunk rows of the kernel for few rows
 //            144 x 15 71 / 66, 144 x 21 96 / 78, 160 x 20 93 / 76, 156 x 463 563 / 406, 192 x 14 70 / 60
 //   D = 64:  2 blocks 7 / 16, 48 14 / 33, 104 137 / 165, 120 x 128 82 / 90, 192 x 14 32 / 38; lost: 156 x 463 267 / 236, 216 x 32
 //            83 / 67, 240 x 35 77 / 67, 256 x 35 90 / 70, 256 x 9 46 / 43, 224 x 49 74 / 67
-// Over 2600 shapes it takes 0.6 - 1.0 of the general kernels' time (medians by number of tiles) just below these lines (96
-// - 128 blocks, D = 64 129 - 192) and 1.0 - 1.3 just above them; walks of 40 tiles and more, which the general dQ
-// kernel splits, have the line lower.
+// Over 3800 shapes it takes 0.6 - 1.0 of the general kernels' time (medians by number of tiles) just below these lines
+// and 1.0 - 1.3 just above them.  Walks of 40 tiles and more, which the general dQ kernel splits, have the line
+// lower, short ones higher (129 - 144 blocks below 15 tiles at D = 128 0.67 - 0.88, 225 - 240 below 10 at D = 64 0.9 - 1.0).
 // Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
 // does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
 // with four), four otherwise (208 x 37: 30.0 against 34.3).
 inline int bwd_few_waves(const CallShape& c) {
   if (c.in_order) return 0;
   const int64_t blocks = (int64_t)blocks_of(c.Nq, 128) * c.pairs;
-  const bool long_walk = (c.max_hist + c.Nq) / kBwdKeyTile >= 40;
-  const int sixteenths = c.D == 128 ? (long_walk ? 7 : 8) : (long_walk ? 8 : 12);  // of the CUs
+  const int tiles = (c.max_hist + c.Nq) / kBwdKeyTile;
+  const int sixteenths = c.D == 128 ? (tiles >= 40 ? 7 : tiles >= 15 ? 8 : 9)  // of the CUs
+                                    : (tiles >= 40 ? 8 : tiles >= 10 ? 12 : tiles >= 3 ? 15 : 16);
   if (c.Nq > kFewMaxRows || 16 * blocks > sixteenths * (int64_t)c.n_cus) return 0;
   const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
   return 8 * wgs <= 5 * (int64_t)c.n_cus && (c.max_hist + c.Nq) / 32 >= 64 ? 8 : 4;

@@ -92,7 +92,7 @@ def test_backward_with_few_rows_gives_way_where_the_general_kernels_are_faster(r
     for call in [(128, 24, 696, 696), (128, 32, 640, 640), (128, 48, 330, 660, 126), (64, 24, 1040, 1040), (64, 32, 960, 1280), (64, 48, 640, 1600),
                  (64, 256, 128, 448), (128, 30, 390, 7800)]:
         assert rules(*call).bwd_few == 0, call
-    for call in [(128, 16, 480, 2400), (128, 32, 390, 520), (64, 48, 390, 520), (64, 32, 390, 7800), (128, 2, 128, 448)]:
+    for call in [(128, 16, 480, 2400), (128, 32, 390, 520), (64, 48, 390, 520), (64, 32, 390, 7800), (128, 2, 128, 448), (128, 48, 330, 330), (64, 120, 200, 260), (64, 128, 130, 30)]:
         assert rules(*call).bwd_few != 0, call
 
 
