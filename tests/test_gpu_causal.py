@@ -47,8 +47,7 @@ def test_f32_debug_path_block_causal(D, pairs, C, S, Fc, bf):
     (128, (22, 21, 21), 16, 20, 1, 2, 4, 1, 3, 1),  # 320-token frames: several query tiles per frame
     (128, (0, 0, 0), 2, 3, 1, 1, 5, 0, 5, 1),       # 6-token frames: many blocks inside one wave
     (128, (22, 21, 21), 6, 7, 1, 2, 6, 0, 5, 3),    # blocks of 3 in a chunk of 5: short last block
-    # 288-token frames on an empty ring: the forward is split in two key ranges, and for the queries of
-    # frame 0 that share a workgroup with queries of frame 1 the second range holds only keys they do not see
+    # 288-token frames on an empty ring (key ranges under the mask: test_gpu_general_kernels.py)
     (128, (22, 21, 21), 16, 18, 1, 2, 3, 0, 3, 1),
     (64, (12, 10, 10), 16, 18, 1, 1, 4, 1, 3, 1),
 ])

@@ -2,10 +2,11 @@
 its waves sharing the walk over the other side), at the sizes where their tiling can go wrong, and of
 the general kernels at ragged sizes just beyond the lines where they take over; fp64 oracle, outputs
 pre-filled with NaN, the kernel that ran taken from the launch names."""
+import numpy as np
 import pytest
 
 import workloads as wl
-from helpers import Lockstep, assert_bf16_close, host_f64
+from helpers import Lockstep, assert_bf16_close, assert_within_model, host_f64
 from test_gpu_parity import _fill_history
 
 pytestmark = pytest.mark.gpu
@@ -14,8 +15,7 @@ P64, P128 = (12, 10, 10), (22, 21, 21)
 
 
 @pytest.mark.parametrize("D,pairs,gh,gw,B,H,C,Fc,bf,resident,fwd_few,bwd_few", [
-    # one query, one ragged tile, waves without a tile.  40 keys: with two, dS = p1 p2 (dP1 - dP2) and a Delta taken from
-    # the bf16 output (error |dO| |O| 2^-9, about 0.5 % of that difference) is past the gates, which are derived at 64 keys and more
+    # one query, one ragged tile, waves without a tile (40 keys: the gates are derived at 64 and more; two keys below)
     (128, P128, 1, 1, 1, 1, 39, 1, 0, 39, True, True),
     (64, P64, 1, 31, 1, 2, 3, 1, 0, 3, True, True),        # a block and every tile one row short
     (128, P128, 3, 11, 2, 3, 4, 2, 1, 2, True, True),      # 33-token frames, causal: one row past a block
@@ -53,4 +53,39 @@ def test_fwd_bwd_on_both_sides_of_the_few_rows_lines(D, pairs, gh, gw, B, H, C, 
                 [(g[b, :, h], r[b, :, h], n) for g, r, n in zip(grads, ref, ("dq", "dk", "dv"))]:
             assert_bf16_close(host_f64(got), r, f"pair {b, h} {what}")
     assert all(bool(torch.isfinite(x.float()).all()) for x in [out, lse] + grads)
+    ls.close()
+
+
+@pytest.mark.parametrize("D,pairs", [(128, P128), (64, P64)])
+def test_one_query_and_two_keys(D, pairs):
+    """dS = p1 p2 (dP1 - dP2), and a Delta taken from the bf16 output is off by |dO| |O| 2^-9, about 0.5 % of that
+    difference: past the fixed gates, so the rounding model on the same inputs judges.  With one query that error is one
+    draw per pair (the model's own from 0.1 to 10 times another's), so the 128 pairs are judged together: of two
+    such samples neither the rms nor the largest differs by the gate's factor of two."""
+    from bf16_model import model_fwd_bwd
+    w = wl.Workload("two_keys", 61, 8, 16, D, 1, 1, 2, 0, 1, 1, pairs)
+    ls = Lockstep(w, max_chunk=1, start_frames=[3, 0, 40, 7, 7, 1, 20, 9])
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), 1)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    dev = [ls.dev(x) for x in (q, k, v, do)]
+    ls.A.astro_profile_begin()
+    out, lse = ls.A.astro_chunk_attn_fwd(ls.cache, *dev[:3], 1)
+    grads = ls.A.astro_chunk_attn_bwd(ls.cache, *dev[:3], out, lse, dev[3], 1)
+    launched = ls.A.astro_profile_end()
+    assert "attn_fwd_few_bf16" in launched and "attn_bwd_few_bf16" in launched, launched
+    wide = [ls.wide(x) for x in (q, k, v, do)]
+    ro, rl = ls.oracle.attn_fwd(*wide[:3], 1)
+    rg = ls.oracle.attn_bwd(*wide, 1)
+    got, ref, model = [[] for _ in range(5)], [[] for _ in range(5)], [[] for _ in range(5)]
+    for b in range(8):
+        for h in range(16):
+            m = model_fwd_bwd(ls.oracle, *wide, 1, b, h)
+            x = [out[b, :, h], lse[b, h]] + [g[b, :, h] for g in grads]
+            r = [ro[b, :, h], rl[b, h]] + [g[b, :, h] for g in rg]
+            for i in range(5):
+                got[i].append(host_f64(x[i]))
+                ref[i].append(r[i])
+                model[i].append(m[i])
+    for x, r, m, what in zip(got, ref, model, ("out", "lse", "dq", "dk", "dv")):
+        assert_within_model(np.stack(x), np.stack(r), np.stack(m), what)
     ls.close()

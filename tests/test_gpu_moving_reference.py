@@ -2,8 +2,8 @@
 probabilities relative to it overflow a bound; with N(0,1) inputs that happens on the first tile
 only (empty accumulators).  Here the logits change by tens of natural units from one ring frame to
 the next, so the reference moves several times with NON-EMPTY accumulators (rising logits), or
-never after the first tile while later tiles underflow to zero (falling logits); both with the
-launch split over the keys (few streams) and unsplit (many streams), for both head dims.
+never after the first tile while later tiles underflow to zero (falling logits), for both head dims.
+All of these sizes take the kernels for few rows; test_gpu_general_kernels.py has the general ones.
 
 Inputs: q = a + noise/2, keys of frame n = c_n + noise/2 in every component, so a logit is about
 a * c_n * sqrt(D) and frame n's logits sit about a * (c_n - c_{n-1}) * sqrt(D) above the previous
@@ -28,10 +28,10 @@ def _inputs(w, seed, a, c, step):
 
 
 @pytest.mark.parametrize("B,H,D,pairs,gh,gw,C,Fc,a,step_c,rising", [
-    (1, 2, 64, (0, 0, 0), 8, 8, 8, 2, 1.0, 5.0, True),         # 80 nats per chunk, key split active
+    (1, 2, 64, (0, 0, 0), 8, 8, 8, 2, 1.0, 5.0, True),         # 80 nats per chunk
     (1, 2, 64, (0, 0, 0), 8, 8, 8, 2, 1.0, 5.0, False),        # falling: the reference never moves again
     (1, 2, 128, (0, 0, 0), 6, 12, 6, 1, 1.0, 3.5, True),       # D = 128: 40 nats per frame
-    (64, 8, 64, (0, 0, 0), 8, 8, 12, 6, 1.0, 5.0, True),       # 1536 workgroups: never split
+    (64, 8, 64, (0, 0, 0), 8, 8, 12, 6, 1.0, 5.0, True),       # 64 streams
     (2, 3, 128, (22, 21, 21), 6, 12, 6, 2, 1.0, 2.0, True),    # rotary pairs
 ])
 def test_bf16_reference_moves_with_filled_accumulators(B, H, D, pairs, gh, gw, C, Fc, a, step_c, rising):
