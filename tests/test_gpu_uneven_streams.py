@@ -37,7 +37,7 @@ def test_streams_of_different_lengths(D, H, gh, gw, C, Fc, bf, lens, group, dq_s
                 for c in (ls.cache, wide):
                     A.astro_kvcache_reset(c, b, 0)
                 ls.oracle.reset(b, 0)
-        k, v = (np.ascontiguousarray(np.broadcast_to(x[step % 3], (B, *x.shape[1:]))) for x in (pool_k, pool_v))
+        k, v = (np.stack([x[step % 3]] * B) for x in (pool_k, pool_v))
         ls.append(k, v, 1)
         A.astro_kvcache_append(wide, rep(ls.dev(k)), rep(ls.dev(v)), 1)
     for b in range(B):
