@@ -14,7 +14,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;  // of the prepare launch
-constexpr int kElemsPerBlock = 16384;  // elements of one sample a workgroup walks
+constexpr int kElemsPerBlock = 16384;  // most elements of one sample a workgroup walks
 
 struct NftParams {
   const void *v_theta, *v_old, *v_ref, *target;
@@ -26,7 +26,7 @@ struct NftParams {
   float* n_masked;  // workspace [1]
   float* partials;  // workspace [n][blocks_per_sample][3]
   int n, blocks_per_sample;
-  int64_t E;
+  int64_t E, share;  // elements per sample, and of it per workgroup
   float inv_a_max, beta, lambda_kl;
 };
 
@@ -71,6 +71,7 @@ struct Chunk {
 // samples itself (a few KB from L2) and the prepare launch is skipped: at one group of 24 clips the
 // three dependent launches took 28 us for 17 us of memory traffic.
 constexpr int kMaxSamplesInline = 1024;
+constexpr int kMaskLoads = 4;  // masks a thread has in flight
 
 // HBM-bound.  A workgroup walks kElemsPerBlock elements of one sample (one triple of partial sums each,
 // which is what the workspace holds).  24 clips are 456 workgroups, fewer than two per CU, so a
@@ -85,8 +86,8 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
   constexpr int kUnroll = C::kUnroll;
   const int threads = blockDim.x, waves = threads / 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = blockIdx.y;
-  const int64_t lo = (int64_t)blockIdx.x * kElemsPerBlock;
-  const int64_t hi = lo + kElemsPerBlock < p.E ? lo + kElemsPerBlock : p.E;
+  const int64_t lo = (int64_t)blockIdx.x * p.share;
+  const int64_t hi = lo + p.share < p.E ? lo + p.share : p.E;
   const int64_t base = (int64_t)i * p.E;
   C vt[kUnroll], vo[kUnroll], vr[kUnroll], tg[kUnroll];
   auto load = [&](int64_t e0) __attribute__((always_inline)) {
@@ -102,13 +103,28 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
     }
   };
   int64_t e0 = lo + (int64_t)threadIdx.x * N;
+  // the masks this thread counts are asked for first: loads return in order, and behind the tensors' the count
+  // and its barriers came when all of these had arrived (700 samples of 5000 in bf16
+  // 15.0 us, now 14.0; 1024 of 5264 in fp32 24.0, now 22.3)
+  int mask[kMaskLoads];
+  if constexpr (kInline) {
+#pragma unroll
+    for (int u = 0; u < kMaskLoads; ++u) {
+      mask[u] = 0;
+      if (u * threads >= p.n) continue;
+      const int j = threadIdx.x + u * threads;
+      if (j < p.n) mask[u] = p.kl_mask[j];
+    }
+  }
   load(e0);
 
   __shared__ float red[3][C::kThreads / 64];
   float r, nm;
   if constexpr (kInline) {
     int c = 0;
-    for (int j = threadIdx.x; j < p.n; j += threads) c += p.kl_mask[j] != 0 ? 1 : 0;
+#pragma unroll
+    for (int u = 0; u < kMaskLoads; ++u) c += mask[u] != 0 ? 1 : 0;
+    for (int j = threadIdx.x + kMaskLoads * threads; j < p.n; j += threads) c += p.kl_mask[j] != 0 ? 1 : 0;
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) c += __shfl_xor(c, sh);
     if (lane == 0) red[0][wave] = (float)c;  // counts up to 1024: exact
@@ -250,17 +266,25 @@ int run_nft_loss(const void* v_theta, const void* v_old, const void* v_ref, cons
   p.n = n_samples;
   p.blocks_per_sample = blocks_per_sample(elems_per_sample);
   p.E = elems_per_sample;
+  // Even shares where the last of a few workgroups of a sample would have little: as many workgroups of full size with a few
+  // elements cost 95 us instead of 69 (1024 samples of 17904 in fp32), 81 instead of 75 (400 of 49312).  A long sample's full
+  // shares are two whole trips of the threads (192 of 299520 in fp32 193 us, 199 in even shares).
+  const int64_t rest = elems_per_sample % kElemsPerBlock;
+  p.share = kElemsPerBlock;
+  if (p.blocks_per_sample == 1)
+    p.share = elems_per_sample;
+  else if (p.blocks_per_sample <= 8 && rest != 0 && rest < kElemsPerBlock / 2)
+    p.share = ((elems_per_sample + p.blocks_per_sample - 1) / p.blocks_per_sample + 255) / 256 * 256;
   p.inv_a_max = 1.f / a_max; p.beta = beta; p.lambda_kl = lambda_kl;
   {
     // the entry point that must not allocate never creates timing events, even while profiling is on
     ProfileScope prof("nft_loss", stream, timed);
     const dim3 grid(p.blocks_per_sample, n_samples);
     // as many threads as a workgroup's share has groups of kUnroll chunks, in whole waves
-    const int64_t share = elems_per_sample < kElemsPerBlock ? elems_per_sample : kElemsPerBlock;
     const bool is_bf16 = dtype == ASTRO_BF16;
     const int per_thread = N * (is_bf16 ? Chunk<__bf16>::kUnroll : Chunk<float>::kUnroll);
     const int most = is_bf16 ? Chunk<__bf16>::kThreads : Chunk<float>::kThreads;
-    const int64_t want = ((share + per_thread - 1) / per_thread + 63) / 64 * 64;
+    const int64_t want = ((p.share + per_thread - 1) / per_thread + 63) / 64 * 64;
     const int threads = want < most ? (int)want : most;
     if (n_samples <= kMaxSamplesInline) {
       if (is_bf16)
