@@ -207,5 +207,8 @@ def test_current_stream_without_the_raw_handle_of_torch(monkeypatch):
 
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
-    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(binding, "_raw_stream", None)
     assert binding._stream(None).value == 0x1234
+    # what the import takes from such a torch
+    source = open(binding.__file__).read()
+    assert 'getattr(torch._C, "_cuda_getCurrentRawStream", None)' in source and "torch._C._cuda" not in source
