@@ -50,12 +50,8 @@ __global__ void __launch_bounds__(kThreads) rope_scatter_kernel(DevGeom g, const
   const int h = blockIdx.y, b = blockIdx.z;
   const bool rope = (g.n_t + g.n_h + g.n_w) != 0;
   const int cpr = g.D / EPC;  // chunks per token row of one head
-  // The staging asks for the frame number here, so that it has it when the table is built (46 us instead of 51 at the
-  // production shape, 4 streams); the append, which also waits for the slot, asks for it there (17.0 instead of 18.4
-  // for 2 streams of 1560 rows, 24 heads).
-  const int first_n = kRotateB ? first_frame.v[b] : 0;
-  auto first_of = [&] { return kRotateB ? first_n : first_frame.v[b]; };
-  const int dst_frame_row = ring ? ring_slot(next_n.v[b] + fi, g.C, g.S) * g.T : fi * g.T;
+  const int first_n = first_frame.v[b], next = next_n.v[b];
+  const int dst_frame_row = ring ? ring_slot(next + fi, g.C, g.S) * g.T : fi * g.T;
   const int64_t in_tok0 = ((int64_t)b * n_frames + fi) * g.T + (int64_t)row * g.gw;
   const int64_t out_row0 = ((int64_t)b * g.H + h) * rows_per_head + dst_frame_row + (int64_t)row * g.gw;
   if constexpr (sizeof(Elem) == 2) {
@@ -80,7 +76,7 @@ __global__ void __launch_bounds__(kThreads) rope_scatter_kernel(DevGeom g, const
         }
       }
       if (rope && base == 0) {
-        fill_block_table(tab, g, first_of() + fi, row);
+        fill_block_table(tab, g, first_n + fi, row);
         // one block per (stream, frame) leaves the temporal pairs' (cos, sin) for the backward's epilogues
         if (tab_t_out && row == 0 && h == 0 && (int)threadIdx.x < g.n_t)
           tab_t_out[((int64_t)b * n_frames + fi) * g.n_t + threadIdx.x] = tab[threadIdx.x];
@@ -121,7 +117,7 @@ __global__ void __launch_bounds__(kThreads) rope_scatter_kernel(DevGeom g, const
     return;
   } else {
     // fp32 debug path: one chunk at a time
-    if (rope) fill_block_table(tab, g, first_of() + fi, row);
+    if (rope) fill_block_table(tab, g, first_n + fi, row);
     for (int idx = threadIdx.x; idx < g.gw * cpr; idx += kThreads) {
       const int w = idx / cpr, c = idx % cpr;
       const int64_t in_off = ((in_tok0 + w) * g.H + h) * g.D + c * EPC;
