@@ -71,7 +71,6 @@ struct Chunk {
 // samples itself (a few KB from L2) and the prepare launch is skipped: at one group of 24 clips the
 // three dependent launches took 28 us for 17 us of memory traffic.
 constexpr int kMaxSamplesInline = 1024;
-constexpr int kMaskLoads = 4;  // masks a thread has in flight
 
 // HBM-bound.  A workgroup walks kElemsPerBlock elements of one sample (one triple of partial sums each,
 // which is what the workspace holds).  24 clips are 456 workgroups, fewer than two per CU, so a
@@ -103,28 +102,13 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
     }
   };
   int64_t e0 = lo + (int64_t)threadIdx.x * N;
-  // the masks this thread counts are asked for first: loads return in order, and behind the tensors' the count
-  // and its barriers came when all of these had arrived (700 samples of 5000 in bf16
-  // 15.0 us, now 14.0; 1024 of 5264 in fp32 24.0, now 22.3)
-  int mask[kMaskLoads];
-  if constexpr (kInline) {
-#pragma unroll
-    for (int u = 0; u < kMaskLoads; ++u) {
-      mask[u] = 0;
-      if (u * threads >= p.n) continue;
-      const int j = threadIdx.x + u * threads;
-      if (j < p.n) mask[u] = p.kl_mask[j];
-    }
-  }
   load(e0);
 
   __shared__ float red[3][C::kThreads / 64];
   float r, nm;
   if constexpr (kInline) {
     int c = 0;
-#pragma unroll
-    for (int u = 0; u < kMaskLoads; ++u) c += mask[u] != 0 ? 1 : 0;
-    for (int j = threadIdx.x + kMaskLoads * threads; j < p.n; j += threads) c += p.kl_mask[j] != 0 ? 1 : 0;
+    for (int j = threadIdx.x; j < p.n; j += threads) c += p.kl_mask[j] != 0 ? 1 : 0;
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) c += __shfl_xor(c, sh);
     if (lane == 0) red[0][wave] = (float)c;  // counts up to 1024: exact
@@ -283,7 +267,10 @@ int run_nft_loss(const void* v_theta, const void* v_old, const void* v_ref, cons
     // as many threads as a workgroup's share has groups of kUnroll chunks, in whole waves
     const bool is_bf16 = dtype == ASTRO_BF16;
     const int per_thread = N * (is_bf16 ? Chunk<__bf16>::kUnroll : Chunk<float>::kUnroll);
-    const int most = is_bf16 ? Chunk<__bf16>::kThreads : Chunk<float>::kThreads;
+    // ... up to the most that pay: with one trip per thread on a small share too few workgroups are on a CU (900 samples
+    // of 4816 in bf16 19.4 us with up to 512 threads, 14.7 with 256; 1024 of 6648 in fp32 32.5 with up to 1024, 26.8 with
+    // 512).  Above the lines more threads are as fast or faster (3000 of 12056 in fp32 136 us, 145 with 512).
+    const int most = is_bf16 ? (p.share < 6144 ? 256 : Chunk<__bf16>::kThreads) : (p.share < 9216 ? 512 : Chunk<float>::kThreads);
     const int64_t want = ((p.share + per_thread - 1) / per_thread + 63) / 64 * 64;
     const int threads = want < most ? (int)want : most;
     if (n_samples <= kMaxSamplesInline) {
