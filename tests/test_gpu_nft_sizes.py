@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
     ("bf16", 1, 8), ("f32", 1, 4), ("bf16", 3, 8200), ("f32", 3, 8196), ("bf16", 2, 16376), ("bf16", 2, 16392),
     ("f32", 2, 16388), ("bf16", 5, 2056), ("f32", 1025, 8), ("bf16", 1024, 8),
     ("f32", 2, 49156), ("bf16", 2, 65544),   # even shares of four and five workgroups, the last one shorter
-    ("bf16", 300, 4104), ("f32", 600, 520),  # more masks than a thread has in flight, and than threads
+    ("bf16", 300, 4104), ("f32", 600, 520),  # more masks than threads
+    ("bf16", 3, 6136), ("bf16", 3, 6144), ("f32", 3, 9212), ("f32", 3, 9216),  # both sides of the lines for the threads
 ])
 def test_nft_loss_at_the_edges_of_its_shares(dtype, n, elems):
     import torch
