@@ -272,7 +272,8 @@ int astro_nft_loss_static(const void *v_theta, const void *v_old, const void *v_
  * between begin and end every kernel launch is bracketed by HIP events recorded on
  * the stream it is launched on.  end() waits for those events (host-synchronous),
  * aggregates by kernel name into out[0 .. *n_entries) (at most max_entries names)
- * and switches timing off.  Process-wide, one host thread. */
+ * and switches timing off.  Process-wide, one host thread.  A forward of a few rows that rotates
+ * its chunk inside the attention launch counts a "chunk_rope_stage" without a time of its own. */
 typedef struct astro_kernel_time {
   char name[48];     /* kernel name, NUL-terminated */
   int32_t launches;  /* launches seen                */

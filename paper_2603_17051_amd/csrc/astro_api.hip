@@ -171,34 +171,40 @@ bool outputs_overlap(const astro_kvcache* c, int n_frames, int group, const void
   return any;
 }
 
-// The same for a forward: out or lse over the chunk's values.  A launch whose key ranges are merged afterwards
-// puts up with it; where there are workgroups enough without key ranges no route does.
-bool output_over_values(const astro_kvcache* c, int n_frames, int group, const void* v_chunk, const void* out, const float* lse) {
+// The same for a forward: out or lse over a tensor of the chunk.  Over its values, a launch whose key ranges are merged
+// afterwards puts up with it; where there are workgroups enough without key ranges no route does.
+bool output_over(const astro_kvcache* c, int n_frames, int group, const void* chunk_tensor, const void* out, const float* lse) {
   const RingGeometry& g = c->geo;
   const size_t rows = (size_t)g.B * group * n_frames * g.T * g.H, chunk = rows * g.D * g.elem_bytes();
-  return overlap({out, chunk}, {v_chunk, chunk}) || overlap({lse, rows * sizeof(float)}, {v_chunk, chunk});
+  return overlap({out, chunk}, {chunk_tensor, chunk}) || overlap({lse, rows * sizeof(float)}, {chunk_tensor, chunk});
 }
 
-// rotate Q and K_chunk into the workspace (head-major), unless the handle may reuse staged copies
-// and the last pre-pass was made for exactly this call's chunk, workspace and table state
+// whether the last pre-pass was made for exactly this call's chunk, workspace and table state and may be reused
+bool is_staged(const astro_kvcache* c, const void* q, const void* k_chunk, const void* ws, int n_frames, int group) {
+  const astro_kvcache::Staged& st = c->staged;
+  return c->geo.reuse_staged && st.valid && st.q == q && st.k == k_chunk && st.ws == ws && st.n_frames == n_frames &&
+         st.group == group && st.epoch == c->epoch;
+}
+
+// The bf16 kernels take the queries pre-multiplied by log2(e)/sqrt(D) (applied in fp32 to the
+// rotated value, before its one rounding to bf16): Q~' K~^T is then directly the exponent of 2,
+// and the row's reference or log-sum-exp enters as the start value of the MFMA accumulators, so
+// no multiply-add per score is left in front of the exponential.
+float query_scale(const astro_kvcache* c) {
+  return c->geo.dtype == ASTRO_BF16 ? 1.4426950408889634f / std::sqrt((float)c->geo.D) : 1.f;
+}
+
+// rotate Q and K_chunk into the workspace (head-major), unless they are there
 hipError_t stage_chunk(astro_kvcache* c, const void* q, const void* k_chunk, char* ws, const Workspace& w,
                        int n_frames, int group, hipStream_t stream) {
-  astro_kvcache::Staged& st = c->staged;
-  if (c->geo.reuse_staged && st.valid && st.q == q && st.k == k_chunk && st.ws == ws && st.n_frames == n_frames &&
-      st.group == group && st.epoch == c->epoch)
-    return hipSuccess;
-  st.valid = false;
+  if (is_staged(c, q, k_chunk, ws, n_frames, group)) return hipSuccess;
+  c->staged.valid = false;
   StreamInts first, next;
   stream_ints(c, &first, &next, nullptr, group);
   ScatterDst dst{ws + w.q_rot, ws + w.kc_rot, (int64_t)n_frames * c->geo.T, 0};
-  // The bf16 kernels take the queries pre-multiplied by log2(e)/sqrt(D) (applied in fp32 to the
-  // rotated value, before its one rounding to bf16): Q~' K~^T is then directly the exponent of 2,
-  // and the row's reference or log-sum-exp enters as the start value of the MFMA accumulators, so
-  // no multiply-add per score is left in front of the exponential.
-  const float q_scale = c->geo.dtype == ASTRO_BF16 ? 1.4426950408889634f / std::sqrt((float)c->geo.D) : 1.f;
   const hipError_t e = launch_rope_scatter(dev_geom(c, group), c->geo.dtype, q, k_chunk, dst, true, n_frames, first, next,
-                                           (float2*)(ws + w.tab_t), q_scale, stream);
-  if (e == hipSuccess) st = astro_kvcache::Staged{q, k_chunk, ws, n_frames, group, c->epoch, true};
+                                           (float2*)(ws + w.tab_t), query_scale(c), stream);
+  if (e == hipSuccess) c->staged = astro_kvcache::Staged{q, k_chunk, ws, n_frames, group, c->epoch, true};
   return e;
 }
 
@@ -390,15 +396,27 @@ int astro_group_attn_fwd(astro_kvcache_t* cache, const void* q, const void* k_ch
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace & 255)) return ASTRO_ERR_WORKSPACE;
   char* ws = (char*)workspace;
   hipStream_t stream = (hipStream_t)hip_stream;
-  if (stage_chunk(cache, q, k_chunk, ws, w, n_frames, group, stream) != hipSuccess) return ASTRO_ERR_HIP;
   AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
-  op.in_order = output_over_values(cache, n_frames, group, v_chunk, out, lse);
+  op.in_order = output_over(cache, n_frames, group, v_chunk, out, lse);
   const DevGeom d = dev_geom(cache, group);
+  ChunkSource raw;
+  // a launch that rotates for itself reads queries and chunk keys while its workgroups write outputs, and the keys by
+  // 16-byte loads straight into LDS
+  if (cache->geo.dtype == ASTRO_BF16 && ((uintptr_t)k_chunk & 15) == 0 && !is_staged(cache, q, k_chunk, ws, n_frames, group) && bf16_fwd_rotates(d, op) &&
+      !output_over(cache, n_frames, group, q, out, lse) && !output_over(cache, n_frames, group, k_chunk, out, lse)) {
+    raw.q = q, raw.k = k_chunk, raw.q_scale = query_scale(cache), raw.leave = cache->geo.reuse_staged;
+    stream_ints(cache, &raw.first_frame, nullptr, nullptr, group);
+    op.raw = &raw;
+    cache->staged.valid = false;
+  } else if (stage_chunk(cache, q, k_chunk, ws, w, n_frames, group, stream) != hipSuccess) {
+    return ASTRO_ERR_HIP;
+  }
   hipError_t e;
   if (cache->geo.dtype == ASTRO_F32)
     e = launch_attn_fwd_f32(d, op, (float*)out, lse, (float*)(ws + w.scratch), stream);
   else
     e = launch_attn_fwd_bf16(d, op, out, lse, w.total > w.scratch ? ws + w.scratch : nullptr, stream);
+  if (e == hipSuccess && op.raw && raw.leave) cache->staged = astro_kvcache::Staged{q, k_chunk, ws, n_frames, group, cache->epoch, true};
   return e == hipSuccess ? ASTRO_OK : ASTRO_ERR_HIP;
 }
 

@@ -57,6 +57,7 @@ struct FwdParams {
   int H, Nq, BH, q_tiles, group;  // BH = candidates * heads; group = candidates per cache stream
   int block_rows;                 // causal block inside the chunk in token rows, 0 = none
   bool by_xcd;                    // order of the workgroups, see order_by_xcd()
+  bool in_turn;                   // few rows: the waves take the key tiles in turn, not a contiguous share each
   int64_t cache_rows;  // C*T
   StreamInts hist_rows;
 };
@@ -459,12 +460,98 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
 // loads reach; calls of a few tiles are the chain launch, operand loads, tile, combine (7 us).
 // The first tile's reference is tried at 0 (init_zero_ref): a wave walks few tiles, so recomputing the
 // first one's scores for its maximum, as the general kernel does, would be a large part of the work.
-template <int D, int kWaves, bool kCausal>
-__global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams p) {
+//
+// RawChunk: the workgroups rotate queries and chunk keys themselves, so no pre-pass has to end before the
+// scores can begin: a call of a few tiles is that chain (one 64-token frame, 2 heads of 64, 4 resident frames: 10.1 -> 6.9 us).
+// With one wave per SIMD every vector instruction costs its latency, about 8 cycles, so their number is what
+// counts: the waves share the rotation of the queries through LDS, and a wave turns a chunk key tile in its
+// buffer with positions found once per row and the lane's four rotary pairs fixed (a lane's own queries and positions
+// per look-up: 45 % more instructions, 1.5 - 3 us more).
+struct StagedChunk {};  // the operands are in q_rot and kc_rot
+struct RawChunk {
+  const __bf16 *q, *k;  // [B, Nq, H, D] as the caller passed them
+  __bf16 *q_rot, *kc_rot;
+  float2* tab_t;  // what the pre-pass would leave here goes there too, for a later call; null = it is not wanted
+  const double* inv_freq_t;
+  const float2 *tab_h, *tab_w;
+  int gh, gw, T, n_t, n_h, n_w, n_frames;
+  float q_scale;
+  StreamInts first_frame;  // by candidate
+};
+
+// The (cos, sin) a workgroup's chunk tokens need, in LDS: [n_frames][n_t], [gh][n_h], [gw][n_w], at most kEntries.
+template <int kEntries>
+struct ChunkTables {
+  const float2* tab;
+  int T, gw, n_t, nb, n_h, n_w, off_h, off_w;
+  float inv_T, inv_gw;
+  static constexpr int kBits = 10;
+  static_assert(kEntries < 1 << kBits, "three entry numbers to a word");
+
+  // fills `to` (the caller's barrier makes it visible)
+  template <int kThreads>
+  __device__ __forceinline__ void init(const RawChunk& r, float2* to, int b) {
+    tab = to;
+    T = r.T, gw = r.gw, n_t = r.n_t, nb = r.n_t + r.n_h, n_h = r.n_h, n_w = r.n_w;
+    off_h = r.n_frames * r.n_t, off_w = off_h + r.gh * r.n_h;
+    inv_T = 1.f / r.T, inv_gw = 1.f / r.gw;
+    const int n_rows = r.gh * r.n_h, n_all = n_rows + r.gw * r.n_w;
+    // the row and column tables are requested before the sines of the frames are computed
+    constexpr int kUnroll = (kEntries + kThreads - 1) / kThreads;
+    float2 x[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int e = u * kThreads + (int)threadIdx.x;
+      if (e < n_all) x[u] = e < n_rows ? r.tab_h[e] : r.tab_w[e - n_rows];
+    }
+    for (int e = threadIdx.x; e < off_h; e += kThreads) {
+      const int fi = e / n_t;
+      double sn, cs;
+      sincos((double)(r.first_frame.v[b] + fi) * r.inv_freq_t[e - fi * n_t], &sn, &cs);
+      to[e] = make_float2((float)cs, (float)sn);
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int e = u * kThreads + (int)threadIdx.x;
+      if (e < n_all) to[off_h + e] = x[u];
+    }
+  }
+  // First entries of the frame, row and column of chunk token `tok`, kBits each.  A quotient's distance from the next
+  // integer is at least half a divisor's inverse, the product's error 2^-23 of it: exact below 2^22 tokens.
+  __device__ __forceinline__ uint32_t position(int tok) const {
+    const int f = (int)(((float)tok + 0.5f) * inv_T), rem = tok - f * T;
+    const int y = (int)(((float)rem + 0.5f) * inv_gw), x = rem - y * gw;
+    return (uint32_t)(f * n_t) | (uint32_t)(off_h + y * n_h) << kBits | (uint32_t)(off_w + x * n_w) << 2 * kBits;
+  }
+  // Which part of a position pairs 4c .. 4c + 3 take and how far behind it they are.
+  struct Quad {
+    uint32_t shift[4], at[4];
+  };
+  __device__ __forceinline__ Quad pairs(int c) const {
+    Quad q;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int j = 4 * c + v;
+      q.shift[v] = j < n_t ? 0 : (j < nb ? kBits : 2 * kBits);
+      q.at[v] = j - (j < n_t ? 0 : (j < nb ? n_t : nb));
+    }
+    return q;
+  }
+  __device__ __forceinline__ void cos_sin(const Quad& q, uint32_t position, float2 (&cs)[4]) const {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) cs[v] = tab[__builtin_amdgcn_ubfe(position, q.shift[v], kBits) + q.at[v]];
+  }
+};
+
+template <int D, int kWaves, bool kCausal, typename Chunk>
+__global__ void __launch_bounds__(kWaves * 64, D == 128 ? 2 : 4) attn_fwd_few_kernel(FwdParams p, Chunk chunk) {
+  constexpr bool kRaw = std::is_same_v<Chunk, RawChunk>;
   using F = FewRows<D, kWaves>;
   using Wave = FwdWave<D>;
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * F::kWaveBytes];
   __shared__ float2 stats[kWaves][32];  // softmax reference and row sum of each wave's keys
+  __shared__ float2 tab[kRaw ? fwd_table_entries(D) : 1];
+  __shared__ __attribute__((aligned(1024))) char qtile[kRaw ? F::kTileBytes : 16];
 
   const WorkItem item = work_item(p.q_tiles, p.BH, p.by_xcd);
   if (!item.valid) return;
@@ -488,24 +575,37 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
   for (int qs = 0; qs < 2; ++qs) vis[qs] = visible_chunk_rows(q0 + 16 * qs < q_last ? q0 + 16 * qs : q_last, p.Nq, block_rows);
   const int hist_tiles = (hist + KT - 1) / KT;
   const int ntiles = hist_tiles + (vis_last + KT - 1) / KT;
-  const int t_begin = F::begin(wave, kWaves, 0, ntiles), t_end = F::begin(wave + 1, kWaves, 0, ntiles);
 
   const u32x4 k_hist = segment_words(p.k_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
   const u32x4 v_hist = segment_words(p.v_cache + (int64_t)pair.cache_bh * p.cache_rows * D, D, hist, D);
-  const u32x4 k_chunk = segment_words(p.kc_rot + bh * p.Nq * D, D, p.Nq, D);
-  const u32x4 v_chunk = segment_words(p.v_chunk + ((int64_t)b * p.Nq * p.H + h) * D, (int64_t)p.H * D, p.Nq, D);
+  const int64_t chunk_at = ((int64_t)b * p.Nq * p.H + h) * D;  // token-major tensors
+  const int token_stride = p.H * D;
+  const u32x4 v_chunk = segment_words(p.v_chunk + chunk_at, token_stride, p.Nq, D);
+  u32x4 k_chunk;
+  uint32_t k_stride = D * 2;
+  if constexpr (kRaw) {
+    k_chunk = segment_words(chunk.k + chunk_at, token_stride, p.Nq, D);
+    k_stride = token_stride * 2;
+  } else {
+    k_chunk = segment_words(p.kc_rot + bh * p.Nq * D, D, p.Nq, D);
+  }
   char* ktile = lds + wave * F::kWaveBytes;
   char* vtile = ktile + F::kTileBytes;
   PrivateStream<D> ps;
   ps.init(lane);
   auto issue_k = [&](int t) __attribute__((always_inline)) {
     const bool in_hist = t < hist_tiles;
-    ps.issue(in_hist ? k_hist : k_chunk, D * 2, (in_hist ? t : t - hist_tiles) * KT, ktile);
+    ps.issue(in_hist ? k_hist : k_chunk, in_hist ? D * 2 : k_stride, (in_hist ? t : t - hist_tiles) * KT, ktile);
   };
   auto issue_v = [&](int t) __attribute__((always_inline)) {
     const bool in_hist = t < hist_tiles;
-    ps.issue(in_hist ? v_hist : v_chunk, in_hist ? D * 2 : p.H * D * 2, (in_hist ? t : t - hist_tiles) * KT, vtile);
+    ps.issue(in_hist ? v_hist : v_chunk, in_hist ? D * 2 : token_stride * 2, (in_hist ? t : t - hist_tiles) * KT, vtile);
   };
+  // in turn where the chunk may have to be rotated, so that its tiles fall to all waves (and the sums are the same if it is
+  // not); else a share each, 0.8 % faster on long walks
+  const bool in_turn = kRaw || p.in_turn;
+  const int t_begin = in_turn ? wave : F::begin(wave, kWaves, 0, ntiles), t_end = in_turn ? ntiles : F::begin(wave + 1, kWaves, 0, ntiles);
+  const int t_step = in_turn ? kWaves : 1;
   if (t_begin < t_end) {
     issue_k(t_begin);
     issue_v(t_begin);
@@ -514,20 +614,88 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
   Wave w;
   w.init(lane);
   w.init_zero_ref();
+  ChunkTables<fwd_table_entries(D)> tables;
+  if constexpr (kRaw) {
+    // a 16-byte unit of the block's queries per thread and trip, rotated into LDS for all waves
+    constexpr int CPR = D / 8, kThreads = kWaves * 64, kTrips = (32 * CPR + kThreads - 1) / kThreads;
+    const int c = threadIdx.x % CPR;
+    bf16x8 x[kTrips];
 #pragma unroll
-  for (int qs = 0; qs < 2; ++qs) {
-    const int q = q0 + 16 * qs;
-    const __bf16* qrow = p.q_rot + (bh * p.Nq + (q < p.Nq ? q : 0)) * D;
+    for (int u = 0; u < kTrips; ++u) {
+      const int row = (u * kThreads + (int)threadIdx.x) / CPR, q = q_first + row;
+      x[u] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      if (row < 32 && q < p.Nq) x[u] = *reinterpret_cast<const bf16x8*>(chunk.q + chunk_at + (int64_t)q * token_stride + c * 8);
+    }
+    tables.template init<kThreads>(chunk, tab, b);
+    __syncthreads();
+    const auto pairs = tables.pairs(c);
 #pragma unroll
-    for (int st = 0; st < Wave::KS; ++st) {
-      bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (q < p.Nq) x = *reinterpret_cast<const bf16x8*>(qrow + st * 32 + g * 8);
-      w.qreg[qs][st] = x;
+    for (int u = 0; u < kTrips; ++u) {
+      const int row = (u * kThreads + (int)threadIdx.x) / CPR, q = q_first + row;
+      if (row >= 32) continue;
+      float2 cs[4];
+      tables.cos_sin(pairs, tables.position(q < p.Nq ? q : q_last), cs);
+      x[u] = rotate8(x[u], cs, chunk.q_scale);
+      *reinterpret_cast<bf16x8*>(qtile + lds_chunk_offset16<D>(row, c)) = x[u];
+      if (chunk.tab_t && q < p.Nq) *reinterpret_cast<bf16x8*>(chunk.q_rot + (bh * p.Nq + q) * D + c * 8) = x[u];
+    }
+    if (chunk.tab_t && item.tile == 0 && h == 0)
+      for (int e = threadIdx.x; e < tables.off_h; e += kThreads) chunk.tab_t[(int64_t)b * tables.off_h + e] = tab[e];
+    __syncthreads();
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs)
+#pragma unroll
+      for (int st = 0; st < Wave::KS; ++st) w.qreg[qs][st] = read_rows16<D>(qtile, w.addr.row[st], 16 * qs);
+  } else {
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs) {
+      const int q = q0 + 16 * qs;
+      const __bf16* qrow = p.q_rot + (bh * p.Nq + (q < p.Nq ? q : 0)) * D;
+#pragma unroll
+      for (int st = 0; st < Wave::KS; ++st) {
+        bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (q < p.Nq) x = *reinterpret_cast<const bf16x8*>(qrow + st * 32 + g * 8);
+        w.qreg[qs][st] = x;
+      }
     }
   }
-  for (int t = t_begin; t < t_end; ++t) {
+  // rotates the wave's tile `t` of chunk keys where it is; the workgroup that owns these rows as queries leaves them for a later call
+  auto rotate_keys = [&](int t) __attribute__((always_inline)) {
+    if constexpr (kRaw) {
+      constexpr int CPR = D / 8, kRows = 64 / CPR, kUnits = KT / kRows;
+      const int c = lane % CPR, r0 = lane / CPR, row0 = (t - hist_tiles) * KT;
+      const auto pairs = tables.pairs(c);
+      const int tok = row0 + (lane & 31);  // each lane finds one row's position
+      const uint32_t position = tables.position(tok < p.Nq ? tok : q_last);
+      // all of the tile first: the compiler cannot tell a unit's place from another's and would wait for each in turn
+      bf16x8 k[kUnits];
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) k[u] = *reinterpret_cast<const bf16x8*>(ktile + lds_chunk_offset16<D>(u * kRows + r0, c));
+#pragma unroll
+      for (int u0 = 0; u0 < kUnits; u0 += 4) {  // the look-ups of four units in flight
+        float2 cs[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) tables.cos_sin(pairs, __shfl(position, (u0 + u) * kRows + r0), cs[u]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k[u0 + u] = rotate8(k[u0 + u], cs[u], 1.f);
+      }
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) *reinterpret_cast<bf16x8*>(ktile + lds_chunk_offset16<D>(u * kRows + r0, c)) = k[u];
+      if (chunk.tab_t && t - hist_tiles == item.tile) {
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+          const int j = row0 + u * kRows + r0;
+          if (j < p.Nq) *reinterpret_cast<bf16x8*>(chunk.kc_rot + (bh * p.Nq + j) * D + c * 8) = k[u];
+        }
+      }
+      wave_lds_sync();
+    }
+  };
+  for (int t = t_begin; t < t_end; t += t_step) {
     wait_vmem_except<PrivateStream<D>::kInsts>();  // the K tile; the V tile behind it may be in flight
     wave_lds_sync();
+    if (t >= hist_tiles) rotate_keys(t);
     bf16x8 kf[Wave::KH];
     w.read_k(ktile, kf);
     const int row0 = (t < hist_tiles ? t : t - hist_tiles) * KT;
@@ -536,8 +704,8 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
     w.template tile<true>(kf, ktile, vtile, live, (t < hist_tiles ? hist : vis_first) - row0 < KT, t == t_begin, [&] {
       wait_lds();
       wave_lds_sync();
-      if (t + 1 < t_end) {
-        issue_k(t + 1);
+      if (t + t_step < t_end) {
+        issue_k(t + t_step);
         wait_vmem_except<PrivateStream<D>::kInsts>();
       } else {
         wait_vmem();
@@ -546,7 +714,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_fwd_few_kernel(FwdParams 
     });
     wait_lds();
     wave_lds_sync();
-    if (t + 1 < t_end) issue_v(t + 1);
+    if (t + t_step < t_end) issue_v(t + t_step);
   }
 
   // every wave leaves its unnormalised result and its statistics (own buffer, own tiles are done) ...
@@ -651,6 +819,7 @@ FwdParams make_params(const DevGeom& g, const AttnOperands& op, void* out, float
   p.BH = g.B * g.H;
   p.q_tiles = 0;
   p.by_xcd = true;
+  p.in_turn = false;
   p.splits = 1;
   p.out_part = nullptr;
   p.lse_part = nullptr;
@@ -661,8 +830,19 @@ template <int D, int kWaves, bool kCausal>
 hipError_t launch_few(const DevGeom& g, const AttnOperands& op, void* out, float* lse, hipStream_t stream) {
   FwdParams p = make_params(g, op, out, lse);
   p.q_tiles = (op.Nq + 31) / 32;
-  ProfileScope prof("attn_fwd_few_bf16", stream);
-  attn_fwd_few_kernel<D, kWaves, kCausal><<<dim3(work_grid_size(p.q_tiles, p.BH)), dim3(kWaves * 64), 0, stream>>>(p);
+  const dim3 grid(work_grid_size(p.q_tiles, p.BH)), block(kWaves * 64);
+  if (const ChunkSource* from = op.raw) {
+    { ProfileScope staged("chunk_rope_stage", stream); }  // counted like a staging of its own, without a time
+    RawChunk c{(const __bf16*)from->q, (const __bf16*)from->k, (__bf16*)op.q_rot, (__bf16*)op.kc_rot,
+               from->leave ? (float2*)op.tab_t : nullptr, g.inv_freq_t, g.tab_h, g.tab_w, g.gh, g.gw, g.T, g.n_t, g.n_h, g.n_w,
+               op.Nq / g.T, from->q_scale, from->first_frame};
+    ProfileScope prof("attn_fwd_few_bf16", stream);
+    attn_fwd_few_kernel<D, kWaves, kCausal, RawChunk><<<grid, block, 0, stream>>>(p, c);
+  } else {
+    p.in_turn = bf16_fwd_rotates(g, op);
+    ProfileScope prof("attn_fwd_few_bf16", stream);
+    attn_fwd_few_kernel<D, kWaves, kCausal, StagedChunk><<<grid, block, 0, stream>>>(p, StagedChunk{});
+  }
   return hipGetLastError();
 }
 
@@ -692,6 +872,11 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
 }
 
 }  // namespace
+
+bool bf16_fwd_rotates(const DevGeom& g, const AttnOperands& op) {
+  const int pairs = g.n_t + g.n_h + g.n_w, n_frames = op.Nq / g.T;
+  return pairs != 0 && fwd_rotates(call_shape(g, op), (int64_t)n_frames * g.n_t + (int64_t)g.gh * g.n_h + (int64_t)g.gw * g.n_w);
+}
 
 size_t bf16_fwd_split_bytes(const DevGeom& g, int Nq) {
   if (!fwd_may_split(g.n_cus, g.B * g.H, Nq)) return 0;

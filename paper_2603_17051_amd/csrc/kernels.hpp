@@ -73,6 +73,15 @@ hipError_t launch_rope_sink_rerotate(const DevGeom& g, int dtype, const void* si
                                      const StreamInts& first_pos, const StreamInts& count,
                                      hipStream_t stream);
 
+// The chunk as the caller passed it, for a launch that rotates it itself (bf16_fwd_rotates).
+struct ChunkSource {
+  const void* q;           // [B, Nq, H, D]
+  const void* k;           // [B, Nq, H, D]
+  float q_scale;           // see launch_rope_scatter's a_scale
+  bool leave;              // leave q_rot, kc_rot and tab_t as the pre-pass would, for a later call
+  StreamInts first_frame;  // by candidate
+};
+
 // Keys / values visible to a chunk: the resident ring rows (a prefix of the ring) and
 // the chunk's own rows.  With group > 1 the chunk tensors hold `group` candidate chunks per
 // cache stream (candidate c = b*group + g, DevGeom::B counts candidates); all candidates of
@@ -91,6 +100,7 @@ struct AttnOperands {
   // An output shares bytes with something that a route of this call would still read after writing it: take the
   // route that reads it all first (see outputs_overlap in astro_api.hip).
   bool in_order = false;
+  const ChunkSource* raw = nullptr;  // non-null: nothing is staged, the launch rotates from here
 };
 
 inline CallShape call_shape(const DevGeom& g, const AttnOperands& op) {
@@ -112,6 +122,8 @@ hipError_t launch_attn_bwd_f32(const DevGeom& g, const AttnOperands& op, const f
 size_t bf16_fwd_split_bytes(const DevGeom& g, int Nq);
 hipError_t launch_attn_fwd_bf16(const DevGeom& g, const AttnOperands& op, void* out, float* lse, void* parts,
                                 hipStream_t stream);
+// Whether the forward of this call may take its chunk from AttnOperands::raw.
+bool bf16_fwd_rotates(const DevGeom& g, const AttnOperands& op);
 size_t bf16_bwd_workspace_bytes(const DevGeom& g, int Nq);  // beyond q_rot / kc_rot
 // dq, dk, dv: [B, Nq, H, D] fp32 w.r.t. the UN-rotated inputs (the kernels turn dQ~ and dK~ back in
 // their epilogues with the tables of `g` and op.tab_t)

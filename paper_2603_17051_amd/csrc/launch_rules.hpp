@@ -162,6 +162,17 @@ inline int fwd_few_waves(const CallShape& c) {
   return wgs <= c.n_cus && tiles >= 64 ? 8 : 4;
 }
 
+// Whether such a launch rotates queries and chunk keys itself instead of waiting for a pre-pass; `entries` =
+// (cos, sin) its chunk needs, which have to fit the LDS next to the tiles of the two (D = 64: four) workgroups of
+// four waves a CU holds.  It saves the pre-pass, 4 us of the chain, and every workgroup rotates all chunk keys it
+// sees, about 1 us per tile of a wave.  Measured (us; rotating / pre-pass and attention), by chunk tiles per wave:
+//   D = 64:  0.5 7.5 / 11.4, 1 8.4 / 10.8, 2 10.5 / 12.0, 2.75 13.2 / 14.3, 3 11.7 / 12.6; lost: 3.25 11.9 / 11.7, 6.5 14.1 / 12.0
+//   D = 128: 0.5 8.5 / 10.6, 1 12.6 / 13.5, 1.25 11.8 / 11.9, 1.5 11.7 / 12.3, 2 10.8 / 11.4; lost: 2.25 16.2 / 14.7, 4.25 18.6 / 15.3
+constexpr int fwd_table_entries(int D) { return D == 128 ? 896 : 384; }
+inline bool fwd_rotates(const CallShape& c, int64_t entries) {
+  return entries <= fwd_table_entries(c.D) && blocks_of(c.Nq, kFwdKeyTile) <= (c.D == 128 ? 2 : 3) * fwd_few_waves(c);
+}
+
 // ==== backward =====================================================================================
 constexpr int kBwdKeyTile = 64;    // keys per LDS tile of the general dQ kernel
 constexpr int kFewMaxRows = 2048;  // most chunk rows of the kernel for few rows (it holds their row terms in LDS)

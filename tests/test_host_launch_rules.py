@@ -7,7 +7,7 @@ from collections import namedtuple
 
 import pytest
 
-Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd", defaults=[1])
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries", defaults=[1, 0])
 
 
 @pytest.fixture(scope="module")
@@ -108,3 +108,12 @@ def test_split_of_the_dq_walk_only_where_it_gains(rules):
         for pairs in range(4, 130, 6):
             uneven = rules(D, pairs, 1560, [1560, 17160])
             assert uneven.k == 1 or uneven.ways == 1
+
+
+def test_forward_rotates_its_chunk_only_with_few_chunk_tiles_per_wave(rules):
+    for D, most, entries in [(64, 12, 384), (128, 8, 896)]:  # four waves: tiles of 32 chunk rows
+        assert rules(D, 4, 32 * most, 64).rotated_entries == entries
+        assert rules(D, 4, 32 * most + 1, 64).rotated_entries == 0
+        assert rules(D, 1, 64 * most, 2048).fwd_few == 8 and rules(D, 1, 64 * most, 2048).rotated_entries == entries
+        assert rules(D, 12, 4680, 28080).rotated_entries == 0  # the general kernel
+        assert rules(D, 4, 64, 64, in_order=True).rotated_entries == 0
