@@ -175,6 +175,17 @@ struct DqWave {
     dq_product(ks, kb, dsb);
   }
 
+  // Q~ and dO rows of the lane's two queries from a block of 32 in LDS
+  __device__ __forceinline__ void take_queries(const char* qtile, const char* dotile) {
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs)
+#pragma unroll
+      for (int st = 0; st < KS; ++st) {
+        qreg[qs][st] = read_rows16<D>(qtile, addr.row[st], 16 * qs);
+        doreg[qs][st] = read_rows16<D>(dotile, addr.row[st], 16 * qs);
+      }
+  }
+
   // Q~ and dO rows of the lane's two queries, their row terms -LSE*log2(e) and -Delta; bh = stream-head
   // pair of the chunk tensors, write_terms: this wave leaves the row terms for later launches
   __device__ __forceinline__ void load_queries(const BwdParams& p, int b, int h, int q0, bool write_terms) {
@@ -825,7 +836,14 @@ __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams
 // other side (FewRows), and both kinds of workgroup go out in ONE launch: the key side takes Delta
 // from dO and O itself instead of waiting for the query side.  All sums over the waves are fp32 in a
 // fixed order.  What bounds it: the tiles a CU pulls per 32 queries, as in the forward's kernel of
-// this kind; for short walks the chain launch, operand loads, tile, combine (7 us at D = 64).
+// this kind; for short walks the chain launch, operand loads, tile, combine (6 us at D = 64).  With one wave per SIMD a
+// chain costs its latency, so before the walk operands are shared through LDS and requested together, and behind it the
+// rotary look-ups are in flight before the waves meet (each wave loading all of its operands, shuffles for the row
+// sums and a look-up per block where it was used took 60 % of a short call).  Backward before / now, us: D = 64 64 rows, 2
+// heads, 320 keys 7.1 / 5.9; 260 rows, 16 pairs, 1040 keys 14.1 / 11.8; 400 rows, 48 pairs, 2000 keys 41.3 / 37.3;
+// D = 128 64 rows, 2 heads, 320 keys 11.2 / 8.5; 234 rows, 16 pairs, 702 keys 17.1 / 13.9; 330 rows, 16 pairs, 1540 keys 28.4 /
+// 22.8;672 rows, 3 pairs, 1120 keys 30.1 / 24.1.  Two tiles per wave in flight (double the LDS)
+// were slower: 41.7 at the 330 rows, where two workgroups no longer share a CU, and 17.1 at the 234, where each has one anyway.
 // One wave of the key side: S = Q~ K~^T, P and dV^T += dO^T P, or (kDk) also dP = dO V^T, dS and
 // dK~^T += Q~^T dS.  One wave of 256 registers does not hold both accumulators at D = 128, so half of
 // the waves take dV and half dK; S is computed by both.  Layout as in the pair of waves above.
@@ -902,8 +920,32 @@ struct FewKeysWave {
   }
 };
 
+// The (cos, sin) with which a wave turns its `kShare` 16 x 16 blocks of a summed gradient back, all requested before
+// the waves meet for the sum (each looked up where it was used they cost about 1000 cycles a block).
+template <int D, int kShare>
+struct FewAngles {
+  QuadAngles q[kShare];
+  bool rope;
+  // blocks unit0 .. unit0 + kShare - 1: rows row0 + 16 * (unit % 2), columns 16 * (unit / 2) + 4 * g ..
+  __device__ __forceinline__ void load(const RotaryTables& r, int b, int unit0, int row0, int row_last, int g) {
+    rope = r.n_t + r.n_h + r.n_w != 0;
+    if (!rope) return;
+    // block u lies in the rows of block u & 1 (unit0 is even where a wave has more than one block)
+    constexpr int kRows = kShare > 1 ? 2 : 1;
+    TokenTables t[kRows];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      const int row = row0 + 16 * ((unit0 + i) & 1);
+      t[i] = token_tables_small(r, b, row < row_last ? row : row_last);
+    }
+#pragma unroll
+    for (int u = 0; u < kShare; ++u) q[u] = quad_angles(r, t[u % kRows], 4 * ((unit0 + u) >> 1) + g);
+  }
+  __device__ __forceinline__ f32x4 turn_back(int u, f32x4 x) const { return rope ? unrotate_quad(q[u], x) : x; }
+};
+
 template <int D, int kWaves>
-__device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item, char* lds) {
+__device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item, char* lds, float (*terms)[kFewMaxRows]) {
   using F = FewRows<D, kWaves>;
   using Wave = DqWave<D>;
   const PairIndex pair = split_pair(item.bh, p.H, p.group);
@@ -943,7 +985,65 @@ __device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item,
   }
   Wave w;
   w.init(lane);
-  w.load_queries(p, b, h, q0, wave == 0);
+  // Q~ and dO of the block, once for all waves (each had loaded all of both, and O for Delta, in 64-byte pieces: 4400 - 8000
+  // cycles until the first product), where the key side has its row terms.  Delta = <dO, O>: 8 components to a lane.
+  char* const qtile = reinterpret_cast<char*>(terms);
+  char* const dotile = qtile + F::kTileBytes;
+  static_assert(sizeof(float[2][kFewMaxRows]) >= 2 * F::kTileBytes, "both tiles fit");
+  {
+    constexpr int CPR = D / 8, kRows = kWaves * 64 / CPR, kTrips = kRows < 32 ? 32 / kRows : 1;
+    const int64_t tok = ((int64_t)b * p.Nq * p.H + h) * D;
+    const int r = threadIdx.x / CPR, c = threadIdx.x % CPR;
+    bf16x8 x[kTrips], y[kTrips];
+    float l[kTrips];
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      const int row = u * kRows + r, q = q_first + row < p.Nq ? q_first + row : q_last;
+      x[u] = *reinterpret_cast<const bf16x8*>(p.dout + tok + (int64_t)q * p.H * D + c * 8);
+      y[u] = *reinterpret_cast<const bf16x8*>(p.out + tok + (int64_t)q * p.H * D + c * 8);
+      l[u] = p.lse[bh * p.Nq + q];
+    }
+    const u32x4 q_rows = segment_words(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
+    const u32x4 do_rows = segment_words(p.dout + tok, (int64_t)p.H * D, p.Nq, D);
+    for (int u = wave; u < PrivateStream<D>::kInsts; u += kWaves) {
+      ps.issue_part(q_rows, D * 2, q_first, u, qtile);
+      ps.issue_part(do_rows, p.H * D * 2, q_first, u, dotile);
+    }
+    float d[kTrips];
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      d[u] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) d[u] = fmaf((float)x[u][j], (float)y[u][j], d[u]);
+      d[u] = sum_neighbours<CPR>(d[u]);
+    }
+    wait_vmem();
+    __syncthreads();
+    w.take_queries(qtile, dotile);
+    __syncthreads();
+    // the row terms go where Q~ was: with room of their own two workgroups would no longer fit a CU's LDS at D = 128
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      const int row = u * kRows + r, q = q_first + row;
+      if (c != 0 || row >= 32) continue;
+      const bool live = q < p.Nq;
+      // a dead query row gets P = exp2(0 - big) = 0 everywhere
+      const float nl = live ? -l[u] * kLog2e : -1.0e30f, nd = live ? -d[u] : 0.f;
+      terms[0][row] = nl;
+      terms[0][32 + row] = nd;
+      if (live) {  // for later launches
+        p.lse2[bh * p.Nq + q] = nl;
+        p.delta[bh * p.Nq + q] = nd;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs) {
+      const float nl = terms[0][16 * qs + i16], nd = terms[0][32 + 16 * qs + i16];
+      w.neg_lse2[qs] = f32x4{nl, nl, nl, nl};
+      w.neg_delta[qs] = f32x4{nd, nd, nd, nd};
+    }
+  }
   for (int t = t_begin; t < t_end; ++t) {
     const int row0 = (t < hist_tiles ? t : t - hist_tiles) * 32;
     const int live[2] = {(t < hist_tiles ? hist : vis[0]) - row0, (t < hist_tiles ? hist : vis[1]) - row0};
@@ -969,24 +1069,23 @@ __device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item,
       issue_v(t + 1);
     }
   }
+  constexpr int kShare = F::kUnits / kWaves;
+  FewAngles<D, kShare> angles;
+  angles.load(p.rot, b, wave * kShare, q0, q_last, g);
   wave_lds_sync();
 #pragma unroll
   for (int dt = 0; dt < Wave::DT; ++dt)
 #pragma unroll
     for (int qs = 0; qs < 2; ++qs) *reinterpret_cast<f32x4*>(ktile + ((dt * 2 + qs) * 64 + lane) * 16) = w.dq[dt][qs];
   __syncthreads();
-  const bool rope = p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
-  constexpr int kShare = F::kUnits / kWaves;
 #pragma unroll
   for (int u = 0; u < kShare; ++u) {
     const int unit = wave * kShare + u, dt = unit >> 1, q = q0 + 16 * (unit & 1);
-    if (q >= p.Nq) continue;
     f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < kWaves; ++wv) x += *reinterpret_cast<const f32x4*>(lds + wv * F::kWaveBytes + (unit * 64 + lane) * 16);
-    x = x * p.scale;
-    if (rope) x = unrotate_quad(p.rot, token_tables(p.rot, b, q), 4 * dt + g, x);
-    *reinterpret_cast<f32x4*>(p.dq + (((int64_t)b * p.Nq + q) * p.H + h) * D + 16 * dt + 4 * g) = x;
+    x = angles.turn_back(u, x * p.scale);
+    if (q < p.Nq) *reinterpret_cast<f32x4*>(p.dq + (((int64_t)b * p.Nq + q) * p.H + h) * D + 16 * dt + 4 * g) = x;
   }
 }
 
@@ -998,12 +1097,13 @@ __device__ __forceinline__ void few_row_terms(const BwdParams& p, int b, int h, 
   const int64_t bh = (int64_t)b * p.H + h;
   const int n = (p.Nq + 31) & ~31;
   const int r = threadIdx.x / CPR, c = threadIdx.x % CPR;
+  const int64_t first = ((int64_t)b * p.Nq * p.H + h) * D + c * 8;
   for (int q0 = 0; q0 < n; q0 += kRows * kUnroll) {
     bf16x8 x[kUnroll], y[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int q = q0 + u * kRows + r;
-      const int64_t at = (((int64_t)b * p.Nq + (q < p.Nq ? q : 0)) * p.H + h) * D + c * 8;
+      const int64_t at = first + (int64_t)(q < p.Nq ? q : 0) * p.H * D;
       x[u] = *reinterpret_cast<const bf16x8*>(p.dout + at);
       y[u] = *reinterpret_cast<const bf16x8*>(p.out + at);
     }
@@ -1013,68 +1113,79 @@ __device__ __forceinline__ void few_row_terms(const BwdParams& p, int b, int h, 
       float d = 0.f;
 #pragma unroll
       for (int j = 0; j < 8; ++j) d = fmaf((float)x[u][j], (float)y[u][j], d);
-#pragma unroll
-      for (int m = 1; m < CPR; m <<= 1) d += __shfl_xor(d, m);
+      d = sum_neighbours<CPR>(d);
       if (c == 0 && q < n) terms[1][q] = q < p.Nq ? -d : 0.f;
     }
   }
   for (int q = threadIdx.x; q < n; q += kWaves * 64) terms[0][q] = q < p.Nq ? -p.lse[bh * p.Nq + q] * kLog2e : 0.f;
 }
 
-// one wave's share of the key side; part = its share of the query tiles among kWaves / 2
-template <int D, int kWaves, bool kDk>
-__device__ __forceinline__ void few_dkv_wave(const BwdParams& p, const WorkItem& item, int wave, char* lds,
-                                             const float (*terms)[kFewMaxRows]) {
+// What a wave of the key side loads before it has the row terms: the workgroup's keys (and their values, which only the dK
+// waves use) and its first tiles.  part = its share of the query tiles among kWaves / 2.
+template <int D, int kWaves>
+struct FewKeysOperands {
   using F = FewRows<D, kWaves>;
+  int j_first, t_begin, t_end;
+  u32x4 q_rows, do_rows;
+  PrivateStream<D> ps;
+  bf16x8 k[2][D / 32], v[2][D / 32];
+
+  __device__ __forceinline__ void issue(const BwdParams& p, int t, char* qtile) const {
+    ps.issue(q_rows, D * 2, t * 32, qtile);
+    ps.issue(do_rows, p.H * D * 2, t * 32, qtile + F::kTileBytes);
+  }
+  __device__ __forceinline__ void init(const BwdParams& p, int b, int h, int tile, int part, char* qtile) {
+    const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
+    const int64_t bh = (int64_t)b * p.H + h, tok = ((int64_t)b * p.Nq * p.H + h) * D;
+    j_first = tile * 32;
+    const int t_first = first_query_row_seeing(j_first, p.block_rows) / 32, ntiles = (p.Nq + 31) / 32;
+    t_begin = F::begin(part, kWaves / 2, t_first, ntiles), t_end = F::begin(part + 1, kWaves / 2, t_first, ntiles);
+    q_rows = segment_words(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
+    do_rows = segment_words(p.dout + tok, (int64_t)p.H * D, p.Nq, D);
+    ps.init(lane);
+    if (t_begin < t_end) issue(p, t_begin, qtile);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int j = j_first + i16 + 16 * ks < p.Nq ? j_first + i16 + 16 * ks : 0;  // a key past the end is computed like key 0 and never stored
+      const __bf16* krow = p.kc_rot + (bh * p.Nq + j) * D;
+      const __bf16* vrow = p.v_chunk + tok + (int64_t)j * p.H * D;
+#pragma unroll
+      for (int st = 0; st < D / 32; ++st) {
+        k[ks][st] = *reinterpret_cast<const bf16x8*>(krow + st * 32 + g * 8);
+        v[ks][st] = *reinterpret_cast<const bf16x8*>(vrow + st * 32 + g * 8);
+      }
+    }
+  }
+};
+
+// one wave's share of the key side
+template <int D, int kWaves, bool kDk>
+__device__ __forceinline__ void few_dkv_wave(const BwdParams& p, const FewKeysOperands<D, kWaves>& op, char* qtile, const float (*terms)[kFewMaxRows]) {
   using Wave = FewKeysWave<D, kDk>;
-  const int part = wave % (kWaves / 2);
-  const int b = item.bh / p.H, h = item.bh % p.H;
   const int lane = threadIdx.x & 63;
-  const int i16 = lane & 15, g = lane >> 4;
-  const int64_t bh = (int64_t)b * p.H + h;
-  const int j_first = item.tile * 32, j0 = j_first + i16, j_last = p.Nq - 1;
+  const int j_first = op.j_first, j0 = j_first + (lane & 15), j_last = p.Nq - 1;
   int first_q[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(j0 + 16 * ks < j_last ? j0 + 16 * ks : j_last, p.block_rows);
   const int first_q_max = first_query_row_seeing(j_first + 31 < j_last ? j_first + 31 : j_last, p.block_rows);
-  const int t_first = first_query_row_seeing(j_first, p.block_rows) / 32, ntiles = (p.Nq + 31) / 32;
-  const int t_begin = F::begin(part, kWaves / 2, t_first, ntiles), t_end = F::begin(part + 1, kWaves / 2, t_first, ntiles);
-
-  const int64_t tok = ((int64_t)b * p.Nq * p.H + h) * D;
-  const u32x4 q_rows = segment_words(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
-  const u32x4 do_rows = segment_words(p.dout + tok, (int64_t)p.H * D, p.Nq, D);
-  char* qtile = lds + wave * F::kWaveBytes;
-  char* dotile = qtile + F::kTileBytes;
-  PrivateStream<D> ps;
-  ps.init(lane);
-  if (t_begin < t_end) {
-    ps.issue(q_rows, D * 2, t_begin * 32, qtile);
-    ps.issue(do_rows, p.H * D * 2, t_begin * 32, dotile);
-  }
+  char* const dotile = qtile + FewRows<D, kWaves>::kTileBytes;
   Wave w;
   w.init(lane);
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int j = j0 + 16 * ks < p.Nq ? j0 + 16 * ks : 0;  // a key past the end is computed like key 0 and never stored
-    const __bf16* krow = p.kc_rot + (bh * p.Nq + j) * D;
-    const __bf16* vrow = p.v_chunk + tok + (int64_t)j * p.H * D;
+  for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
     for (int st = 0; st < D / 32; ++st) {
-      w.kreg[ks][st] = *reinterpret_cast<const bf16x8*>(krow + st * 32 + g * 8);
-      if constexpr (kDk) w.vreg[ks][st] = *reinterpret_cast<const bf16x8*>(vrow + st * 32 + g * 8);
+      w.kreg[ks][st] = op.k[ks][st];
+      if constexpr (kDk) w.vreg[ks][st] = op.v[ks][st];
     }
-  }
-  for (int t = t_begin; t < t_end; ++t) {
+  for (int t = op.t_begin; t < op.t_end; ++t) {
     const int first[2] = {first_q[0] - t * 32, first_q[1] - t * 32};
     wait_vmem();
     wave_lds_sync();
     w.tile(qtile, dotile, terms[0] + t * 32, terms[1] + t * 32, first, first_q_max - t * 32);
     wait_lds();
     wave_lds_sync();
-    if (t + 1 < t_end) {
-      ps.issue(q_rows, D * 2, (t + 1) * 32, qtile);
-      ps.issue(do_rows, p.H * D * 2, (t + 1) * 32, dotile);
-    }
+    if (t + 1 < op.t_end) op.issue(p, t + 1, qtile);
   }
   wave_lds_sync();
 #pragma unroll
@@ -1089,28 +1200,33 @@ __device__ __forceinline__ void few_dkv(const BwdParams& p, const WorkItem& item
   const int b = item.bh / p.H, h = item.bh % p.H;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
+  constexpr int kHalf = kWaves / 2;
+  char* const qtile = lds + wave * F::kWaveBytes;
+  FewKeysOperands<D, kWaves> op;
+  op.init(p, b, h, item.tile, wave % kHalf, qtile);
   few_row_terms<D, kWaves>(p, b, h, terms);
   __syncthreads();
-  constexpr int kHalf = kWaves / 2;
   const bool is_dv = wave < kHalf;
-  if (is_dv)
-    few_dkv_wave<D, kWaves, false>(p, item, wave, lds, terms);
-  else
-    few_dkv_wave<D, kWaves, true>(p, item, wave, lds, terms);
-  __syncthreads();
-  const bool rope = !is_dv && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
   constexpr int kShare = F::kUnits / kHalf;
+  const int unit0 = (wave % kHalf) * kShare, j0 = item.tile * 32 + i16;
+  FewAngles<D, kShare> angles;
+  angles.rope = false;
+  if (is_dv) {
+    few_dkv_wave<D, kWaves, false>(p, op, qtile, terms);
+  } else {
+    few_dkv_wave<D, kWaves, true>(p, op, qtile, terms);
+    angles.load(p.rot, b, unit0, j0, p.Nq - 1, g);
+  }
+  __syncthreads();
 #pragma unroll
   for (int u = 0; u < kShare; ++u) {
-    const int unit = (wave % kHalf) * kShare + u, dt = unit >> 1, j = item.tile * 32 + i16 + 16 * (unit & 1);
-    if (j >= p.Nq) continue;
+    const int unit = unit0 + u, dt = unit >> 1, j = j0 + 16 * (unit & 1);
     f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < kHalf; ++wv)
       x += *reinterpret_cast<const f32x4*>(lds + (wv + (is_dv ? 0 : kHalf)) * F::kWaveBytes + (unit * 64 + lane) * 16);
-    if (!is_dv) x = x * kLn2;  // dK~ = dS^T Q~ / sqrt(D), and the staged Q~ carries log2(e)/sqrt(D)
-    if (rope) x = unrotate_quad(p.rot, token_tables(p.rot, b, j), 4 * dt + g, x);
-    *reinterpret_cast<f32x4*>((is_dv ? p.dv : p.dk) + (((int64_t)b * p.Nq + j) * p.H + h) * D + 16 * dt + 4 * g) = x;
+    if (!is_dv) x = angles.turn_back(u, x * kLn2);  // dK~ = dS^T Q~ / sqrt(D), and the staged Q~ carries log2(e)/sqrt(D)
+    if (j < p.Nq) *reinterpret_cast<f32x4*>((is_dv ? p.dv : p.dk) + (((int64_t)b * p.Nq + j) * p.H + h) * D + 16 * dt + 4 * g) = x;
   }
 }
 
@@ -1127,7 +1243,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_bwd_few_kernel(BwdParams 
   if (key_side)
     few_dkv<D, kWaves>(p, item, lds, terms);
   else
-    few_dq<D, kWaves>(p, item, lds);
+    few_dq<D, kWaves>(p, item, lds, terms);
 }
 
 template <int D>

@@ -101,10 +101,7 @@ struct FwdWave {
   }
 
   // over the four lanes that share a query
-  static __device__ __forceinline__ float row_sum(float x) {
-    x += __shfl_xor(x, 16);
-    return x + __shfl_xor(x, 32);
-  }
+  static __device__ __forceinline__ float row_sum(float x) { return sum_quarters(x); }
 
   // p = exp2(s - mc) (kZeroRef: mc is 0 for the whole wave, no subtraction) rounded to bf16, packed as the B operands of the PV
   // product (k-slots 8g .. 8g+3 <- keys 4g .., 8g+4 .. <- keys 16 + 4g ..); sum = this lane's

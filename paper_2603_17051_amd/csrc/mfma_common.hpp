@@ -42,6 +42,33 @@ __device__ __forceinline__ float add_pair(bf16x2 p, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(p, ones, acc, false);
 }
 
+// Sum over the N = 8 or 16 neighbouring lanes that share a row, in every one of them.  Data-parallel-primitive moves
+// (neighbour, next pair, mirrored eight, mirrored sixteen) instead of shuffles, which go through the LDS and cost a
+// wave that is alone on its SIMD some 100 cycles each; the same bits as a butterfly over lanes 1, 2, 4, 8 apart.
+template <int N>
+__device__ __forceinline__ float sum_neighbours(float x) {
+  static_assert(N == 8 || N == 16, "a row of 64 or 128 values, 8 to a lane");
+  auto moved = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  x += moved(x, std::integral_constant<int, 0xB1>{});   // lanes 1 0 3 2
+  x += moved(x, std::integral_constant<int, 0x4E>{});   // lanes 2 3 0 1
+  x += moved(x, std::integral_constant<int, 0x141>{});  // eight lanes mirrored
+  if constexpr (N == 16) x += moved(x, std::integral_constant<int, 0x140>{});  // sixteen lanes mirrored
+  return x;
+}
+
+// Sum over lanes i, i + 16, i + 32, i + 48 (the four that share a query), in every one of them.  In assembly: of the
+// builtin's two results for one value passed twice the compiler took the first for both.  The two wait states are what the
+// swap needs behind the vector instruction that wrote its operand.
+__device__ __forceinline__ float sum_quarters(float x) {
+  float a = x, b = x;
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));  // rows of 16 lanes {0, 0, 2, 2} and {1, 1, 3, 3}
+  b = a = a + b;
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));  // halves {0, 0} and {1, 1}
+  return a + b;
+}
+
 // ---- tiles read as operands of v_mfma_f32_16x16x32_bf16 ------------------------------------
 // D[16x16] += A[16x32] * B[32x16].  Lane l (i = l % 16, g = l / 16) holds A[i][8g .. 8g+7],
 // B[8g .. 8g+7][i] and D[4g + r][i] in accumulator register r.  Under the chip's power limit this
@@ -190,6 +217,14 @@ struct PrivateStream {
 #pragma unroll
     for (int u = 0; u < kPatterns; ++u) chunk[u] = ((lane % CPR) ^ swizzle16<CPR>(u * kRowsPerInst + lane / CPR)) * 16;
   }
+  // one instruction's worth (rows u * kRowsPerInst .. of the tile at row0), for a tile that several waves fill together
+  __device__ __forceinline__ void issue_part(const u32x4 rsrc, uint32_t stride_bytes, int row0, int u, const char* lds_tile) const {
+    typedef const char __attribute__((address_space(3))) * lds_ptr;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr)lds_tile) + u * 1024;
+    const uint32_t r = u * kRowsPerInst + lane_row;
+    const uint32_t off = (row0 + r) * stride_bytes + (((threadIdx.x & 63) % CPR) ^ swizzle16<CPR>(r)) * 16;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc) : "memory", "m0");
+  }
   __device__ __forceinline__ void issue(const u32x4 rsrc, uint32_t stride_bytes, int row0, const char* lds_tile) const {
     typedef const char __attribute__((address_space(3))) * lds_ptr;
     const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr)lds_tile);
@@ -332,11 +367,27 @@ __device__ __forceinline__ float2 pair_cos_sin(const RotaryTables& r, const Toke
   const float2* base = pair < r.n_t ? t.t : (pair < nb ? t.h : t.w);
   return base[pair < r.n_t ? pair : (pair < nb ? pair - r.n_t : pair - nb)];
 }
+// The same for chunk tokens below 2^20, by a reciprocal: a quotient lies at least half a divisor's inverse from the next
+// integer, the product's error is below 2^-21 of it.  (The two integer divisions are 40 instructions each.)
+__device__ __forceinline__ TokenTables token_tables_small(const RotaryTables& r, int b, int tok) {
+  const int fi = (int)(((float)tok + 0.5f) * __builtin_amdgcn_rcpf((float)r.T)), rem = tok - fi * r.T;
+  const int row = (int)(((float)rem + 0.5f) * __builtin_amdgcn_rcpf((float)r.gw)), col = rem - row * r.gw;
+  return TokenTables{r.tab_t + (int64_t)b * r.n_frames * r.n_t + fi * r.n_t, r.tab_h + row * r.n_h, r.tab_w + col * r.n_w};
+}
 // x = four consecutive components 4*quad .. 4*quad+3 (two adjacent pairs) of a gradient w.r.t. the
 // rotated vector; returns them w.r.t. the un-rotated one: R(phi)^T applied to each pair.
-__device__ __forceinline__ f32x4 unrotate_quad(const RotaryTables& r, const TokenTables& t, int quad, f32x4 x) {
-  const float2 a = pair_cos_sin(r, t, 2 * quad), b = pair_cos_sin(r, t, 2 * quad + 1);
+struct QuadAngles {
+  float2 a, b;
+};
+__device__ __forceinline__ QuadAngles quad_angles(const RotaryTables& r, const TokenTables& t, int quad) {
+  return QuadAngles{pair_cos_sin(r, t, 2 * quad), pair_cos_sin(r, t, 2 * quad + 1)};
+}
+__device__ __forceinline__ f32x4 unrotate_quad(const QuadAngles& q, f32x4 x) {
+  const float2 a = q.a, b = q.b;
   return f32x4{x[0] * a.x + x[1] * a.y, x[1] * a.x - x[0] * a.y, x[2] * b.x + x[3] * b.y, x[3] * b.x - x[2] * b.y};
+}
+__device__ __forceinline__ f32x4 unrotate_quad(const RotaryTables& r, const TokenTables& t, int quad, f32x4 x) {
+  return unrotate_quad(quad_angles(r, t, quad), x);
 }
 
 // wait until this wave's outstanding LDS accesses are done
