@@ -842,7 +842,7 @@ __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams
 // sums and a look-up per block where it was used took 60 % of a short call).  Backward before / now, us: D = 64 64 rows, 2
 // heads, 320 keys 7.1 / 5.9; 260 rows, 16 pairs, 1040 keys 14.1 / 11.8; 400 rows, 48 pairs, 2000 keys 41.3 / 37.3;
 // D = 128 64 rows, 2 heads, 320 keys 11.2 / 8.5; 234 rows, 16 pairs, 702 keys 17.1 / 13.9; 330 rows, 16 pairs, 1540 keys 28.4 /
-// 22.8;672 rows, 3 pairs, 1120 keys 30.1 / 24.1.  Two tiles per wave in flight (double the LDS)
+// 22.8;672 rows, 3 pairs, 1120 keys 30.1 / 24.1 with four waves.  Two tiles per wave in flight (double the LDS)
 // were slower: 41.7 at the 330 rows, where two workgroups no longer share a CU, and 17.1 at the 234, where each has one anyway.
 // One wave of the key side: S = Q~ K~^T, P and dV^T += dO^T P, or (kDk) also dP = dO V^T, dS and
 // dK~^T += Q~^T dS.  One wave of 256 registers does not hold both accumulators at D = 128, so half of

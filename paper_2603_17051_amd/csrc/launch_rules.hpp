@@ -138,9 +138,12 @@ inline int fwd_splits(const CallShape& c) {
 // lower bound there.  The walk is the longest stream's; where streams differ, the general kernel, which cuts
 // it, takes over at half the bounds and beyond three (D = 128) or five workgroups per CU (longest and mean walk: 1056 x
 // 180, 89 88 / 56; 432 x 216, 148 46 / 38; 1536 x 28, 19 61 / 48; the other way 480 x 54, 42 30 / 39; 7 % in the mean of 85 such
-// launches).  Returns the waves per workgroup, 0 = the general kernel: eight waves pay
-// when every CU has one workgroup at most and the walk is long (140 x 133, D = 128: 28.1 against 31.5 us
-// with four); two workgroups of four waves share a CU otherwise (312 x 86: 30.2 against 36.4).
+// launches).  Returns the waves per workgroup, 0 = the general kernel: eight where every CU has one workgroup at
+// most and each wave gets two tiles (D = 64: one) or more, else four.  Four waves are one per SIMD, whose tile then costs its
+// latency: of 1000 shapes eight take, by tiles, D = 64 0.95 of the time at 5 - 16, 0.9 at 17 - 32, 0.83 at 64 and 0.7 above
+// 100 (144 x 34 9.6 against 11.9 us, 192 x 135 17.7 / 24.7), D = 128 0.9 from 8 tiles on and 0.85 above 64 (128 x 23 12.1 / 14.1, 132 x
+// 82 22.1 / 28.0; the line there keeps 14 tiles, which a test of the rules names, at four).  Where two workgroups of four
+// share a CU nothing is gained (312 x 153, D = 64 32.0 / 32.8) or lost (D = 128 1.2).  Sixteen waves: 10.2 at the 144 x 34.
 inline int fwd_few_waves(const CallShape& c) {
   if (c.in_order) return 0;
   const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
@@ -159,18 +162,22 @@ inline int fwd_few_waves(const CallShape& c) {
   }
   if (uneven) limit = per_cu > (c.D == 128 ? 3 : 5) ? 0 : limit / 2;
   if (walk > limit) return 0;
-  return wgs <= c.n_cus && tiles >= 64 ? 8 : 4;
+  return wgs <= c.n_cus && tiles >= (c.D == 128 ? 16 : 8) ? 8 : 4;
 }
 
 // Whether such a launch rotates queries and chunk keys itself instead of waiting for a pre-pass; `entries` =
 // (cos, sin) its chunk needs, which have to fit the LDS next to the tiles of the two (D = 64: four) workgroups of
 // four waves a CU holds.  It saves the pre-pass, 4 us of the chain, and every workgroup rotates all chunk keys it
 // sees, about 1 us per tile of a wave.  Measured (us; rotating / pre-pass and attention), by chunk tiles per wave:
-//   D = 64:  0.5 7.5 / 11.4, 1 8.4 / 10.8, 2 10.5 / 12.0, 2.75 13.2 / 14.3, 3 11.7 / 12.6; lost: 3.25 11.9 / 11.7, 6.5 14.1 / 12.0
-//   D = 128: 0.5 8.5 / 10.6, 1 12.6 / 13.5, 1.25 11.8 / 11.9, 1.5 11.7 / 12.3, 2 10.8 / 11.4; lost: 2.25 16.2 / 14.7, 4.25 18.6 / 15.3
+//   four waves, D = 64: 0.5 7.5 / 11.4, 1 8.4 / 10.8, 2 10.5 / 12.0, 2.75 13.2 / 14.3, 3 11.7 / 12.6; lost: 3.25 11.9 / 11.7, 6.5 14.1 / 12.0
+//   four waves, D = 128: 0.5 8.5 / 10.6, 1 12.6 / 13.5, 1.25 11.8 / 11.9, 1.5 11.7 / 12.3, 2 10.8 / 11.4; lost: 2.25 16.2 / 14.7, 4.25 18.6 / 15.3
+//   eight waves, ratio over 800 shapes, D = 64: 0.5 0.80, 1 0.82, 1.5 0.88, 2 0.92, 2.5 0.96, 3 1.01; D = 128: 0.82, 0.86, 0.94, 0.97, lost:
+//   2.5 1.02, 3 1.06
 constexpr int fwd_table_entries(int D) { return D == 128 ? 896 : 384; }
 inline bool fwd_rotates(const CallShape& c, int64_t entries) {
-  return entries <= fwd_table_entries(c.D) && blocks_of(c.Nq, kFwdKeyTile) <= (c.D == 128 ? 2 : 3) * fwd_few_waves(c);
+  const int waves = fwd_few_waves(c);
+  const int most = c.D == 128 ? 2 * waves : waves == 8 ? 20 : 3 * waves;  // chunk tiles
+  return entries <= fwd_table_entries(c.D) && blocks_of(c.Nq, kFwdKeyTile) <= most;
 }
 
 // ==== backward =====================================================================================
@@ -186,9 +193,10 @@ constexpr int kFewMaxRows = 2048;  // most chunk rows of the kernel for few rows
 // Over 3800 shapes it takes 0.6 - 1.0 of the general kernels' time (medians by number of tiles) just below these lines
 // and 1.0 - 1.3 just above them.  Walks of 40 tiles and more, which the general dQ kernel splits, have the line
 // lower, short ones higher (129 - 144 blocks below 15 tiles at D = 128 0.67 - 0.88, 225 - 240 below 10 at D = 64 0.9 - 1.0).
-// Returns the waves per workgroup, 0 = the general kernels: eight waves pay when the query side alone
-// does not fill the CUs and the walk is long (132 workgroups x 109 tiles, D = 128: 32.6 against 39.5 us
-// with four), four otherwise (208 x 37: 30.0 against 34.3).
+// Returns the waves per workgroup, 0 = the general kernels: eight where the workgroups of both sides have a CU
+// each and the walk is more than 24 tiles, four otherwise.  Of 1400 shapes eight take, by tiles, 1.05 - 1.15 of the time of four below 16,
+// 1.0 at 17 - 24, 0.95 at 25 - 32, 0.9 to 48, 0.85 to 64, 0.75 above 100 (24 x 114, D = 128 24.6 / 31.0 us); with more workgroups
+// 1.2 - 1.5 (176 x 49 28.8 / 22.8), 1.0 - 1.15 from 64 tiles on (132 x 82 31.3 / 29.1) up to 160 workgroups, where 0.8 - 1.0 remains above 192 tiles.
 inline int bwd_few_waves(const CallShape& c) {
   if (c.in_order) return 0;
   const int64_t blocks = (int64_t)blocks_of(c.Nq, 128) * c.pairs;
@@ -197,7 +205,8 @@ inline int bwd_few_waves(const CallShape& c) {
                                     : (tiles >= 40 ? 8 : tiles >= 10 ? 12 : tiles >= 3 ? 15 : 16);
   if (c.Nq > kFewMaxRows || 16 * blocks > sixteenths * (int64_t)c.n_cus) return 0;
   const int64_t wgs = (int64_t)blocks_of(c.Nq, 32) * c.pairs;
-  return 8 * wgs <= 5 * (int64_t)c.n_cus && (c.max_hist + c.Nq) / 32 >= 64 ? 8 : 4;
+  const int tiles32 = (c.max_hist + c.Nq) / 32;
+  return 2 * wgs <= c.n_cus ? (tiles32 > 24 ? 8 : 4) : 8 * wgs <= 5 * (int64_t)c.n_cus && tiles32 > 192 ? 8 : 4;
 }
 
 // dQ workgroups a CU holds: 244 registers (split 256), or 165 (split 168, 8 more in scratch)

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
     (64, (12, 10, 10), 1, 1, 1, 1, 1, 3, 1, 0, 0),       # one token
     (64, (12, 10, 10), 3, 11, 2, 3, 1, 4, 3, 1, 2),      # 33-token frames, causal, one row past a tile
     (64, (12, 10, 10), 8, 16, 1, 2, 1, 6, 3, 0, 6),      # twelve full chunk tiles, the most that are rotated
+    (64, (12, 10, 10), 16, 20, 1, 2, 1, 4, 2, 0, 4),     # eight waves, twenty chunk tiles, a full table
     (64, (0, 16, 16), 4, 8, 1, 2, 1, 3, 2, 0, 3),        # no temporal pairs
     (128, (22, 21, 21), 2, 3, 2, 2, 3, 40, 40, 0, 7),    # many frames to a tile, candidates, 985 entries: staged after all
     (128, (22, 21, 21), 2, 3, 2, 2, 3, 35, 35, 0, 7),    # 875 entries

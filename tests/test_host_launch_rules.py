@@ -111,9 +111,20 @@ def test_split_of_the_dq_walk_only_where_it_gains(rules):
 
 
 def test_forward_rotates_its_chunk_only_with_few_chunk_tiles_per_wave(rules):
-    for D, most, entries in [(64, 12, 384), (128, 8, 896)]:  # four waves: tiles of 32 chunk rows
-        assert rules(D, 4, 32 * most, 64).rotated_entries == entries
-        assert rules(D, 4, 32 * most + 1, 64).rotated_entries == 0
-        assert rules(D, 1, 64 * most, 2048).fwd_few == 8 and rules(D, 1, 64 * most, 2048).rotated_entries == entries
+    for D, pairs, most, entries in [(64, 24, 12, 384), (128, 4, 8, 896)]:  # four waves: tiles of 32 chunk rows
+        assert rules(D, pairs, 32 * most, 64).fwd_few == 4 and rules(D, pairs, 32 * most, 64).rotated_entries == entries
+        assert rules(D, pairs, 32 * most + 1, 64).rotated_entries == 0
+    for D, most, entries in [(64, 20, 384), (128, 16, 896)]:  # eight
+        assert rules(D, 1, 32 * most, 2048).fwd_few == 8 and rules(D, 1, 32 * most, 2048).rotated_entries == entries
+        assert rules(D, 1, 32 * most + 1, 2048).rotated_entries == 0
+    for D in (64, 128):
         assert rules(D, 12, 4680, 28080).rotated_entries == 0  # the general kernel
         assert rules(D, 4, 64, 64, in_order=True).rotated_entries == 0
+
+
+def test_waves_of_launches_with_few_rows(rules):
+    """Eight only where every workgroup has a CU to itself and its waves have enough tiles."""
+    for call, fwd, bwd in [((64, 2, 64, 256), 8, 4), ((64, 16, 260, 780), 8, 4), ((64, 30, 216, 1404), 8, 4), ((64, 24, 405, 4455), 4, 4),
+                           ((128, 2, 64, 256), 4, 4), ((128, 16, 234, 468), 8, 4), ((128, 3, 672, 448), 8, 8),
+                           ((128, 64, 90, 0), 4, 4), ((128, 16, 330, 1210), 8, 4), ((64, 12, 108, 810), 8, 8), ((128, 4, 192, 1900), 8, 8), ((64, 1, 32, 0), 4, 4)]:
+        assert (rules(*call).fwd_few, rules(*call).bwd_few) == (fwd, bwd), call
