@@ -1,4 +1,5 @@
-"""ctypes binding of the C ABI in include/astro.h: argument marshalling only.
+"""Binding of the C ABI in include/astro.h: argument marshalling only, by ctypes; the calls of every layer and step go
+through a CPython module (csrc/binding_native.cpp) when their arguments are plain, complete and on the current stream.
 
 torch is used for device memory and streams; every computation happens in the
 HIP library.  If libastro.so is missing the import of this module fails
@@ -12,7 +13,7 @@ from ctypes import POINTER, byref, c_double, c_float, c_int, c_int32, c_size_t, 
 
 import torch
 
-from .build import LIB_PATH
+from .build import LIB_PATH, NATIVE_PATH
 
 ASTRO_OK = 0
 ASTRO_ERR_INVALID_ARG = -1
@@ -106,7 +107,22 @@ def _load() -> ctypes.CDLL:
     return lib
 
 
+def _load_native():
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(
+            f"{NATIVE_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+    from . import _binding_native
+    functions = (_lib.astro_kvcache_append, _lib.astro_chunk_attn_fwd, _lib.astro_group_attn_fwd, _lib.astro_chunk_attn_bwd,
+                 _lib.astro_group_attn_bwd, _lib.astro_chunk_attn_bwd_full, _lib.astro_nft_loss_workspace_bytes,
+                 _lib.astro_nft_loss)
+    _binding_native.bind(tuple(ctypes.cast(f, c_void_p).value for f in functions))
+    return _binding_native
+
+
 _lib = _load()
+# Each of its functions answers None, with nothing done, for a call it does not take as it is: the ctypes path below it
+# then checks the arguments and raises.
+_native = _load_native()
 
 
 def library() -> ctypes.CDLL:
@@ -172,6 +188,7 @@ class KVCache:
         # the desc as plain values: every call checks its tensors against them
         self._dims = (desc.batch, desc.grid_h * desc.grid_w, desc.heads, desc.head_dim)
         self._torch_dtype = torch.bfloat16 if desc.dtype == ASTRO_BF16 else torch.float32
+        self._native_dims = (*self._dims, desc.dtype == ASTRO_BF16)
 
     @property
     def tokens_per_frame(self) -> int:
@@ -242,6 +259,10 @@ def _check_chunk_tensor(cache: KVCache, t: torch.Tensor, n_frames: int, name: st
 
 def astro_kvcache_append(cache: KVCache, k=None, v=None, n_frames: int = 1, stream=None) -> None:
     host_only = bool(cache.desc.flags & ASTRO_FLAG_HOST_ONLY)
+    if stream is None and not host_only:
+        code = _native.append(cache.handle, cache._native_dims, k, v, n_frames)
+        if code is not None:
+            return _check(code, "astro_kvcache_append")
     if not host_only:
         _check_chunk_tensor(cache, k, n_frames, "k")
         _check_chunk_tensor(cache, v, n_frames, "v")
@@ -269,6 +290,11 @@ def astro_group_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, gro
                          workspace=None, stream=None):
     """`group` candidate chunks per cache stream, tensors [B*group, Nq, H, D].
     Returns (out [B*group, Nq, H, D], lse [B*group, H, Nq] fp32)."""
+    if stream is None and group:
+        code = _native.fwd(cache.handle, cache._native_dims, q, k_chunk, v_chunk, n_frames, group, out, lse, workspace)
+        if code is not None:
+            _check(code, "astro_group_attn_fwd")
+            return out, lse
     for name, t in (("q", q), ("k_chunk", k_chunk), ("v_chunk", v_chunk)):
         _check_chunk_tensor(cache, t, n_frames, name, group=group)
     d = cache.desc
@@ -290,6 +316,12 @@ def astro_group_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, gro
 def astro_group_attn_bwd(cache: KVCache, q, k_chunk, v_chunk, out, lse, dout, n_frames: int, group: int,
                          dq=None, dk_chunk=None, dv_chunk=None, workspace=None, stream=None):
     """Returns fp32 (dq, dk_chunk, dv_chunk), each [B*group, Nq, H, D]."""
+    if stream is None and group:
+        code = _native.bwd(cache.handle, cache._native_dims, q, k_chunk, v_chunk, out, lse, dout, n_frames, group, dq,
+                           dk_chunk, dv_chunk, workspace)
+        if code is not None:
+            _check(code, "astro_group_attn_bwd")
+            return dq, dk_chunk, dv_chunk
     for name, t in (("q", q), ("k_chunk", k_chunk), ("v_chunk", v_chunk), ("out", out), ("dout", dout)):
         _check_chunk_tensor(cache, t, n_frames, name, group=group)
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
@@ -320,6 +352,11 @@ def astro_chunk_attn_workspace_bytes(cache: KVCache, n_frames: int):
 def astro_chunk_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, out=None, lse=None,
                          workspace=None, stream=None):
     """Returns (out [B, Nq, H, D], lse [B, H, Nq] fp32)."""
+    if stream is None:
+        code = _native.fwd(cache.handle, cache._native_dims, q, k_chunk, v_chunk, n_frames, 0, out, lse, workspace)
+        if code is not None:
+            _check(code, "astro_chunk_attn_fwd")
+            return out, lse
     for name, t in (("q", q), ("k_chunk", k_chunk), ("v_chunk", v_chunk)):
         _check_chunk_tensor(cache, t, n_frames, name)
     d = cache.desc
@@ -339,6 +376,12 @@ def astro_chunk_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, out
 def astro_chunk_attn_bwd(cache: KVCache, q, k_chunk, v_chunk, out, lse, dout, n_frames: int,
                          dq=None, dk_chunk=None, dv_chunk=None, workspace=None, stream=None):
     """Returns fp32 (dq, dk_chunk, dv_chunk), each [B, Nq, H, D]."""
+    if stream is None:
+        code = _native.bwd(cache.handle, cache._native_dims, q, k_chunk, v_chunk, out, lse, dout, n_frames, 0, dq, dk_chunk,
+                           dv_chunk, workspace)
+        if code is not None:
+            _check(code, "astro_chunk_attn_bwd")
+            return dq, dk_chunk, dv_chunk
     for name, t in (("q", q), ("k_chunk", k_chunk), ("v_chunk", v_chunk), ("out", out), ("dout", dout)):
         _check_chunk_tensor(cache, t, n_frames, name)
     mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
@@ -397,6 +440,11 @@ def astro_nft_loss(v_theta, v_old, v_ref, target, advantage, kl_mask, a_max: flo
                    loss=None, grad=None, workspace=None, stream=None):
     """Fused clip-level loss: tensors [n, ...] (bf16 or fp32, contiguous), advantage fp32 [n],
     kl_mask int32 [n].  Returns (loss [3] fp32 = total, policy, kl; grad fp32 like v_theta)."""
+    if stream is None:
+        code = _native.loss(v_theta, v_old, v_ref, target, advantage, kl_mask, a_max, beta, lambda_kl, loss, grad, workspace)
+        if code is not None:
+            _check(code, "astro_nft_loss")
+            return loss, grad
     n = v_theta.shape[0]
     elems = v_theta.numel() // n
     for name, t in (("v_old", v_old), ("v_ref", v_ref), ("target", target)):
@@ -463,6 +511,12 @@ def astro_chunk_attn_bwd_full(cache: KVCache, q, k_chunk, v_chunk, out, lse, dou
     """The backward without the detach.  Returns fp32 (dq, dk_chunk, dv_chunk [B, Nq, H, D],
     dk_cache, dv_cache [B, C*T, H, D]); rows of empty slots of the last two stay as they were
     (zero when allocated here)."""
+    if stream is None:
+        code = _native.bwd(cache.handle, cache._native_dims, q, k_chunk, v_chunk, out, lse, dout, n_frames, 0, dq, dk_chunk,
+                           dv_chunk, workspace, dk_cache, dv_cache, cache.desc.capacity_frames)
+        if code is not None:
+            _check(code, "astro_chunk_attn_bwd_full")
+            return dq, dk_chunk, dv_chunk, dk_cache, dv_cache
     for name, t in (("q", q), ("k_chunk", k_chunk), ("v_chunk", v_chunk), ("out", out), ("dout", dout)):
         _check_chunk_tensor(cache, t, n_frames, name)
     d = cache.desc

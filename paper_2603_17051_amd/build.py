@@ -1,15 +1,17 @@
-"""Build the HIP library (gfx950) in-tree: paper_2603_17051_amd/libastro.so."""
+"""Build the HIP library (gfx950) in-tree, paper_2603_17051_amd/libastro.so, and beside it the CPython module of the binding."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libastro.so")
+NATIVE_PATH = os.path.join(PKG_DIR, "_binding_native.so")
 SOURCES = ["astro_api.hip", "rope_scatter.hip", "attn_f32.hip", "attn_fwd_bf16.hip", "attn_bwd_bf16.hip", "profile.hip", "calib.hip", "nft_loss.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-unused-value",
@@ -54,5 +56,27 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+def build_native() -> str:
+    """Host code only, against the installed torch's headers and libraries."""
+    import torch  # where its headers are
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(_hipcc())))
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        raise RuntimeError("no C++ compiler: the binding's module cannot be built")
+    tmp = NATIVE_PATH + ".tmp"
+    cmd = [cxx, "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(rocm, "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "binding_native.cpp"), "-o", tmp,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building the binding's module failed:\n{r.stderr}")
+    os.replace(tmp, NATIVE_PATH)
+    return NATIVE_PATH
+
+
 if __name__ == "__main__":
     print(build_library(verbose="-v" in sys.argv))
+    print(build_native())

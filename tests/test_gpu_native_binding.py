@@ -1,0 +1,94 @@
+"""The binding's CPython module: the same results as the ctypes path (which a call with its stream named takes), and the
+calls it does not take, which go there."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2603_17051_amd as A
+from paper_2603_17051_amd import binding
+
+GOOD = dict(batch=2, heads=2, head_dim=64, grid_h=4, grid_w=8, capacity_frames=4, sink_frames=1, max_chunk_frames=2,
+            rope_pairs=(12, 10, 10))
+
+
+def test_calls_it_does_not_take_are_left_alone():
+    cache = A.astro_kvcache_create(host_only=True, **GOOD)
+    x, dims = torch.zeros(2, 32, 2, 64, dtype=torch.bfloat16), cache._native_dims
+    append = binding._native.append
+    assert append(cache.handle, dims, x, x, 1) is None  # not on a device
+    assert append(cache.handle, dims, None, x, 1) is None and append(cache.handle, dims, x) is None
+    for handle in (None, 7, ctypes.c_void_p(None)):
+        assert append(handle, dims, x, x, 1) is None
+    for frames in (True, 1.0, -1, 1 << 40, None):
+        assert append(cache.handle, dims, x, x, frames) is None
+    assert append(cache.handle, dims[:4], x, x, 1) is None
+    one = torch.ones(1)
+    assert binding._native.loss(one, one, one, one, one, one, 1.0, 1.0, 0.1, None, None, None) is None
+    with pytest.raises(TypeError):
+        binding._native.bind((1, 2))
+    cache.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("group", [1, 3])
+def test_attention_calls_give_what_the_ctypes_path_gives(group):
+    gen = torch.Generator("cuda:0").manual_seed(3)
+    draw = lambda b, n: torch.randn((b, n * 32, 2, 64), generator=gen, device="cuda:0").bfloat16()
+    k0, v0 = draw(2, 2), draw(2, 2)
+    q, k, v, do = (draw(2 * group, 2) for _ in range(4))
+    results = []
+    for stream in (None, torch.cuda.current_stream()):
+        cache = A.astro_kvcache_create(**GOOD)
+        A.astro_kvcache_append(cache, k0, v0, 2, stream=stream)
+        need = max(A.astro_group_attn_workspace_bytes(cache, 2, group))
+        ws = torch.empty(max(need, A.astro_chunk_attn_bwd_full_workspace_bytes(cache, 2)), dtype=torch.uint8, device="cuda:0")
+        out, lse = torch.empty_like(q), torch.empty((2 * group, 2, 64), device="cuda:0")
+        g = [torch.empty(q.shape, device="cuda:0") for _ in range(3)]
+        ring = [torch.zeros((2, 4 * 32, 2, 64), device="cuda:0") for _ in range(2)]
+        if group == 1:
+            got = A.astro_chunk_attn_fwd(cache, q, k, v, 2, out, lse, ws, stream=stream)
+            got += A.astro_chunk_attn_bwd(cache, q, k, v, out, lse, do, 2, *g, ws, stream=stream)
+            got = [x.clone() for x in got]
+            got += A.astro_chunk_attn_bwd_full(cache, q, k, v, out, lse, do, 2, *g, *ring, ws, stream=stream)
+        else:
+            got = A.astro_group_attn_fwd(cache, q, k, v, 2, group, out, lse, ws, stream=stream)
+            got += A.astro_group_attn_bwd(cache, q, k, v, out, lse, do, 2, group, *g, ws, stream=stream)
+        results.append([x.clone() for x in got] + [cache.k_storage.clone()])
+        # refused on both ways
+        for change in (dict(q=q.float()), dict(q=q[:1]), dict(q=q.transpose(0, 1)), dict(q=q.cpu()), dict(lse=lse[:1] if group > 1 else None, out=out[:1])):
+            a = dict(q=q, out=out, lse=lse)
+            a.update(change)
+            with pytest.raises(ValueError):
+                A.astro_group_attn_fwd(cache, a["q"], k, v, 2, group, a["out"], a["lse"], ws, stream=stream)
+        with pytest.raises(A.AstroError) as e:
+            A.astro_group_attn_fwd(cache, q, k, v, 2, group, out, lse, ws[:256], stream=stream)
+        assert e.value.code == binding.ASTRO_ERR_WORKSPACE
+        # a subclass of Tensor still goes through
+        A.astro_group_attn_fwd(cache, q.as_subclass(type("Sub", (torch.Tensor,), {})), k, v, 2, group, out, lse, ws, stream=stream)
+        assert torch.equal(out, results[-1][0])
+        cache.close()
+        with pytest.raises(A.AstroError):
+            A.astro_kvcache_append(cache, k0, v0, 2, stream=stream)
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_loss_gives_what_the_ctypes_path_gives_on_the_current_stream():
+    gen = torch.Generator("cuda:0").manual_seed(5)
+    x = [torch.randn((3, 5, 104), generator=gen, device="cuda:0").bfloat16() for _ in range(4)]
+    adv, mask = torch.randn(3, generator=gen, device="cuda:0"), torch.tensor([0, 1, 1], dtype=torch.int32, device="cuda:0")
+    ws = torch.empty(A.astro_nft_loss_workspace_bytes(3, 520), dtype=torch.uint8, device="cuda:0")
+    side, results = torch.cuda.Stream(), []
+    for stream, a_max in ((None, 1.0), (side, 1.0), (None, 1)):  # an int goes through ctypes
+        loss, grad = torch.full((3,), -1.0, device="cuda:0"), torch.full(x[0].shape, -1.0, device="cuda:0")
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            A.astro_nft_loss(*x, adv, mask, a_max, 0.9, 0.1, loss, grad, ws, stream=stream)
+        side.synchronize()
+        results.append((loss, grad))
+    for r in results[1:]:
+        assert torch.equal(r[0], results[0][0]) and torch.equal(r[1], results[0][1])
+    with pytest.raises(ValueError):
+        A.astro_nft_loss(x[0], x[1].float(), x[2], x[3], adv, mask, 1.0, 0.9, 0.1, loss, grad, ws)
