@@ -7,11 +7,10 @@
 #include <mutex>
 
 #include "kernels.hpp"
+#include "mfma_common.hpp"
 
 namespace astro {
 namespace {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;  // of the prepare launch
 constexpr int kElemsPerBlock = 16384;  // most elements of one sample a workgroup walks
@@ -108,9 +107,7 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
   float r, nm;
   if constexpr (kInline) {
     int c = 0;
-    for (int j = threadIdx.x; j < p.n; j += threads) c += p.kl_mask[j] != 0 ? 1 : 0;
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) c += __shfl_xor(c, sh);
+    for (int j0 = 0; j0 < p.n; j0 += threads) c += __popcll(__ballot(j0 + (int)threadIdx.x < p.n && p.kl_mask[j0 + threadIdx.x] != 0));
     if (lane == 0) red[0][wave] = (float)c;  // counts up to 1024: exact
     __syncthreads();
     nm = 0.f;
@@ -158,8 +155,7 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
   float v[3] = {s_pos, s_neg, s_ref};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) v[k] += __shfl_xor(v[k], s);
+    v[k] = sum_quarters(sum_neighbours<16>(v[k]));
     if (lane == 0) red[k][wave] = v[k];
   }
   __syncthreads();
@@ -170,26 +166,49 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
   }
 }
 
+// Sum over a wave, in every lane of it: the two 32-bit halves are moved as sum_neighbours() and sum_quarters() do.
+__device__ __forceinline__ double wave_sum(double x) {
+  auto moved = [](double v, auto ctrl) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)u, decltype(ctrl)::value, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), decltype(ctrl)::value, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  };
+  x += moved(x, std::integral_constant<int, 0xB1>{});
+  x += moved(x, std::integral_constant<int, 0x4E>{});
+  x += moved(x, std::integral_constant<int, 0x141>{});
+  x += moved(x, std::integral_constant<int, 0x140>{});
+#pragma unroll
+  for (int s = 16; s < 64; s <<= 1) x += __shfl_xor(x, s);
+  return x;
+}
+
 // One workgroup: L_policy = (1/n) sum_i [r~_i S+_i + (1 - r~_i) S-_i], L_KL = (1/|M|) sum_{i in M} Sref_i.
 // Both are sums over all triples of partial sums with the weights of their sample, so the threads
 // share the triples (one thread per sample walked its triples one after another: 5.5 us at 24 clips
 // of 19 triples, most of it latency).  fp64, fixed order.
+// What it takes is the chain launch, loads, sum.  Moves between lanes instead of shuffles through the LDS (here and in the
+// main kernel), a division of 32 bits, the count requested with the triples and no more waves than there are triples for: 4
+// clips of 30784 elements in bf16 9.3 -> 8.3 us for both launches, 109 of 1856 7.3 -> 6.3, 24 of 299520 20.0 -> 19.4, 148 of 33240 in
+// fp32 22.3 -> 21.4.
 constexpr int kFinalThreads = 1024;
 __global__ void __launch_bounds__(kFinalThreads) nft_finalize_kernel(NftParams p) {
   __shared__ double pol[kFinalThreads / 64], kl[kFinalThreads / 64];
   const int64_t n_triples = (int64_t)p.n * p.blocks_per_sample;
+  const int threads = blockDim.x, waves = threads / 64;
+  const double nm = (double)*p.n_masked;
   double a = 0.0, b = 0.0;
-  for (int64_t t = threadIdx.x; t < n_triples; t += kFinalThreads) {
-    const int i = (int)(t / p.blocks_per_sample);
+  auto add = [&](int64_t t, int i) __attribute__((always_inline)) {
     const double r = (double)p.r_tilde[i];
     a += r * (double)p.partials[3 * t] + (1.0 - r) * (double)p.partials[3 * t + 1];
-    if (p.kl_mask[i] != 0) b += (double)p.partials[3 * t + 2];
-  }
-#pragma unroll
-  for (int s = 32; s > 0; s >>= 1) {
-    a += __shfl_xor(a, s);
-    b += __shfl_xor(b, s);
-  }
+    b += p.kl_mask[i] != 0 ? (double)p.partials[3 * t + 2] : 0.0;
+  };
+  if (n_triples <= INT32_MAX - kFinalThreads)
+    for (uint32_t t = threadIdx.x; t < (uint32_t)n_triples; t += threads) add(t, (int)(t / (uint32_t)p.blocks_per_sample));
+  else
+    for (int64_t t = threadIdx.x; t < n_triples; t += threads) add(t, (int)(t / p.blocks_per_sample));
+  a = wave_sum(a);
+  b = wave_sum(b);
   if ((threadIdx.x & 63) == 0) {
     pol[threadIdx.x >> 6] = a;
     kl[threadIdx.x >> 6] = b;
@@ -197,11 +216,11 @@ __global__ void __launch_bounds__(kFinalThreads) nft_finalize_kernel(NftParams p
   __syncthreads();
   if (threadIdx.x == 0) {
     a = b = 0.0;
+#pragma unroll
     for (int wv = 0; wv < kFinalThreads / 64; ++wv) {
-      a += pol[wv];
-      b += kl[wv];
+      a += wv < waves ? pol[wv] : 0.0;
+      b += wv < waves ? kl[wv] : 0.0;
     }
-    const double nm = (double)*p.n_masked;
     const double l_pol = a / (double)p.n;
     const double l_kl = nm > 0.0 ? b / nm : 0.0;
     p.loss[0] = (float)(l_pol + (double)p.lambda_kl * l_kl);
@@ -285,7 +304,8 @@ int run_nft_loss(const void* v_theta, const void* v_old, const void* v_ref, cons
       else
         nft_loss_kernel<float, false><<<grid, threads, 0, stream>>>(p);
     }
-    nft_finalize_kernel<<<1, kFinalThreads, 0, stream>>>(p);
+    const int64_t n_triples = (int64_t)n_samples * p.blocks_per_sample;
+    nft_finalize_kernel<<<1, n_triples < kFinalThreads ? (int)(n_triples + 63) / 64 * 64 : kFinalThreads, 0, stream>>>(p);
   }
   return hipGetLastError() == hipSuccess ? ASTRO_OK : ASTRO_ERR_HIP;
 }
