@@ -320,19 +320,26 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, const DqSplit& split
   // dQ~ -> dQ: the rotation is turned back here (each lane holds both halves of its pairs), so the
   // gradient goes out once, token-major, instead of through a rotated fp32 copy and another pass
   const bool rope = !kSplit && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  QuadAngles angles[2][Wave::DT];
+  if (rope) {  // all requested before the first store, see dkv_wave()
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs) {
+      const TokenTables tt = token_tables(p.rot, b, q0 + 16 * qs < q_last ? q0 + 16 * qs : q_last);
+#pragma unroll
+      for (int dt = 0; dt < Wave::DT; ++dt) angles[qs][dt] = quad_angles(p.rot, tt, 4 * dt + g);
+    }
+  }
 #pragma unroll
   for (int qs = 0; qs < 2; ++qs) {
     const int q = q0 + 16 * qs;
     if (q < p.Nq) {
       float* row = (which == 0 ? p.dq : (which == 1 ? split.part1 : split.part2)) + (((int64_t)b * p.Nq + q) * p.H + h) * D;
-      TokenTables tt{};
-      if (rope) tt = token_tables(p.rot, b, q);
 #pragma unroll
       for (int dt = 0; dt < Wave::DT; ++dt) {
         f32x4 x = w.dq[dt][qs];
         if constexpr (!kSplit) {
           x = x * p.scale;
-          if (rope) x = unrotate_quad(p.rot, tt, 4 * dt + g, x);
+          if (rope) x = unrotate_quad(angles[qs][dt], x);
         }
         *reinterpret_cast<f32x4*>(row + 16 * dt + 4 * g) = x;
       }
@@ -375,6 +382,7 @@ __global__ void __launch_bounds__(256) dq_merge_kernel(BwdParams p, DqSplit spli
   const bool rope = p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
   const int64_t i0 = (int64_t)blockIdx.x * (256 * kUnroll) + threadIdx.x;
   f32x4 x[kWays][kUnroll];
+  QuadAngles angles[kUnroll];  // requested with the sums, before the first store
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const int64_t i = i0 + u * 256;
@@ -382,6 +390,11 @@ __global__ void __launch_bounds__(256) dq_merge_kernel(BwdParams p, DqSplit spli
       x[0][u] = *reinterpret_cast<const f32x4*>(p.dq + i * 4);
       x[1][u] = *reinterpret_cast<const f32x4*>(split.part1 + i * 4);
       if constexpr (kWays == 3) x[2][u] = *reinterpret_cast<const f32x4*>(split.part2 + i * 4);
+      if (rope) {
+        // (rows of 256 bytes and more: their number fits 32 bits)
+        const uint32_t bq = (uint32_t)(i / QPR) / (uint32_t)p.H, b = bq / (uint32_t)p.Nq;
+        angles[u] = quad_angles(p.rot, token_tables(p.rot, (int)b, (int)(bq - b * (uint32_t)p.Nq)), (int)(i % QPR));
+      }
     }
   }
 #pragma unroll
@@ -392,11 +405,7 @@ __global__ void __launch_bounds__(256) dq_merge_kernel(BwdParams p, DqSplit spli
 #pragma unroll
     for (int w = 1; w < kWays; ++w) v += x[w][u];
     v = v * p.scale;
-    if (rope) {
-      const int64_t bq = i / QPR / p.H;
-      const int b = (int)(bq / p.Nq);
-      v = unrotate_quad(p.rot, token_tables(p.rot, b, (int)(bq - (int64_t)b * p.Nq)), (int)(i % QPR), v);
-    }
+    if (rope) v = unrotate_quad(angles[u], v);
     *reinterpret_cast<f32x4*>(p.dq + i * 4) = v;
   }
 }
@@ -778,30 +787,40 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
     if (!(kKey ? grads.dk : grads.dv)) return;
   }
 
-  // dV as it is; dK~ is turned back to dK here
+  // dV as it is; dK~ is turned back to dK here.  All look-ups are requested before the first store: the compiler cannot tell
+  // the gradients from the tables, so one behind a store waited for it, about 1000 cycles for each of the 16 blocks.
   const bool rope = kKey && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  QuadAngles angles[2][D / 16];
+  if (rope) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int j = jc + 16 * ks < j_last ? jc + 16 * ks : j_last;
+      TokenTables tt;
+      if constexpr (kRing) {
+        const int slot = j / p.rot.T, rem = j - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
+        tt = TokenTables{slot_tab + (slot - slot_first) * p.rot.n_t, p.rot.tab_h + y * p.rot.n_h, p.rot.tab_w + x * p.rot.n_w};
+      } else {
+        tt = token_tables(p.rot, b, j);
+      }
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) angles[ks][dt] = quad_angles(p.rot, tt, 4 * dt + g);
+    }
+  }
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     const int j = jc + 16 * ks;
     if (j >= n_keys) continue;
     float* row;
-    TokenTables tt{};
-    if constexpr (kRing) {
+    if constexpr (kRing)
       row = (kKey ? grads.dk : grads.dv) + (((int64_t)b * p.cache_rows + j) * p.H + h) * D;
-      if (rope) {
-        const int slot = j / p.rot.T, rem = j - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
-        tt = TokenTables{slot_tab + (slot - slot_first) * p.rot.n_t, p.rot.tab_h + y * p.rot.n_h, p.rot.tab_w + x * p.rot.n_w};
-      }
-    } else {
+    else
       row = (kKey ? p.dk : p.dv) + (((int64_t)b * p.Nq + j) * p.H + h) * D;
-      if (rope) tt = token_tables(p.rot, b, j);
-    }
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt) {
       f32x4 x;
       if constexpr (kKey) {
         x = w.dk[dt][ks] * kLn2;  // dK~ = dS^T Q~ / sqrt(D), and the staged Q~ carries log2(e)/sqrt(D)
-        if (rope) x = unrotate_quad(p.rot, tt, 4 * dt + g, x);
+        if (rope) x = unrotate_quad(angles[ks][dt], x);
       } else {
         x = w.dv[dt][ks];
       }

@@ -765,11 +765,10 @@ __global__ void __launch_bounds__(256) fwd_merge_kernel(FwdParams p, int64_t n_r
   const int64_t row = (int64_t)blockIdx.x * (256 / CPR) + threadIdx.x / CPR;  // (b*Nq + q)*H + h
   if (row >= n_rows) return;
   const int c = threadIdx.x % CPR;
-  const int h = (int)(row % p.H);
-  const int64_t bq = row / p.H;
-  const int q = (int)(bq % p.Nq);
-  const int64_t b = bq / p.Nq;
-  const int64_t lse_at = (b * p.H + h) * p.Nq + q;
+  // (rows of 128 bytes and more: their number fits 32 bits)
+  const uint32_t bq = (uint32_t)row / (uint32_t)p.H, b = bq / (uint32_t)p.Nq;
+  const int h = (int)((uint32_t)row - bq * p.H), q = (int)(bq - b * p.Nq);
+  const int64_t lse_at = ((int64_t)b * p.H + h) * p.Nq + q;
   const int64_t out_stride = (int64_t)p.BH * p.Nq * D, lse_stride = (int64_t)p.BH * p.Nq;
   bf16x8 o[kMaxFwdSplits];
   float l[kMaxFwdSplits];
