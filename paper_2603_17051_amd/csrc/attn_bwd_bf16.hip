@@ -44,6 +44,7 @@ struct BwdParams {
   int group;             // candidates per cache stream
   int block_rows;        // causal block inside the chunk in token rows, 0 = none
   bool by_xcd;           // order of the workgroups, see order_by_xcd()
+  bool terms_ready;      // few rows: delta and lse2 are there already
   int64_t cache_rows;
   float scale;
   StreamInts hist_rows;
@@ -1050,7 +1051,7 @@ __device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item,
       const float nl = live ? -l[u] * kLog2e : -1.0e30f, nd = live ? -d[u] : 0.f;
       terms[0][row] = nl;
       terms[0][32 + row] = nd;
-      if (live) {  // for later launches
+      if (live && !p.terms_ready) {  // for later launches
         p.lse2[bh * p.Nq + q] = nl;
         p.delta[bh * p.Nq + q] = nd;
       }
@@ -1177,6 +1178,37 @@ struct FewKeysOperands {
   }
 };
 
+// The row terms of all pairs in a launch of its own.  Bound by its bytes (out, dout once) and a launch, 2 us; a row to 8 or
+// 16 lanes, in the order in which the tensors lie in memory.
+template <int D>
+__global__ void __launch_bounds__(256) few_row_terms_kernel(BwdParams p, uint32_t n_rows) {
+  constexpr int CPR = D / 8, kRows = 256 / CPR, kUnroll = 2;
+  const int c = threadIdx.x % CPR;
+  bf16x8 x[kUnroll], y[kUnroll];
+  float l[kUnroll];
+  int64_t at[kUnroll];
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    const uint32_t i = (blockIdx.x * kUnroll + u) * kRows + threadIdx.x / CPR, row = i < n_rows ? i : n_rows - 1;  // (b * Nq + q) * H + h
+    const uint32_t bq = row / (uint32_t)p.H, b = bq / (uint32_t)p.Nq;
+    at[u] = ((int64_t)b * p.H + (row - bq * p.H)) * p.Nq + (bq - b * p.Nq);
+    x[u] = *reinterpret_cast<const bf16x8*>(p.dout + (int64_t)row * D + c * 8);
+    y[u] = *reinterpret_cast<const bf16x8*>(p.out + (int64_t)row * D + c * 8);
+    l[u] = p.lse[at[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    float d = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) d = fmaf((float)x[u][j], (float)y[u][j], d);
+    d = sum_neighbours<CPR>(d);
+    if (c == 0 && (blockIdx.x * kUnroll + u) * kRows + threadIdx.x / CPR < n_rows) {
+      p.delta[at[u]] = -d;
+      p.lse2[at[u]] = -l[u] * kLog2e;
+    }
+  }
+}
+
 // one wave's share of the key side
 template <int D, int kWaves, bool kDk>
 __device__ __forceinline__ void few_dkv_wave(const BwdParams& p, const FewKeysOperands<D, kWaves>& op, char* qtile, const float (*terms)[kFewMaxRows]) {
@@ -1223,7 +1255,15 @@ __device__ __forceinline__ void few_dkv(const BwdParams& p, const WorkItem& item
   char* const qtile = lds + wave * F::kWaveBytes;
   FewKeysOperands<D, kWaves> op;
   op.init(p, b, h, item.tile, wave % kHalf, qtile);
-  few_row_terms<D, kWaves>(p, b, h, terms);
+  if (p.terms_ready) {
+    const int64_t at = ((int64_t)b * p.H + h) * p.Nq;
+    for (int q = threadIdx.x; q < ((p.Nq + 31) & ~31); q += kWaves * 64) {
+      terms[0][q] = q < p.Nq ? p.lse2[at + q] : 0.f;
+      terms[1][q] = q < p.Nq ? p.delta[at + q] : 0.f;
+    }
+  } else {
+    few_row_terms<D, kWaves>(p, b, h, terms);
+  }
   __syncthreads();
   const bool is_dv = wave < kHalf;
   constexpr int kShare = F::kUnits / kHalf;
@@ -1293,6 +1333,7 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   p.group = op.group;
   p.block_rows = op.block_rows;
   p.by_xcd = true;
+  p.terms_ready = false;
   return p;
 }
 
@@ -1305,6 +1346,12 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   BwdParams p = make_params<D>(g, op, out, lse, dout, dq, dk, dv, scratch);
   const CallShape shape = call_shape(g, op);
   if (const int waves = bwd_few_waves(shape)) {
+    p.terms_ready = bwd_terms_first(shape);
+    if (p.terms_ready) {
+      ProfileScope prof("attn_bwd_few_row_terms", stream);
+      const uint32_t n_rows = (uint32_t)p.BH * op.Nq, per_block = 2 * 256 / (D / 8);
+      few_row_terms_kernel<D><<<dim3((n_rows + per_block - 1) / per_block), 256, 0, stream>>>(p, n_rows);
+    }
     ProfileScope prof("attn_bwd_few_bf16", stream);
     p.tiles = (op.Nq + 31) / 32;
     const dim3 grid(2 * work_grid_size(p.tiles, p.BH));

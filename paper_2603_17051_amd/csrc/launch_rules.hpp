@@ -209,6 +209,16 @@ inline int bwd_few_waves(const CallShape& c) {
   return 2 * wgs <= c.n_cus ? (tiles32 > 24 ? 8 : 4) : 8 * wgs <= 5 * (int64_t)c.n_cus && tiles32 > 192 ? 8 : 4;
 }
 
+// Whether the row terms of such a launch (-LSE log2(e) and -Delta of every query) come from a launch of their own.  Otherwise
+// every workgroup of the key side computes those of its whole pair, dO and O once more for each block of 32 keys; that is
+// cheaper than a launch (2 us) for short chunks, and hidden behind the query side where the ring is much longer
+// than the chunk.  Backward with the launch over without, by chunk rows, at 400 shapes: D = 128, ring below 3 chunks 256 - 383 0.95 -
+// 1.00, 384 - 511 0.92 - 1.00, 512 - 699 0.90 - 0.95, 700 - 999 0.86 - 0.97, above 0.83 - 1.00 (one 1.05), ring above 1.0 - 1.1; D = 64, ring below
+// 2 chunks 384 - 511 0.98 - 1.08, 512 - 699 0.93 - 1.03, above 0.82 - 0.98, ring above up to 1.1.  672 rows, 3 pairs, 448 ring rows 21.1 -> 19.0 us.
+inline bool bwd_terms_first(const CallShape& c) {
+  return c.D == 128 ? c.Nq >= 384 && c.max_hist < 3 * (int64_t)c.Nq : c.Nq >= 512 && c.max_hist < 2 * (int64_t)c.Nq;
+}
+
 // dQ workgroups a CU holds: 244 registers (split 256), or 165 (split 168, 8 more in scratch)
 constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }
 

@@ -19,7 +19,9 @@ P64, P128, NONE = (12, 10, 10), (22, 21, 21), (0, 0, 0)
     (64, P64, 32, 64, 1, 1, 2, 1, 0, 1),      # the most rows: eight waves
     (128, P128, 31, 66, 1, 1, 2, 1, 0, 1),    # 2046 of them, ragged
     (64, NONE, 16, 24, 2, 1, 4, 2, 1, 4),     # eight waves, causal, streams two
-    (128, P128, 11, 23, 1, 3, 5, 3, 0, 5),    # eight waves, ragged frames
+    (128, P128, 11, 23, 1, 3, 5, 3, 0, 5),    # eight waves, ragged frames, row terms in a launch before
+    (64, P64, 19, 27, 2, 3, 3, 2, 1, 1),      # the same at D = 64, causal, streams two
+    (128, P128, 16, 24, 1, 2, 4, 1, 0, 3),    # 384 rows over 1152 of the ring: within the launch
 ])
 def test_backward_with_few_rows(D, pairs, gh, gw, B, H, C, Fc, bf, resident):
     import torch
@@ -32,7 +34,10 @@ def test_backward_with_few_rows(D, pairs, gh, gw, B, H, C, Fc, bf, resident):
     ls.A.astro_profile_begin()
     out, lse = ls.A.astro_chunk_attn_fwd(ls.cache, *dev[:3], Fc)
     ls.A.astro_chunk_attn_bwd(ls.cache, *dev[:3], out, lse, dev[3], Fc, *grads)
-    assert "attn_bwd_few_bf16" in ls.A.astro_profile_end()
+    launched = ls.A.astro_profile_end()
+    ring = resident * gh * gw
+    assert "attn_bwd_few_bf16" in launched
+    assert ("attn_bwd_few_row_terms" in launched) == (w.n_q >= 384 and ring < 3 * w.n_q if D == 128 else w.n_q >= 512 and ring < 2 * w.n_q)
     wide = [ls.wide(x) for x in (q, k, v, do)]
     for b, h in {(0, 0), (B - 1, H - 1)}:
         ref = ls.oracle.attn_bwd(*wide, Fc, streams=[b], heads=[h])

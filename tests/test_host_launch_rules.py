@@ -7,7 +7,7 @@ from collections import namedtuple
 
 import pytest
 
-Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries", defaults=[1, 0])
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries terms_first", defaults=[1, 0, 0])
 
 
 @pytest.fixture(scope="module")
@@ -128,3 +128,9 @@ def test_waves_of_launches_with_few_rows(rules):
                            ((128, 2, 64, 256), 4, 4), ((128, 16, 234, 468), 8, 4), ((128, 3, 672, 448), 8, 8),
                            ((128, 64, 90, 0), 4, 4), ((128, 16, 330, 1210), 8, 4), ((64, 12, 108, 810), 8, 8), ((128, 4, 192, 1900), 8, 8), ((64, 1, 32, 0), 4, 4)]:
         assert (rules(*call).fwd_few, rules(*call).bwd_few) == (fwd, bwd), call
+
+
+def test_row_terms_of_a_backward_with_few_rows_come_first_for_long_chunks_over_short_rings(rules):
+    for call, want in [((128, 3, 672, 448), 1), ((128, 3, 384, 1151), 1), ((128, 3, 384, 1152), 0), ((128, 3, 383, 0), 0),
+                       ((64, 3, 512, 1023), 1), ((64, 3, 512, 1024), 0), ((64, 3, 511, 0), 0), ((64, 1, 2048, [0, 5000]), 0)]:
+        assert rules(*call).bwd_few and rules(*call).terms_first == want, call
