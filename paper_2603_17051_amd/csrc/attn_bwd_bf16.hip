@@ -321,26 +321,22 @@ __device__ __forceinline__ void dq_item(const BwdParams& p, const DqSplit& split
   // dQ~ -> dQ: the rotation is turned back here (each lane holds both halves of its pairs), so the
   // gradient goes out once, token-major, instead of through a rotated fp32 copy and another pass
   const bool rope = !kSplit && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
-  QuadAngles angles[2][Wave::DT];
-  if (rope) {  // all requested before the first store, see dkv_wave()
-#pragma unroll
-    for (int qs = 0; qs < 2; ++qs) {
-      const TokenTables tt = token_tables(p.rot, b, q0 + 16 * qs < q_last ? q0 + 16 * qs : q_last);
-#pragma unroll
-      for (int dt = 0; dt < Wave::DT; ++dt) angles[qs][dt] = quad_angles(p.rot, tt, 4 * dt + g);
-    }
-  }
+  // (Here a look-up stays with its store: all of them ahead of the first, as in dkv_wave(), gained nothing at 30 - 128 pairs and cost 0.7 % of a step
+  // of four clips, 12 heads, 4680 rows, where 8608 us became 8665; the other workgroup of the CU
+  // covers them.)
 #pragma unroll
   for (int qs = 0; qs < 2; ++qs) {
     const int q = q0 + 16 * qs;
     if (q < p.Nq) {
       float* row = (which == 0 ? p.dq : (which == 1 ? split.part1 : split.part2)) + (((int64_t)b * p.Nq + q) * p.H + h) * D;
+      TokenTables tt{};
+      if (rope) tt = token_tables(p.rot, b, q);
 #pragma unroll
       for (int dt = 0; dt < Wave::DT; ++dt) {
         f32x4 x = w.dq[dt][qs];
         if constexpr (!kSplit) {
           x = x * p.scale;
-          if (rope) x = unrotate_quad(angles[qs][dt], x);
+          if (rope) x = unrotate_quad(p.rot, tt, 4 * dt + g, x);
         }
         *reinterpret_cast<f32x4*>(row + 16 * dt + 4 * g) = x;
       }
