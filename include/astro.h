@@ -273,7 +273,8 @@ int astro_nft_loss_static(const void *v_theta, const void *v_old, const void *v_
  * the stream it is launched on.  end() waits for those events (host-synchronous),
  * aggregates by kernel name into out[0 .. *n_entries) (at most max_entries names)
  * and switches timing off.  Process-wide, one host thread.  A forward of a few rows that rotates
- * its chunk inside the attention launch counts a "chunk_rope_stage" without a time of its own. */
+ * its chunk inside the attention launch is "attn_fwd_few_rotating_bf16", without a "chunk_rope_stage"
+ * (the rotation pre-pass) before it. */
 typedef struct astro_kernel_time {
   char name[48];     /* kernel name, NUL-terminated */
   int32_t launches;  /* launches seen                */

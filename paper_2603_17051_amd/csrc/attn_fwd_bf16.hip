@@ -828,11 +828,10 @@ hipError_t launch_few(const DevGeom& g, const AttnOperands& op, void* out, float
   p.q_tiles = (op.Nq + 31) / 32;
   const dim3 grid(work_grid_size(p.q_tiles, p.BH)), block(kWaves * 64);
   if (const ChunkSource* from = op.raw) {
-    { ProfileScope staged("chunk_rope_stage", stream); }  // counted like a staging of its own, without a time
     RawChunk c{(const __bf16*)from->q, (const __bf16*)from->k, (__bf16*)op.q_rot, (__bf16*)op.kc_rot,
                from->leave ? (float2*)op.tab_t : nullptr, g.inv_freq_t, g.tab_h, g.tab_w, g.gh, g.gw, g.T, g.n_t, g.n_h, g.n_w,
                op.Nq / g.T, from->q_scale, from->first_frame};
-    ProfileScope prof("attn_fwd_few_bf16", stream);
+    ProfileScope prof("attn_fwd_few_rotating_bf16", stream);
     attn_fwd_few_kernel<D, kWaves, kCausal, RawChunk><<<grid, block, 0, stream>>>(p, c);
   } else {
     p.in_turn = bf16_fwd_rotates(g, op);

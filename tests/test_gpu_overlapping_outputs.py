@@ -49,7 +49,7 @@ def test_backward_outputs_over_memory_the_query_side_reads(D, H, gh, gw, residen
 
 
 @pytest.mark.parametrize("H,gh,gw,resident,apart", [
-    (2, 7, 9, 3, "attn_fwd_few_bf16"),
+    (2, 7, 9, 3, "attn_fwd_few_rotating_bf16"),
     (12, 30, 36, 2, "attn_fwd_merge"),  # 408 workgroups
 ])
 def test_forward_in_place_of_the_chunk_values(H, gh, gw, resident, apart):

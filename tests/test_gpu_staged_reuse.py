@@ -1,6 +1,6 @@
 """ASTRO_FLAG_REUSE_STAGED: a backward that follows a forward of the same chunk through the same
 workspace skips the rotation pre-pass.  The results must be bit-identical to a handle without the
-flag, the pre-pass must really be skipped exactly when the call matches, and anything that moves
+flag, the rotation (a pre-pass, or a forward of few rows that rotates for itself) must really be skipped exactly when the call matches, and anything that moves
 the chunk (an append, a reset) or changes the call (other tensors, another workspace) must stage
 again."""
 import numpy as np
@@ -26,13 +26,15 @@ def _cache(A, w, reuse):
 def _stage_launches(A, fn):
     A.astro_profile_begin()
     res = fn()
-    return res, A.astro_profile_end().get("chunk_rope_stage", (0, 0.0))[0]
+    launched = A.astro_profile_end()
+    return res, sum(launched.get(name, (0, 0.0))[0] for name in ("chunk_rope_stage", "attn_fwd_few_rotating_bf16"))
 
 
-def test_backward_reuses_what_the_forward_staged_only_when_the_call_matches():
+@pytest.mark.parametrize("grid_h,grid_w,rotates", [(5, 7, True), (18, 16, False)])
+def test_backward_reuses_what_the_forward_staged_only_when_the_call_matches(grid_h, grid_w, rotates):
     import torch
     import paper_2603_17051_amd as A
-    w = wl.Workload("reuse", 17, 2, 3, 128, 5, 7, 4, 1, 2, 0, (22, 21, 21))
+    w = wl.Workload("reuse", 17, 2, 3, 128, grid_h, grid_w, 4, 1, 2, 0, (22, 21, 21))
     on, off = _cache(A, w, True), _cache(A, w, False)
     Fc = w.chunk_frames
     q, k, v, do = (dev_bf16(x) for x in wl.chunk_inputs(w, with_dout=True))
@@ -45,6 +47,9 @@ def test_backward_reuses_what_the_forward_staged_only_when_the_call_matches():
         out, lse = A.astro_chunk_attn_fwd(c, qq, k, v, Fc, workspace=ws)
         return (out, lse) + A.astro_chunk_attn_bwd(c, qq, k, v, out, lse, do, Fc, workspace=ws_bwd if ws_bwd is not None else ws)
 
+    A.astro_profile_begin()
+    A.astro_chunk_attn_fwd(off, q, k, v, Fc, workspace=ws_off)
+    assert ("attn_fwd_few_rotating_bf16" in A.astro_profile_end()) == rotates
     ref, n_off = _stage_launches(A, lambda: fwd_bwd(off, ws_off, q))
     got, n_on = _stage_launches(A, lambda: fwd_bwd(on, ws_on, q))
     assert (n_off, n_on) == (2, 1)
