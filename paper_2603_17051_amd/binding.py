@@ -1,5 +1,6 @@
 """Binding of the C ABI in include/astro.h: argument marshalling only, by ctypes; the calls of every layer and step go
 through a CPython module (csrc/binding_native.cpp) when their arguments are plain, complete and on the current stream.
+A module that is missing, or built for another Python or torch, only costs its time: all calls then go by ctypes.
 
 torch is used for device memory and streams; every computation happens in the
 HIP library.  If libastro.so is missing the import of this module fails
@@ -8,7 +9,9 @@ loudly; there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import warnings
 from ctypes import POINTER, byref, c_double, c_float, c_int, c_int32, c_size_t, c_void_p
 
 import torch
@@ -107,16 +110,29 @@ def _load() -> ctypes.CDLL:
     return lib
 
 
+class _NotBuilt:
+    """In the module's place: takes no call."""
+    append = fwd = bwd = loss = staticmethod(lambda *args: None)
+
+
 def _load_native():
-    if not os.path.exists(NATIVE_PATH):
-        raise ImportError(
-            f"{NATIVE_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
-    from . import _binding_native
+    built = None
+    if os.path.exists(NATIVE_PATH):
+        spec = importlib.util.spec_from_file_location(__package__ + "._binding_native", NATIVE_PATH)
+        try:
+            built = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(built)
+        except ImportError:  # linked against another torch
+            built = None
+    if built is None or getattr(built, "built_for_torch", "") != f"{torch.__version__} {torch.version.git_version}":
+        warnings.warn(f"{NATIVE_PATH} is not built for this torch; calls go through ctypes, which takes some microseconds "
+                      "longer (`python -c 'import __graft_entry__ as g; g.build()'`)", RuntimeWarning, stacklevel=2)
+        return _NotBuilt
     functions = (_lib.astro_kvcache_append, _lib.astro_chunk_attn_fwd, _lib.astro_group_attn_fwd, _lib.astro_chunk_attn_bwd,
                  _lib.astro_group_attn_bwd, _lib.astro_chunk_attn_bwd_full, _lib.astro_nft_loss_workspace_bytes,
                  _lib.astro_nft_loss)
-    _binding_native.bind(tuple(ctypes.cast(f, c_void_p).value for f in functions))
-    return _binding_native
+    built.bind(tuple(ctypes.cast(f, c_void_p).value for f in functions))
+    return built
 
 
 _lib = _load()

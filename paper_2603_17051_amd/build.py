@@ -11,7 +11,8 @@ from concurrent.futures import ThreadPoolExecutor
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libastro.so")
-NATIVE_PATH = os.path.join(PKG_DIR, "_binding_native.so")
+# (tagged with the Python it is built for: another one looks for another file)
+NATIVE_PATH = os.path.join(PKG_DIR, "_binding_native" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["astro_api.hip", "rope_scatter.hip", "attn_f32.hip", "attn_fwd_bf16.hip", "attn_bwd_bf16.hip", "profile.hip", "calib.hip", "nft_loss.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-unused-value",
@@ -67,6 +68,7 @@ def build_native() -> str:
     tmp = NATIVE_PATH + ".tmp"
     cmd = [cxx, "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DBUILT_FOR_TORCH="{torch.__version__} {torch.version.git_version}"',
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(rocm, "include"),
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "binding_native.cpp"), "-o", tmp,
            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

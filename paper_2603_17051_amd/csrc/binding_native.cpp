@@ -256,4 +256,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding_native", nullptr, -1, met
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding_native() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__binding_native() {
+  PyObject* const m = PyModule_Create(&module);
+  // the torch whose tensors this file's headers describe: binding.py binds no other's
+  if (m && PyModule_AddStringConstant(m, "built_for_torch", BUILT_FOR_TORCH) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -1,12 +1,17 @@
 """The binding's CPython module: the same results as the ctypes path (which a call with its stream named takes), and the
 calls it does not take, which go there."""
 import ctypes
+import os
+import shutil
+import subprocess
+import sys
+import sysconfig
 
 import pytest
 import torch
 
 import paper_2603_17051_amd as A
-from paper_2603_17051_amd import binding
+from paper_2603_17051_amd import binding, build
 
 GOOD = dict(batch=2, heads=2, head_dim=64, grid_h=4, grid_w=8, capacity_frames=4, sink_frames=1, max_chunk_frames=2,
             rope_pairs=(12, 10, 10))
@@ -92,3 +97,44 @@ def test_loss_gives_what_the_ctypes_path_gives_on_the_current_stream():
         assert torch.equal(r[0], results[0][0]) and torch.equal(r[1], results[0][1])
     with pytest.raises(ValueError):
         A.astro_nft_loss(x[0], x[1].float(), x[2], x[3], adv, mask, 1.0, 0.9, 0.1, loss, grad, ws)
+
+
+ALONE = """
+import sys, warnings
+sys.path.insert(0, {root!r})
+import torch
+if {other!r}:
+    torch.version.git_version = "another"
+with warnings.catch_warnings(record=True) as told:
+    warnings.simplefilter("always")
+    import paper_2603_17051_amd as A
+assert A.__file__.startswith({root!r})
+assert any("ctypes" in str(w.message) for w in told), told
+c = A.astro_kvcache_create(2, 2, 64, 4, 8, 4, 1, 2, (12, 10, 10), host_only=True)
+A.astro_kvcache_append(c, n_frames=2)
+assert A.astro_kvcache_tables(c)[2] == [2, 2]
+x = torch.zeros(2, 32, 2, 64, dtype=torch.bfloat16)
+try:
+    A.astro_chunk_attn_fwd(c, x, x, x, 1, torch.zeros(1), torch.zeros(1), torch.zeros(1))
+except ValueError as e:
+    assert "device tensor" in str(e)
+else:
+    raise SystemExit("a host tensor was taken")
+"""
+
+
+@pytest.mark.parametrize("other", [False, True])
+def test_a_module_that_is_missing_or_of_another_torch_leaves_all_calls_to_ctypes(other, tmp_path):
+    package = os.path.dirname(binding.__file__)
+    copy = tmp_path / "paper_2603_17051_amd"
+    copy.mkdir()
+    for name in os.listdir(package):
+        if name.endswith(".py") or name == "libastro.so" or (other and name == os.path.basename(build.NATIVE_PATH)):
+            shutil.copy(os.path.join(package, name), copy)
+    r = subprocess.run([sys.executable, "-c", ALONE.format(root=str(tmp_path), other=other)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+
+def test_the_module_is_the_one_of_this_python_and_torch():
+    assert binding._native.__file__ == build.NATIVE_PATH and build.NATIVE_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert binding._native.built_for_torch.startswith(torch.__version__)
