@@ -273,6 +273,12 @@ def _check_chunk_tensor(cache: KVCache, t: torch.Tensor, n_frames: int, name: st
         raise ValueError(f"{name}: must be a device tensor")
 
 
+def _check_lse(lse: torch.Tensor, rows: int) -> None:
+    """of the calls without candidates, which also take a longer buffer"""
+    if lse.dtype != torch.float32 or not lse.is_contiguous() or lse.numel() < rows:
+        raise ValueError("lse: expected contiguous fp32 [B, H, Nq]")
+
+
 def astro_kvcache_append(cache: KVCache, k=None, v=None, n_frames: int = 1, stream=None) -> None:
     host_only = bool(cache.desc.flags & ASTRO_FLAG_HOST_ONLY)
     if stream is None and not host_only:
@@ -381,6 +387,7 @@ def astro_chunk_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, out
     if lse is None:
         lse = torch.empty((d.batch, d.heads, q.shape[1]), dtype=torch.float32, device=q.device)
     _check_chunk_tensor(cache, out, n_frames, "out")
+    _check_lse(lse, d.batch * d.heads * q.shape[1])
     if workspace is None:
         workspace = cache.workspace(astro_chunk_attn_workspace_bytes(cache, n_frames)[0], q.device)
     _check(_lib.astro_chunk_attn_fwd(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), n_frames, _ptr(out),
@@ -406,8 +413,7 @@ def astro_chunk_attn_bwd(cache: KVCache, q, k_chunk, v_chunk, out, lse, dout, n_
     dv_chunk = mk() if dv_chunk is None else dv_chunk
     for name, t in (("dq", dq), ("dk_chunk", dk_chunk), ("dv_chunk", dv_chunk)):
         _check_chunk_tensor(cache, t, n_frames, name, torch.float32)
-    if lse.dtype != torch.float32 or not lse.is_contiguous():
-        raise ValueError("lse: expected contiguous fp32")
+    _check_lse(lse, cache.desc.batch * cache.desc.heads * q.shape[1])
     if workspace is None:
         workspace = cache.workspace(astro_chunk_attn_workspace_bytes(cache, n_frames)[1], q.device)
     _check(_lib.astro_chunk_attn_bwd(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), _ptr(out), _ptr(lse),
@@ -549,8 +555,7 @@ def astro_chunk_attn_bwd_full(cache: KVCache, q, k_chunk, v_chunk, out, lse, dou
     for name, t in (("dk_cache", dk_cache), ("dv_cache", dv_cache)):
         if tuple(t.shape) != ring_shape or t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda:
             raise ValueError(f"{name}: expected contiguous fp32 device tensor of shape {ring_shape}")
-    if lse.dtype != torch.float32 or not lse.is_contiguous():
-        raise ValueError("lse: expected contiguous fp32")
+    _check_lse(lse, cache.desc.batch * cache.desc.heads * q.shape[1])
     if workspace is None:
         workspace = cache.workspace(astro_chunk_attn_bwd_full_workspace_bytes(cache, n_frames), q.device)
     _check(_lib.astro_chunk_attn_bwd_full(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), _ptr(out), _ptr(lse),

@@ -69,15 +69,16 @@ struct Reader {
     }
     return &THPVariable_Unpack(o);
   }
-  // any plain tensor's address (as data_ptr() gives it)
-  void* address(PyObject* o) {
+  void* of_type(PyObject* o, at::ScalarType type, int64_t numel) {
     const at::Tensor* t = plain(o);
-    return t ? t->data_ptr() : nullptr;
-  }
-  void* of_type(PyObject* o, at::ScalarType type, int64_t numel, bool contiguous) {
-    const at::Tensor* t = plain(o);
-    ok = ok && t->scalar_type() == type && t->numel() == numel && (!contiguous || t->is_contiguous());
+    ok = ok && t->scalar_type() == type && t->numel() == numel;
     return ok ? t->data_ptr() : nullptr;
+  }
+  // the log-sum-exps of `rows` queries; a call without candidates also takes a longer buffer
+  float* lse(PyObject* o, int64_t rows, bool longer) {
+    const at::Tensor* t = plain(o);
+    ok = ok && t->scalar_type() == at::kFloat && t->is_contiguous() && (t->numel() == rows || (longer && t->numel() > rows));
+    return ok ? static_cast<float*>(t->data_ptr()) : nullptr;
   }
   // a contiguous device tensor [rows, tokens, heads, head dim]
   void* rows(PyObject* o, at::ScalarType type, int64_t n_batch, int64_t n_rows) {
@@ -147,16 +148,16 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     r.dims(a[1]);
     const int64_t frames = r.integer(a[5], INT32_MAX), group = r.integer(a[6], INT32_MAX);
     const int64_t batch = r.batch * (group ? group : 1), rows = frames * r.tokens;
-    void *t[4], *lse;
+    void* t[4];
     PyObject* const from[4] = {a[2], a[3], a[4], a[7]};
     for (int i = 0; i < 4; ++i) t[i] = r.rows(from[i], r.dtype, batch, rows);
-    lse = group ? r.of_type(a[8], at::kFloat, batch * r.heads * rows, true) : r.address(a[8]);
+    float* const lse = r.lse(a[8], batch * r.heads * rows, !group);
     size_t bytes = 0;
     void* const ws = r.workspace(a[9], &bytes);
     if (!r.ok) return nullptr;
     return run([&](void* s) {
-      return group ? lib.group_fwd(cache, t[0], t[1], t[2], (int32_t)frames, (int32_t)group, t[3], (float*)lse, ws, bytes, s)
-                   : lib.chunk_fwd(cache, t[0], t[1], t[2], (int32_t)frames, t[3], (float*)lse, ws, bytes, s);
+      return group ? lib.group_fwd(cache, t[0], t[1], t[2], (int32_t)frames, (int32_t)group, t[3], lse, ws, bytes, s)
+                   : lib.chunk_fwd(cache, t[0], t[1], t[2], (int32_t)frames, t[3], lse, ws, bytes, s);
     });
   });
 }
@@ -179,11 +180,7 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
       const int64_t capacity = r.integer(a[16], INT32_MAX);
       for (int i = 0; i < 2; ++i) grad[3 + i] = r.rows(a[14 + i], at::kFloat, r.batch, capacity * r.tokens);
     }
-    float* lse = nullptr;
-    if (const at::Tensor* l = r.plain(a[6])) {
-      r.ok = l->scalar_type() == at::kFloat && l->is_contiguous() && (!group || l->numel() == batch * r.heads * rows);
-      lse = (float*)l->data_ptr();
-    }
+    float* const lse = r.lse(a[6], batch * r.heads * rows, !group);
     size_t bytes = 0;
     void* const ws = r.workspace(a[13], &bytes);
     if (!r.ok) return nullptr;
@@ -213,13 +210,13 @@ PyObject* loss(PyObject*, PyObject* const* a, Py_ssize_t n) {
       if (!y || y->sizes() != x->sizes() || y->scalar_type() != type || !y->is_contiguous()) return nullptr;
       t[i] = y->data_ptr();
     }
-    void* const advantage = r.of_type(a[4], at::kFloat, samples, false);
-    void* const mask = r.of_type(a[5], at::kInt, samples, false);
+    void* const advantage = r.of_type(a[4], at::kFloat, samples);
+    void* const mask = r.of_type(a[5], at::kInt, samples);
     const float a_max = r.number(a[6]), beta = r.number(a[7]), lambda = r.number(a[8]);
     const at::Tensor* const l = r.plain(a[9]);
     if (!l || l->scalar_type() != at::kFloat || l->numel() < 3) return nullptr;
     void* const to = l->data_ptr();
-    void* const grad = r.of_type(a[10], at::kFloat, numel, false);
+    void* const grad = r.of_type(a[10], at::kFloat, numel);
     size_t bytes = 0, need = 0;
     void* const ws = r.workspace(a[11], &bytes);
     if (!r.ok || lib.loss_workspace_bytes((int32_t)samples, numel / samples, &need) != ASTRO_OK) return nullptr;

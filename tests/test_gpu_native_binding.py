@@ -1,6 +1,7 @@
 """The binding's CPython module: the same results as the ctypes path (which a call with its stream named takes), and the
 calls it does not take, which go there."""
 import ctypes
+import math
 import os
 import shutil
 import subprocess
@@ -66,6 +67,13 @@ def test_attention_calls_give_what_the_ctypes_path_gives(group):
             a.update(change)
             with pytest.raises(ValueError):
                 A.astro_group_attn_fwd(cache, a["q"], k, v, 2, group, a["out"], a["lse"], ws, stream=stream)
+        if group == 1:
+            for call in (lambda x: A.astro_chunk_attn_fwd(cache, q, k, v, 2, out, x, ws, stream=stream),
+                         lambda x: A.astro_chunk_attn_bwd(cache, q, k, v, out, x, do, 2, *g, ws, stream=stream),
+                         lambda x: A.astro_chunk_attn_bwd_full(cache, q, k, v, out, x, do, 2, *g, *ring, ws, stream=stream)):
+                for x in (lse.flatten()[1:], lse.half(), lse.transpose(1, 2)):
+                    with pytest.raises(ValueError):
+                        call(x)
         with pytest.raises(A.AstroError) as e:
             A.astro_group_attn_fwd(cache, q, k, v, 2, group, out, lse, ws[:256], stream=stream)
         assert e.value.code == binding.ASTRO_ERR_WORKSPACE
@@ -138,3 +146,37 @@ def test_a_module_that_is_missing_or_of_another_torch_leaves_all_calls_to_ctypes
 def test_the_module_is_the_one_of_this_python_and_torch():
     assert binding._native.__file__ == build.NATIVE_PATH and build.NATIVE_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
     assert binding._native.built_for_torch.startswith(torch.__version__)
+
+
+class OnDevice:
+    """What the binding's checks see of a contiguous device tensor."""
+    is_cuda = True
+
+    def __init__(self, dtype, *shape, dense=True):
+        self.dtype, self.shape, self.is_contiguous, self.device = dtype, shape, lambda: dense, "cuda:0"
+
+    def numel(self):
+        return math.prod(self.shape)
+
+    def element_size(self):
+        return 2 if self.dtype is torch.bfloat16 else 4
+
+    def data_ptr(self):
+        return 1 << 20
+
+
+@pytest.mark.parametrize("lse,fits", [
+    (OnDevice(torch.float32, 2, 2, 32), True), (OnDevice(torch.float32, 200), True), (OnDevice(torch.float32, 127), False),
+    (OnDevice(torch.bfloat16, 2, 2, 32), False), (OnDevice(torch.float32, 2, 2, 32, dense=False), False)])
+def test_log_sum_exps_of_the_calls_without_candidates_have_room(lse, fits, monkeypatch):
+    """(a host-only handle answers the C ABI's calls with a state error: nothing is launched)"""
+    monkeypatch.setattr(binding, "_stream", lambda stream: ctypes.c_void_p(None))
+    cache = A.astro_kvcache_create(host_only=True, **GOOD)
+    x, ws = OnDevice(torch.bfloat16, 2, 32, 2, 64), OnDevice(torch.float32, 1 << 16)
+    g, ring = [OnDevice(torch.float32, 2, 32, 2, 64)] * 3, [OnDevice(torch.float32, 2, 128, 2, 64)] * 2
+    for call in (lambda: A.astro_chunk_attn_fwd(cache, x, x, x, 1, x, lse, ws),
+                 lambda: A.astro_chunk_attn_bwd(cache, x, x, x, x, lse, x, 1, *g, ws),
+                 lambda: A.astro_chunk_attn_bwd_full(cache, x, x, x, x, lse, x, 1, *g, *ring, ws)):
+        with pytest.raises(A.AstroError if fits else ValueError):
+            call()
+    cache.close()
