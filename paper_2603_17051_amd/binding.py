@@ -474,13 +474,15 @@ def astro_nft_loss(v_theta, v_old, v_ref, target, advantage, kl_mask, a_max: flo
             raise ValueError(f"{name}: must match v_theta in shape and dtype and be contiguous")
     if v_theta.dtype not in (torch.bfloat16, torch.float32) or not v_theta.is_contiguous():
         raise ValueError("v_theta: expected contiguous bf16 or fp32")
-    if advantage.dtype != torch.float32 or advantage.numel() != n or kl_mask.dtype != torch.int32 or kl_mask.numel() != n:
-        raise ValueError("advantage: fp32 [n]; kl_mask: int32 [n]")
+    if (advantage.dtype != torch.float32 or advantage.numel() != n or kl_mask.dtype != torch.int32 or kl_mask.numel() != n
+            or not advantage.is_contiguous() or not kl_mask.is_contiguous()):
+        raise ValueError("advantage: contiguous fp32 [n]; kl_mask: contiguous int32 [n]")
     dev = v_theta.device
     loss = torch.empty(3, dtype=torch.float32, device=dev) if loss is None else loss
     grad = torch.empty(v_theta.shape, dtype=torch.float32, device=dev) if grad is None else grad
-    if grad.dtype != torch.float32 or grad.numel() != v_theta.numel() or loss.dtype != torch.float32 or loss.numel() < 3:
-        raise ValueError("grad: fp32 like v_theta; loss: fp32 [3]")
+    if (grad.dtype != torch.float32 or grad.numel() != v_theta.numel() or loss.dtype != torch.float32 or loss.numel() < 3
+            or not grad.is_contiguous() or not loss.is_contiguous()):
+        raise ValueError("grad: contiguous fp32 like v_theta; loss: contiguous fp32 [3]")
     need = astro_nft_loss_workspace_bytes(n, elems)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
@@ -509,10 +511,12 @@ def astro_nft_loss_static(v_theta, v_old, v_ref, target, advantage, kl_mask, a_m
             raise ValueError(f"{name}: must match v_theta in shape and dtype and be contiguous")
     if v_theta.dtype not in (torch.bfloat16, torch.float32) or not v_theta.is_contiguous():
         raise ValueError("v_theta: expected contiguous bf16 or fp32")
-    if advantage.dtype != torch.float32 or advantage.numel() != n or kl_mask.dtype != torch.int32 or kl_mask.numel() != n:
-        raise ValueError("advantage: fp32 [n]; kl_mask: int32 [n]")
-    if grad.dtype != torch.float32 or grad.numel() != v_theta.numel() or loss.dtype != torch.float32 or loss.numel() < 3:
-        raise ValueError("grad: fp32 like v_theta; loss: fp32 [3]")
+    if (advantage.dtype != torch.float32 or advantage.numel() != n or kl_mask.dtype != torch.int32 or kl_mask.numel() != n
+            or not advantage.is_contiguous() or not kl_mask.is_contiguous()):
+        raise ValueError("advantage: contiguous fp32 [n]; kl_mask: contiguous int32 [n]")
+    if (grad.dtype != torch.float32 or grad.numel() != v_theta.numel() or loss.dtype != torch.float32 or loss.numel() < 3
+            or not grad.is_contiguous() or not loss.is_contiguous()):
+        raise ValueError("grad: contiguous fp32 like v_theta; loss: contiguous fp32 [3]")
     dtype = ASTRO_BF16 if v_theta.dtype == torch.bfloat16 else ASTRO_F32
     _check(_lib.astro_nft_loss_static(_ptr(v_theta), _ptr(v_old), _ptr(v_ref), _ptr(target), _ptr(advantage), _ptr(kl_mask),
                                       n, elems, dtype, float(a_max), float(beta), float(lambda_kl), _ptr(loss), _ptr(grad),

@@ -71,7 +71,7 @@ struct Reader {
   }
   void* of_type(PyObject* o, at::ScalarType type, int64_t numel) {
     const at::Tensor* t = plain(o);
-    ok = ok && t->scalar_type() == type && t->numel() == numel;
+    ok = ok && t->scalar_type() == type && t->numel() == numel && t->is_contiguous();
     return ok ? t->data_ptr() : nullptr;
   }
   // the log-sum-exps of `rows` queries; a call without candidates also takes a longer buffer
@@ -214,7 +214,7 @@ PyObject* loss(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* const mask = r.of_type(a[5], at::kInt, samples);
     const float a_max = r.number(a[6]), beta = r.number(a[7]), lambda = r.number(a[8]);
     const at::Tensor* const l = r.plain(a[9]);
-    if (!l || l->scalar_type() != at::kFloat || l->numel() < 3) return nullptr;
+    if (!l || l->scalar_type() != at::kFloat || l->numel() < 3 || !l->is_contiguous()) return nullptr;
     void* const to = l->data_ptr();
     void* const grad = r.of_type(a[10], at::kFloat, numel);
     size_t bytes = 0, need = 0;

@@ -103,8 +103,12 @@ def test_loss_gives_what_the_ctypes_path_gives_on_the_current_stream():
         results.append((loss, grad))
     for r in results[1:]:
         assert torch.equal(r[0], results[0][0]) and torch.equal(r[1], results[0][1])
-    with pytest.raises(ValueError):
-        A.astro_nft_loss(x[0], x[1].float(), x[2], x[3], adv, mask, 1.0, 0.9, 0.1, loss, grad, ws)
+    for change in (dict(old=x[1].float()), dict(adv=adv[:1].expand(3)), dict(mask=mask.repeat(2)[::2]), dict(loss=loss.repeat(2)[::2]),
+                   dict(grad=grad.transpose(0, 1))):
+        a = dict(old=x[1], adv=adv, mask=mask, loss=loss, grad=grad)
+        a.update(change)
+        with pytest.raises(ValueError):
+            A.astro_nft_loss(x[0], a["old"], x[2], x[3], a["adv"], a["mask"], 1.0, 0.9, 0.1, a["loss"], a["grad"], ws)
 
 
 ALONE = """
@@ -180,3 +184,25 @@ def test_log_sum_exps_of_the_calls_without_candidates_have_room(lse, fits, monke
         with pytest.raises(A.AstroError if fits else ValueError):
             call()
     cache.close()
+
+
+def test_the_loss_takes_its_small_arguments_and_outputs_dense_only(monkeypatch):
+    """The kernels read and write them one after another from their addresses, whatever their strides."""
+    took = []
+    for name in ("astro_nft_loss", "astro_nft_loss_static"):
+        monkeypatch.setattr(binding._lib, name, lambda *args: took.append(args) or 0)
+    monkeypatch.setattr(binding, "_stream", lambda stream: ctypes.c_void_p(None))
+    x, ws = OnDevice(torch.bfloat16, 3, 8), OnDevice(torch.float32, 1 << 16)
+    for strided in (None, 0, 1, 2, 3):
+        adv, mask, loss, grad = (OnDevice(t, *shape, dense=i != strided) for i, (t, shape) in enumerate(
+            [(torch.float32, (3,)), (torch.int32, (3,)), (torch.float32, (3,)), (torch.float32, (3, 8))]))
+        for call in (lambda: A.astro_nft_loss(x, x, x, x, adv, mask, 1.0, 1.0, 0.1, loss, grad, ws),
+                     lambda: A.astro_nft_loss_static(x, x, x, x, adv, mask, 1.0, 1.0, 0.1, loss, grad)):
+            del took[:]
+            if strided is None:
+                call()
+                assert len(took) == 1
+            else:
+                with pytest.raises(ValueError):
+                    call()
+                assert not took
