@@ -273,6 +273,13 @@ def _check_chunk_tensor(cache: KVCache, t: torch.Tensor, n_frames: int, name: st
         raise ValueError(f"{name}: must be a device tensor")
 
 
+def _check_reachable(**tensors) -> None:
+    """Device memory, or pinned host memory: kernels read and write these from their addresses."""
+    for name, t in tensors.items():
+        if not (t.is_cuda or t.is_pinned()):
+            raise ValueError(f"{name}: must be a device tensor")
+
+
 def _check_lse(lse: torch.Tensor, rows: int) -> None:
     """of the calls without candidates, which also take a longer buffer"""
     if lse.dtype != torch.float32 or not lse.is_contiguous() or lse.numel() < rows:
@@ -329,6 +336,7 @@ def astro_group_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, gro
         raise ValueError("lse: expected contiguous fp32 [B*group, H, Nq]")
     if workspace is None:
         workspace = cache.workspace(astro_group_attn_workspace_bytes(cache, n_frames, group)[0], q.device)
+    _check_reachable(lse=lse, workspace=workspace)
     _check(_lib.astro_group_attn_fwd(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), n_frames, group, _ptr(out),
                                      _ptr(lse), _ptr(workspace), workspace.numel() * workspace.element_size(),
                                      _stream(stream)), "astro_group_attn_fwd")
@@ -357,6 +365,7 @@ def astro_group_attn_bwd(cache: KVCache, q, k_chunk, v_chunk, out, lse, dout, n_
         raise ValueError("lse: expected contiguous fp32 [B*group, H, Nq]")
     if workspace is None:
         workspace = cache.workspace(astro_group_attn_workspace_bytes(cache, n_frames, group)[1], q.device)
+    _check_reachable(lse=lse, workspace=workspace)
     _check(_lib.astro_group_attn_bwd(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), _ptr(out), _ptr(lse),
                                      _ptr(dout), n_frames, group, _ptr(dq), _ptr(dk_chunk), _ptr(dv_chunk),
                                      _ptr(workspace), workspace.numel() * workspace.element_size(),
@@ -390,6 +399,7 @@ def astro_chunk_attn_fwd(cache: KVCache, q, k_chunk, v_chunk, n_frames: int, out
     _check_lse(lse, d.batch * d.heads * q.shape[1])
     if workspace is None:
         workspace = cache.workspace(astro_chunk_attn_workspace_bytes(cache, n_frames)[0], q.device)
+    _check_reachable(lse=lse, workspace=workspace)
     _check(_lib.astro_chunk_attn_fwd(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), n_frames, _ptr(out),
                                      _ptr(lse), _ptr(workspace), workspace.numel() * workspace.element_size(),
                                      _stream(stream)), "astro_chunk_attn_fwd")
@@ -416,6 +426,7 @@ def astro_chunk_attn_bwd(cache: KVCache, q, k_chunk, v_chunk, out, lse, dout, n_
     _check_lse(lse, cache.desc.batch * cache.desc.heads * q.shape[1])
     if workspace is None:
         workspace = cache.workspace(astro_chunk_attn_workspace_bytes(cache, n_frames)[1], q.device)
+    _check_reachable(lse=lse, workspace=workspace)
     _check(_lib.astro_chunk_attn_bwd(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), _ptr(out), _ptr(lse),
                                      _ptr(dout), n_frames, _ptr(dq), _ptr(dk_chunk), _ptr(dv_chunk),
                                      _ptr(workspace), workspace.numel() * workspace.element_size(),
@@ -439,6 +450,7 @@ def astro_calib_mfma(operands: torch.Tensor, workgroups: int, iters: int, sink: 
     """Launch the MFMA-only calibration kernel (timed via astro_profile_* as "calib_mfma_bf16")."""
     if operands.numel() * operands.element_size() < 8 * 256 * 16 or sink.numel() < workgroups * 256:
         raise ValueError("operand or sink buffer too small")
+    _check_reachable(operands=operands, sink=sink)
     _check(_lib.astro_calib_mfma(_ptr(operands), int(workgroups), int(iters), _ptr(sink), _stream(stream)),
            "astro_calib_mfma")
 
@@ -448,6 +460,7 @@ def astro_calib_copy(src: torch.Tensor, dst: torch.Tensor, stream=None) -> None:
     nbytes = src.numel() * src.element_size()
     if dst.numel() * dst.element_size() < nbytes:
         raise ValueError("dst smaller than src")
+    _check_reachable(src=src, dst=dst)
     _check(_lib.astro_calib_copy(_ptr(src), _ptr(dst), c_size_t(nbytes), _stream(stream)), "astro_calib_copy")
 
 
@@ -487,6 +500,8 @@ def astro_nft_loss(v_theta, v_old, v_ref, target, advantage, kl_mask, a_max: flo
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     dtype = ASTRO_BF16 if v_theta.dtype == torch.bfloat16 else ASTRO_F32
+    _check_reachable(v_theta=v_theta, v_old=v_old, v_ref=v_ref, target=target, advantage=advantage, kl_mask=kl_mask, loss=loss, grad=grad,
+                     workspace=workspace)
     _check(_lib.astro_nft_loss(_ptr(v_theta), _ptr(v_old), _ptr(v_ref), _ptr(target), _ptr(advantage), _ptr(kl_mask),
                                n, elems, dtype, float(a_max), float(beta), float(lambda_kl), _ptr(loss), _ptr(grad),
                                _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)),
@@ -518,6 +533,7 @@ def astro_nft_loss_static(v_theta, v_old, v_ref, target, advantage, kl_mask, a_m
             or not grad.is_contiguous() or not loss.is_contiguous()):
         raise ValueError("grad: contiguous fp32 like v_theta; loss: contiguous fp32 [3]")
     dtype = ASTRO_BF16 if v_theta.dtype == torch.bfloat16 else ASTRO_F32
+    _check_reachable(v_theta=v_theta, v_old=v_old, v_ref=v_ref, target=target, advantage=advantage, kl_mask=kl_mask, loss=loss, grad=grad)
     _check(_lib.astro_nft_loss_static(_ptr(v_theta), _ptr(v_old), _ptr(v_ref), _ptr(target), _ptr(advantage), _ptr(kl_mask),
                                       n, elems, dtype, float(a_max), float(beta), float(lambda_kl), _ptr(loss), _ptr(grad),
                                       _stream(stream)), "astro_nft_loss_static")
@@ -562,6 +578,7 @@ def astro_chunk_attn_bwd_full(cache: KVCache, q, k_chunk, v_chunk, out, lse, dou
     _check_lse(lse, cache.desc.batch * cache.desc.heads * q.shape[1])
     if workspace is None:
         workspace = cache.workspace(astro_chunk_attn_bwd_full_workspace_bytes(cache, n_frames), q.device)
+    _check_reachable(lse=lse, workspace=workspace)
     _check(_lib.astro_chunk_attn_bwd_full(cache.handle, _ptr(q), _ptr(k_chunk), _ptr(v_chunk), _ptr(out), _ptr(lse),
                                           _ptr(dout), n_frames, _ptr(dq), _ptr(dk_chunk), _ptr(dv_chunk),
                                           _ptr(dk_cache), _ptr(dv_cache), _ptr(workspace),

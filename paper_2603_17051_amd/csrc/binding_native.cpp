@@ -62,12 +62,10 @@ struct Reader {
     for (int i = 0; i < 4; ++i) *to[i] = integer(PyTuple_GET_ITEM(o, i), INT32_MAX);
     dtype = PyTuple_GET_ITEM(o, 4) == Py_True ? at::kBFloat16 : at::kFloat;
   }
+  // a plain tensor in device memory
   const at::Tensor* plain(PyObject* o) {
-    if (!ok || !THPVariable_CheckExact(o)) {
-      ok = false;
-      return nullptr;
-    }
-    return &THPVariable_Unpack(o);
+    ok = ok && THPVariable_CheckExact(o) && THPVariable_Unpack(o).is_cuda();
+    return ok ? &THPVariable_Unpack(o) : nullptr;
   }
   void* of_type(PyObject* o, at::ScalarType type, int64_t numel) {
     const at::Tensor* t = plain(o);
@@ -80,12 +78,12 @@ struct Reader {
     ok = ok && t->scalar_type() == at::kFloat && t->is_contiguous() && (t->numel() == rows || (longer && t->numel() > rows));
     return ok ? static_cast<float*>(t->data_ptr()) : nullptr;
   }
-  // a contiguous device tensor [rows, tokens, heads, head dim]
+  // a contiguous tensor [rows, tokens, heads, head dim]
   void* rows(PyObject* o, at::ScalarType type, int64_t n_batch, int64_t n_rows) {
     const at::Tensor* t = plain(o);
     if (!t) return nullptr;
     const at::IntArrayRef s = t->sizes();
-    ok = t->is_cuda() && t->scalar_type() == type && s.size() == 4 && s[0] == n_batch && s[1] == n_rows && s[2] == heads &&
+    ok = t->scalar_type() == type && s.size() == 4 && s[0] == n_batch && s[1] == n_rows && s[2] == heads &&
          s[3] == head_dim && t->is_contiguous();
     return ok ? t->data_ptr() : nullptr;
   }

@@ -206,3 +206,37 @@ def test_the_loss_takes_its_small_arguments_and_outputs_dense_only(monkeypatch):
                 with pytest.raises(ValueError):
                     call()
                 assert not took
+
+
+def test_memory_that_kernels_cannot_reach_is_refused(monkeypatch):
+    """Log-sum-exps, workspaces and everything of the loss, whose kernels would have been given host addresses."""
+    took = []
+    for name in ("astro_nft_loss", "astro_nft_loss_static"):
+        monkeypatch.setattr(binding._lib, name, lambda *args: took.append(args) or 0)
+    monkeypatch.setattr(binding, "_stream", lambda stream: ctypes.c_void_p(None))
+    cache = A.astro_kvcache_create(host_only=True, **GOOD)
+    x, ws, lse = OnDevice(torch.bfloat16, 2, 32, 2, 64), OnDevice(torch.float32, 1 << 16), OnDevice(torch.float32, 2, 2, 32)
+    g, ring = [OnDevice(torch.float32, 2, 32, 2, 64)] * 3, [OnDevice(torch.float32, 2, 128, 2, 64)] * 2
+    for l, w in [(torch.zeros(2, 2, 32), ws), (lse, torch.zeros(1 << 16))]:
+        for call in (lambda: A.astro_chunk_attn_fwd(cache, x, x, x, 1, x, l, w),
+                     lambda: A.astro_group_attn_fwd(cache, x, x, x, 1, 1, x, l, w),
+                     lambda: A.astro_chunk_attn_bwd(cache, x, x, x, x, l, x, 1, *g, w),
+                     lambda: A.astro_group_attn_bwd(cache, x, x, x, x, l, x, 1, 1, *g, w),
+                     lambda: A.astro_chunk_attn_bwd_full(cache, x, x, x, x, l, x, 1, *g, *ring, w)):
+            with pytest.raises(ValueError, match="device tensor"):
+                call()
+    cache.close()
+    elems, n = OnDevice(torch.bfloat16, 3, 8), OnDevice(torch.float32, 3)
+    good = [elems] * 4 + [n, OnDevice(torch.int32, 3), n, OnDevice(torch.float32, 3, 8), ws]
+    for i, t in enumerate(good):
+        a = list(good)
+        a[i] = torch.zeros(t.shape, dtype=t.dtype)
+        for call, args in ((A.astro_nft_loss, a), (A.astro_nft_loss_static, a[:8])):
+            if i < len(args):
+                with pytest.raises(ValueError, match="device tensor"):
+                    call(*args[:6], 1.0, 1.0, 0.1, *args[6:])
+    assert not took
+    with pytest.raises(ValueError, match="device tensor"):
+        A.astro_calib_copy(torch.zeros(4), torch.zeros(4))
+    with pytest.raises(ValueError, match="device tensor"):
+        A.astro_calib_mfma(torch.zeros(8 * 256 * 4), 1, 1, torch.zeros(256))
