@@ -36,9 +36,28 @@ def test_calls_it_does_not_take_are_left_alone():
     cache.close()
 
 
+class Answers:
+    """The module's functions, and what each of their calls answered."""
+
+    def __init__(self):
+        self.module, self.got = binding._native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.got.append((name, len(args), getattr(self.module, name)(*args)))
+            return self.got[-1][2]
+        return call
+
+
+@pytest.fixture
+def answers(monkeypatch):
+    monkeypatch.setattr(binding, "_native", Answers())
+    return binding._native.got
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("group", [1, 3])
-def test_attention_calls_give_what_the_ctypes_path_gives(group):
+def test_attention_calls_give_what_the_ctypes_path_gives(group, answers):
     gen = torch.Generator("cuda:0").manual_seed(3)
     draw = lambda b, n: torch.randn((b, n * 32, 2, 64), generator=gen, device="cuda:0").bfloat16()
     k0, v0 = draw(2, 2), draw(2, 2)
@@ -60,6 +79,9 @@ def test_attention_calls_give_what_the_ctypes_path_gives(group):
         else:
             got = A.astro_group_attn_fwd(cache, q, k, v, 2, group, out, lse, ws, stream=stream)
             got += A.astro_group_attn_bwd(cache, q, k, v, out, lse, do, 2, group, *g, ws, stream=stream)
+        # the module took every one of these calls, or (stream named) was not asked
+        took = [("append", 5, 0), ("fwd", 10, 0), ("bwd", 14, 0)] + ([("bwd", 17, 0)] if group == 1 else [])
+        assert answers == (took if stream is None else [])
         results.append([x.clone() for x in got] + [cache.k_storage.clone()])
         # refused on both ways
         for change in (dict(q=q.float()), dict(q=q[:1]), dict(q=q.transpose(0, 1)), dict(q=q.cpu()), dict(lse=lse[:1] if group > 1 else None, out=out[:1])):
@@ -80,15 +102,18 @@ def test_attention_calls_give_what_the_ctypes_path_gives(group):
         # a subclass of Tensor still goes through
         A.astro_group_attn_fwd(cache, q.as_subclass(type("Sub", (torch.Tensor,), {})), k, v, 2, group, out, lse, ws, stream=stream)
         assert torch.equal(out, results[-1][0])
+        # what both refuse, an error of the library and a subclass
+        assert [a for *_, a in answers[len(took):]] == ([None] * (14 if group == 1 else 5) + [binding.ASTRO_ERR_WORKSPACE, None] if stream is None else [])
         cache.close()
         with pytest.raises(A.AstroError):
             A.astro_kvcache_append(cache, k0, v0, 2, stream=stream)
+        del answers[:]
     for a, b in zip(*results):
         assert torch.equal(a, b)
 
 
 @pytest.mark.gpu
-def test_loss_gives_what_the_ctypes_path_gives_on_the_current_stream():
+def test_loss_gives_what_the_ctypes_path_gives_on_the_current_stream(answers):
     gen = torch.Generator("cuda:0").manual_seed(5)
     x = [torch.randn((3, 5, 104), generator=gen, device="cuda:0").bfloat16() for _ in range(4)]
     adv, mask = torch.randn(3, generator=gen, device="cuda:0"), torch.tensor([0, 1, 1], dtype=torch.int32, device="cuda:0")
@@ -101,6 +126,7 @@ def test_loss_gives_what_the_ctypes_path_gives_on_the_current_stream():
             A.astro_nft_loss(*x, adv, mask, a_max, 0.9, 0.1, loss, grad, ws, stream=stream)
         side.synchronize()
         results.append((loss, grad))
+    assert answers == [("loss", 12, 0), ("loss", 12, None)]  # the call with an int is not taken
     for r in results[1:]:
         assert torch.equal(r[0], results[0][0]) and torch.equal(r[1], results[0][1])
     for change in (dict(old=x[1].float()), dict(adv=adv[:1].expand(3)), dict(mask=mask.repeat(2)[::2]), dict(loss=loss.repeat(2)[::2]),

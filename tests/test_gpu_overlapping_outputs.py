@@ -70,6 +70,33 @@ def test_forward_in_place_of_the_chunk_values(H, gh, gw, resident, apart):
     ls.close()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("layout", ["apart", "out over q", "out over k", "lse in q", "lse in k"])
+def test_few_rows_forward_with_outputs_over_its_queries_and_keys(D, layout):
+    """A launch that rotates for itself reads both to its end, by every workgroup of a pair: such calls go behind
+    the pre-pass, which has read them before the first output is written."""
+    import torch
+    Fc = 4
+    w = wl.Workload("overlap_chunk", 57, 1, 2, D, 7, 9, 4, 0, Fc, 3, wl.default_rope_pairs(D))
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[9])
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), 3)
+    q, k, v = wl.chunk_inputs(w)
+    dq, dk, dv = (ls.dev(x) for x in (q, k, v))
+    into = dq if layout.endswith("q") else dk
+    out = into if layout.startswith("out") else torch.empty_like(dq)
+    lse = torch.empty((1, 2, w.n_q), device="cuda:0")
+    if layout.startswith("lse"):  # the bytes of rows in the middle
+        lse = into.view(-1)[into.numel() // 2:into.numel() // 2 + 2 * lse.numel()].view(torch.float32).view(lse.shape)
+    ls.A.astro_profile_begin()
+    ls.A.astro_chunk_attn_fwd(ls.cache, dq, dk, dv, Fc, out, lse)
+    launched = ls.A.astro_profile_end()
+    assert set(launched) == ({"attn_fwd_few_rotating_bf16"} if layout == "apart" else {"chunk_rope_stage", "attn_fwd_few_bf16"}), launched
+    ref, ref_lse = ls.oracle.attn_fwd(*[ls.wide(x) for x in (q, k, v)], Fc)
+    assert_bf16_close(host_f64(out), ref, f"{layout}: out")
+    assert_bf16_close(host_f64(lse), ref_lse, f"{layout}: lse")
+    ls.close()
+
+
 @pytest.mark.parametrize("D,window_relative", [(128, False), (64, True)])
 @pytest.mark.parametrize("layout", ["one buffer for dk_cache and dv_cache", "dk_cache over dout", "dk_cache over dout and dv_cache"])
 def test_ring_gradients_over_each_other_and_over_dout(D, window_relative, layout):
