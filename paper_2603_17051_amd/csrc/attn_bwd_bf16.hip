@@ -372,7 +372,8 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_bwd_dq_kernel(BwdParams
 }
 
 // dQ = R(phi)^T (main + helper sums) / sqrt(D) of a split launch: bytes only (ways + 1 times dQ), four quads
-// of D per thread in flight
+// of D per thread in flight.  Look-ups ahead of the first store and divisions of 32 bits, us: two ways, 12 pairs of 128 20.0 ->
+// 15.4, 16 of 64 15.1 -> 10.9; three, 3 pairs of 128 8.7 -> 6.4, 14 23.8 -> 22.8, 4 of 64 7.2 -> 5.4 (81 registers instead of 62).
 template <int D, int kWays>
 __global__ void __launch_bounds__(256) dq_merge_kernel(BwdParams p, DqSplit split, int64_t n_quads) {
   constexpr int kUnroll = 4, QPR = D / 4;
@@ -785,7 +786,9 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
   }
 
   // dV as it is; dK~ is turned back to dK here.  All look-ups are requested before the first store: the compiler cannot tell
-  // the gradients from the tables, so one behind a store waited for it, about 1000 cycles for each of the 16 blocks.
+  // the gradients from the tables, so one behind a store waits for it.  Launch with each look-up at its store / so, us: chunk, D = 128
+  // 48 pairs x 4680 rows 952 / 948, 12 pairs 254 / 251.5, D = 64 16 pairs 160 / 158, 48 pairs x 1200 52.5 / 50.5; ring of 18 frames, 12
+  // pairs of 128 1432 / 1418, 16 of 64 with 12 frames 778 / 766.  The price is 74 (ring 102) scalar registers kept in vector registers.
   const bool rope = kKey && p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
   QuadAngles angles[2][D / 16];
   if (rope) {

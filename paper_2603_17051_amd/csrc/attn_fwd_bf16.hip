@@ -449,8 +449,8 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
 // ---- launches with few queries -------------------------------------------------------------------
 // With 128 queries per workgroup a call of a few hundred queries and a few heads is a handful of
 // workgroups that walk all keys one tile after another while most of the chip idles.  Here a
-// workgroup owns ONE block of 32 queries and its waves share the KEYS: wave w walks its own
-// contiguous part of the key tiles through its own LDS buffers (no barrier in the loop), and the
+// workgroup owns ONE block of 32 queries and its waves share the KEYS: wave w walks its own part of
+// the key tiles, contiguous or every kWaves-th, through its own LDS buffers (no barrier in the loop), and the
 // waves' unnormalised results are combined through LDS at the end.  Against the key split over
 // workgroups that needs no second launch, and partial results stay fp32.  What bounds it: a CU pulls
 // 16 KB of tiles (D = 128) per 32 keys for 32 queries, about 0.18 us at the 40 B per clock and CU these
@@ -463,7 +463,8 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
 // With one wave per SIMD every vector instruction costs its latency, about 8 cycles, so their number is what
 // counts: the waves share the rotation of the queries through LDS, and a wave turns a chunk key tile in its
 // buffer with positions found once per row and the lane's four rotary pairs fixed (a lane's own queries and positions
-// per look-up: 45 % more instructions, 1.5 - 3 us more).
+// per look-up: 45 % more instructions, 1.5 - 3 us more).  At D = 64 it keeps to the 128 registers of four workgroups per CU
+// with one or two of them in scratch.
 struct StagedChunk {};  // the operands are in q_rot and kc_rot
 struct RawChunk {
   const __bf16 *q, *k;  // [B, Nq, H, D] as the caller passed them

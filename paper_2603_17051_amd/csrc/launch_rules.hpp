@@ -139,10 +139,11 @@ inline int fwd_splits(const CallShape& c) {
 // it, takes over at half the bounds and beyond three (D = 128) or five workgroups per CU (longest and mean walk: 1056 x
 // 180, 89 88 / 56; 432 x 216, 148 46 / 38; 1536 x 28, 19 61 / 48; the other way 480 x 54, 42 30 / 39; 7 % in the mean of 85 such
 // launches).  Returns the waves per workgroup, 0 = the general kernel: eight where every CU has one workgroup at
-// most and each wave gets two tiles (D = 64: one) or more, else four.  Four waves are one per SIMD, whose tile then costs its
+// most and the walk has 16 tiles (D = 64: 8) or more, else four.  Four waves are one per SIMD, whose tile then costs its
 // latency: of 1000 shapes eight take, by tiles, D = 64 0.95 of the time at 5 - 16, 0.9 at 17 - 32, 0.83 at 64 and 0.7 above
 // 100 (144 x 34 9.6 against 11.9 us, 192 x 135 17.7 / 24.7), D = 128 0.9 from 8 tiles on and 0.85 above 64 (128 x 23 12.1 / 14.1, 132 x
-// 82 22.1 / 28.0; the line there keeps 14 tiles, which a test of the rules names, at four).  Where two workgroups of four
+// 82 22.1 / 28.0).  At D = 128 the line could lie at 8 tiles by that (medians 0.90 at 8 - 11 tiles, 39 shapes, 0.91 at 12 - 15, 44); it
+// is not there yet.  Where two workgroups of four
 // share a CU nothing is gained (312 x 153, D = 64 32.0 / 32.8) or lost (D = 128 1.2).  Sixteen waves: 10.2 at the 144 x 34.
 inline int fwd_few_waves(const CallShape& c) {
   if (c.in_order) return 0;

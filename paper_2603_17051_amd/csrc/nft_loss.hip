@@ -166,7 +166,8 @@ __global__ void __launch_bounds__(Chunk<Elem>::kThreads) nft_loss_kernel(NftPara
   }
 }
 
-// Sum over a wave, in every lane of it: the two 32-bit halves are moved as sum_neighbours() and sum_quarters() do.
+// Sum over a wave, in every lane of it: within 16 lanes the two 32-bit halves are moved as sum_neighbours() does, across them
+// by shuffles.
 __device__ __forceinline__ double wave_sum(double x) {
   auto moved = [](double v, auto ctrl) {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
@@ -187,10 +188,11 @@ __device__ __forceinline__ double wave_sum(double x) {
 // Both are sums over all triples of partial sums with the weights of their sample, so the threads
 // share the triples (one thread per sample walked its triples one after another: 5.5 us at 24 clips
 // of 19 triples, most of it latency).  fp64, fixed order.
-// What it takes is the chain launch, loads, sum.  Moves between lanes instead of shuffles through the LDS (here and in the
-// main kernel), a division of 32 bits, the count requested with the triples and no more waves than there are triples for: 4
-// clips of 30784 elements in bf16 9.3 -> 8.3 us for both launches, 109 of 1856 7.3 -> 6.3, 24 of 299520 20.0 -> 19.4, 148 of 33240 in
-// fp32 22.3 -> 21.4.
+// What it takes is the chain launch, loads, sum.  Moves between lanes instead of shuffles through the LDS, a division of 32
+// bits, the count requested with the triples and no more waves than there are triples for: 2.3 -> 1.8 us at up to 109 triples, where
+// one or two waves are left of sixteen, 3.8 as before at 444 and 456.  The main kernel's sums, which take the same moves, gained 0.5 -
+// 1.1 us of it at every size; both launches: 4 clips of 30784 elements in bf16 9.3 -> 8.4 us, 109 of 1856 7.4 -> 6.5, 24 of
+// 299520 20.1 -> 19.5, 148 of 33240 in fp32 22.4 -> 21.3.
 constexpr int kFinalThreads = 1024;
 __global__ void __launch_bounds__(kFinalThreads) nft_finalize_kernel(NftParams p) {
   __shared__ double pol[kFinalThreads / 64], kl[kFinalThreads / 64];
