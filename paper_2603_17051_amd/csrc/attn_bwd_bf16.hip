@@ -47,6 +47,7 @@ struct BwdParams {
   bool terms_ready;      // few rows: delta and lse2 are there already
   int64_t cache_rows;
   float scale;
+  FewDivisors div;  // few rows
   StreamInts hist_rows;
 };
 
@@ -964,14 +965,14 @@ struct FewAngles {
 };
 
 template <int D, int kWaves>
-__device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item, char* lds, float (*terms)[kFewMaxRows]) {
+__device__ __forceinline__ void few_dq(const BwdParams& p, const WorkItem& item, int hist_of_lane, char* lds, float (*terms)[kFewMaxRows]) {
   using F = FewRows<D, kWaves>;
   using Wave = DqWave<D>;
-  const PairIndex pair = split_pair(item.bh, p.H, p.group);
+  const PairIndex pair = few_split_pair(item.bh, p.H, p.group, p.div);
   const int b = pair.b, h = pair.h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
-  const int hist = p.hist_rows.v[pair.cache_b];
+  const int hist = __builtin_amdgcn_readlane(hist_of_lane, pair.cache_b);
   const int64_t bh = (int64_t)b * p.H + h;
   const int q_first = item.tile * 32, q0 = q_first + i16, q_last = p.Nq - 1;
   const int vis_first = visible_chunk_rows(q_first, p.Nq, p.block_rows);
@@ -1247,7 +1248,7 @@ __device__ __forceinline__ void few_dkv_wave(const BwdParams& p, const FewKeysOp
 template <int D, int kWaves>
 __device__ __forceinline__ void few_dkv(const BwdParams& p, const WorkItem& item, char* lds, float (*terms)[kFewMaxRows]) {
   using F = FewRows<D, kWaves>;
-  const int b = item.bh / p.H, h = item.bh % p.H;
+  const int b = quotient(item.bh, p.div.heads), h = item.bh - b * p.H;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   constexpr int kHalf = kWaves / 2;
@@ -1294,14 +1295,20 @@ template <int D, int kWaves>
 __global__ void __launch_bounds__(kWaves * 64, 2) attn_bwd_few_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * FewRows<D, kWaves>::kWaveBytes];
   __shared__ __attribute__((aligned(16))) float terms[2][kFewMaxRows];
+  static_assert(ASTRO_MAX_BATCH == 64, "one stream per lane");
+  const int hist_of_lane = p.hist_rows.v[threadIdx.x & 63];
+  // the arguments in one round of scalar loads, as in the forward's kernel of this kind
+  asm volatile("" ::"s"(p.tiles), "s"(p.BH), "s"((int)p.by_xcd), "s"(p.H), "s"(p.group), "s"(p.Nq), "s"(p.block_rows), "s"(p.div.tiles),
+               "s"(p.div.group), "s"(p.div.heads), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kc_rot), "s"(p.v_chunk), "s"(p.cache_rows),
+               "s"(p.q_rot), "s"(p.dout), "s"(p.out), "s"(p.lse), "s"((int)p.terms_ready));
   const int n_side = p.tiles * p.BH;
   const bool key_side = (int)blockIdx.x >= n_side;
-  const WorkItem item = work_item(p.tiles, p.BH, p.by_xcd, (int)blockIdx.x - (key_side ? n_side : 0));
+  const WorkItem item = few_work_item(p.tiles, p.BH, p.by_xcd, p.div, (int)blockIdx.x - (key_side ? n_side : 0));
   if (!item.valid) return;
   if (key_side)
     few_dkv<D, kWaves>(p, item, lds, terms);
   else
-    few_dq<D, kWaves>(p, item, lds, terms);
+    few_dq<D, kWaves>(p, item, hist_of_lane, lds, terms);
 }
 
 template <int D>
@@ -1333,6 +1340,7 @@ BwdParams make_params(const DevGeom& g, const AttnOperands& op, const void* out,
   p.block_rows = op.block_rows;
   p.by_xcd = true;
   p.terms_ready = false;
+  p.div = FewDivisors{};
   return p;
 }
 
@@ -1353,6 +1361,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
     }
     ProfileScope prof("attn_bwd_few_bf16", stream);
     p.tiles = (op.Nq + 31) / 32;
+    p.div = few_divisors(p.tiles, p.group, p.H);
     const dim3 grid(2 * work_grid_size(p.tiles, p.BH));
     if (waves == 8)
       attn_bwd_few_kernel<D, 8><<<grid, 8 * 64, 0, stream>>>(p);

@@ -59,6 +59,7 @@ struct FwdParams {
   bool by_xcd;                    // order of the workgroups, see order_by_xcd()
   bool in_turn;                   // few rows: the waves take the key tiles in turn, not a contiguous share each
   int64_t cache_rows;  // C*T
+  FewDivisors div;     // few rows
   StreamInts hist_rows;
 };
 
@@ -551,17 +552,28 @@ __global__ void __launch_bounds__(kWaves * 64, D == 128 ? 2 : 4) attn_fwd_few_ke
   __shared__ float2 tab[kRaw ? fwd_table_entries(D) : 1];
   __shared__ __attribute__((aligned(1024))) char qtile[kRaw ? F::kTileBytes : 16];
 
-  const WorkItem item = work_item(p.q_tiles, p.BH, p.by_xcd);
+  const int hist_of_lane = p.hist_rows.v[threadIdx.x & 63];
+  // What the first loads' addresses come from, in one round of scalar loads: read where they are used, one after another, the
+  // arguments were four rounds to memory, and with three integer divisions 2300 of a short call's 12000 cycles (64 rows, 2
+  // heads of 64, 256 resident 6.26 -> 5.74 us, forward and backward 12.98 -> 12.21; 72 rows, 6 pairs of 128 9.8 -> 9.2).
+  asm volatile("" ::"s"(p.q_tiles), "s"(p.BH), "s"((int)p.by_xcd), "s"(p.H), "s"(p.group), "s"(p.Nq), "s"(p.div.tiles), "s"(p.div.group),
+               "s"(p.div.heads), "s"(p.k_cache), "s"(p.v_cache), "s"(p.v_chunk), "s"(p.cache_rows));
+  if constexpr (kRaw)
+    asm volatile("" ::"s"(chunk.q), "s"(chunk.k), "s"(chunk.inv_freq_t), "s"(chunk.tab_h), "s"(chunk.tab_w), "s"(chunk.gh), "s"(chunk.gw),
+                 "s"(chunk.T), "s"(chunk.n_t), "s"(chunk.n_h), "s"(chunk.n_w), "s"(chunk.n_frames));
+  else
+    asm volatile("" ::"s"(p.q_rot), "s"(p.kc_rot), "s"((int)p.in_turn));
+  if constexpr (kCausal) asm volatile("" ::"s"(p.block_rows));
+  const WorkItem item = few_work_item(p.q_tiles, p.BH, p.by_xcd, p.div, (int)blockIdx.x);
   if (!item.valid) return;
-  const PairIndex pair = split_pair(item.bh, p.H, p.group);
+  const PairIndex pair = few_split_pair(item.bh, p.H, p.group, p.div);
   const int b = pair.b, h = pair.h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   // Every lane loads one stream's count and the wanted one is picked: indexed, the load would wait for the pair to be
-  // computed from other arguments (512 rows, 16 heads, empty ring 17.7 against 18.0 us, three 99-row frames at D = 64 10.3 and 10.6;
-  // in the backward's kernel of this kind it gains nothing and at D = 64 loses 0.3).
+  // computed from other arguments (512 rows, 16 heads, empty ring 17.7 against 18.0 us, three 99-row frames at D = 64 10.3 and 10.6).
   static_assert(ASTRO_MAX_BATCH == 64, "one stream per lane");
-  const int hist = __builtin_amdgcn_readlane(p.hist_rows.v[threadIdx.x & 63], pair.cache_b);
+  const int hist = __builtin_amdgcn_readlane(hist_of_lane, pair.cache_b);
   const int64_t bh = (int64_t)b * p.H + h;
   const int q_first = item.tile * 32, q_last = p.Nq - 1;
   const int q0 = q_first + i16;  // this lane's queries: q0 and q0 + 16
@@ -817,6 +829,7 @@ FwdParams make_params(const DevGeom& g, const AttnOperands& op, void* out, float
   p.q_tiles = 0;
   p.by_xcd = true;
   p.in_turn = false;
+  p.div = FewDivisors{};
   p.splits = 1;
   p.out_part = nullptr;
   p.lse_part = nullptr;
@@ -827,6 +840,7 @@ template <int D, int kWaves, bool kCausal>
 hipError_t launch_few(const DevGeom& g, const AttnOperands& op, void* out, float* lse, hipStream_t stream) {
   FwdParams p = make_params(g, op, out, lse);
   p.q_tiles = (op.Nq + 31) / 32;
+  p.div = few_divisors(p.q_tiles, p.group, p.H);
   const dim3 grid(work_grid_size(p.q_tiles, p.BH)), block(kWaves * 64);
   if (const ChunkSource* from = op.raw) {
     RawChunk c{(const __bf16*)from->q, (const __bf16*)from->k, (__bf16*)op.q_rot, (__bf16*)op.kc_rot,

@@ -70,6 +70,16 @@ inline double mean_keys(const CallShape& c) {
 // rows keep the contiguous order: their workgroups are short and pull more through the L2s.)
 inline bool order_by_xcd(const CallShape& c, int workgroups) { return c.xcd_load < 1.15 || workgroups <= c.n_cus; }
 
+// n / d for 0 <= n and 0 < d below 2^15, from the divisor's inverse that the host passes: (n + 1/2) / d lies at least 1 / 2d
+// from an integer, and the inverse, rounded down, takes less than (2n + 1) / 2^32 off.  A launch of few rows has three
+// such divisions in front of its first load, 40 dependent instructions each by the compiler's way.
+constexpr uint32_t inverse_of(int d) { return 0x80000000u / (uint32_t)d; }
+constexpr int quotient(int n, uint32_t inverse) { return (int)((uint64_t)(2u * (uint32_t)n + 1u) * inverse >> 32); }
+struct FewDivisors {
+  uint32_t tiles, group, heads;
+};
+inline FewDivisors few_divisors(int tiles, int group, int heads) { return {inverse_of(tiles), inverse_of(group), inverse_of(heads)}; }
+
 // ==== forward ======================================================================================
 constexpr int kMaxFwdSplits = 8;  // most key ranges of a launch
 constexpr int kFwdKeyTile = 32;   // keys per LDS tile

@@ -6,6 +6,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "launch_rules.hpp"
+
 namespace astro {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -295,6 +297,17 @@ __device__ __forceinline__ WorkItem work_item(int tiles_per_head, int BH, bool b
   return work_item(tiles_per_head, BH, by_xcd, (int)blockIdx.x);
 }
 
+__device__ __forceinline__ WorkItem few_work_item(int tiles, int BH, bool by_xcd, const FewDivisors& div, int i) {
+  WorkItem w;
+  const int n = tiles * BH;
+  w.valid = i < n;
+  const uint32_t x = (uint32_t)i % kXcds, q = (uint32_t)n / kXcds, r = (uint32_t)n % kXcds;  // as xcd_order()
+  const int j = by_xcd ? (int)(x * q + (x < r ? x : r) + (uint32_t)i / kXcds) : i;
+  w.bh = quotient(j, div.tiles);
+  w.tile = j - w.bh * tiles;
+  return w;
+}
+
 // A work item's pair index -> candidate, head and cache stream.  Pairs are ordered (cache
 // stream, head, candidate), so the `group` candidates that share one head's ring rows are
 // neighbours (same XCD under the contiguous split, same time otherwise).
@@ -311,6 +324,15 @@ __device__ __forceinline__ PairIndex split_pair(int pair, int H, int group) {
   x.cache_b = x.cache_bh / H;
   x.h = x.cache_bh - x.cache_b * H;
   x.b = x.cache_b * group + g;
+  return x;
+}
+
+__device__ __forceinline__ PairIndex few_split_pair(int pair, int H, int group, const FewDivisors& div) {
+  PairIndex x;
+  x.cache_bh = quotient(pair, div.group);
+  x.cache_b = quotient(x.cache_bh, div.heads);
+  x.h = x.cache_bh - x.cache_b * H;
+  x.b = x.cache_b * group + (pair - x.cache_bh * group);
   return x;
 }
 
