@@ -477,6 +477,10 @@ struct RawChunk {
   float q_scale;
   StreamInts first_frame;  // by candidate
 };
+// The same with the chunk's keys turned by all waves together before the walk (fwd_turns_together): a wave that turns a tile
+// on its way spends 1770 cycles on it and 1000 waiting for its keys behind the tile before, of 11200 in a short call; the
+// eight waves share them in about 700, next to the queries', and a chunk tile's values are requested a tile earlier.
+struct RawChunkTogether : RawChunk {};
 
 // The (cos, sin) a workgroup's chunk tokens need, in LDS: [n_frames][n_t], [gh][n_h], [gw][n_w], at most kEntries.
 template <int kEntries>
@@ -544,12 +548,15 @@ struct ChunkTables {
 
 template <int D, int kWaves, bool kCausal, typename Chunk>
 __global__ void __launch_bounds__(kWaves * 64, D == 128 ? 2 : 4) attn_fwd_few_kernel(FwdParams p, Chunk chunk) {
-  constexpr bool kRaw = std::is_same_v<Chunk, RawChunk>;
+  constexpr bool kRaw = std::is_base_of_v<RawChunk, Chunk>;
+  constexpr bool kTogether = std::is_same_v<Chunk, RawChunkTogether>;
   using F = FewRows<D, kWaves>;
   using Wave = FwdWave<D>;
   __shared__ __attribute__((aligned(1024))) char lds[kWaves * F::kWaveBytes];
+  __shared__ __attribute__((aligned(1024))) char ctiles[kTogether ? fwd_together_tiles(D) * F::kTileBytes : 16];
   __shared__ float2 stats[kWaves][32];  // softmax reference and row sum of each wave's keys
-  __shared__ float2 tab[kRaw ? fwd_table_entries(D) : 1];
+  constexpr int kEntries = kTogether ? fwd_together_entries(D) : fwd_table_entries(D);
+  __shared__ float2 tab[kRaw ? kEntries : 1];
   __shared__ __attribute__((aligned(1024))) char qtile[kRaw ? F::kTileBytes : 16];
 
   const int hist_of_lane = p.hist_rows.v[threadIdx.x & 63];
@@ -617,15 +624,62 @@ __global__ void __launch_bounds__(kWaves * 64, D == 128 ? 2 : 4) attn_fwd_few_ke
   const int t_begin = in_turn ? wave : F::begin(wave, kWaves, 0, ntiles), t_end = in_turn ? ntiles : F::begin(wave + 1, kWaves, 0, ntiles);
   const int t_step = in_turn ? kWaves : 1;
   if (t_begin < t_end) {
-    issue_k(t_begin);
+    if (!kTogether || t_begin < hist_tiles) issue_k(t_begin);
     issue_v(t_begin);
   }
 
   Wave w;
   w.init(lane);
   w.init_zero_ref();
-  ChunkTables<fwd_table_entries(D)> tables;
-  if constexpr (kRaw) {
+  ChunkTables<kEntries> tables;
+  if constexpr (kTogether) {
+    // A 16-byte unit of the chunk's keys per thread and trip, and of the block's queries where the rows are the same, turned
+    // into LDS for all waves.
+    constexpr int CPR = D / 8, kRows = kWaves * 64 / CPR, kTrips = fwd_together_tiles(D) * KT / kRows;
+    static_assert(kRows % 32 == 0 && kTrips * kRows == fwd_together_tiles(D) * KT, "the rows of a trip are whole tiles, and the trips all of them");
+    const int c = threadIdx.x % CPR, r0 = threadIdx.x / CPR, n_rows = (ntiles - hist_tiles) * KT;
+    bf16x8 xk[kTrips], xq[kTrips];
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      const int row = u * kRows + r0;
+      xk[u] = xq[u] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      if (row < n_rows && row < p.Nq) {
+        const int64_t at = chunk_at + row * token_stride + c * 8;
+        xk[u] = *reinterpret_cast<const bf16x8*>(chunk.k + at);
+        if ((uint32_t)(row - q_first) < 32u) xq[u] = *reinterpret_cast<const bf16x8*>(chunk.q + at);
+      }
+    }
+    tables.template init<kWaves * 64>(chunk, tab, b);
+    const auto pairs = tables.pairs(c);
+    uint32_t position[kTrips];
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) position[u] = tables.position(u * kRows + r0 < p.Nq ? u * kRows + r0 : q_last);
+    __syncthreads();
+    if (chunk.tab_t && item.tile == 0 && h == 0)
+      for (int e = threadIdx.x; e < tables.off_h; e += kWaves * 64) chunk.tab_t[(int64_t)b * tables.off_h + e] = tab[e];
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      const int row = u * kRows + r0;
+      if (row >= n_rows) continue;
+      float2 cs[4];
+      tables.cos_sin(pairs, position[u], cs);
+      const bf16x8 k = rotate8(xk[u], cs, 1.f);
+      *reinterpret_cast<bf16x8*>(ctiles + lds_chunk_offset16<D>(row, c)) = k;
+      if ((uint32_t)(row - q_first) < 32u) {
+        const bf16x8 q = rotate8(xq[u], cs, chunk.q_scale);
+        *reinterpret_cast<bf16x8*>(qtile + lds_chunk_offset16<D>(row - q_first, c)) = q;
+        if (chunk.tab_t && row < p.Nq) {
+          *reinterpret_cast<bf16x8*>(chunk.q_rot + (bh * p.Nq + row) * D + c * 8) = q;
+          *reinterpret_cast<bf16x8*>(chunk.kc_rot + (bh * p.Nq + row) * D + c * 8) = k;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int qs = 0; qs < 2; ++qs)
+#pragma unroll
+      for (int st = 0; st < Wave::KS; ++st) w.qreg[qs][st] = read_rows16<D>(qtile, w.addr.row[st], 16 * qs);
+  } else if constexpr (kRaw) {
     // a 16-byte unit of the block's queries per thread and trip, rotated into LDS for all waves
     constexpr int CPR = D / 8, kThreads = kWaves * 64, kTrips = (32 * CPR + kThreads - 1) / kThreads;
     const int c = threadIdx.x % CPR;
@@ -702,29 +756,70 @@ __global__ void __launch_bounds__(kWaves * 64, D == 128 ? 2 : 4) attn_fwd_few_ke
       wave_lds_sync();
     }
   };
-  for (int t = t_begin; t < t_end; t += t_step) {
-    wait_vmem_except<PrivateStream<D>::kInsts>();  // the K tile; the V tile behind it may be in flight
-    wave_lds_sync();
-    if (t >= hist_tiles) rotate_keys(t);
-    bf16x8 kf[Wave::KH];
-    w.read_k(ktile, kf);
-    const int row0 = (t < hist_tiles ? t : t - hist_tiles) * KT;
-    const int live[2] = {(t < hist_tiles ? hist : vis[0]) - row0, (t < hist_tiles ? hist : vis[1]) - row0};
-    // each buffer is refilled as soon as its tile is done with
-    w.template tile<true>(kf, ktile, vtile, live, (t < hist_tiles ? hist : vis_first) - row0 < KT, t == t_begin, [&] {
+  if constexpr (kTogether) {
+    // Ring tiles as below, then the wave's one chunk tile: its keys are there, and its values have been requested into
+    // the buffer that the last ring tile's keys had left.
+    static_assert(fwd_together_tiles(D) <= kWaves, "a wave has one of them at most");
+    int t = t_begin;
+    for (; t < hist_tiles; t += t_step) {
+      wait_vmem_except<PrivateStream<D>::kInsts>();  // the K tile; the V tile behind it may be in flight
+      wave_lds_sync();
+      bf16x8 kf[Wave::KH];
+      w.read_k(ktile, kf);
+      const int live[2] = {hist - t * KT, hist - t * KT};
+      w.template tile<true>(kf, ktile, vtile, live, hist - t * KT < KT, t == t_begin, [&] {
+        wait_lds();
+        wave_lds_sync();
+        if (t + t_step < hist_tiles)
+          issue_k(t + t_step);
+        else if (t + t_step < t_end)
+          ps.issue(v_chunk, token_stride * 2, (t + t_step - hist_tiles) * KT, ktile);
+        if (t + t_step < t_end)
+          wait_vmem_except<PrivateStream<D>::kInsts>();
+        else
+          wait_vmem();
+        wave_lds_sync();
+      });
       wait_lds();
       wave_lds_sync();
-      if (t + t_step < t_end) {
-        issue_k(t + t_step);
-        wait_vmem_except<PrivateStream<D>::kInsts>();
-      } else {
+      if (t + t_step < hist_tiles) issue_v(t + t_step);
+    }
+    if (t < t_end) {
+      const int row0 = (t - hist_tiles) * KT;
+      const char* kt = ctiles + row0 * D * 2;
+      bf16x8 kf[Wave::KH];
+      w.read_k(kt, kf);
+      const int live[2] = {vis[0] - row0, vis[1] - row0};
+      w.template tile<true>(kf, kt, t == t_begin ? vtile : ktile, live, vis_first - row0 < KT, t == t_begin, [&] {
         wait_vmem();
-      }
+        wave_lds_sync();
+      });
+    }
+  } else {
+    for (int t = t_begin; t < t_end; t += t_step) {
+      wait_vmem_except<PrivateStream<D>::kInsts>();  // the K tile; the V tile behind it may be in flight
       wave_lds_sync();
-    });
-    wait_lds();
-    wave_lds_sync();
-    if (t + t_step < t_end) issue_v(t + t_step);
+      if (t >= hist_tiles) rotate_keys(t);
+      bf16x8 kf[Wave::KH];
+      w.read_k(ktile, kf);
+      const int row0 = (t < hist_tiles ? t : t - hist_tiles) * KT;
+      const int live[2] = {(t < hist_tiles ? hist : vis[0]) - row0, (t < hist_tiles ? hist : vis[1]) - row0};
+      // each buffer is refilled as soon as its tile is done with
+      w.template tile<true>(kf, ktile, vtile, live, (t < hist_tiles ? hist : vis_first) - row0 < KT, t == t_begin, [&] {
+        wait_lds();
+        wave_lds_sync();
+        if (t + t_step < t_end) {
+          issue_k(t + t_step);
+          wait_vmem_except<PrivateStream<D>::kInsts>();
+        } else {
+          wait_vmem();
+        }
+        wave_lds_sync();
+      });
+      wait_lds();
+      wave_lds_sync();
+      if (t + t_step < t_end) issue_v(t + t_step);
+    }
   }
 
   // every wave leaves its unnormalised result and its statistics (own buffer, own tiles are done) ...
@@ -836,6 +931,11 @@ FwdParams make_params(const DevGeom& g, const AttnOperands& op, void* out, float
   return p;
 }
 
+// (cos, sin) that a chunk's rotation takes
+int64_t fwd_entries(const DevGeom& g, const AttnOperands& op) {
+  return (int64_t)(op.Nq / g.T) * g.n_t + (int64_t)g.gh * g.n_h + (int64_t)g.gw * g.n_w;
+}
+
 template <int D, int kWaves, bool kCausal>
 hipError_t launch_few(const DevGeom& g, const AttnOperands& op, void* out, float* lse, hipStream_t stream) {
   FwdParams p = make_params(g, op, out, lse);
@@ -843,10 +943,16 @@ hipError_t launch_few(const DevGeom& g, const AttnOperands& op, void* out, float
   p.div = few_divisors(p.q_tiles, p.group, p.H);
   const dim3 grid(work_grid_size(p.q_tiles, p.BH)), block(kWaves * 64);
   if (const ChunkSource* from = op.raw) {
-    RawChunk c{(const __bf16*)from->q, (const __bf16*)from->k, (__bf16*)op.q_rot, (__bf16*)op.kc_rot,
+    const RawChunk c{(const __bf16*)from->q, (const __bf16*)from->k, (__bf16*)op.q_rot, (__bf16*)op.kc_rot,
                from->leave ? (float2*)op.tab_t : nullptr, g.inv_freq_t, g.tab_h, g.tab_w, g.gh, g.gw, g.T, g.n_t, g.n_h, g.n_w,
                op.Nq / g.T, from->q_scale, from->first_frame};
     ProfileScope prof("attn_fwd_few_rotating_bf16", stream);
+    if constexpr (kWaves == 8) {
+      if (fwd_turns_together(call_shape(g, op), fwd_entries(g, op))) {
+        attn_fwd_few_kernel<D, kWaves, kCausal, RawChunkTogether><<<grid, block, 0, stream>>>(p, RawChunkTogether{c});
+        return hipGetLastError();
+      }
+    }
     attn_fwd_few_kernel<D, kWaves, kCausal, RawChunk><<<grid, block, 0, stream>>>(p, c);
   } else {
     p.in_turn = bf16_fwd_rotates(g, op);
@@ -884,8 +990,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, void* out, float* ls
 }  // namespace
 
 bool bf16_fwd_rotates(const DevGeom& g, const AttnOperands& op) {
-  const int pairs = g.n_t + g.n_h + g.n_w, n_frames = op.Nq / g.T;
-  return pairs != 0 && fwd_rotates(call_shape(g, op), (int64_t)n_frames * g.n_t + (int64_t)g.gh * g.n_h + (int64_t)g.gw * g.n_w);
+  return g.n_t + g.n_h + g.n_w != 0 && fwd_rotates(call_shape(g, op), fwd_entries(g, op));
 }
 
 size_t bf16_fwd_split_bytes(const DevGeom& g, int Nq) {

@@ -184,11 +184,23 @@ inline int fwd_few_waves(const CallShape& c) {
 //   four waves, D = 128: 0.5 8.5 / 10.6, 1 12.6 / 13.5, 1.25 11.8 / 11.9, 1.5 11.7 / 12.3, 2 10.8 / 11.4; lost: 2.25 16.2 / 14.7, 4.25 18.6 / 15.3
 //   eight waves, ratio over 800 shapes, D = 64: 0.5 0.80, 1 0.82, 1.5 0.88, 2 0.92, 2.5 0.96, 3 1.01; D = 128: 0.82, 0.86, 0.94, 0.97, lost:
 //   2.5 1.02, 3 1.06
+// most chunk tiles of such a launch
+constexpr int fwd_rotated_tiles(int D, int waves) { return D == 128 ? 2 * waves : waves == 8 ? 20 : 3 * waves; }
 constexpr int fwd_table_entries(int D) { return D == 128 ? 896 : 384; }
 inline bool fwd_rotates(const CallShape& c, int64_t entries) {
   const int waves = fwd_few_waves(c);
-  const int most = c.D == 128 ? 2 * waves : waves == 8 ? 20 : 3 * waves;  // chunk tiles
-  return entries <= fwd_table_entries(c.D) && blocks_of(c.Nq, kFwdKeyTile) <= most;
+  return entries <= fwd_table_entries(c.D) && blocks_of(c.Nq, kFwdKeyTile) <= fwd_rotated_tiles(c.D, waves);
+}
+
+// Whether the eight waves of such a launch turn the chunk's keys together into LDS before the walk instead of each its own
+// tiles on the way.  All wait for all of it, so the chunk has to be short: up to a tile a wave at D = 64, and what fits the LDS
+// next to the tiles at D = 128.  Measured (us, each its own / together): D = 64, chunk + ring tiles, 2 + 8 5.8 / 5.3, 4 + 13 6.6 / 6.3, 4 + 72
+// 10.8 / 10.3, 4 + 23 7.9 / 7.4, 7 + 100 14.1 / 12.7; D = 128, 2 + 16 9.2 / 8.4, 2 + 24 10.2 / 9.3.  With room for sixteen tiles, two to a wave,
+// 9 + 25 gained 0.2 and 16 + 48 0.3, but the short ones lost 0.3 to the longer code.
+constexpr int fwd_together_tiles(int D) { return D == 128 ? 2 : 8; }
+constexpr int fwd_together_entries(int D) { return D == 128 ? 512 : 384; }
+inline bool fwd_turns_together(const CallShape& c, int64_t entries) {
+  return fwd_few_waves(c) == 8 && blocks_of(c.Nq, kFwdKeyTile) <= fwd_together_tiles(c.D) && entries <= fwd_together_entries(c.D);
 }
 
 // ==== backward =====================================================================================
