@@ -849,6 +849,283 @@ __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams
     dkv_wave<D, false>(p, grads, item, wave, lds);
 }
 
+// ---- the same at D = 64 --------------------------------------------------------------------------------
+// Both gradients of 32 keys fit one wave's registers (64 accumulators), so there are no roles: a workgroup is four waves, each with
+// its own block of 32 of the 128 keys, P does not go through LDS, dS is formed from it in 32 bits, and three workgroups share a CU (34 KB of LDS,
+// 168 registers, 28 bytes of scratch outside the loop) instead of one (100 KB).  Bound by the overlap of the 32 MFMAs, 16 exponentials and 32
+// vector instructions of a block.  Which launches take it: dkv_halves().
+template <int D>
+struct KeyBlockWave {
+  static constexpr int KS = D / 32, DT = D / 16;
+  bf16x8 kreg[2][KS], vreg[2][KS];  // B operands: K~ and V rows of this lane's two keys
+  f32x4 dk[DT][2], dv[DT][2];
+  OperandAddr16<D> addr;
+  int g;
+
+  __device__ __forceinline__ void init(int lane) {
+    g = lane >> 4;
+    addr.init(lane);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) dk[dt][ks] = dv[dt][ks] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // rows of a tile from row0 on times the lane's keys, the accumulators starting from the rows' terms
+  __device__ __forceinline__ void product(const char* tile, int row0, const float* terms, const bf16x8 (&keys)[2][KS], f32x4 (&s)[2][2]) const {
+    f32x4 t4[2];
+#pragma unroll
+    for (int qh = 0; qh < 2; ++qh) t4[qh] = *reinterpret_cast<const f32x4*>(terms + row0 + 16 * qh + 4 * g);
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+#pragma unroll
+      for (int qh = 0; qh < 2; ++qh) {
+        const bf16x8 a = read_rows16<D>(tile, addr.row[st], row0 + 16 * qh);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) s[qh][ks] = mfma16(a, keys[ks][st], st == 0 ? t4[qh] : s[qh][ks]);
+      }
+  }
+  __device__ __forceinline__ void accumulate(const char* tile, int row0, const bf16x8 (&x)[2], f32x4 (&acc)[DT][2]) const {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const bf16x8 a = read_cols16<D>(tile, addr.tr[dt], row0);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) acc[dt][ks] = mfma16(a, x[ks], acc[dt][ks]);
+    }
+  }
+  // 32 queries of a tile: lse_t / delta_t = -LSE*log2(e) and -Delta of its rows; rows below first[ks] do not see the lane's key
+  // ks (first_max, wave-uniform: largest over the wave)
+  __device__ __forceinline__ void block(const char* qs, const char* dos, const float* lse_t, const float* delta_t, int row0,
+                                        const int (&first)[2], int first_max) {
+    f32x4 s[2][2], dp[2][2];
+    bf16x8 pb[2], dsb[2];
+    product(qs, row0, lse_t, kreg, s);
+    if (first_max > row0) {
+#pragma unroll
+      for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[qh][ks][r] = row0 + 16 * qh + 4 * g + r < first[ks] ? kNegBig : s[qh][ks][r];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[qh][ks][r] = fast_exp2(s[qh][ks][r]);
+    product(dos, row0, delta_t, vreg, dp);
+#pragma unroll
+    for (int i = 0; i < 4 * KS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // two exponentials
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          pb[ks][4 * qh + r] = (__bf16)s[qh][ks][r];
+          dsb[ks][4 * qh + r] = (__bf16)(s[qh][ks][r] * dp[qh][ks][r]);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    accumulate(dos, row0, pb, dv);
+    accumulate(qs, row0, dsb, dk);
+  }
+};
+
+// kHalves = 2: twice the waves, each takes one of a tile's two blocks of queries, and the two waves of a key block add up
+// through LDS at the end.
+template <int D, int kHalves, typename Grads>
+__global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_dkv_block_kernel(BwdParams p, Grads grads) {
+  constexpr bool kRing = std::is_same_v<Grads, RingGrads>;
+  constexpr int TILE_BYTES = QT * D * 2, SLOT_BYTES = 2 * TILE_BYTES, SLOT_TERMS = 2 * QT * 4;
+  constexpr int kWaves = 4 * kHalves, kSumBytes = 2 * (D / 16) * 1024;  // one gradient of 32 keys
+  // tiles of all slots, then their row terms; alone on a CU a block takes less time than a tile takes to land, so there two are in flight
+  constexpr int kSlots = kHalves + 1, kTerms = kSlots * SLOT_BYTES, kTileBytes = kTerms + kSlots * SLOT_TERMS;
+  __shared__ __attribute__((aligned(1024))) char lds[kHalves == 1 || kTileBytes > 8 * kSumBytes ? kTileBytes : 8 * kSumBytes];
+  const WorkItem item = work_item(p.tiles, p.BH, !kRing || p.by_xcd);
+  if (!item.valid) return;
+  const int b = item.bh / p.H, h = item.bh % p.H;
+  // this lane's two keys jc and jc + 16: chunk rows, or (non-detached backward) resident ring rows of the stream
+  const int n_keys = kRing ? p.hist_rows.v[b] : p.Nq;
+  if (item.tile * 128 >= n_keys) return;  // whole workgroup, before any barrier
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = wave & 3, half = wave >> 2;
+  const int i16 = lane & 15, g = lane >> 4;
+  const int64_t bh = (int64_t)b * p.H + h;
+  const int j_wave = (item.tile * 4 + kw) * 32, jc = j_wave + i16, j_last = n_keys - 1;
+  const int ntiles = (p.Nq + QT - 1) / QT;
+  // as in dkv_wave()
+  const int block_rows = kRing ? 0 : p.block_rows;
+  int first_q[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last, block_rows);
+  const int first_q_wave = first_query_row_seeing(j_wave + 31 < j_last ? j_wave + 31 : j_last, block_rows);
+  const int t_begin = first_query_row_seeing(item.tile * 128, block_rows) / QT;
+
+  const RowSegment q_rows = make_segment(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
+  const RowSegment do_rows = make_segment(p.dout + ((int64_t)b * p.Nq * p.H + h) * D, (int64_t)p.H * D, p.Nq, D);
+  TileStreamer<D, QT, kWaves> ts;
+  ts.init();
+  const uint32_t off_q = ts.lane_offset(q_rows), off_do = ts.lane_offset(do_rows);
+  // Row terms as in dkv_wave(): rows past Nq read as zeros, and their Q~ and dO rows are zero in LDS as well
+  const __amdgpu_buffer_rsrc_t term_rows =
+      __builtin_amdgcn_make_buffer_rsrc((void*)((wave == 0 ? p.lse2 : p.delta) + bh * p.Nq), 0, p.Nq * 4, 0x00020000);
+  auto issue = [&](int t, int slot) __attribute__((always_inline)) {
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    char* qbuf = lds + slot * SLOT_BYTES;
+    ts.issue(q_rows, off_q, t * QT, qbuf);
+    ts.issue(do_rows, off_do, t * QT, qbuf + TILE_BYTES);
+    if (wave < 2)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(term_rows, (lds_ptr)(lds + kTerms + slot * SLOT_TERMS + wave * QT * 4), 4,
+                                               t * QT * 4 + lane * 4, 0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u + 1 < kSlots; ++u)
+    if (t_begin + u < ntiles) issue(t_begin + u, u);
+
+  KeyBlockWave<D> w;
+  w.init(lane);
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const bool live = jc + 16 * ks < n_keys;
+    const int j0 = live ? jc + 16 * ks : 0;
+    const __bf16* krow = kRing ? p.k_cache + (bh * p.cache_rows + j0) * D : p.kc_rot + (bh * p.Nq + j0) * D;
+    const __bf16* vrow = kRing ? p.v_cache + (bh * p.cache_rows + j0) * D : p.v_chunk + (((int64_t)b * p.Nq + j0) * p.H + h) * D;
+#pragma unroll
+    for (int st = 0; st < D / 32; ++st) {
+      bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0}, y = x;
+      if (live) {
+        x = *reinterpret_cast<const bf16x8*>(krow + st * 32 + g * 8);
+        y = *reinterpret_cast<const bf16x8*>(vrow + st * 32 + g * 8);
+      }
+      w.kreg[ks][st] = x;
+      w.vreg[ks][st] = y;
+    }
+  }
+  wait_vmem();
+  __syncthreads();
+  auto step = [&](int t, auto slot_c) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot_c)::value;
+    const bool ahead = t + kSlots - 1 < ntiles;
+    if (ahead) issue(t + kSlots - 1, (S + kSlots - 1) % kSlots);
+    const char* qs = lds + S * SLOT_BYTES;
+    const float* terms = reinterpret_cast<const float*>(lds + kTerms + S * SLOT_TERMS);
+    const int first[2] = {first_q[0] - t * QT, first_q[1] - t * QT};
+    if constexpr (kHalves == 2) {
+      w.block(qs, qs + TILE_BYTES, terms, terms + QT, 32 * half, first, first_q_wave - t * QT);
+    } else {
+#pragma unroll
+      for (int qb = 0; qb < QT / 32; ++qb) w.block(qs, qs + TILE_BYTES, terms, terms + QT, 32 * qb, first, first_q_wave - t * QT);
+    }
+    // the next tile has landed, the one behind it may be in flight
+    constexpr int kLoads = 2 * decltype(ts)::kInsts;
+    if (kSlots == 2 || !ahead)
+      wait_vmem();
+    else if (wave < 2)
+      wait_vmem_except<kLoads + 1>();
+    else
+      wait_vmem_except<kLoads>();
+    __syncthreads();
+  };
+  for (int t = t_begin; t < ntiles; t += kSlots) {
+    step(t, std::integral_constant<int, 0>{});
+    if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
+    if constexpr (kSlots == 3)
+      if (t + 2 < ntiles) step(t + 2, std::integral_constant<int, 2>{});
+  }
+
+  // the first half's waves finish dV, the second's dK, each with what the other has of it
+  const bool has_dv = kHalves == 1 || half == 0, has_dk = kHalves == 1 || half == 1;
+  if constexpr (kHalves == 2) {
+    f32x4* const mine = reinterpret_cast<f32x4*>(lds + wave * kSumBytes);
+    const f32x4* const others = reinterpret_cast<const f32x4*>(lds + (wave ^ 4) * kSumBytes);
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) mine[(2 * dt + ks) * 64 + lane] = has_dv ? w.dk[dt][ks] : w.dv[dt][ks];
+    __syncthreads();
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const f32x4 x = others[(2 * dt + ks) * 64 + lane];
+        w.dv[dt][ks] += x;  // (only one of the two is stored)
+        w.dk[dt][ks] += x;
+      }
+    __syncthreads();
+  }
+
+  // ring rows: (cos, sin) of the temporal pairs at the frames of this workgroup's keys, in the idle slots
+  const bool rope = p.rot.n_t + p.rot.n_h + p.rot.n_w != 0;
+  const float2* slot_tab = nullptr;
+  int slot_first = 0;
+  if constexpr (kRing) {
+    const int j_first = item.tile * 128, j_end = j_first + 128 < n_keys ? j_first + 128 : n_keys;
+    static_assert(129 * (D / 2) * 8 <= sizeof lds, "the largest table fits");
+    slot_first = j_first / p.rot.T;
+    slot_tab = reinterpret_cast<const float2*>(lds);
+    fill_slot_table(reinterpret_cast<float2*>(lds), p, grads, b, slot_first, (j_end - 1) / p.rot.T - slot_first + 1, threadIdx.x, kWaves * 64);
+    __syncthreads();
+  }
+  // all look-ups before the first store, as in dkv_wave()
+  float *dk_to, *dv_to;
+  if constexpr (kRing)
+    dk_to = grads.dk, dv_to = grads.dv;
+  else
+    dk_to = p.dk, dv_to = p.dv;
+  const int64_t rows = kRing ? p.cache_rows : p.Nq;
+  QuadAngles angles[2][D / 16];
+  if (rope && has_dk) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int j = jc + 16 * ks < j_last ? jc + 16 * ks : j_last;
+      TokenTables tt;
+      if constexpr (kRing) {
+        const int slot = j / p.rot.T, rem = j - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
+        tt = TokenTables{slot_tab + (slot - slot_first) * p.rot.n_t, p.rot.tab_h + y * p.rot.n_h, p.rot.tab_w + x * p.rot.n_w};
+      } else {
+        tt = token_tables(p.rot, b, j);
+      }
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) angles[ks][dt] = quad_angles(p.rot, tt, 4 * dt + g);
+    }
+  }
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int j = jc + 16 * ks;
+    if (j >= n_keys) continue;
+    const int64_t at = (((int64_t)b * rows + j) * p.H + h) * D + 4 * g;
+    if (has_dv && (!kRing || dv_to)) {
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<f32x4*>(dv_to + at + 16 * dt) = w.dv[dt][ks];
+    }
+    if (has_dk && (!kRing || dk_to)) {
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) {
+        f32x4 x = w.dk[dt][ks] * kLn2;  // dK~ = dS^T Q~ / sqrt(D), and the staged Q~ carries log2(e)/sqrt(D)
+        if (rope) x = unrotate_quad(angles[ks][dt], x);
+        *reinterpret_cast<f32x4*>(dk_to + at + 16 * dt) = x;
+      }
+    }
+  }
+}
+
+// the dK / dV launch of p.tiles blocks of 128 keys per pair
+template <int D, typename Grads>
+void launch_dkv(const BwdParams& p, const Grads& grads, int n_cus, hipStream_t stream) {
+  const int workgroups = work_grid_size(p.tiles, p.BH), halves = dkv_halves(D, n_cus, workgroups);
+  if constexpr (D == 64) {
+    if (halves == 1)
+      attn_bwd_dkv_block_kernel<D, 1><<<dim3(workgroups), 256, 0, stream>>>(p, grads);
+    else if (halves == 2)
+      attn_bwd_dkv_block_kernel<D, 2><<<dim3(workgroups), 512, 0, stream>>>(p, grads);
+  }
+  if (halves == 0) attn_bwd_dkv_kernel<D><<<dim3(workgroups), kPairThreads, 0, stream>>>(p, grads);
+}
+
 // ---- launches with few rows ------------------------------------------------------------------------
 // With 128 queries (or keys) per workgroup a chunk of a few hundred tokens and a few heads is a
 // handful of workgroups that walk all rows of the other side one tile after another.  Here a
@@ -1394,7 +1671,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   {
     ProfileScope prof("attn_bwd_dkv_bf16", stream);
     p.tiles = (op.Nq + ktile - 1) / ktile;
-    attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, ChunkGrads{});
+    launch_dkv<D>(p, ChunkGrads{}, g.n_cus, stream);
   }
   return hipGetLastError();
 }
@@ -1411,7 +1688,7 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   p.by_xcd = order_by_xcd(call_shape(g, op), work_grid_size(p.tiles, p.BH));
   auto run = [&](const RingGrads& to) {
     ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
-    attn_bwd_dkv_kernel<D><<<dim3(work_grid_size(p.tiles, p.BH)), kPairThreads, 0, stream>>>(p, to);
+    launch_dkv<D>(p, to, g.n_cus, stream);
   };
   if (op.in_order) {  // dV and dK share bytes, dK's stay: one after the other
     RingGrads one = grads;

@@ -242,6 +242,18 @@ inline bool bwd_terms_first(const CallShape& c) {
   return c.D == 128 ? c.Nq >= 384 && c.max_hist < 3 * (int64_t)c.Nq : c.Nq >= 512 && c.max_hist < 2 * (int64_t)c.Nq;
 }
 
+// Which kernel a dK / dV launch of so many workgroups takes: 0 = a pair of waves per block of 32 keys (roles), 1 or 2 = that
+// many waves with both gradients each.  At D = 64 one wave holds both; three such workgroups share a CU where a workgroup
+// of roles has it alone, so full launches gain.  Where each CU has one workgroup at most, two waves per block share the
+// queries, and below half of that the roles, whose table of ring frames is computed beside the last tile, end their short
+// chains earlier.  Measured (us, roles / both; the whole forward and backward, or with the ring's gradients, D = 64):
+//   one wave: ring of 8 frames, 2112 workgroups, 950 / 858, chunk of 2368 3157 / 3002, 592 in causal blocks 1126 / 1107, 540
+//             313 / 290, 315 205 / 194; lost: 240 144 / 156
+//   two waves: 240 143 / 141; lost: 120 34.9 / 35.4, 28 36.4 / 38.0, 21 29.3 / 30.7
+inline int dkv_halves(int D, int n_cus, int workgroups) {
+  return D == 128 || 2 * workgroups <= n_cus ? 0 : workgroups <= n_cus ? 2 : 1;
+}
+
 // dQ workgroups a CU holds: 244 registers (split 256), or 165 (split 168, 8 more in scratch)
 constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }
 

@@ -1,0 +1,51 @@
+"""dK and dV at D = 64 where one wave holds both gradients of its keys (launches of more than half a workgroup per CU): chunk
+and ring launches with one and with two waves to a block of keys, at the edges of key blocks, query tiles and causal blocks,
+against the fp64 oracle; the gates hold for each gradient over all its heads."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from helpers import Lockstep, assert_bf16_close, host_f64
+from oracle.rolling_attention import rope_angles, rope_rotate, visible_history
+from test_gpu_full_bwd import _slot
+from test_gpu_parity import _fill_history
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed", [
+    (4, 65, 3, 11, 2, 0, 1, 0, 3),    # chunk 260 workgroups of 33 keys, ring 260 of 66: one wave a block
+    (4, 65, 8, 8, 2, 1, 1, 0, 4),     # whole tiles, ring of 128 rows: every key block full
+    (4, 65, 7, 9, 3, 1, 1, 0, 2),     # a row short of a tile, one slot empty
+    (5, 52, 1, 43, 3, 0, 3, 1, 0),    # 129 chunk rows in causal blocks of 43, nothing resident
+    (2, 65, 6, 7, 3, 0, 1, 0, 4),     # ring 130 workgroups of 126 rows: two waves a block
+    (2, 65, 1, 43, 3, 1, 2, 1, 5),    # ring 260 of 129 rows, causal blocks
+    (1, 65, 10, 13, 20, 1, 1, 0, 23), # chunk 130 workgroups: two waves a block; ring 1365
+    (1, 65, 5, 13, 40, 0, 2, 1, 40),  # the same under causal blocks
+    (1, 129, 1, 1, 100, 0, 1, 0, 70), # ring 129 workgroups of one-token frames: the table of frames behind the walk
+])
+def test_both_gradients_in_one_wave(B, H, gh, gw, C, S, Fc, bf, streamed):
+    D, T = 64, gh * gw
+    w = wl.Workload("key_blocks", 57, B, H, D, gh, gw, C, S, Fc, streamed, (12, 10, 10))
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[3 + 100 * b for b in range(B)], block_frames=bf)
+    _fill_history(ls, w, *wl.history_frame_pool(w, 7), streamed)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    out, lse = ls.fwd(q, k, v, Fc)
+    _, dk, dv, dkc, dvc = ls.A.astro_chunk_attn_bwd_full(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
+    _, rk, rv, extra = ls.oracle.attn_bwd(*[ls.wide(x) for x in (q, k, v, do)], Fc, history_grads=True)
+    assert_bf16_close(host_f64(dk), rk, "dk")
+    assert_bf16_close(host_f64(dv), rv, "dv")
+    ref_k, ref_v = np.zeros((B, C * T, H, D)), np.zeros((B, C * T, H, D))
+    for b in range(B):
+        for i, n in enumerate(visible_history(streamed, S, C - S)):
+            rows = slice(_slot(n, C, S) * T, (_slot(n, C, S) + 1) * T)
+            phi = rope_angles(ls.oracle.start[b] + n, gh, gw, w.rope_pairs, w.rope_base)
+            for h in range(H):
+                ref_k[b, rows, h] = rope_rotate(extra[(b, h)]["dk_hist_rot"][i * T:(i + 1) * T, None, :], -phi)[:, 0]
+                ref_v[b, rows, h] = extra[(b, h)]["dv_hist"][i * T:(i + 1) * T]
+    if streamed:
+        assert_bf16_close(host_f64(dkc), ref_k, "dk_cache")
+        assert_bf16_close(host_f64(dvc), ref_v, "dv_cache")
+    else:
+        assert (dkc == 0).all() and (dvc == 0).all()
+    ls.close()
