@@ -210,6 +210,43 @@ hipError_t stage_chunk(astro_kvcache* c, const void* q, const void* k_chunk, cha
 
 }  // namespace
 
+namespace {
+// keys_later (may be null): in, whether dK and dV of the chunk may be left to the launch over the ring; out, whether they are
+int group_backward(astro_kvcache_t* cache, const void* q, const void* k_chunk, const void* v_chunk, const void* out, const float* lse,
+                   const void* dout, int32_t n_frames, int32_t group, float* dq, float* dk_chunk, float* dv_chunk, void* workspace,
+                   size_t workspace_bytes, void* hip_stream, bool* keys_later) {
+  const int rc = check_chunk_call(cache, n_frames, group);
+  if (rc != ASTRO_OK) return rc;
+  if (!q || !k_chunk || !v_chunk || !out || !lse || !dout || !dq || !dk_chunk || !dv_chunk) return ASTRO_ERR_INVALID_ARG;
+  const Workspace w = carve(cache, n_frames, true, group);
+  if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace & 255)) return ASTRO_ERR_WORKSPACE;
+  char* ws = (char*)workspace;
+  hipStream_t stream = (hipStream_t)hip_stream;
+  if (stage_chunk(cache, q, k_chunk, ws, w, n_frames, group, stream) != hipSuccess) return ASTRO_ERR_HIP;
+  AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
+  op.in_order = outputs_overlap(cache, n_frames, group, out, lse, dq, dk_chunk, dv_chunk);
+  const DevGeom d = dev_geom(cache, group);
+  if (cache->geo.dtype == ASTRO_BF16) {  // gradients leave the kernels un-rotated and token-major
+    const bool later = keys_later && *keys_later && bf16_bwd_joins(d, op);
+    if (keys_later) *keys_later = later;
+    return launch_attn_bwd_bf16(d, op, out, lse, dout, dq, dk_chunk, dv_chunk, ws + w.scratch, later, stream) == hipSuccess
+               ? ASTRO_OK
+               : ASTRO_ERR_HIP;
+  }
+  float* dq_rot = (float*)(ws + w.dq_rot);
+  float* dk_rot = (float*)(ws + w.dk_rot);
+  if (launch_attn_bwd_f32(d, op, (const float*)out, lse, (const float*)dout, dq_rot, dk_rot, dv_chunk,
+                          (float*)(ws + w.scratch), stream) != hipSuccess)
+    return ASTRO_ERR_HIP;
+  // gradients w.r.t. the un-rotated Q and K_chunk: inverse rotation, back to token-major
+  StreamInts first;
+  stream_ints(cache, &first, nullptr, nullptr, group);
+  if (launch_rope_unscatter_f32(d, dq_rot, dq, n_frames, first, stream) != hipSuccess) return ASTRO_ERR_HIP;
+  if (launch_rope_unscatter_f32(d, dk_rot, dk_chunk, n_frames, first, stream) != hipSuccess) return ASTRO_ERR_HIP;
+  return ASTRO_OK;
+}
+}  // namespace
+
 extern "C" {
 
 int astro_kvcache_bytes(const astro_kvcache_desc_t* desc, size_t* k_bytes, size_t* v_bytes) {
@@ -424,32 +461,8 @@ int astro_group_attn_bwd(astro_kvcache_t* cache, const void* q, const void* k_ch
                          const void* out, const float* lse, const void* dout, int32_t n_frames, int32_t group,
                          float* dq, float* dk_chunk, float* dv_chunk, void* workspace, size_t workspace_bytes,
                          void* hip_stream) {
-  const int rc = check_chunk_call(cache, n_frames, group);
-  if (rc != ASTRO_OK) return rc;
-  if (!q || !k_chunk || !v_chunk || !out || !lse || !dout || !dq || !dk_chunk || !dv_chunk) return ASTRO_ERR_INVALID_ARG;
-  const Workspace w = carve(cache, n_frames, true, group);
-  if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace & 255)) return ASTRO_ERR_WORKSPACE;
-  char* ws = (char*)workspace;
-  hipStream_t stream = (hipStream_t)hip_stream;
-  if (stage_chunk(cache, q, k_chunk, ws, w, n_frames, group, stream) != hipSuccess) return ASTRO_ERR_HIP;
-  AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, group);
-  op.in_order = outputs_overlap(cache, n_frames, group, out, lse, dq, dk_chunk, dv_chunk);
-  const DevGeom d = dev_geom(cache, group);
-  if (cache->geo.dtype == ASTRO_BF16)  // gradients leave the kernels un-rotated and token-major
-    return launch_attn_bwd_bf16(d, op, out, lse, dout, dq, dk_chunk, dv_chunk, ws + w.scratch, stream) == hipSuccess
-               ? ASTRO_OK
-               : ASTRO_ERR_HIP;
-  float* dq_rot = (float*)(ws + w.dq_rot);
-  float* dk_rot = (float*)(ws + w.dk_rot);
-  if (launch_attn_bwd_f32(d, op, (const float*)out, lse, (const float*)dout, dq_rot, dk_rot, dv_chunk,
-                          (float*)(ws + w.scratch), stream) != hipSuccess)
-    return ASTRO_ERR_HIP;
-  // gradients w.r.t. the un-rotated Q and K_chunk: inverse rotation, back to token-major
-  StreamInts first;
-  stream_ints(cache, &first, nullptr, nullptr, group);
-  if (launch_rope_unscatter_f32(d, dq_rot, dq, n_frames, first, stream) != hipSuccess) return ASTRO_ERR_HIP;
-  if (launch_rope_unscatter_f32(d, dk_rot, dk_chunk, n_frames, first, stream) != hipSuccess) return ASTRO_ERR_HIP;
-  return ASTRO_OK;
+  return group_backward(cache, q, k_chunk, v_chunk, out, lse, dout, n_frames, group, dq, dk_chunk, dv_chunk, workspace, workspace_bytes,
+                        hip_stream, nullptr);
 }
 
 int astro_chunk_attn_bwd_full_workspace_bytes(const astro_kvcache_t* cache, int32_t n_frames, size_t* bytes) {
@@ -470,18 +483,27 @@ int astro_chunk_attn_bwd_full(astro_kvcache_t* cache, const void* q, const void*
   if (!dk_cache || !dv_cache) return ASTRO_ERR_INVALID_ARG;
   const Workspace w = carve(cache, n_frames, true, 1);
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace & 255)) return ASTRO_ERR_WORKSPACE;
+  const RingGeometry& g = cache->geo;
+  const size_t chunk = (size_t)g.B * n_frames * g.T * g.H * g.D * g.elem_bytes();
+  const size_t ring = (size_t)g.B * g.rows_per_head() * g.H * g.D * sizeof(float);
+  // The ring's gradients and the chunk's dK, dV can go out in one launch where nothing that it writes lies over anything
+  // else it writes or reads
+  const Span written[] = {{dk_cache, ring}, {dv_cache, ring}, {dk_chunk, 2 * chunk}, {dv_chunk, 2 * chunk}};
+  const Span read[] = {{dout, chunk}, {v_chunk, chunk}, {workspace, w.total}, {cache->k_storage, g.storage_bytes()}, {cache->v_storage, g.storage_bytes()}};
+  bool joined = dk_chunk && dv_chunk && dout && v_chunk;
+  for (const Span& a : written) {
+    for (const Span& b : written) joined = joined && (&a == &b || !overlap(a, b));
+    for (const Span& b : read) joined = joined && !overlap(a, b);
+  }
   // the detached backward first (it also leaves the row terms the ring-row kernels need) ...
-  const int rc2 = astro_group_attn_bwd(cache, q, k_chunk, v_chunk, out, lse, dout, n_frames, 1, dq, dk_chunk, dv_chunk,
-                                       workspace, workspace_bytes, hip_stream);
+  const int rc2 = group_backward(cache, q, k_chunk, v_chunk, out, lse, dout, n_frames, 1, dq, dk_chunk, dv_chunk, workspace,
+                                 workspace_bytes, hip_stream, &joined);
   if (rc2 != ASTRO_OK) return rc2;
   // ... then dK, dV of the resident ring rows
   char* ws = (char*)workspace;
   AttnOperands op = attn_operands(cache, ws, w, v_chunk, n_frames, 1);
   // dK over dV, or over dout, which the launch reads to its end: dK is what stays, so dV goes out in a launch of
   // its own, and dout is read from a copy where the rotated chunk keys were (done with by now)
-  const RingGeometry& g = cache->geo;
-  const size_t chunk = (size_t)g.B * n_frames * g.T * g.H * g.D * g.elem_bytes();
-  const size_t ring = (size_t)g.B * g.rows_per_head() * g.H * g.D * sizeof(float);
   op.in_order = overlap({dk_cache, ring}, {dv_cache, ring});
   if (overlap({dk_cache, ring}, {dout, chunk})) {
     cache->staged.valid = false;
@@ -497,8 +519,8 @@ int astro_chunk_attn_bwd_full(astro_kvcache_t* cache, const void* q, const void*
     next.v[b] = b < cache->geo.B ? cache->tables.next_n(b) : 0;
     sink_shift.v[b] = b < cache->geo.B && cache->geo.sinks_move() ? cache->tables.evicted(b) : 0;
   }
-  return launch_attn_bwd_hist_bf16(dev_geom(cache), op, lse, dout, dk_cache, dv_cache, start, next, sink_shift, ws + w.scratch,
-                                   (hipStream_t)hip_stream) == hipSuccess
+  return launch_attn_bwd_hist_bf16(dev_geom(cache), op, lse, dout, joined ? dk_chunk : nullptr, joined ? dv_chunk : nullptr,
+                                   dk_cache, dv_cache, start, next, sink_shift, ws + w.scratch, (hipStream_t)hip_stream) == hipSuccess
              ? ASTRO_OK
              : ASTRO_ERR_HIP;
 }

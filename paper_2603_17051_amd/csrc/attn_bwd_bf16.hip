@@ -638,6 +638,29 @@ struct RingGrads {
   StreamInts start, next_n, sink_shift;  // see launch_attn_bwd_hist_bf16
 };
 struct ChunkGrads {};  // the chunk's keys: everything is in BwdParams
+// Both in one launch: a pair's keys are its resident ring rows and then the chunk's, cut into blocks of 128 without regard to
+// where the chunk begins.  Two launches each end with a partly filled round of workgroups (12 pairs, 28080 + 4680 rows: 2640
+// and 444 on 256 CUs, eleven rounds and two, against 3072, twelve: the whole pass 3455 -> 3375 us; D = 64, 16 pairs, 12480 + 3120
+// rows 858 -> 810, 16 pairs of 4200 + 1200 147 -> 126).
+struct AllGrads : RingGrads {};
+template <typename Grads>
+constexpr bool kHasRing = !std::is_same_v<Grads, ChunkGrads>;
+// Row of a key of the launch: of the ring, or (with in_chunk) of the chunk
+struct KeyRow {
+  int row;
+  bool in_chunk;
+};
+template <typename Grads>
+__device__ __forceinline__ int keys_of(int hist, int Nq) {
+  return std::is_same_v<Grads, AllGrads> ? hist + Nq : kHasRing<Grads> ? hist : Nq;
+}
+template <typename Grads>
+__device__ __forceinline__ KeyRow key_row(int j, int hist) {
+  if constexpr (std::is_same_v<Grads, AllGrads>)
+    return j < hist ? KeyRow{j, false} : KeyRow{j - hist, true};
+  else
+    return KeyRow{j, !kHasRing<Grads>};
+}
 
 // (cos, sin) of the temporal pairs at the frames of ring slots first .. first + n - 1 of stream b, for `threads` threads
 __device__ __forceinline__ void fill_slot_table(float2* tab, const BwdParams& p, const RingGrads& r, int b, int first, int n,
@@ -655,7 +678,7 @@ __device__ __forceinline__ void fill_slot_table(float2* tab, const BwdParams& p,
 // stream the tiles and meet at the same barriers, one per period.
 template <int D, bool kKey, typename Grads>
 __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads, const WorkItem& item, int wave, char* lds) {
-  constexpr bool kRing = std::is_same_v<Grads, RingGrads>;
+  constexpr bool kRing = kHasRing<Grads>;
   using L = DkvLds<D>;
   using Wave = std::conditional_t<kKey, KeyWave<D>, ValueWave<D>>;
   const int b = item.bh / p.H, h = item.bh % p.H;
@@ -664,19 +687,22 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
   const int i16 = lane & 15, g = lane >> 4;
   const int64_t bh = (int64_t)b * p.H + h;
   // this lane's two keys jc and jc + 16: chunk rows, or (non-detached backward) resident ring rows of the stream
-  const int n_keys = kRing ? p.hist_rows.v[b] : p.Nq;
+  const int hist = kRing ? p.hist_rows.v[b] : 0, n_keys = keys_of<Grads>(hist, p.Nq);
   const int jc = (item.tile * 4 + kw) * 32 + i16;
   const int ntiles = (p.Nq + QT - 1) / QT;
   // first query row that sees each of this lane's keys (ring rows are seen by every query), the
   // largest over the wave (its last key) and the smallest over the workgroup (its first key)
-  const int block_rows = kRing ? 0 : p.block_rows;
+  auto first_row_seeing = [&](int j) __attribute__((always_inline)) {
+    const KeyRow key = key_row<Grads>(j, hist);
+    return key.in_chunk ? first_query_row_seeing(key.row, p.block_rows) : 0;
+  };
   const int j_last = n_keys - 1;
   int first_q[2];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last, block_rows);
+  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last);
   const int j_wave = (item.tile * 4 + kw) * 32 + 31;
-  const int first_q_wave = first_query_row_seeing(j_wave < j_last ? j_wave : j_last, block_rows);
-  const int t_begin = first_query_row_seeing(item.tile * 128, block_rows) / QT;
+  const int first_q_wave = first_row_seeing(j_wave < j_last ? j_wave : j_last);
+  const int t_begin = first_row_seeing(item.tile * 128) / QT;
 
   Wave w;
   w.init(lane);
@@ -684,12 +710,12 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
   for (int ks = 0; ks < 2; ++ks) {
     // B operand of the role's first product: V row (key wave) or K~ row (value wave) of the lane's key ks
     const bool live = jc + 16 * ks < n_keys;
-    const int j0 = live ? jc + 16 * ks : 0;
+    const KeyRow j0 = key_row<Grads>(live ? jc + 16 * ks : 0, hist);
     const __bf16* row;
     if constexpr (kKey)
-      row = kRing ? p.v_cache + (bh * p.cache_rows + j0) * D : p.v_chunk + (((int64_t)b * p.Nq + j0) * p.H + h) * D;
+      row = j0.in_chunk ? p.v_chunk + (((int64_t)b * p.Nq + j0.row) * p.H + h) * D : p.v_cache + (bh * p.cache_rows + j0.row) * D;
     else
-      row = kRing ? p.k_cache + (bh * p.cache_rows + j0) * D : p.kc_rot + (bh * p.Nq + j0) * D;
+      row = j0.in_chunk ? p.kc_rot + (bh * p.Nq + j0.row) * D : p.k_cache + (bh * p.cache_rows + j0.row) * D;
 #pragma unroll
     for (int st = 0; st < D / 32; ++st) {
       bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -738,9 +764,9 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
   int slot_first = 0, slot_count = 0;
   bool in_slot = true;
   if constexpr (kRing) {
-    const int j_first = item.tile * 128, j_end = j_first + 128 < n_keys ? j_first + 128 : n_keys;
+    const int j_first = item.tile * 128, j_end = j_first + 128 < hist ? j_first + 128 : hist;
     slot_first = j_first / p.rot.T;
-    slot_count = (j_end - 1) / p.rot.T - slot_first + 1;
+    slot_count = j_first < j_end ? (j_end - 1) / p.rot.T - slot_first + 1 : 0;
     static_assert(129 * (D / 2) * 8 <= 3 * L::SLOT_TILES, "the largest table fits the tile ring");
     in_slot = slot_count * p.rot.n_t * (int)sizeof(float2) <= L::SLOT_TILES;
   }
@@ -797,11 +823,12 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
     for (int ks = 0; ks < 2; ++ks) {
       const int j = jc + 16 * ks < j_last ? jc + 16 * ks : j_last;
       TokenTables tt;
-      if constexpr (kRing) {
-        const int slot = j / p.rot.T, rem = j - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
+      const KeyRow key = key_row<Grads>(j, hist);
+      if (!key.in_chunk) {
+        const int slot = key.row / p.rot.T, rem = key.row - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
         tt = TokenTables{slot_tab + (slot - slot_first) * p.rot.n_t, p.rot.tab_h + y * p.rot.n_h, p.rot.tab_w + x * p.rot.n_w};
       } else {
-        tt = token_tables(p.rot, b, j);
+        tt = token_tables(p.rot, b, key.row);
       }
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) angles[ks][dt] = quad_angles(p.rot, tt, 4 * dt + g);
@@ -811,11 +838,10 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
   for (int ks = 0; ks < 2; ++ks) {
     const int j = jc + 16 * ks;
     if (j >= n_keys) continue;
-    float* row;
-    if constexpr (kRing)
-      row = (kKey ? grads.dk : grads.dv) + (((int64_t)b * p.cache_rows + j) * p.H + h) * D;
-    else
-      row = (kKey ? p.dk : p.dv) + (((int64_t)b * p.Nq + j) * p.H + h) * D;
+    const KeyRow key = key_row<Grads>(j, hist);
+    float* row = nullptr;
+    if constexpr (kRing) row = (kKey ? grads.dk : grads.dv) + (((int64_t)b * p.cache_rows + key.row) * p.H + h) * D;
+    if (key.in_chunk) row = (kKey ? p.dk : p.dv) + (((int64_t)b * p.Nq + key.row) * p.H + h) * D;
 #pragma unroll
     for (int dt = 0; dt < D / 16; ++dt) {
       f32x4 x;
@@ -832,13 +858,13 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
 
 template <int D, typename Grads>
 __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams p, Grads grads) {
-  constexpr bool kRing = std::is_same_v<Grads, RingGrads>;
+  constexpr bool kRing = kHasRing<Grads>;
   __shared__ __attribute__((aligned(1024))) char lds[DkvLds<D>::kTotal];
   // one pair's operands through one L2: 183 instead of 202 us at D = 64 (16 heads, 592 workgroups, causal); at D = 128,
   // where a pair's operands alone are half an L2, no gain (1.01 against 1.00 ms at batch 4)
   const WorkItem item = work_item(p.tiles, p.BH, D == 64 && (!kRing || p.by_xcd));
   if (!item.valid) return;
-  const int n_keys = kRing ? p.hist_rows.v[item.bh / p.H] : p.Nq;
+  const int n_keys = keys_of<Grads>(kRing ? p.hist_rows.v[item.bh / p.H] : 0, p.Nq);
   if (item.tile * 128 >= n_keys) return;  // whole workgroup, before any barrier
   // waves 0..3 accumulate dV, waves 4..7 dK; the branch is per wave, and both sides execute
   // the same sequence of barriers
@@ -940,7 +966,7 @@ struct KeyBlockWave {
 // through LDS at the end.
 template <int D, int kHalves, typename Grads>
 __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_dkv_block_kernel(BwdParams p, Grads grads) {
-  constexpr bool kRing = std::is_same_v<Grads, RingGrads>;
+  constexpr bool kRing = kHasRing<Grads>;
   constexpr int TILE_BYTES = QT * D * 2, SLOT_BYTES = 2 * TILE_BYTES, SLOT_TERMS = 2 * QT * 4;
   constexpr int kWaves = 4 * kHalves, kSumBytes = 2 * (D / 16) * 1024;  // one gradient of 32 keys
   // tiles of all slots, then their row terms; alone on a CU a block takes less time than a tile takes to land, so there two are in flight
@@ -950,7 +976,7 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   if (!item.valid) return;
   const int b = item.bh / p.H, h = item.bh % p.H;
   // this lane's two keys jc and jc + 16: chunk rows, or (non-detached backward) resident ring rows of the stream
-  const int n_keys = kRing ? p.hist_rows.v[b] : p.Nq;
+  const int hist = kRing ? p.hist_rows.v[b] : 0, n_keys = keys_of<Grads>(hist, p.Nq);
   if (item.tile * 128 >= n_keys) return;  // whole workgroup, before any barrier
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = wave & 3, half = wave >> 2;
   const int i16 = lane & 15, g = lane >> 4;
@@ -958,12 +984,15 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   const int j_wave = (item.tile * 4 + kw) * 32, jc = j_wave + i16, j_last = n_keys - 1;
   const int ntiles = (p.Nq + QT - 1) / QT;
   // as in dkv_wave()
-  const int block_rows = kRing ? 0 : p.block_rows;
+  auto first_row_seeing = [&](int j) __attribute__((always_inline)) {
+    const KeyRow key = key_row<Grads>(j, hist);
+    return key.in_chunk ? first_query_row_seeing(key.row, p.block_rows) : 0;
+  };
   int first_q[2];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last, block_rows);
-  const int first_q_wave = first_query_row_seeing(j_wave + 31 < j_last ? j_wave + 31 : j_last, block_rows);
-  const int t_begin = first_query_row_seeing(item.tile * 128, block_rows) / QT;
+  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last);
+  const int first_q_wave = first_row_seeing(j_wave + 31 < j_last ? j_wave + 31 : j_last);
+  const int t_begin = first_row_seeing(item.tile * 128) / QT;
 
   const RowSegment q_rows = make_segment(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
   const RowSegment do_rows = make_segment(p.dout + ((int64_t)b * p.Nq * p.H + h) * D, (int64_t)p.H * D, p.Nq, D);
@@ -991,9 +1020,9 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     const bool live = jc + 16 * ks < n_keys;
-    const int j0 = live ? jc + 16 * ks : 0;
-    const __bf16* krow = kRing ? p.k_cache + (bh * p.cache_rows + j0) * D : p.kc_rot + (bh * p.Nq + j0) * D;
-    const __bf16* vrow = kRing ? p.v_cache + (bh * p.cache_rows + j0) * D : p.v_chunk + (((int64_t)b * p.Nq + j0) * p.H + h) * D;
+    const KeyRow j0 = key_row<Grads>(live ? jc + 16 * ks : 0, hist);
+    const __bf16* krow = j0.in_chunk ? p.kc_rot + (bh * p.Nq + j0.row) * D : p.k_cache + (bh * p.cache_rows + j0.row) * D;
+    const __bf16* vrow = j0.in_chunk ? p.v_chunk + (((int64_t)b * p.Nq + j0.row) * p.H + h) * D : p.v_cache + (bh * p.cache_rows + j0.row) * D;
 #pragma unroll
     for (int st = 0; st < D / 32; ++st) {
       bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0}, y = x;
@@ -1063,31 +1092,26 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   const float2* slot_tab = nullptr;
   int slot_first = 0;
   if constexpr (kRing) {
-    const int j_first = item.tile * 128, j_end = j_first + 128 < n_keys ? j_first + 128 : n_keys;
+    const int j_first = item.tile * 128, j_end = j_first + 128 < hist ? j_first + 128 : hist;
     static_assert(129 * (D / 2) * 8 <= sizeof lds, "the largest table fits");
     slot_first = j_first / p.rot.T;
     slot_tab = reinterpret_cast<const float2*>(lds);
-    fill_slot_table(reinterpret_cast<float2*>(lds), p, grads, b, slot_first, (j_end - 1) / p.rot.T - slot_first + 1, threadIdx.x, kWaves * 64);
+    fill_slot_table(reinterpret_cast<float2*>(lds), p, grads, b, slot_first, j_first < j_end ? (j_end - 1) / p.rot.T - slot_first + 1 : 0, threadIdx.x, kWaves * 64);
     __syncthreads();
   }
   // all look-ups before the first store, as in dkv_wave()
-  float *dk_to, *dv_to;
-  if constexpr (kRing)
-    dk_to = grads.dk, dv_to = grads.dv;
-  else
-    dk_to = p.dk, dv_to = p.dv;
-  const int64_t rows = kRing ? p.cache_rows : p.Nq;
   QuadAngles angles[2][D / 16];
   if (rope && has_dk) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       const int j = jc + 16 * ks < j_last ? jc + 16 * ks : j_last;
       TokenTables tt;
-      if constexpr (kRing) {
-        const int slot = j / p.rot.T, rem = j - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
+      const KeyRow key = key_row<Grads>(j, hist);
+      if (!key.in_chunk) {
+        const int slot = key.row / p.rot.T, rem = key.row - slot * p.rot.T, y = rem / p.rot.gw, x = rem - y * p.rot.gw;
         tt = TokenTables{slot_tab + (slot - slot_first) * p.rot.n_t, p.rot.tab_h + y * p.rot.n_h, p.rot.tab_w + x * p.rot.n_w};
       } else {
-        tt = token_tables(p.rot, b, j);
+        tt = token_tables(p.rot, b, key.row);
       }
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) angles[ks][dt] = quad_angles(p.rot, tt, 4 * dt + g);
@@ -1097,7 +1121,11 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   for (int ks = 0; ks < 2; ++ks) {
     const int j = jc + 16 * ks;
     if (j >= n_keys) continue;
-    const int64_t at = (((int64_t)b * rows + j) * p.H + h) * D + 4 * g;
+    const KeyRow key = key_row<Grads>(j, hist);
+    float *dk_to = p.dk, *dv_to = p.dv;
+    if constexpr (kRing)
+      if (!key.in_chunk) dk_to = grads.dk, dv_to = grads.dv;
+    const int64_t at = (((int64_t)b * (key.in_chunk ? p.Nq : p.cache_rows) + key.row) * p.H + h) * D + 4 * g;
     if (has_dv && (!kRing || dv_to)) {
 #pragma unroll
       for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<f32x4*>(dv_to + at + 16 * dt) = w.dv[dt][ks];
@@ -1626,7 +1654,7 @@ constexpr int kDqPlaces = dq_places_per_cu(D);
 
 template <int D>
 hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, const float* lse, const void* dout,
-                  float* dq, float* dk, float* dv, void* scratch, hipStream_t stream) {
+                  float* dq, float* dk, float* dv, void* scratch, bool keys_later, hipStream_t stream) {
   BwdParams p = make_params<D>(g, op, out, lse, dout, dq, dk, dv, scratch);
   const CallShape shape = call_shape(g, op);
   if (const int waves = bwd_few_waves(shape)) {
@@ -1668,7 +1696,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
       dq_merge_kernel<D, 3><<<grid, 256, 0, stream>>>(p, split, n_quads);
   }
   const int ktile = 128;
-  {
+  if (!keys_later) {
     ProfileScope prof("attn_bwd_dkv_bf16", stream);
     p.tiles = (op.Nq + ktile - 1) / ktile;
     launch_dkv<D>(p, ChunkGrads{}, g.n_cus, stream);
@@ -1677,20 +1705,22 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
 }
 
 template <int D>
-hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* lse, const void* dout, const RingGrads& grads,
-                       const void* scratch, hipStream_t stream) {
-  BwdParams p = make_params<D>(g, op, nullptr, lse, dout, nullptr, nullptr, nullptr, const_cast<void*>(scratch));
+hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* lse, const void* dout, float* dk, float* dv,
+                       const RingGrads& grads, const void* scratch, hipStream_t stream) {
+  BwdParams p = make_params<D>(g, op, nullptr, lse, dout, nullptr, dk, dv, const_cast<void*>(scratch));
   int max_hist = 0;
   for (int b = 0; b < g.B; ++b) max_hist = op.hist_rows.v[b] > max_hist ? op.hist_rows.v[b] : max_hist;
   if (max_hist == 0) return hipSuccess;
   const int ktile = 128;
-  p.tiles = (max_hist + ktile - 1) / ktile;
+  p.tiles = (max_hist + (dk ? op.Nq : 0) + ktile - 1) / ktile;
   p.by_xcd = order_by_xcd(call_shape(g, op), work_grid_size(p.tiles, p.BH));
-  auto run = [&](const RingGrads& to) {
+  auto run = [&](const auto& to) {
     ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
     launch_dkv<D>(p, to, g.n_cus, stream);
   };
-  if (op.in_order) {  // dV and dK share bytes, dK's stay: one after the other
+  if (dk) {
+    run(AllGrads{grads});
+  } else if (op.in_order) {  // dV and dK share bytes, dK's stay: one after the other
     RingGrads one = grads;
     one.dk = nullptr;
     run(one);
@@ -1706,22 +1736,27 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
 }  // namespace
 
 hipError_t launch_attn_bwd_hist_bf16(const DevGeom& g, const AttnOperands& op, const float* lse, const void* dout,
-                                     float* dk_hist, float* dv_hist, const StreamInts& start, const StreamInts& next_n,
-                                     const StreamInts& sink_shift, const void* scratch, hipStream_t stream) {
+                                     float* dk, float* dv, float* dk_hist, float* dv_hist, const StreamInts& start,
+                                     const StreamInts& next_n, const StreamInts& sink_shift, const void* scratch, hipStream_t stream) {
   if (op.group != 1) return hipErrorInvalidValue;
   const RingGrads grads{dk_hist, dv_hist, g.inv_freq_t, g.C, g.S, start, next_n, sink_shift};
-  if (g.D == 128) return launch_hist<128>(g, op, lse, dout, grads, scratch, stream);
-  return launch_hist<64>(g, op, lse, dout, grads, scratch, stream);
+  if (g.D == 128) return launch_hist<128>(g, op, lse, dout, dk, dv, grads, scratch, stream);
+  return launch_hist<64>(g, op, lse, dout, dk, dv, grads, scratch, stream);
+}
+
+bool bf16_bwd_joins(const DevGeom& g, const AttnOperands& op) {
+  const CallShape c = call_shape(g, op);
+  return !op.in_order && c.max_hist > 0 && bwd_few_waves(c) == 0;
 }
 
 // Delta and LSE*log2e per (stream, head, query)
 size_t bf16_bwd_workspace_bytes(const DevGeom& g, int Nq) { return 2 * (size_t)g.B * g.H * Nq * sizeof(float); }
 
 hipError_t launch_attn_bwd_bf16(const DevGeom& g, const AttnOperands& op, const void* out, const float* lse,
-                                const void* dout, float* dq, float* dk, float* dv, void* scratch,
+                                const void* dout, float* dq, float* dk, float* dv, void* scratch, bool keys_later,
                                 hipStream_t stream) {
-  if (g.D == 128) return launch<128>(g, op, out, lse, dout, dq, dk, dv, scratch, stream);
-  return launch<64>(g, op, out, lse, dout, dq, dk, dv, scratch, stream);
+  if (g.D == 128) return launch<128>(g, op, out, lse, dout, dq, dk, dv, scratch, keys_later, stream);
+  return launch<64>(g, op, out, lse, dout, dq, dk, dv, scratch, keys_later, stream);
 }
 
 }  // namespace astro

@@ -129,15 +129,17 @@ size_t bf16_bwd_workspace_bytes(const DevGeom& g, int Nq);  // beyond q_rot / kc
 // their epilogues with the tables of `g` and op.tab_t)
 hipError_t launch_attn_bwd_bf16(const DevGeom& g, const AttnOperands& op, const void* out,
                                 const float* lse, const void* dout, float* dq, float* dk,
-                                float* dv, void* scratch, hipStream_t stream);
+                                float* dv, void* scratch, bool keys_later, hipStream_t stream);
 // Gradients of the ring rows (the non-detached backward): dk_hist, dv_hist [B, C*T, H, D] w.r.t. the
 // keys as they were appended (un-rotated) and the values; rows of empty slots are not written.  The
 // frame a slot holds follows from start and next_n (frames appended); sink_shift.v[b] = how far ahead
 // of their own frame index stream b's sink slots are rotated (0 with absolute positions).  Needs
 // the row terms launch_attn_bwd_bf16 left in `scratch` (same call sequence, same stream);
-// group must be 1.
+// group must be 1.  dk, dv: the chunk's, where launch_attn_bwd_bf16 was told to leave them to this launch (keys_later, which
+// bf16_bwd_joins has to allow), else null.
+bool bf16_bwd_joins(const DevGeom& g, const AttnOperands& op);
 hipError_t launch_attn_bwd_hist_bf16(const DevGeom& g, const AttnOperands& op, const float* lse,
-                                     const void* dout, float* dk_hist, float* dv_hist, const StreamInts& start,
+                                     const void* dout, float* dk, float* dv, float* dk_hist, float* dv_hist, const StreamInts& start,
                                      const StreamInts& next_n, const StreamInts& sink_shift, const void* scratch,
                                      hipStream_t stream);
 

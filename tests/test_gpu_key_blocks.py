@@ -1,6 +1,7 @@
-"""dK and dV at D = 64 where one wave holds both gradients of its keys (launches of more than half a workgroup per CU): chunk
-and ring launches with one and with two waves to a block of keys, at the edges of key blocks, query tiles and causal blocks,
-against the fp64 oracle; the gates hold for each gradient over all its heads."""
+"""The non-detached backward's dK and dV where ring and chunk go out in one launch (not taken by the kernels for few rows), at D =
+64 with one and with two waves that hold both gradients of a block of keys, at the edges of key blocks, query tiles, causal blocks
+and of the ring, against the fp64 oracle (the gates hold for each gradient over all its heads); at D = 128 the
+chunk's are those of the detached backward, whose launch has the chunk only, bit for bit."""
 import numpy as np
 import pytest
 
@@ -25,21 +26,45 @@ pytestmark = pytest.mark.gpu
     (1, 129, 1, 1, 100, 0, 1, 0, 70), # ring 129 workgroups of one-token frames: the table of frames behind the walk
 ])
 def test_both_gradients_in_one_wave(B, H, gh, gw, C, S, Fc, bf, streamed):
-    D, T = 64, gh * gw
-    w = wl.Workload("key_blocks", 57, B, H, D, gh, gw, C, S, Fc, streamed, (12, 10, 10))
+    check(64, (12, 10, 10), B, H, gh, gw, C, S, Fc, bf, streamed)
+
+
+@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only", [
+    (2, 73, 3, 11, 2, 0, 1, 0, 3, 2),    # one block of 66 ring and 33 chunk rows
+    (2, 73, 1, 43, 3, 1, 2, 1, 5, 2),    # the chunk begins inside the second block, causal blocks
+    (2, 73, 8, 8, 2, 0, 1, 0, 2, 2),     # ... at a block
+    (3, 49, 6, 7, 4, 1, 2, 1, 6, 2),     # streams of different lengths: the last one is empty
+    (1, 146, 7, 9, 3, 1, 1, 0, 0, 1),    # nothing resident: a launch of its own
+])
+def test_ring_and_chunk_in_one_launch(B, H, gh, gw, C, S, Fc, bf, streamed, only):
+    check(128, (22, 21, 21), B, H, gh, gw, C, S, Fc, bf, streamed, only)
+
+
+def check(D, pairs, B, H, gh, gw, C, S, Fc, bf, streamed, only=None):
+    """`only`: streams with history, all by default"""
+    T = gh * gw
+    w = wl.Workload("key_blocks", 57, B, H, D, gh, gw, C, S, Fc, streamed, pairs)
     ls = Lockstep(w, max_chunk=Fc, start_frames=[3 + 100 * b for b in range(B)], block_frames=bf)
     _fill_history(ls, w, *wl.history_frame_pool(w, 7), streamed)
+    n = [streamed if only is None or b < only else 0 for b in range(B)]
+    for b in range(B):
+        if n[b] != streamed:
+            ls.A.astro_kvcache_reset(ls.cache, b, 3 + 100 * b)
+            ls.oracle.reset(b, 3 + 100 * b)
     q, k, v, do = wl.chunk_inputs(w, with_dout=True)
     out, lse = ls.fwd(q, k, v, Fc)
     _, dk, dv, dkc, dvc = ls.A.astro_chunk_attn_bwd_full(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
+    detached = ls.A.astro_chunk_attn_bwd(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
+    if D == 128:  # (at D = 64 the two launches may have another number of waves to a block, which sum in another order)
+        assert (dk == detached[1]).all() and (dv == detached[2]).all()
     _, rk, rv, extra = ls.oracle.attn_bwd(*[ls.wide(x) for x in (q, k, v, do)], Fc, history_grads=True)
     assert_bf16_close(host_f64(dk), rk, "dk")
     assert_bf16_close(host_f64(dv), rv, "dv")
     ref_k, ref_v = np.zeros((B, C * T, H, D)), np.zeros((B, C * T, H, D))
     for b in range(B):
-        for i, n in enumerate(visible_history(streamed, S, C - S)):
-            rows = slice(_slot(n, C, S) * T, (_slot(n, C, S) + 1) * T)
-            phi = rope_angles(ls.oracle.start[b] + n, gh, gw, w.rope_pairs, w.rope_base)
+        for i, f in enumerate(visible_history(n[b], S, C - S)):
+            rows = slice(_slot(f, C, S) * T, (_slot(f, C, S) + 1) * T)
+            phi = rope_angles(ls.oracle.start[b] + f, gh, gw, w.rope_pairs, w.rope_base)
             for h in range(H):
                 ref_k[b, rows, h] = rope_rotate(extra[(b, h)]["dk_hist_rot"][i * T:(i + 1) * T, None, :], -phi)[:, 0]
                 ref_v[b, rows, h] = extra[(b, h)]["dv_hist"][i * T:(i + 1) * T]
