@@ -860,8 +860,8 @@ template <int D, typename Grads>
 __global__ void __launch_bounds__(kPairThreads, 1) attn_bwd_dkv_kernel(BwdParams p, Grads grads) {
   constexpr bool kRing = kHasRing<Grads>;
   __shared__ __attribute__((aligned(1024))) char lds[DkvLds<D>::kTotal];
-  // one pair's operands through one L2: 183 instead of 202 us at D = 64 (16 heads, 592 workgroups, causal); at D = 128,
-  // where a pair's operands alone are half an L2, no gain (1.01 against 1.00 ms at batch 4)
+  // one pair's operands through one L2: 183 instead of 202 us at D = 64 (16 heads, 592 workgroups, causal, which take the
+  // kernel below now); at D = 128, where a pair's operands alone are half an L2, no gain (1.01 against 1.00 ms at batch 4)
   const WorkItem item = work_item(p.tiles, p.BH, D == 64 && (!kRing || p.by_xcd));
   if (!item.valid) return;
   const int n_keys = keys_of<Grads>(kRing ? p.hist_rows.v[item.bh / p.H] : 0, p.Nq);

@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(kWaves * 64, OCC) attn_fwd_bf16_kernel(FwdPara
 // waves' unnormalised results are combined through LDS at the end.  Against the key split over
 // workgroups that needs no second launch, and partial results stay fp32.  What bounds it: a CU pulls
 // 16 KB of tiles (D = 128) per 32 keys for 32 queries, about 0.18 us at the 40 B per clock and CU these
-// loads reach; calls of a few tiles are the chain launch, operand loads, tile, combine (7 us).
+// loads reach; calls of a few tiles are the chain launch, operand loads, tile, combine (5 us).
 // The first tile's reference is tried at 0 (init_zero_ref): a wave walks few tiles, so recomputing the
 // first one's scores for its maximum, as the general kernel does, would be a large part of the work.
 //
