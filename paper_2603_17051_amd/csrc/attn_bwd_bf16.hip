@@ -639,7 +639,8 @@ struct RingGrads {
 };
 struct ChunkGrads {};  // the chunk's keys: everything is in BwdParams
 // Both in one launch: a pair's keys are its resident ring rows and then the chunk's, cut into blocks of 128 without regard to
-// where the chunk begins.  Two launches each end with a partly filled round of workgroups (12 pairs, 28080 + 4680 rows: 2640
+// where the chunk begins, and every query sees all of them: under causal blocks a block of both would take its chunk rows
+// past queries that do not see them, where a gradient that is not finite leaves 0 * inf in theirs.  Two launches each end with a partly filled round of workgroups (12 pairs, 28080 + 4680 rows: 2640
 // and 444 on 256 CUs, eleven rounds and two, against 3072, twelve: the whole pass 3455 -> 3375 us; D = 64, 16 pairs, 12480 + 3120
 // rows 858 -> 810, 16 pairs of 4200 + 1200 147 -> 126).
 struct AllGrads : RingGrads {};
@@ -690,19 +691,16 @@ __device__ __forceinline__ void dkv_wave(const BwdParams& p, const Grads& grads,
   const int hist = kRing ? p.hist_rows.v[b] : 0, n_keys = keys_of<Grads>(hist, p.Nq);
   const int jc = (item.tile * 4 + kw) * 32 + i16;
   const int ntiles = (p.Nq + QT - 1) / QT;
-  // first query row that sees each of this lane's keys (ring rows are seen by every query), the
-  // largest over the wave (its last key) and the smallest over the workgroup (its first key)
-  auto first_row_seeing = [&](int j) __attribute__((always_inline)) {
-    const KeyRow key = key_row<Grads>(j, hist);
-    return key.in_chunk ? first_query_row_seeing(key.row, p.block_rows) : 0;
-  };
+  // first query row that sees each of this lane's keys (ring rows and what goes out with them are seen by every query),
+  // the largest over the wave (its last key) and the smallest over the workgroup (its first key)
+  const int block_rows = kRing ? 0 : p.block_rows;
   const int j_last = n_keys - 1;
   int first_q[2];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last);
+  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last, block_rows);
   const int j_wave = (item.tile * 4 + kw) * 32 + 31;
-  const int first_q_wave = first_row_seeing(j_wave < j_last ? j_wave : j_last);
-  const int t_begin = first_row_seeing(item.tile * 128) / QT;
+  const int first_q_wave = first_query_row_seeing(j_wave < j_last ? j_wave : j_last, block_rows);
+  const int t_begin = first_query_row_seeing(item.tile * 128, block_rows) / QT;
 
   Wave w;
   w.init(lane);
@@ -984,15 +982,12 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   const int j_wave = (item.tile * 4 + kw) * 32, jc = j_wave + i16, j_last = n_keys - 1;
   const int ntiles = (p.Nq + QT - 1) / QT;
   // as in dkv_wave()
-  auto first_row_seeing = [&](int j) __attribute__((always_inline)) {
-    const KeyRow key = key_row<Grads>(j, hist);
-    return key.in_chunk ? first_query_row_seeing(key.row, p.block_rows) : 0;
-  };
+  const int block_rows = kRing ? 0 : p.block_rows;
   int first_q[2];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last);
-  const int first_q_wave = first_row_seeing(j_wave + 31 < j_last ? j_wave + 31 : j_last);
-  const int t_begin = first_row_seeing(item.tile * 128) / QT;
+  for (int ks = 0; ks < 2; ++ks) first_q[ks] = first_query_row_seeing(jc + 16 * ks < j_last ? jc + 16 * ks : j_last, block_rows);
+  const int first_q_wave = first_query_row_seeing(j_wave + 31 < j_last ? j_wave + 31 : j_last, block_rows);
+  const int t_begin = first_query_row_seeing(item.tile * 128, block_rows) / QT;
 
   const RowSegment q_rows = make_segment(p.q_rot + bh * p.Nq * D, D, p.Nq, D);
   const RowSegment do_rows = make_segment(p.dout + ((int64_t)b * p.Nq * p.H + h) * D, (int64_t)p.H * D, p.Nq, D);
@@ -1746,7 +1741,7 @@ hipError_t launch_attn_bwd_hist_bf16(const DevGeom& g, const AttnOperands& op, c
 
 bool bf16_bwd_joins(const DevGeom& g, const AttnOperands& op) {
   const CallShape c = call_shape(g, op);
-  return !op.in_order && c.max_hist > 0 && bwd_few_waves(c) == 0;
+  return !op.in_order && c.block_rows == 0 && c.max_hist > 0 && bwd_few_waves(c) == 0;
 }
 
 // Delta and LSE*log2e per (stream, head, query)

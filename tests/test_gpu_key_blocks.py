@@ -74,3 +74,25 @@ def check(D, pairs, B, H, gh, gw, C, S, Fc, bf, streamed, only=None):
     else:
         assert (dkc == 0).all() and (dvc == 0).all()
     ls.close()
+
+
+@pytest.mark.parametrize("D,pairs,B,H", [(64, (12, 10, 10), 2, 65), (128, (22, 21, 21), 1, 73)])
+def test_a_gradient_that_is_not_finite_reaches_the_same_chunk_keys_as_detached(D, pairs, B, H):
+    """Causal frames of 65 tokens behind one resident: no key of the second block of 128 chunk rows is seen by the first tile of
+    queries.  Where a query of that tile has infinite output gradients, theirs stay what they are without it."""
+    Fc, T, C = 3, 65, 3
+    w = wl.Workload("not_finite", 58, B, H, D, 5, 13, C, 0, Fc, 1, pairs)
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[3 + b for b in range(B)], block_frames=1)
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), 1)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    dev = [ls.dev(x) for x in (q, k, v)]
+    out, lse = ls.fwd(q, k, v, Fc)
+    dout = ls.dev(do)
+    clean = ls.A.astro_chunk_attn_bwd(ls.cache, *dev, out, lse, dout, Fc)
+    dout[:, 10] = float("inf")
+    detached = ls.A.astro_chunk_attn_bwd(ls.cache, *dev, out, lse, dout, Fc)
+    full = ls.A.astro_chunk_attn_bwd_full(ls.cache, *dev, out, lse, dout, Fc)
+    for kept, got, want in zip(clean[1:], full[1:3], detached[1:]):
+        assert (got.isfinite() == want.isfinite()).all()
+        assert got[:, 2 * T:].equal(kept[:, 2 * T:]) and not got[:, :T].isfinite().any()
+    ls.close()
