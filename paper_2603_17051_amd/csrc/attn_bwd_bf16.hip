@@ -1136,10 +1136,10 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   }
 }
 
-// the dK / dV launch of p.tiles blocks of 128 keys per pair
+// the dK / dV launch of p.tiles blocks of 128 keys per pair, by the kernel that dkv_halves() says
 template <int D, typename Grads>
-void launch_dkv(const BwdParams& p, const Grads& grads, int n_cus, hipStream_t stream) {
-  const int workgroups = work_grid_size(p.tiles, p.BH), halves = dkv_halves(D, n_cus, workgroups);
+void launch_dkv(const BwdParams& p, const Grads& grads, int halves, hipStream_t stream) {
+  const int workgroups = work_grid_size(p.tiles, p.BH);
   if constexpr (D == 64) {
     if (halves == 1)
       attn_bwd_dkv_block_kernel<D, 1><<<dim3(workgroups), 256, 0, stream>>>(p, grads);
@@ -1694,7 +1694,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   if (!keys_later) {
     ProfileScope prof("attn_bwd_dkv_bf16", stream);
     p.tiles = (op.Nq + ktile - 1) / ktile;
-    launch_dkv<D>(p, ChunkGrads{}, g.n_cus, stream);
+    launch_dkv<D>(p, ChunkGrads{}, dkv_halves(shape, chunk_blocks(shape)), stream);
   }
   return hipGetLastError();
 }
@@ -1708,10 +1708,12 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   if (max_hist == 0) return hipSuccess;
   const int ktile = 128;
   p.tiles = (max_hist + (dk ? op.Nq : 0) + ktile - 1) / ktile;
-  p.by_xcd = order_by_xcd(call_shape(g, op), work_grid_size(p.tiles, p.BH));
+  const CallShape shape = call_shape(g, op);
+  p.by_xcd = order_by_xcd(shape, work_grid_size(p.tiles, p.BH));
+  const int halves = dkv_halves(shape, dk ? shape.joint_blocks : shape.ring_blocks);
   auto run = [&](const auto& to) {
     ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
-    launch_dkv<D>(p, to, g.n_cus, stream);
+    launch_dkv<D>(p, to, halves, stream);
   };
   if (dk) {
     run(AllGrads{grads});

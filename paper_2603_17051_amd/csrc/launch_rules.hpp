@@ -7,6 +7,8 @@
 
 namespace astro {
 
+inline int blocks_of(int rows, int block) { return (rows + block - 1) / block; }
+
 // What the rules look at of one call.
 struct CallShape {
   int D, n_cus;
@@ -16,6 +18,7 @@ struct CallShape {
   double mean_hist;
   double xcd_load;  // key rows in the heaviest contiguous eighth of the workgroups over the mean eighth's
   bool in_order;    // see AttnOperands::in_order
+  int ring_blocks, joint_blocks;  // blocks of 128 keys over all pairs: of resident rows, of resident and then chunk rows
 };
 
 // xcd_load of streams with these many key rows each
@@ -35,20 +38,21 @@ inline double heaviest_eighth(const int32_t* hist, int streams, int Nq) {
 }
 
 inline CallShape make_call_shape(int D, int n_cus, int pairs, int Nq, int block_rows, bool in_order, const int32_t* hist, int streams) {
-  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], 0., 1., in_order};
+  CallShape c{D, n_cus, pairs, Nq, block_rows, hist[0], 0., 1., in_order, 0, 0};
   int64_t sum = 0;
   bool even = true;
   for (int b = 0; b < streams; ++b) {
     c.max_hist = hist[b] > c.max_hist ? hist[b] : c.max_hist;
     even = even && hist[b] == hist[0];
     sum += hist[b];
+    c.ring_blocks += pairs / streams * blocks_of(hist[b], 128);
+    c.joint_blocks += pairs / streams * blocks_of(hist[b] + Nq, 128);
   }
   c.mean_hist = (double)sum / streams;
   if (!even) c.xcd_load = heaviest_eighth(hist, streams, Nq);
   return c;
 }
 
-inline int blocks_of(int rows, int block) { return (rows + block - 1) / block; }
 
 // keys a query sees, over all streams and, under causal blocks, over the chunk
 inline double mean_keys(const CallShape& c) {
@@ -242,7 +246,8 @@ inline bool bwd_terms_first(const CallShape& c) {
   return c.D == 128 ? c.Nq >= 384 && c.max_hist < 3 * (int64_t)c.Nq : c.Nq >= 512 && c.max_hist < 2 * (int64_t)c.Nq;
 }
 
-// Which kernel a dK / dV launch of so many workgroups takes: 0 = a pair of waves per block of 32 keys (roles), 1 or 2 = that
+// Which kernel a dK / dV launch over so many blocks of 128 keys takes (blocks with keys: workgroups past the end of a shorter stream
+// return at once): 0 = a pair of waves per block of 32 keys (roles), 1 or 2 = that
 // many waves with both gradients each.  At D = 64 one wave holds both; three such workgroups share a CU where a workgroup
 // of roles has it alone, so full launches gain.  Where each CU has one workgroup at most, two waves per block share the
 // queries, and below half of that the roles, whose table of ring frames is computed beside the last tile, end their short
@@ -250,9 +255,10 @@ inline bool bwd_terms_first(const CallShape& c) {
 //   one wave: ring of 8 frames, 2112 workgroups, 950 / 858, chunk of 2368 3157 / 3002, 592 in causal blocks 1126 / 1107, 540
 //             313 / 290, 315 205 / 194; lost: 240 144 / 156
 //   two waves: 240 143 / 141; lost: 120 34.9 / 35.4, 28 36.4 / 38.0, 21 29.3 / 30.7
-inline int dkv_halves(int D, int n_cus, int workgroups) {
-  return D == 128 || 2 * workgroups <= n_cus ? 0 : workgroups <= n_cus ? 2 : 1;
+inline int dkv_halves(const CallShape& c, int blocks) {
+  return c.D == 128 || 2 * blocks <= c.n_cus ? 0 : blocks <= c.n_cus ? 2 : 1;
 }
+inline int chunk_blocks(const CallShape& c) { return blocks_of(c.Nq, 128) * c.pairs; }
 
 // dQ workgroups a CU holds: 244 registers (split 256), or 165 (split 168, 8 more in scratch)
 constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }

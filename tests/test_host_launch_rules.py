@@ -7,7 +7,8 @@ from collections import namedtuple
 
 import pytest
 
-Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries terms_first", defaults=[1, 0, 0])
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries terms_first dkv_chunk dkv_ring",
+                  defaults=[1, 0, 0, 0, 0])
 
 
 @pytest.fixture(scope="module")
@@ -134,3 +135,11 @@ def test_row_terms_of_a_backward_with_few_rows_come_first_for_long_chunks_over_s
     for call, want in [((128, 3, 672, 448), 1), ((128, 3, 384, 1151), 1), ((128, 3, 384, 1152), 0), ((128, 3, 383, 0), 0),
                        ((64, 3, 512, 1023), 1), ((64, 3, 512, 1024), 0), ((64, 3, 511, 0), 0), ((64, 1, 2048, [0, 5000]), 0)]:
         assert rules(*call).bwd_few and rules(*call).terms_first == want, call
+
+
+def test_key_blocks_of_shorter_streams_do_not_count(rules):
+    """A ring launch's kernel goes by the blocks that have keys: one long stream among empty ones is a few workgroups, whatever
+    the grid (16 pairs of 64, 2340 rows in one stream of eight, 19 blocks each)."""
+    assert rules(64, 16, 260, [2340] + [0] * 7).dkv_ring == 0
+    assert rules(64, 16, 260, [2340] * 8).dkv_ring == 1
+    assert rules(64, 24, 2080, [4160] + [1] * 7).dkv_ring == rules(64, 3, 2080, [4160 + 7 * 128]).dkv_ring
