@@ -247,16 +247,20 @@ inline bool bwd_terms_first(const CallShape& c) {
 }
 
 // Which kernel a dK / dV launch over so many blocks of 128 keys takes (blocks with keys: workgroups past the end of a shorter stream
-// return at once): 0 = a pair of waves per block of 32 keys (roles), 1 or 2 = that
-// many waves with both gradients each.  At D = 64 one wave holds both; three such workgroups share a CU where a workgroup
-// of roles has it alone, so full launches gain.  Where each CU has one workgroup at most, two waves per block share the
-// queries, and below half of that the roles, whose table of ring frames is computed beside the last tile, end their short
-// chains earlier.  Measured (us, roles / both; the whole forward and backward, or with the ring's gradients, D = 64):
-//   one wave: ring of 8 frames, 2112 workgroups, 950 / 858, chunk of 2368 3157 / 3002, 592 in causal blocks 1126 / 1107, 540
-//             313 / 290, 315 205 / 194; lost: 240 144 / 156
-//   two waves: 240 143 / 141; lost: 120 34.9 / 35.4, 28 36.4 / 38.0, 21 29.3 / 30.7
-inline int dkv_halves(const CallShape& c, int blocks) {
-  return c.D == 128 || 2 * blocks <= c.n_cus ? 0 : blocks <= c.n_cus ? 2 : 1;
+// return at once): 0 = a pair of waves per block of 32 keys (roles), 1 or 2 = that many waves with both gradients each.  At D = 64
+// one wave holds both; three such workgroups share a CU where a workgroup of roles has it alone, so launches of more than one to a
+// CU gain.  Up to there two waves per block share the queries, and it is the length of the walk that decides: the roles' epilogue is
+// shorter, and with ring rows their table of frames is computed beside the last tile.  Measured (us of the launch, D = 64; tiles of 64
+// queries, roles / two waves / one wave, the same at 17 and at 255 workgroups within a tenth):
+//   chunk: 7 tiles 15.8 / 16.9 / 19.4, 8 19.0 / 19.6, 10 20.9 / 21.1, 12 22.9 / 22.7, 14 24.5 / 24.2, 16 26.6 / 26.0, 20 30.1 / 28.9, 25 35.4 / 33.8 / 44.7, 28 37.4 / 35.2,
+//          34 42.4 / 39.9 / 55.8
+//   ring:  2 11.2 / 13.2 / 12.5, 4 13.2 / 15.2 / 15.8, 8 17.2 / 18.8 / 19.8, 12 20.8 / 22.0 / 24.3, 16 24.3 / 25.5 / 28.8, 20 27.8 / 28.7 / 33.5, 24 31.6 / 32.2 / 37.9,
+//          74 78.5 / 76.2
+//   more than one to a CU: 7 tiles, 288 workgroups 27.9 / 29.8 / 24.7, 34 tiles, 272 77.9 / 72.9 / 65.3, 340 79.5 / 73.5 / 66.6
+inline int dkv_halves(const CallShape& c, int blocks, bool ring) {
+  if (c.D == 128) return 0;
+  if (blocks > c.n_cus) return 1;
+  return blocks_of(c.Nq, 64) >= (ring ? 32 : 12) ? 2 : 0;
 }
 inline int chunk_blocks(const CallShape& c) { return blocks_of(c.Nq, 128) * c.pairs; }
 
