@@ -967,8 +967,9 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   constexpr bool kRing = kHasRing<Grads>;
   constexpr int TILE_BYTES = QT * D * 2, SLOT_BYTES = 2 * TILE_BYTES, SLOT_TERMS = 2 * QT * 4;
   constexpr int kWaves = 4 * kHalves, kSumBytes = 2 * (D / 16) * 1024;  // one gradient of 32 keys
-  // tiles of all slots, then their row terms; alone on a CU a block takes less time than a tile takes to land, so there two are in flight
-  constexpr int kSlots = kHalves + 1, kTerms = kSlots * SLOT_BYTES, kTileBytes = kTerms + kSlots * SLOT_TERMS;
+  // Two tiles, then their row terms.  (A third slot gains nothing here: the compiler cannot tell which LDS the loads of a step write
+  // and waits for them in front of its first transposing read, so a tile has half a block's time to land either way.)
+  constexpr int kTerms = 2 * SLOT_BYTES, kTileBytes = kTerms + 2 * SLOT_TERMS;
   __shared__ __attribute__((aligned(1024))) char lds[kHalves == 1 || kTileBytes > 8 * kSumBytes ? kTileBytes : 8 * kSumBytes];
   const WorkItem item = work_item(p.tiles, p.BH, !kRing || p.by_xcd);
   if (!item.valid) return;
@@ -1006,9 +1007,7 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
       __builtin_amdgcn_raw_ptr_buffer_load_lds(term_rows, (lds_ptr)(lds + kTerms + slot * SLOT_TERMS + wave * QT * 4), 4,
                                                t * QT * 4 + lane * 4, 0, 0, 0);
   };
-#pragma unroll
-  for (int u = 0; u + 1 < kSlots; ++u)
-    if (t_begin + u < ntiles) issue(t_begin + u, u);
+  issue(t_begin, 0);
 
   KeyBlockWave<D> w;
   w.init(lane);
@@ -1033,8 +1032,7 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
   __syncthreads();
   auto step = [&](int t, auto slot_c) __attribute__((always_inline)) {
     constexpr int S = decltype(slot_c)::value;
-    const bool ahead = t + kSlots - 1 < ntiles;
-    if (ahead) issue(t + kSlots - 1, (S + kSlots - 1) % kSlots);
+    if (t + 1 < ntiles) issue(t + 1, S ^ 1);
     const char* qs = lds + S * SLOT_BYTES;
     const float* terms = reinterpret_cast<const float*>(lds + kTerms + S * SLOT_TERMS);
     const int first[2] = {first_q[0] - t * QT, first_q[1] - t * QT};
@@ -1044,21 +1042,12 @@ __global__ void __launch_bounds__(kHalves * 256, kHalves == 1 ? 3 : 2) attn_bwd_
 #pragma unroll
       for (int qb = 0; qb < QT / 32; ++qb) w.block(qs, qs + TILE_BYTES, terms, terms + QT, 32 * qb, first, first_q_wave - t * QT);
     }
-    // the next tile has landed, the one behind it may be in flight
-    constexpr int kLoads = 2 * decltype(ts)::kInsts;
-    if (kSlots == 2 || !ahead)
-      wait_vmem();
-    else if (wave < 2)
-      wait_vmem_except<kLoads + 1>();
-    else
-      wait_vmem_except<kLoads>();
+    wait_vmem();
     __syncthreads();
   };
-  for (int t = t_begin; t < ntiles; t += kSlots) {
+  for (int t = t_begin; t < ntiles; t += 2) {
     step(t, std::integral_constant<int, 0>{});
     if (t + 1 < ntiles) step(t + 1, std::integral_constant<int, 1>{});
-    if constexpr (kSlots == 3)
-      if (t + 2 < ntiles) step(t + 2, std::integral_constant<int, 2>{});
   }
 
   // the first half's waves finish dV, the second's dK, each with what the other has of it
