@@ -1683,7 +1683,7 @@ hipError_t launch(const DevGeom& g, const AttnOperands& op, const void* out, con
   if (!keys_later) {
     ProfileScope prof("attn_bwd_dkv_bf16", stream);
     p.tiles = (op.Nq + ktile - 1) / ktile;
-    launch_dkv<D>(p, ChunkGrads{}, dkv_halves(shape, chunk_blocks(shape), false), stream);
+    launch_dkv<D>(p, ChunkGrads{}, dkv_halves(shape, chunk_blocks(shape)), stream);
   }
   return hipGetLastError();
 }
@@ -1699,7 +1699,7 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   p.tiles = (max_hist + (dk ? op.Nq : 0) + ktile - 1) / ktile;
   const CallShape shape = call_shape(g, op);
   p.by_xcd = order_by_xcd(shape, work_grid_size(p.tiles, p.BH));
-  const int halves = dkv_halves(shape, dk ? shape.joint_blocks : shape.ring_blocks, true);
+  const int halves = dkv_halves(shape, dk ? shape.joint_blocks : shape.ring_blocks);
   auto run = [&](const auto& to) {
     ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
     launch_dkv<D>(p, to, halves, stream);

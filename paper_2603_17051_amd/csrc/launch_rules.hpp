@@ -252,15 +252,14 @@ inline bool bwd_terms_first(const CallShape& c) {
 // CU gain.  Up to there two waves per block share the queries, and it is the length of the walk that decides: the roles' epilogue is
 // shorter, and with ring rows their table of frames is computed beside the last tile.  Measured (us of the launch, D = 64; tiles of 64
 // queries, roles / two waves / one wave, the same at 17 and at 255 workgroups within a tenth):
-//   chunk: 7 tiles 15.8 / 16.9 / 19.4, 8 19.0 / 19.6, 10 20.9 / 21.1, 12 22.9 / 22.7, 14 24.5 / 24.2, 16 26.6 / 26.0, 20 30.1 / 28.9, 25 35.4 / 33.8 / 44.7, 28 37.4 / 35.2,
-//          34 42.4 / 39.9 / 55.8
-//   ring:  2 11.2 / 13.2 / 12.5, 4 13.2 / 15.2 / 15.8, 8 17.2 / 18.8 / 19.8, 12 20.8 / 22.0 / 24.3, 16 24.3 / 25.5 / 28.8, 20 27.8 / 28.7 / 33.5, 24 31.6 / 32.2 / 37.9,
-//          74 78.5 / 76.2
-//   more than one to a CU: 7 tiles, 288 workgroups 27.9 / 29.8 / 24.7, 34 tiles, 272 77.9 / 72.9 / 65.3, 340 79.5 / 73.5 / 66.6
-inline int dkv_halves(const CallShape& c, int blocks, bool ring) {
+//   chunk: 7 tiles 17.1 / 17.9 / 20.1, 10 20.9 / 21.0 / 24.8, 12 23.2 / 22.6 / 27.4, 14 24.5 / 24.3 / 29.9, 16 26.5 / 25.8 / 32.7, 20 30.2 / 28.7 / 37.8, 25 35.7 /
+//          33.7 / 45.4, 28 37.4 / 34.8 / 48.1, 34 39.6 / 36.7 / 53.9
+//   ring:  8 tiles 16.8 / 17.6, 12 20.5 / 20.7, 16 24.1 / 23.8, 20 27.6 / 26.8 / 33.4, 24 31.2 / 29.7, 28 34.7 / 32.9, 32 38.3 / 36.0
+//   more than one to a CU: 7 tiles, 288 workgroups 27.9 / 29.6 / 24.1, 34 tiles, 272 78.1 / 72.6 / 65.4, 340 79.2 / 72.5 / 66.8
+inline int dkv_halves(const CallShape& c, int blocks) {
   if (c.D == 128) return 0;
   if (blocks > c.n_cus) return 1;
-  return blocks_of(c.Nq, 64) >= (ring ? 32 : 12) ? 2 : 0;
+  return blocks_of(c.Nq, 64) >= 14 ? 2 : 0;
 }
 inline int chunk_blocks(const CallShape& c) { return blocks_of(c.Nq, 128) * c.pairs; }
 

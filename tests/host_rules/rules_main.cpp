@@ -19,7 +19,7 @@ int main() {
     while (entries > 0 && !astro::fwd_rotates(c, entries)) --entries;
     std::printf("%d %d %d %d %d %d %d %d %d %d\n", astro::fwd_few_waves(c), astro::fwd_splits(c), astro::bwd_few_waves(c), w.ways, w.k,
                 astro::order_by_xcd(c, astro::blocks_of(Nq, 128) * pairs), entries, astro::bwd_terms_first(c),
-                astro::dkv_halves(c, astro::chunk_blocks(c), false), astro::dkv_halves(c, c.ring_blocks, true));
+                astro::dkv_halves(c, astro::chunk_blocks(c)), astro::dkv_halves(c, c.ring_blocks));
   }
   return 0;
 }

@@ -147,10 +147,10 @@ def test_key_blocks_of_shorter_streams_do_not_count(rules):
 
 def test_kernel_of_dk_and_dv_by_key_blocks_and_length_of_the_walk(rules):
     """D = 64, on both sides of each line: roles and two waves with a workgroup per CU, one wave with more, D = 128 roles only."""
-    for Nq, pairs, want in [(704, 42, 0), (705, 42, 2), (768, 42, 2), (390, 64, 0), (390, 65, 1), (2176, 15, 2), (2176, 16, 1), (4680, 1, 2), (4680, 6, 2), (4680, 7, 1)]:
+    for Nq, pairs, want in [(832, 36, 0), (833, 36, 2), (896, 36, 2), (390, 64, 0), (390, 65, 1), (2176, 15, 2), (2176, 16, 1), (4680, 1, 2), (4680, 6, 2), (4680, 7, 1)]:
         assert rules(64, pairs, Nq, 3000).dkv_chunk == want, (Nq, pairs)
         assert rules(128, pairs, Nq, 3000).dkv_chunk == 0
-    for Nq, pairs, hist, want in [(1984, 2, 3840, 0), (1985, 2, 3840, 2), (512, 7, 3840, 0), (512, 9, 3584, 0), (512, 9, 3585, 1), (2048, 8, 4096, 2),
+    for Nq, pairs, hist, want in [(832, 2, 3840, 0), (833, 2, 3840, 2), (512, 7, 3840, 0), (512, 9, 3584, 0), (512, 9, 3585, 1), (2048, 8, 4096, 2),
                                   (2048, 8, 4097, 1)]:
         assert rules(64, pairs, Nq, hist).dkv_ring == want, (Nq, pairs, hist)
         assert rules(128, pairs, Nq, hist).dkv_ring == 0
