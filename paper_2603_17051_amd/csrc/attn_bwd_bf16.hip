@@ -638,11 +638,11 @@ struct RingGrads {
   StreamInts start, next_n, sink_shift;  // see launch_attn_bwd_hist_bf16
 };
 struct ChunkGrads {};  // the chunk's keys: everything is in BwdParams
-// Both in one launch: a pair's keys are its resident ring rows and then the chunk's, cut into blocks of 128 without regard to
-// where the chunk begins, and every query sees all of them: under causal blocks a block of both would take its chunk rows
-// past queries that do not see them, where a gradient that is not finite leaves 0 * inf in theirs.  Two launches each end with a partly filled round of workgroups (12 pairs, 28080 + 4680 rows: 2640
-// and 444 on 256 CUs, eleven rounds and two, against 3072, twelve: the whole pass 3455 -> 3375 us; D = 64, 16 pairs, 12480 + 3120
-// rows 858 -> 810, 16 pairs of 4200 + 1200 147 -> 126).
+// Both in one launch (bwd_joins): a pair's keys are its resident ring rows and then the chunk's, cut into blocks of 128 without
+// regard to where the chunk begins, and every query sees all of them: under causal blocks a block of both would take its chunk rows
+// past queries that do not see them, where a gradient that is not finite leaves 0 * inf in theirs.  Two launches each end with a
+// partly filled round of workgroups (12 pairs, 28080 + 4680 rows: 2640 and 444 on 256 CUs, eleven rounds and two, against 3072,
+// twelve: the whole pass 3513 -> 3419 us; D = 64, 16 pairs, 12480 + 3120 rows 877 -> 830).
 struct AllGrads : RingGrads {};
 template <typename Grads>
 constexpr bool kHasRing = !std::is_same_v<Grads, ChunkGrads>;
@@ -1135,7 +1135,8 @@ void launch_dkv(const BwdParams& p, const Grads& grads, int halves, hipStream_t 
     else if (halves == 2)
       attn_bwd_dkv_block_kernel<D, 2><<<dim3(workgroups), 512, 0, stream>>>(p, grads);
   }
-  if (halves == 0) attn_bwd_dkv_kernel<D><<<dim3(workgroups), kPairThreads, 0, stream>>>(p, grads);
+  if constexpr (D == 128 || !std::is_same_v<Grads, AllGrads>)
+    if (halves == 0) attn_bwd_dkv_kernel<D><<<dim3(workgroups), kPairThreads, 0, stream>>>(p, grads);
 }
 
 // ---- launches with few rows ------------------------------------------------------------------------
@@ -1699,7 +1700,7 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   p.tiles = (max_hist + (dk ? op.Nq : 0) + ktile - 1) / ktile;
   const CallShape shape = call_shape(g, op);
   p.by_xcd = order_by_xcd(shape, work_grid_size(p.tiles, p.BH));
-  const int halves = dkv_halves(shape, dk ? shape.joint_blocks : shape.ring_blocks);
+  const int halves = dkv_halves(shape, dk ? chunk_blocks(shape) : shape.ring_blocks);  // (of both: see bwd_joins())
   auto run = [&](const auto& to) {
     ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
     launch_dkv<D>(p, to, halves, stream);
@@ -1730,10 +1731,7 @@ hipError_t launch_attn_bwd_hist_bf16(const DevGeom& g, const AttnOperands& op, c
   return launch_hist<64>(g, op, lse, dout, dk, dv, grads, scratch, stream);
 }
 
-bool bf16_bwd_joins(const DevGeom& g, const AttnOperands& op) {
-  const CallShape c = call_shape(g, op);
-  return !op.in_order && c.block_rows == 0 && c.max_hist > 0 && bwd_few_waves(c) == 0;
-}
+bool bf16_bwd_joins(const DevGeom& g, const AttnOperands& op) { return bwd_joins(call_shape(g, op)); }
 
 // Delta and LSE*log2e per (stream, head, query)
 size_t bf16_bwd_workspace_bytes(const DevGeom& g, int Nq) { return 2 * (size_t)g.B * g.H * Nq * sizeof(float); }

@@ -263,6 +263,27 @@ inline int dkv_halves(const CallShape& c, int blocks) {
 }
 inline int chunk_blocks(const CallShape& c) { return blocks_of(c.Nq, 128) * c.pairs; }
 
+// Whether the ring's key blocks and the chunk's go out in one launch (non-detached backward).  It takes the kernel that the chunk's
+// launch takes by itself, so dK and dV of the chunk are the detached backward's bit for bit.  Under causal blocks it would take keys
+// past queries that do not see them.  One wave per block: a launch less with a partly filled end of its own, always a gain.  Otherwise
+// a CU works on one block at a time, and the launch has to save a round of them; where it saves none, a short walk still gains
+// from the launch that is not there, and a long one loses to the instance for both, which is 1 % slower.  Measured (us of forward and
+// backward, one launch / two, or their ratio; rounds of the launch / of chunk + ring):
+//   D = 128: 12 / 2 + 11 3419 / 3513, 24 / 4 + 21 6950 / 7087, 48 / 7 + 42 13549 / 13964, 7 / 2 + 6 619 / 655, 2 / 1 + 2 554 / 671; as many rounds, by rounds times
+//           tiles of 64 queries: to 12 0.94 - 0.97, to 32 0.96 - 1.01, to 66 0.985 - 1.00, 116 - 148 1.01
+//   D = 64, one wave: 296 chunk and 392 ring blocks 472 / 530, 592 and 2352 1766 / 1811
+//   D = 64, two waves: 2 / 1 + 2 333 / 384, 342 / 394, 3 / 1 + 3 510 / 545, 165 / 176, 5 / 1 + 5 860 / 878, 6 / 1 + 6 982 / 992; as many, to 62 0.96 - 1.003, 105 - 222 1.02 -
+//           1.06 (2 / 1 + 1 at 148 0.99)
+//   D = 64, roles: 5 / 1 + 5 123 / 116, 7 / 1 + 7 167 / 151 (in two launches the ring's takes one wave)
+inline bool bwd_joins(const CallShape& c) {
+  if (c.in_order || c.block_rows != 0 || c.max_hist == 0 || bwd_few_waves(c) != 0) return false;
+  const int chunk = chunk_blocks(c), halves = dkv_halves(c, chunk);
+  if (halves == 1) return true;
+  if (c.D == 64 && halves == 0) return false;
+  const int rounds = blocks_of(c.joint_blocks, c.n_cus), apart = blocks_of(chunk, c.n_cus) + blocks_of(c.ring_blocks, c.n_cus);
+  return rounds < apart || rounds * blocks_of(c.Nq, 64) <= 64;
+}
+
 // dQ workgroups a CU holds: 244 registers (split 256), or 165 (split 168, 8 more in scratch)
 constexpr int dq_places_per_cu(int D) { return D == 128 ? 2 : 3; }
 

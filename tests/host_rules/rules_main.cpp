@@ -2,7 +2,7 @@
 // CUs), and prints what the launch rules of paper_2603_17051_amd/csrc/launch_rules.hpp answer: few-rows
 // waves and key ranges of the forward, few-rows waves, ways and k of the backward, contiguous eighths or not,
 // the most (cos, sin) of a forward that rotates for itself (0 = it does not), whether a backward of few rows has its row
-// terms computed first, which kernel dK and dV take over the chunk's keys and over the ring's.
+// terms computed first, which kernel dK and dV take over the chunk's keys and over the ring's, whether those go out in one launch.
 #include <cstdio>
 
 #include "../../paper_2603_17051_amd/csrc/launch_rules.hpp"
@@ -17,9 +17,9 @@ int main() {
     const astro::DqWays w = astro::dq_ways(c);
     int entries = 1024;
     while (entries > 0 && !astro::fwd_rotates(c, entries)) --entries;
-    std::printf("%d %d %d %d %d %d %d %d %d %d\n", astro::fwd_few_waves(c), astro::fwd_splits(c), astro::bwd_few_waves(c), w.ways, w.k,
+    std::printf("%d %d %d %d %d %d %d %d %d %d %d\n", astro::fwd_few_waves(c), astro::fwd_splits(c), astro::bwd_few_waves(c), w.ways, w.k,
                 astro::order_by_xcd(c, astro::blocks_of(Nq, 128) * pairs), entries, astro::bwd_terms_first(c),
-                astro::dkv_halves(c, astro::chunk_blocks(c)), astro::dkv_halves(c, c.ring_blocks));
+                astro::dkv_halves(c, astro::chunk_blocks(c)), astro::dkv_halves(c, c.ring_blocks), astro::bwd_joins(c));
   }
   return 0;
 }

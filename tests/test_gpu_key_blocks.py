@@ -1,7 +1,7 @@
-"""The non-detached backward's dK and dV where ring and chunk go out in one launch (not taken by the kernels for few rows), at D =
-64 with one and with two waves that hold both gradients of a block of keys, at the edges of key blocks, query tiles, causal blocks
-and of the ring, against the fp64 oracle (the gates hold for each gradient over all its heads); at D = 128 the
-chunk's are those of the detached backward, whose launch has the chunk only, bit for bit."""
+"""The backward's dK and dV over key blocks: at D = 64 with roles, with one wave and with two waves that hold both gradients of a block of
+keys, and where ring and chunk go out in one launch (non-detached, not under causal blocks nor by the kernels for few rows), at the
+edges of key blocks, query tiles, causal blocks and of the ring, against the fp64 oracle (the gates hold for each
+gradient over all its heads); the chunk's are those of the detached backward, whose launch has the chunk only, bit for bit."""
 import numpy as np
 import pytest
 
@@ -14,26 +14,35 @@ from test_gpu_parity import _fill_history
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed", [
-    (4, 65, 3, 11, 2, 0, 1, 0, 3),    # chunk 260 workgroups of 33 keys, ring 260 of 66: one wave a block
-    (4, 65, 8, 8, 2, 1, 1, 0, 4),     # whole tiles, ring of 128 rows: every key block full
-    (4, 65, 7, 9, 3, 1, 1, 0, 2),     # a row short of a tile, one slot empty
-    (5, 52, 1, 43, 3, 0, 3, 1, 0),    # 129 chunk rows in causal blocks of 43, nothing resident
-    (2, 65, 6, 7, 3, 0, 1, 0, 4),     # ring 130 workgroups of 126 rows: two waves a block
-    (2, 65, 1, 43, 3, 1, 2, 1, 5),    # ring 260 of 129 rows, causal blocks
-    (1, 65, 10, 13, 20, 1, 1, 0, 23), # chunk 130 workgroups: two waves a block; ring 1365
-    (1, 65, 5, 13, 40, 0, 2, 1, 40),  # the same under causal blocks
-    (1, 129, 1, 1, 100, 0, 1, 0, 70), # ring 129 workgroups of one-token frames: the table of frames behind the walk
+@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only", [
+    # one wave a block, chunk of 260 workgroups and more
+    (4, 65, 3, 11, 2, 0, 1, 0, 3, None),    # one block of 66 ring and 33 chunk rows
+    (4, 65, 8, 8, 2, 1, 1, 0, 4, None),     # whole tiles, 128 + 64 rows: the chunk begins at a block
+    (4, 65, 7, 9, 3, 1, 1, 0, 2, None),     # a row short of a tile, one slot empty: two chunk rows in the ring's block
+    (5, 52, 1, 43, 3, 0, 3, 1, 0, None),    # 129 chunk rows in causal blocks of 43, nothing resident
+    (5, 52, 1, 43, 3, 0, 3, 1, 3, None),    # ... over as many resident: two launches
+    # two waves a block, 33 query tiles
+    (1, 1, 18, 38, 3, 0, 3, 0, 3, None),    # 2052 + 2052 rows: the last tile has four, the chunk begins inside a block
+    (1, 1, 18, 38, 3, 0, 3, 1, 3, None),    # causal blocks: two launches
+    (1, 1, 22, 32, 3, 0, 3, 0, 2, None),    # whole tiles of 64, the chunk begins at a block
+    (3, 2, 18, 38, 3, 0, 3, 0, 2, 2),       # streams of different lengths: the last one is empty
+    (1, 1, 12, 35, 4, 1, 2, 0, 6, None),    # 14 tiles, the chunk by the kernel for few rows: the ring by itself
+    # roles
+    (2, 65, 6, 7, 3, 0, 1, 0, 4, None),     # ring of 130 workgroups
+    (1, 129, 1, 1, 100, 0, 1, 0, 70, None), # ... of 129, frames of one token: the table of frames behind the walk
+    (1, 65, 10, 13, 20, 1, 1, 0, 23, None), # chunk of 130; ring of 1365 by one wave
+    (1, 65, 5, 13, 40, 0, 2, 1, 40, None),  # the same under causal blocks
+    (2, 65, 1, 43, 3, 1, 2, 1, 5, None),    # few chunk rows, ring of 260 workgroups by one wave
 ])
-def test_both_gradients_in_one_wave(B, H, gh, gw, C, S, Fc, bf, streamed):
-    check(64, (12, 10, 10), B, H, gh, gw, C, S, Fc, bf, streamed)
+def test_both_gradients_of_a_block_at_64(B, H, gh, gw, C, S, Fc, bf, streamed, only):
+    check(64, (12, 10, 10), B, H, gh, gw, C, S, Fc, bf, streamed, only)
 
 
 @pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only", [
     (2, 73, 3, 11, 2, 0, 1, 0, 3, 2),    # one block of 66 ring and 33 chunk rows
-    (2, 73, 1, 43, 3, 1, 2, 1, 5, 2),    # the chunk begins inside the second block, causal blocks
-    (2, 73, 8, 8, 2, 0, 1, 0, 2, 2),     # ... at a block
-    (3, 49, 6, 7, 4, 1, 2, 1, 6, 2),     # streams of different lengths: the last one is empty
+    (2, 73, 1, 43, 3, 1, 2, 1, 5, 2),    # causal blocks: two launches
+    (2, 73, 8, 8, 2, 0, 1, 0, 2, 2),     # the chunk begins at a block
+    (3, 49, 6, 7, 4, 1, 2, 0, 6, 2),     # streams of different lengths: the last one is empty
     (1, 146, 7, 9, 3, 1, 1, 0, 0, 1),    # nothing resident: a launch of its own
 ])
 def test_ring_and_chunk_in_one_launch(B, H, gh, gw, C, S, Fc, bf, streamed, only):
@@ -55,8 +64,7 @@ def check(D, pairs, B, H, gh, gw, C, S, Fc, bf, streamed, only=None):
     out, lse = ls.fwd(q, k, v, Fc)
     _, dk, dv, dkc, dvc = ls.A.astro_chunk_attn_bwd_full(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
     detached = ls.A.astro_chunk_attn_bwd(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
-    if D == 128:  # (at D = 64 the two launches may have another number of waves to a block, which sum in another order)
-        assert (dk == detached[1]).all() and (dv == detached[2]).all()
+    assert dk.equal(detached[1]) and dv.equal(detached[2])
     _, rk, rv, extra = ls.oracle.attn_bwd(*[ls.wide(x) for x in (q, k, v, do)], Fc, history_grads=True)
     assert_bf16_close(host_f64(dk), rk, "dk")
     assert_bf16_close(host_f64(dv), rv, "dv")

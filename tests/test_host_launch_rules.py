@@ -7,8 +7,8 @@ from collections import namedtuple
 
 import pytest
 
-Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries terms_first dkv_chunk dkv_ring",
-                  defaults=[1, 0, 0, 0, 0])
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries terms_first dkv_chunk dkv_ring "
+                          "joined", defaults=[1, 0, 0, 0, 0, 0])
 
 
 @pytest.fixture(scope="module")
@@ -154,3 +154,17 @@ def test_kernel_of_dk_and_dv_by_key_blocks_and_length_of_the_walk(rules):
                                   (2048, 8, 4097, 1)]:
         assert rules(64, pairs, Nq, hist).dkv_ring == want, (Nq, pairs, hist)
         assert rules(128, pairs, Nq, hist).dkv_ring == 0
+
+
+def test_ring_and_chunk_in_one_launch_only_where_it_gains(rules):
+    """Sizes measured both ways, and the calls whose routes or outputs keep them apart."""
+    for call in [(128, 12, 4680, 28080), (128, 48, 4680, 28080), (128, 32, 1200, 5400), (64, 8, 4680, 6240), (64, 16, 4680, 18720), (64, 2, 4680, 18720), (64, 4, 4680, 18720),
+                 (64, 16, 1200, 4200), (64, 1, 4680, 6240), (64, 16, 1200, 1800), (128, 48, 600, 1200)]:
+        assert rules(*call).joined == 1, call
+        assert rules(*call, block_rows=call[2] // 3).joined == 0 and rules(*call, in_order=True).joined == 0
+        assert rules(*call[:3], 0).joined == 0
+    for call in [(128, 5, 4680, 18720), (128, 8, 3120, 14040), (128, 5, 4680, 4680), (64, 4, 4680, 4680), (64, 5, 4680, 9360), (64, 4, 4680, 23400), (64, 6, 4680, 23400), (64, 50, 512, 2560), (64, 60, 260, 2340),
+                 (64, 2, 128, 512), (128, 2, 252, 189)]:
+        assert rules(*call).joined == 0, call
+    # blocks with keys: three empty streams beside a full one do not make it eleven rounds
+    assert rules(128, 12, 4680, [28080, 0, 0, 0]).joined == 0
