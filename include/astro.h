@@ -274,7 +274,9 @@ int astro_nft_loss_static(const void *v_theta, const void *v_old, const void *v_
  * aggregates by kernel name into out[0 .. *n_entries) (at most max_entries names)
  * and switches timing off.  Process-wide, one host thread.  A forward of a few rows that rotates
  * its chunk inside the attention launch is "attn_fwd_few_rotating_bf16", without a "chunk_rope_stage"
- * (the rotation pre-pass) before it. */
+ * (the rotation pre-pass) before it.  dK and dV of a non-detached backward are "attn_bwd_dkv_bf16" (the
+ * chunk's) and "attn_bwd_dkv_hist_bf16" (the ring's), or "attn_bwd_dkv_joint_bf16" where both go out in
+ * one launch. */
 typedef struct astro_kernel_time {
   char name[48];     /* kernel name, NUL-terminated */
   int32_t launches;  /* launches seen                */

@@ -1702,7 +1702,7 @@ hipError_t launch_hist(const DevGeom& g, const AttnOperands& op, const float* ls
   p.by_xcd = order_by_xcd(shape, work_grid_size(p.tiles, p.BH));
   const int halves = dkv_halves(shape, dk ? chunk_blocks(shape) : shape.ring_blocks);  // (of both: see bwd_joins())
   auto run = [&](const auto& to) {
-    ProfileScope prof("attn_bwd_dkv_hist_bf16", stream);
+    ProfileScope prof(dk ? "attn_bwd_dkv_joint_bf16" : "attn_bwd_dkv_hist_bf16", stream);
     launch_dkv<D>(p, to, halves, stream);
   };
   if (dk) {

@@ -14,43 +14,43 @@ from test_gpu_parity import _fill_history
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only", [
+@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only,joint", [
     # one wave a block, chunk of 260 workgroups and more
-    (4, 65, 3, 11, 2, 0, 1, 0, 3, None),    # one block of 66 ring and 33 chunk rows
-    (4, 65, 8, 8, 2, 1, 1, 0, 4, None),     # whole tiles, 128 + 64 rows: the chunk begins at a block
-    (4, 65, 7, 9, 3, 1, 1, 0, 2, None),     # a row short of a tile, one slot empty: two chunk rows in the ring's block
-    (5, 52, 1, 43, 3, 0, 3, 1, 0, None),    # 129 chunk rows in causal blocks of 43, nothing resident
-    (5, 52, 1, 43, 3, 0, 3, 1, 3, None),    # ... over as many resident: two launches
+    (4, 65, 3, 11, 2, 0, 1, 0, 3, None, True),    # one block of 66 ring and 33 chunk rows
+    (4, 65, 8, 8, 2, 1, 1, 0, 4, None, True),     # whole tiles, 128 + 64 rows: the chunk begins at a block
+    (4, 65, 7, 9, 3, 1, 1, 0, 2, None, True),     # a row short of a tile, one slot empty: two chunk rows in the ring's block
+    (5, 52, 1, 43, 3, 0, 3, 1, 0, None, False),    # 129 chunk rows in causal blocks of 43, nothing resident
+    (5, 52, 1, 43, 3, 0, 3, 1, 3, None, False),    # ... over as many resident: two launches
     # two waves a block, 33 query tiles
-    (1, 1, 18, 38, 3, 0, 3, 0, 3, None),    # 2052 + 2052 rows: the last tile has four, the chunk begins inside a block
-    (1, 1, 18, 38, 3, 0, 3, 1, 3, None),    # causal blocks: two launches
-    (1, 1, 22, 32, 3, 0, 3, 0, 2, None),    # whole tiles of 64, the chunk begins at a block
-    (3, 2, 18, 38, 3, 0, 3, 0, 2, 2),       # streams of different lengths: the last one is empty
-    (1, 1, 12, 35, 4, 1, 2, 0, 6, None),    # 14 tiles, the chunk by the kernel for few rows: the ring by itself
+    (1, 1, 18, 38, 3, 0, 3, 0, 3, None, True),    # 2052 + 2052 rows: the last tile has four, the chunk begins inside a block
+    (1, 1, 18, 38, 3, 0, 3, 1, 3, None, False),    # causal blocks: two launches
+    (1, 1, 22, 32, 3, 0, 3, 0, 2, None, True),    # whole tiles of 64, the chunk begins at a block
+    (3, 2, 18, 38, 3, 0, 3, 0, 2, 2, True),       # streams of different lengths: the last one is empty
+    (1, 1, 12, 35, 4, 1, 2, 0, 6, None, False),    # 14 tiles, the chunk by the kernel for few rows: the ring by itself
     # roles
-    (2, 65, 6, 7, 3, 0, 1, 0, 4, None),     # ring of 130 workgroups
-    (1, 129, 1, 1, 100, 0, 1, 0, 70, None), # ... of 129, frames of one token: the table of frames behind the walk
-    (1, 65, 10, 13, 20, 1, 1, 0, 23, None), # chunk of 130; ring of 1365 by one wave
-    (1, 65, 5, 13, 40, 0, 2, 1, 40, None),  # the same under causal blocks
-    (2, 65, 1, 43, 3, 1, 2, 1, 5, None),    # few chunk rows, ring of 260 workgroups by one wave
+    (2, 65, 6, 7, 3, 0, 1, 0, 4, None, False),     # ring of 130 workgroups
+    (1, 129, 1, 1, 100, 0, 1, 0, 70, None, False), # ... of 129, frames of one token: the table of frames behind the walk
+    (1, 65, 10, 13, 20, 1, 1, 0, 23, None, False), # chunk of 130; ring of 1365 by one wave
+    (1, 65, 5, 13, 40, 0, 2, 1, 40, None, False),  # the same under causal blocks
+    (2, 65, 1, 43, 3, 1, 2, 1, 5, None, False),    # few chunk rows, ring of 260 workgroups by one wave
 ])
-def test_both_gradients_of_a_block_at_64(B, H, gh, gw, C, S, Fc, bf, streamed, only):
-    check(64, (12, 10, 10), B, H, gh, gw, C, S, Fc, bf, streamed, only)
+def test_both_gradients_of_a_block_at_64(B, H, gh, gw, C, S, Fc, bf, streamed, only, joint):
+    check(64, (12, 10, 10), B, H, gh, gw, C, S, Fc, bf, streamed, only, joint)
 
 
-@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only", [
-    (2, 73, 3, 11, 2, 0, 1, 0, 3, 2),    # one block of 66 ring and 33 chunk rows
-    (2, 73, 1, 43, 3, 1, 2, 1, 5, 2),    # causal blocks: two launches
-    (2, 73, 8, 8, 2, 0, 1, 0, 2, 2),     # the chunk begins at a block
-    (3, 49, 6, 7, 4, 1, 2, 0, 6, 2),     # streams of different lengths: the last one is empty
-    (1, 146, 7, 9, 3, 1, 1, 0, 0, 1),    # nothing resident: a launch of its own
+@pytest.mark.parametrize("B,H,gh,gw,C,S,Fc,bf,streamed,only,joint", [
+    (2, 73, 3, 11, 2, 0, 1, 0, 3, 2, True),    # one block of 66 ring and 33 chunk rows
+    (2, 73, 1, 43, 3, 1, 2, 1, 5, 2, False),    # causal blocks: two launches
+    (2, 73, 8, 8, 2, 0, 1, 0, 2, 2, True),     # the chunk begins at a block
+    (3, 49, 6, 7, 4, 1, 2, 0, 6, 2, True),     # streams of different lengths: the last one is empty
+    (1, 146, 7, 9, 3, 1, 1, 0, 0, 1, False),    # nothing resident: a launch of its own
 ])
-def test_ring_and_chunk_in_one_launch(B, H, gh, gw, C, S, Fc, bf, streamed, only):
-    check(128, (22, 21, 21), B, H, gh, gw, C, S, Fc, bf, streamed, only)
+def test_ring_and_chunk_in_one_launch(B, H, gh, gw, C, S, Fc, bf, streamed, only, joint):
+    check(128, (22, 21, 21), B, H, gh, gw, C, S, Fc, bf, streamed, only, joint)
 
 
-def check(D, pairs, B, H, gh, gw, C, S, Fc, bf, streamed, only=None):
-    """`only`: streams with history, all by default"""
+def check(D, pairs, B, H, gh, gw, C, S, Fc, bf, streamed, only, joint):
+    """`only`: streams with history, None = all; `joint`: whether the ring's and the chunk's are one launch"""
     T = gh * gw
     w = wl.Workload("key_blocks", 57, B, H, D, gh, gw, C, S, Fc, streamed, pairs)
     ls = Lockstep(w, max_chunk=Fc, start_frames=[3 + 100 * b for b in range(B)], block_frames=bf)
@@ -62,7 +62,10 @@ def check(D, pairs, B, H, gh, gw, C, S, Fc, bf, streamed, only=None):
             ls.oracle.reset(b, 3 + 100 * b)
     q, k, v, do = wl.chunk_inputs(w, with_dout=True)
     out, lse = ls.fwd(q, k, v, Fc)
+    ls.A.astro_profile_begin()
     _, dk, dv, dkc, dvc = ls.A.astro_chunk_attn_bwd_full(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
+    launched = ls.A.astro_profile_end()
+    assert ("attn_bwd_dkv_joint_bf16" in launched) == joint and ("attn_bwd_dkv_hist_bf16" in launched) == (streamed > 0 and not joint), launched
     detached = ls.A.astro_chunk_attn_bwd(ls.cache, *[ls.dev(x) for x in (q, k, v)], out, lse, ls.dev(do), Fc)
     assert dk.equal(detached[1]) and dv.equal(detached[2])
     _, rk, rv, extra = ls.oracle.attn_bwd(*[ls.wide(x) for x in (q, k, v, do)], Fc, history_grads=True)
