@@ -1,10 +1,12 @@
 """Outputs over memory that the call still reads on another route: such calls take the route that reads it all
-first (backward: the two plain launches instead of one for both sides or partial sums in dK and dV;
-forward: key ranges merged at the end).  Each layout at a size of either route, against the fp64 oracle."""
+first (backward: the two plain launches instead of one for both sides or partial sums in dK and dV, and
+ring and chunk in a launch each; forward: key ranges merged at the end).  Each layout at a size of either route, against the fp64 oracle."""
+import numpy as np
 import pytest
 
 import workloads as wl
 from helpers import Lockstep, assert_bf16_close, host_f64
+from oracle import rope_angles, rope_rotate
 from test_gpu_parity import _fill_history
 
 pytestmark = pytest.mark.gpu
@@ -119,4 +121,50 @@ def test_ring_gradients_over_each_other_and_over_dout(D, window_relative, layout
     assert all(torch.equal(a, b) for a, b in zip(got[:4], want[:4]))  # the same kernels in the same order of sums
     if dvc is not dkc:
         assert torch.equal(dvc, want[4])
+    ls.close()
+
+
+@pytest.mark.parametrize("D,B,H,gh,gw,C,Fc,resident", [
+    (128, 2, 73, 3, 11, 2, 1, 2),
+    (64, 4, 65, 3, 11, 2, 1, 2),   # one wave a block of keys
+    (64, 1, 2, 18, 38, 3, 3, 2),   # two
+])
+@pytest.mark.parametrize("layout", ["apart", "one buffer for dk_cache and dv_cache", "dk_cache over dout", "dk_cache over dout and dv_cache",
+                                    "dv_cache over dk_chunk"])
+def test_ring_gradients_of_calls_that_are_one_launch_otherwise(D, B, H, gh, gw, C, Fc, resident, layout):
+    """Sizes at which ring and chunk go out together where nothing overlaps."""
+    import torch
+    T, pairs = gh * gw, wl.default_rope_pairs(D)
+    w = wl.Workload("overlap_joint", 59, B, H, D, gh, gw, C, 0, Fc, resident, pairs)
+    ls = Lockstep(w, max_chunk=Fc, start_frames=[9 + b for b in range(B)])
+    _fill_history(ls, w, *wl.history_frame_pool(w, 3), resident)
+    q, k, v, do = wl.chunk_inputs(w, with_dout=True)
+    dev = [ls.dev(x) for x in (q, k, v, do)]
+    out, lse = ls.A.astro_chunk_attn_fwd(ls.cache, *dev[:3], Fc)
+    detached = ls.A.astro_chunk_attn_bwd(ls.cache, *dev[:3], out, lse, dev[3], Fc)
+    nan = lambda *shape: torch.full(shape, float("nan"), device="cuda:0")
+    dq, dk, dv, dkc, dvc = [nan(*dev[0].shape) for _ in range(3)] + [nan(B, C * T, H, D) for _ in range(2)]
+    dout, wanted = dev[3], {"dq", "dk", "dv", "dk_cache", "dv_cache"}
+    if "dout" in layout:
+        dout = dkc.view(-1).view(torch.bfloat16)[-dout.numel():].view(dout.shape)
+        dout.copy_(dev[3])
+    if layout == "dv_cache over dk_chunk":
+        dk, wanted = dvc.view(-1)[-dk.numel():].view(dk.shape), wanted - {"dk"}
+    elif "dv_cache" in layout:
+        dvc, wanted = dkc, wanted - {"dv_cache"}
+    ls.A.astro_profile_begin()
+    ls.A.astro_chunk_attn_bwd_full(ls.cache, *dev[:3], out, lse, dout, Fc, dq, dk, dv, dkc, dvc)
+    launched = ls.A.astro_profile_end()
+    assert ("attn_bwd_dkv_joint_bf16" in launched) == (layout == "apart"), launched
+    for name, got, want in zip(("dq", "dk", "dv"), (dq, dk, dv), detached):
+        assert name not in wanted or got.equal(want), name
+    b, h = B - 1, H - 1
+    extra = ls.oracle.attn_bwd(*[ls.wide(x) for x in (q, k, v, do)], Fc, streams=[b], heads=[h], history_grads=True)[3][(b, h)]
+    rows = resident * T
+    if "dk_cache" in wanted:
+        ref = np.concatenate([rope_rotate(extra["dk_hist_rot"][f * T:(f + 1) * T, None, :], -rope_angles(ls.oracle.start[b] + f, gh, gw, pairs, w.rope_base))[:, 0]
+                              for f in range(resident)])
+        assert_bf16_close(host_f64(dkc[b, :rows, h]), ref, f"{layout}: dk_cache")
+    if "dv_cache" in wanted:
+        assert_bf16_close(host_f64(dvc[b, :rows, h]), extra["dv_hist"], f"{layout}: dv_cache")
     ls.close()
