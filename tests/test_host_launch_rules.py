@@ -7,8 +7,8 @@ from collections import namedtuple
 
 import pytest
 
-Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries terms_first dkv_chunk dkv_ring "
-                          "joined", defaults=[1, 0, 0, 0, 0, 0])
+Rule = namedtuple("Rule", "fwd_few fwd_splits bwd_few ways k by_xcd rotated_entries together_entries terms_first "
+                          "dkv_chunk dkv_ring joined", defaults=[1, 0, 0, 0, 0, 0, 0])
 
 
 @pytest.fixture(scope="module")
@@ -121,6 +121,16 @@ def test_forward_rotates_its_chunk_only_with_few_chunk_tiles_per_wave(rules):
     for D in (64, 128):
         assert rules(D, 12, 4680, 28080).rotated_entries == 0  # the general kernel
         assert rules(D, 4, 64, 64, in_order=True).rotated_entries == 0
+
+
+def test_waves_turn_short_chunks_together(rules):
+    """Launches of eight waves only, on both sides of the most tiles and (cos, sin); a forward rotates for itself where they do."""
+    for D, pairs, Nq, hist, together in [(64, 2, 31, 248, 384), (64, 6, 32, 288, 384), (64, 4, 33, 264, 384), (64, 2, 255, 510, 384), (64, 2, 256, 0, 384),
+                                         (64, 3, 256, 256, 384), (64, 1, 257, 257, 0), (128, 2, 63, 567, 512), (128, 12, 64, 512, 512), (128, 1, 65, 585, 0),
+                                         (64, 2, 64, 64, 0), (128, 2, 64, 256, 0)]:
+        got = rules(D, pairs, Nq, hist)
+        assert got.together_entries == together and (got.fwd_few == 8 or not together), (D, pairs, Nq, hist)
+        assert got.rotated_entries >= got.together_entries
 
 
 def test_waves_of_launches_with_few_rows(rules):
