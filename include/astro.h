@@ -194,7 +194,7 @@ int astro_chunk_attn_bwd(astro_kvcache_t *cache, const void *q, const void *k_ch
                          void *hip_stream);
 
 /* The non-detached backward ("Clip + Full BP" of the paper's streaming-training ablation,
- * Sec. 4.5, Table 4(a)): everything astro_chunk_attn_bwd writes, plus the gradients the detach drops,
+ * Sec. 4.5, Table 4(a)): everything astro_chunk_attn_bwd writes, bit for bit, plus the gradients the detach drops,
  *   dk_cache, dv_cache: device fp32 [B, C*T, H, D], row = slot*T + token, w.r.t. the keys
  *   (UN-rotated, as they were appended) and values of the frames resident in the ring.
  * Rows of slots that hold no frame are not written.  They are written after everything else;

@@ -478,8 +478,9 @@ struct RawChunk {
   StreamInts first_frame;  // by candidate
 };
 // The same with the chunk's keys turned by all waves together before the walk (fwd_turns_together): a wave that turns a tile
-// on its way spends 1770 cycles on it and 1000 waiting for its keys behind the tile before, of 11200 in a short call; the
-// eight waves share them in about 700, next to the queries', and a chunk tile's values are requested a tile earlier.
+// on its way spends 1770 cycles on it and 1000 waiting for its keys behind the tile before, of 11200 in a short call.  The
+// eight waves turn theirs next to the queries, which are waited for and turned either way (2150 cycles of 9900 with both), and
+// a chunk tile's values are requested a tile earlier.
 struct RawChunkTogether : RawChunk {};
 
 // The (cos, sin) a workgroup's chunk tokens need, in LDS: [n_frames][n_t], [gh][n_h], [gw][n_w], at most kEntries.

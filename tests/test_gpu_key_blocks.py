@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     (4, 65, 3, 11, 2, 0, 1, 0, 3, None, True),    # one block of 66 ring and 33 chunk rows
     (4, 65, 8, 8, 2, 1, 1, 0, 4, None, True),     # whole tiles, 128 + 64 rows: the chunk begins at a block
     (4, 65, 7, 9, 3, 1, 1, 0, 2, None, True),     # a row short of a tile, one slot empty: two chunk rows in the ring's block
+    (2, 65, 10, 13, 3, 0, 1, 0, 3, None, True),   # three query tiles, the last of two rows
     (5, 52, 1, 43, 3, 0, 3, 1, 0, None, False),    # 129 chunk rows in causal blocks of 43, nothing resident
     (5, 52, 1, 43, 3, 0, 3, 1, 3, None, False),    # ... over as many resident: two launches
     # two waves a block, 33 query tiles
