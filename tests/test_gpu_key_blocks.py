@@ -44,6 +44,7 @@ def test_both_gradients_of_a_block_at_64(B, H, gh, gw, C, S, Fc, bf, streamed, o
     (2, 73, 1, 43, 3, 1, 2, 1, 5, 2, False),    # causal blocks: two launches
     (2, 73, 8, 8, 2, 0, 1, 0, 2, 2, True),     # the chunk begins at a block
     (3, 49, 6, 7, 4, 1, 2, 0, 6, 2, True),     # streams of different lengths: the last one is empty
+    (3, 49, 6, 7, 4, 1, 2, 1, 6, 2, False),    # ... under causal blocks: two launches
     (1, 146, 7, 9, 3, 1, 1, 0, 0, 1, False),    # nothing resident: a launch of its own
 ])
 def test_ring_and_chunk_in_one_launch(B, H, gh, gw, C, S, Fc, bf, streamed, only, joint):
